@@ -190,7 +190,7 @@ class _State:
         return t
 
     def __del__(self):
-        if self.pool is not None:
+        if self.pool is not None and torch is not None:     # (a module's names are None at the interpreter's end)
             torch.cuda.synchronize()
             E.ellm_pool_destroy(self.pool)
             self.pool = None
