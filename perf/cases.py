@@ -19,6 +19,7 @@ over the pool by a seeded permutation, as they are in a pool that has been in us
 from __future__ import annotations
 
 import math
+import sys
 
 import numpy as np
 import torch
@@ -190,7 +191,7 @@ class _State:
         return t
 
     def __del__(self):
-        if self.pool is not None and torch is not None:     # (a module's names are None at the interpreter's end)
+        if self.pool is not None and not sys.is_finalizing():
             torch.cuda.synchronize()
             E.ellm_pool_destroy(self.pool)
             self.pool = None
