@@ -153,7 +153,7 @@ struct ellm_pool {
   int32_t split_override = 0;
   int32_t wave_slots = 0;              // waves of a decode launch: one per SIMD of the GPU (0 = not asked yet)
   int32_t waves_percent = 100;         // waves of a launch, as a share of what the GPU holds at once
-  int64_t plan_total_tiles = 0;        // of the launch planned last: tiles per kv head,
+  int64_t plan_total_units = 0;        // of the launch planned last: units per kv head,
   int64_t plan_waves = 0, plan_slots = 0;   // waves per kv head, partial slots
 
   // optional timing of the partial (dominant) kernel with events on the caller's stream
@@ -165,7 +165,7 @@ struct ellm_pool {
   std::vector<int32_t> n_eff;
   std::vector<ellm::Move> moves;
   std::vector<ellm::BatchArgs> launches;
-  std::vector<int32_t> tiles_tmp;
+  std::vector<int32_t> units_tmp;
 };
 
 namespace {
@@ -195,6 +195,7 @@ ellm::PoolView view_of(const ellm_pool* p) {
   v.chunk_bytes = p->geom.chunk_bytes;
   v.tokens_per_chunk = p->geom.tokens_per_chunk;
   v.tiles_per_chunk = (p->geom.tokens_per_chunk + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
+  v.units_per_chunk = (p->geom.tokens_per_chunk + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
   v.max_slots = p->geom.max_slots;
   v.n_q_heads = p->geom.n_q_heads;
   v.n_kv_heads = p->geom.n_kv_heads;
@@ -264,7 +265,7 @@ int ensure_device(ellm_pool* p) {
     if (e) return hip_err((hipError_t)e, "hipGetSymbolAddress(fixed workspace)");
     p->static_ws_slots = (int64_t)(bytes / slot_bytes(p->geom.group, p->geom.head_dim));
     p->launches.reserve(((size_t)p->geom.max_tensors + ellm::MAX_LAUNCH_REQ - 1) / ellm::MAX_LAUNCH_REQ);
-    p->tiles_tmp.reserve(ellm::MAX_LAUNCH_REQ);
+    p->units_tmp.reserve(ellm::MAX_LAUNCH_REQ);
   }
   if (p->geom.n_host_slots > 0 || p->vmm) {
     p->chunk_compute.assign(p->geom.n_chunks, 0);
@@ -748,7 +749,7 @@ int32_t wave_slots(ellm_pool* p) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
-      slots = cus * std::min(ellm::SIMDS_PER_CU, ellm::partial_waves_per_cu(p->geom.head_dim, p->geom.group));
+      slots = cus * std::min(ellm::SIMDS_PER_CU, ellm::partial_waves_per_cu(p->geom.head_dim, p->geom.group, p->geom.tokens_per_chunk));
     else
       (void)hipGetLastError();
   }
@@ -756,78 +757,119 @@ int32_t wave_slots(ellm_pool* p) {
   return slots;
 }
 
-// The partition of one launch (at most MAX_LAUNCH_REQ requests). For each kv head the tiles of all
-// requests form one sequence, dealt out evenly to as many waves as the GPU has SIMDs (all kv
-// heads together): every wave reads the same amount, all are resident from the start, and a wave
-// whose share crosses from one request into the next finishes a result for each. The cut
-// depends only on the batch's lengths, the pool geometry and the device's wave capacity, never on
-// physical chunk ids or on which wave runs when: every rounding is reproducible and invariant
+// The partition of one launch (at most MAX_LAUNCH_REQ requests). For each kv head the units (up to
+// UNIT_TOKENS tokens of one chunk) of all requests form one sequence, dealt out evenly to as many waves
+// as the GPU has SIMDs (all kv heads together): every wave reads the same amount to within one unit,
+// all are resident from the start, and a wave whose share crosses from one request into the next
+// finishes a result for each. A launch that has no STEP_UNITS units for each of them is cut at every
+// STEP_UNITS-th unit of each request instead, one wave each: a smaller share is not worth its partial
+// result (its first loads take as long), and the cut of a request does not depend on its neighbours.
+// The cut depends only on the batch's lengths, the pool geometry and the device's wave capacity, never
+// on physical chunk ids or on which wave runs when: every rounding is reproducible and invariant
 // under remapping.
-// With an override (tests) every wave gets the given number of tokens' worth of tiles.
-void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
-  const int32_t Tc = p->geom.tokens_per_chunk;
-  const int32_t tpc = (Tc + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
-  int64_t total = 0;
-  std::vector<int32_t>& tiles = p->tiles_tmp;
-  tiles.resize(n_req);
-  for (int32_t i = 0; i < n_req; i++) {
-    const int64_t len = p->core->tensor(ids[i])->len + extra;   // extra: tokens of a fused append
-    const int64_t full = len / Tc, rem = len - full * Tc;
-    tiles[i] = (int32_t)(full * tpc + (rem + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS);
-    a.req[i].tensor = ids[i];
-    a.req[i].len = (int32_t)len;
-    a.req[i].tile_prefix = (int32_t)std::min<int64_t>(total, 0x7fffffff);
-    total += tiles[i];
-  }
-  int64_t waves;
-  if (p->split_override > 0) {
-    const int64_t per = std::max<int64_t>(1, p->split_override / ellm::TILE_TOKENS);
-    waves = (total + per - 1) / per;
-  } else {
-    waves = (int64_t)wave_slots(p) * p->waves_percent / 100 / p->geom.n_kv_heads;
-  }
-  waves = std::max<int64_t>(1, std::min<int64_t>(waves, total));
+// With an override (tests) every wave gets the given number of tokens' worth of units.
+using ellm::TILE_TOKENS;
+
+// how many partial slots per kv head the cut of sequences of n[i] steps into `waves` shares needs; with
+// a != NULL the cut is written there
+int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a) {
   const int64_t each = total / waves, more = total - each * waves;
-  // wave that holds tile x: the first `more` waves hold each + 1 tiles, the others each
+  // wave that holds step x: the first `more` waves hold each + 1 steps, the others each
   auto wave_of = [&](int64_t x) { return x < more * (each + 1) ? x / (each + 1) : more + (x - more * (each + 1)) / each; };
-  std::memset(a.split_req, 0, sizeof(a.split_req));
   int64_t at = 0, parts = 0;
   int32_t n_split = 0;
-  for (int32_t i = 0; i < n_req; i++) {
-    const int64_t w0 = wave_of(at), w1 = wave_of(at + tiles[i] - 1);
-    a.req[i].wave_first = (int32_t)w0;
-    a.req[i].n_part = (int32_t)(w1 - w0 + 1);
-    a.req[i].part0 = 0;
+  for (size_t i = 0; i < n.size(); i++) {
+    const int64_t w0 = wave_of(at), w1 = wave_of(at + n[i] - 1);
+    if (a) {
+      a->req[i].unit_prefix = (int32_t)std::min<int64_t>(at, 0x7fffffff);
+      a->req[i].wave_first = (int32_t)w0;
+      a->req[i].n_part = (int32_t)(w1 - w0 + 1);
+      a->req[i].part0 = w1 > w0 ? (int32_t)std::min<int64_t>(parts, 0x7fffffff) : 0;
+      if (w1 > w0) a->split_req[n_split >> 2] |= (uint32_t)i << ((n_split & 3) * 8);
+    }
     if (w1 > w0) {               // a request shared by several waves: partial results and a combine pass
-      a.req[i].part0 = (int32_t)std::min<int64_t>(parts, 0x7fffffff);
       parts += w1 - w0 + 1;
-      a.split_req[n_split >> 2] |= (uint32_t)i << ((n_split & 3) * 8);
       n_split++;
     }
-    at += tiles[i];
+    at += n[i];
   }
+  if (a) {
+    a->units_each = (int32_t)each;
+    a->units_extra = (int32_t)more;
+    a->n_split_req = n_split;
+  }
+  return parts;
+}
+
+void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
+  const int32_t Tc = p->geom.tokens_per_chunk, n_kv = p->geom.n_kv_heads;
+  auto pieces = [&](int64_t len, int32_t most) {      // pieces of up to `most` tokens of one chunk
+    const int64_t full = len / Tc, rem = len - full * Tc;
+    return full * ((Tc + most - 1) / most) + (rem + most - 1) / most;
+  };
+  const bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
+  a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
+  a.step_units = 1;
+  int64_t total = 0, steps = 0;
+  std::vector<int32_t>& units = p->units_tmp;
+  units.resize(n_req);
+  for (int32_t i = 0; i < n_req; i++) {
+    const int64_t len = p->core->tensor(ids[i])->len + extra;   // extra: tokens of a fused append
+    units[i] = (int32_t)pieces(len, a.unit_tokens);
+    a.req[i].tensor = ids[i];
+    a.req[i].len = (int32_t)len;
+    total += units[i];
+    steps += (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
+  }
+  const int64_t room = std::max<int64_t>(1, (int64_t)wave_slots(p) * p->waves_percent / 100 / n_kv);
+  int64_t waves;
+  if (p->split_override > 0) {
+    const int64_t per = std::max<int64_t>(1, p->split_override / TILE_TOKENS) * (TILE_TOKENS / a.unit_tokens);
+    waves = std::max<int64_t>(1, std::min((total + per - 1) / per, total));
+  } else {
+    waves = std::max<int64_t>(1, std::min(room, total));
+    if (!tiles) {
+      // The entry point with the fixed workspace takes every batch whose cut in 64-token pieces of a chunk
+      // fits there; where that cut would fit and this one does not, it is made coarser until it does
+      // (for both entry points, which share the cut).
+      const int64_t cap = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim)) / n_kv;
+      bool coarser = false;
+      if (std::min(waves, steps) + n_req - 1 > cap) {
+        std::vector<int32_t> by64(n_req);
+        int64_t n64 = 0;
+        for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)pieces(a.req[i].len, TILE_TOKENS);
+        coarser = cut_shares(by64, n64, std::min(room, n64), nullptr) <= cap;
+      }
+      if (coarser) {
+        while (waves > 1 && cut_shares(units, total, waves, nullptr) > cap) waves -= (waves + 15) / 16;
+      } else if (steps <= room) {
+        a.step_units = ellm::STEP_UNITS;
+        for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
+        total = waves = steps;
+      }
+    }
+  }
+  std::memset(a.split_req, 0, sizeof(a.split_req));
+  const int64_t parts = cut_shares(units, total, waves, &a);
   a.n_req = n_req;
   a.q_row0 = q_row0;
-  a.tiles_per_head = (int32_t)std::min<int64_t>(total, 0x7fffffff);
+  a.units_per_head = (int32_t)std::min<int64_t>(total, 0x7fffffff);
   a.waves_per_head = (int32_t)std::min<int64_t>(waves, 0x7fffffff);
-  a.tiles_each = (int32_t)each;
-  a.tiles_extra = (int32_t)more;
   a.parts_per_head = (int32_t)std::min<int64_t>(parts, 0x7fffffff);
-  a.ws_slots = (int32_t)std::min<int64_t>(parts * p->geom.n_kv_heads, 0x7fffffff);
-  a.n_split_req = n_split;
+  a.ws_slots = (int32_t)std::min<int64_t>(parts * n_kv, 0x7fffffff);
   a.use_wave_req = waves <= ellm::MAX_WAVE_REQ ? 1 : 0;
   if (a.use_wave_req) {
     std::memset(a.wave_req, 0, sizeof(a.wave_req));
     int32_t i = 0;
     for (int64_t w = 0; w < waves; w++) {
-      const int64_t lo = w * each + std::min<int64_t>(w, more);
-      while (a.req[i].tile_prefix + (int64_t)tiles[i] <= lo) i++;
+      const int64_t lo = w * a.units_each + std::min<int64_t>(w, a.units_extra);
+      while (a.req[i].unit_prefix + (int64_t)units[i] <= lo) i++;
       a.wave_req[w >> 2] |= (uint32_t)i << ((w & 3) * 8);
     }
   }
-  p->plan_total_tiles = total;
+  p->plan_total_units = total;
   p->plan_waves = waves;
-  p->plan_slots = parts * p->geom.n_kv_heads;
+  p->plan_slots = parts * n_kv;
 }
 
 // a debug hook can make the n-th launch from now fail as if the runtime had refused it
@@ -1073,12 +1115,14 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
     const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
     plan_launch(p, ids + b0, nb, b0, a);
-    per_wave = std::max(per_wave, a.tiles_each + (a.tiles_extra > 0 ? 1 : 0));
+    per_wave = std::max(per_wave, (a.units_each + (a.units_extra > 0 ? 1 : 0)) * a.step_units * a.unit_tokens);
     if (n_split)
       for (int32_t i = 0; i < nb; i++)
         n_split[b0 + i] = a.req[i].n_part;
   }
-  if (split_tokens) *split_tokens = per_wave * ellm::TILE_TOKENS;
+  // reported in whole 64-token steps, rounded up
+  if (split_tokens)
+    *split_tokens = (per_wave + TILE_TOKENS - 1) / TILE_TOKENS * TILE_TOKENS;
   return ELLM_OK;
 }
 
@@ -1104,7 +1148,7 @@ static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, c
     const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
     launches.emplace_back();
     plan_launch(p, ids + b0, nb, b0, launches.back(), extra);
-    if (p->plan_total_tiles > 0x7fffffffll || p->plan_waves * p->geom.n_kv_heads > 0x7fffffffll || p->plan_slots > 0x7fffffffll)
+    if (p->plan_total_units > 0x7fffffffll || p->plan_waves * p->geom.n_kv_heads > 0x7fffffffll || p->plan_slots > 0x7fffffffll)
       return set_err(ELLM_ERR_RANGE, "decode_attention: too much work for one call");
     most_slots = std::max(most_slots, p->plan_slots);
   }

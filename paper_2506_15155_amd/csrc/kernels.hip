@@ -3,9 +3,11 @@
 // Decode attention is a streaming read of every cached K and V row once per step (the paper calls
 // auto-regressive generation memory-bound, Introduction and Sec. 2.2.1), so the kernels are built
 // around 128-bit coalesced loads from the scattered chunks. With one query token per request the
-// arithmetic is G (q heads per kv head) flops per byte read: for one or two heads it stays on
-// ordinary vector lanes; for four and eight, where the lanes of a wave could no longer keep up with
-// the bytes, the two small products of a tile run on the matrix cores.
+// arithmetic is G (q heads per kv head) flops per byte read. Two kernels share the work cut, the
+// workspace and the combine pass: one walks 64-row tiles of a chunk, with an instance per group size (1
+// and 2 heads on ordinary vector lanes; 4 and 8, where the lanes of a wave could no longer keep up with
+// the bytes, on 4x4x4 matrix instructions); the other walks 16-row units and takes any group size and
+// any chunk size with 16x16x32 matrix instructions. Which is used where: tile_kernel() in kernels.hpp.
 //
 // Per-launch metadata (which tensors, their lengths, how the tiles are dealt out) is passed by value
 // in the kernel arguments, so a launch needs no host-to-device copy and no staging buffer whose
@@ -127,6 +129,7 @@ __device__ __forceinline__ void store_stream16(void* p, uint4 v) {
   const u32x4_t t = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
 }
+
 constexpr int CPOL_NT = 2;    // cache-policy operand of the load-to-LDS builtin: non-temporal
 
 typedef const __attribute__((address_space(1))) void* global_cptr_t;
@@ -239,27 +242,28 @@ __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool
 // ---------------------------------------------------------------------------------------------
 // work partition shared by the partial pass, the combine pass and the calibration kernel
 // ---------------------------------------------------------------------------------------------
-// number of tiles of a sequence of len tokens (a tile never straddles a chunk)
-__device__ __forceinline__ int32_t tiles_of(int32_t len, int32_t Tc, int32_t tiles_per_chunk) {
+// number of units (tiles) of a sequence of len tokens (neither straddles a chunk)
+__device__ __forceinline__ int32_t units_of(int32_t len, int32_t Tc, int32_t units_per_chunk, int32_t unit_tokens = UNIT_TOKENS) {
   const int32_t full = len / Tc, rest = len - full * Tc;
-  return full * tiles_per_chunk + (rest + TILE_TOKENS - 1) / TILE_TOKENS;
+  return full * units_per_chunk + (rest + unit_tokens - 1) / unit_tokens;
 }
 
-// request whose tiles include tile number pos of a kv head's sequence: the last b with
-// tile_prefix[b] <= pos (wave-uniform result)
+// request whose units include unit number pos of a kv head's sequence: the last b with
+// unit_prefix[b] <= pos (wave-uniform result)
 __device__ __forceinline__ int find_request(const BatchArgs& a, int pos, int lane) {
   int cnt = 0;
   for (int base = 0; base < a.n_req; base += 64) {
     const int i = base + lane;
-    const bool below = i < a.n_req && a.req[i].tile_prefix <= pos;
+    const bool below = i < a.n_req && a.req[i].unit_prefix <= pos;
     cnt += __popcll(__ballot(below));
   }
   return __builtin_amdgcn_readfirstlane(cnt - 1);
 }
 
-// what a workgroup (one wave) handles: kv head g, wave w of that head, n_tiles tiles of the head's
-// sequence from tile t_lo on, the first of which belongs to request b
-struct Share { int32_t g, w, t_lo, n_tiles, b; };
+// what a workgroup (one wave) handles: kv head g, wave w of that head, n_units steps of the head's
+// sequence from step u_lo on, the first of which belongs to request b. A step is a unit (a tile in the
+// kernel that walks tiles) or, where every wave gets one step, up to step_units units of one request
+struct Share { int32_t g, w, u_lo, n_units, b; };
 
 // Every level of dependent scalar loads costs a wave about a microsecond before its first K/V
 // request can go out, and while the memory system is saturated more than that, so the look-up is
@@ -267,18 +271,19 @@ struct Share { int32_t g, w, t_lo, n_tiles, b; };
 // everything about the request at once.
 __device__ __forceinline__ Share locate_share(const BatchArgs& a, int32_t index, int lane) {
   Share s;
-  const int32_t W = a.waves_per_head, each = a.tiles_each, extra = a.tiles_extra;
+  const int32_t W = a.waves_per_head, each = a.units_each, extra = a.units_extra;
   s.g = index / W;
   s.w = index - s.g * W;
-  s.t_lo = s.w * each + min(s.w, extra);
-  s.n_tiles = each + (s.w < extra ? 1 : 0);
+  s.u_lo = s.w * each + min(s.w, extra);
+  s.n_units = each + (s.w < extra ? 1 : 0);
   if (a.use_wave_req) s.b = (a.wave_req[s.w >> 2] >> ((s.w & 3) * 8)) & 0xff;
-  else s.b = find_request(a, s.t_lo, lane);
+  else s.b = find_request(a, s.u_lo, lane);
   return s;
 }
 
 // ---------------------------------------------------------------------------------------------
-// decode attention, partial pass (split-K): one wave per equal share of a kv head's tiles
+// decode attention, partial pass (split-K), for 1, 2, 4 and 8 q heads per kv head and chunks that whole
+// tiles fill (see tile_kernel): one wave per equal share of a kv head's tiles
 //
 // A tile is up to 64 consecutive rows of one chunk of one (request, kv head). A wave walks its
 // share tile by tile; where a request ends inside the share it writes that request's partial
@@ -299,7 +304,7 @@ __device__ __forceinline__ Share locate_share(const BatchArgs& a, int32_t index,
 // Scores are kept in log2 units (scale_log2 = scale * log2 e).
 // ---------------------------------------------------------------------------------------------
 template <int D, int G, bool APPEND, bool DIRECT>
-__device__ __forceinline__ void decode_partial_body(const PoolView& pv, const uint16_t* __restrict__ q,
+__device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                                     const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
                                                     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
                                                     int32_t g_first, const BatchArgs& a) {
@@ -358,7 +363,7 @@ __device__ __forceinline__ void decode_partial_body(const PoolView& pv, const ui
     cb += 1;                                                                                        \
     const BatchArgs::Req nx_ = a.req[cb];                                                           \
     len = nx_.len;                                                                                  \
-    left = tiles_of(len, Tc, pv.tiles_per_chunk);                                                   \
+    left = units_of(len, Tc, pv.tiles_per_chunk, TILE_TOKENS);                                                   \
     c_np = nx_.n_part;                                                                              \
     c_p0 = nx_.part0;                                                                               \
     walk = tensor_walk<DIRECT>(pv, nx_.tensor);                                                     \
@@ -526,7 +531,7 @@ __device__ __forceinline__ void decode_partial_body(const PoolView& pv, const ui
 
   {
     const Share sh = locate_share(a, blockIdx.x, lane);
-    const int32_t g = sh.g, n_tiles = sh.n_tiles;
+    const int32_t g = sh.g, n_tiles = sh.n_units;
     const int hq0 = g * pv.group + g_first;            // first q head handled here
     // cursor: the tile whose K is in LDS or on its way there. cb: its request; len, walk: that
     // request's length and its table row or base address (read-only for the kernel's lifetime: uniform loads)
@@ -534,8 +539,8 @@ __device__ __forceinline__ void decode_partial_body(const PoolView& pv, const ui
     const BatchArgs::Req first = a.req[cb];
     int32_t len = first.len;
     TensorWalk walk = tensor_walk<DIRECT>(pv, first.tensor);
-    const int32_t tile0 = sh.t_lo - first.tile_prefix;
-    int32_t left = tiles_of(len, Tc, pv.tiles_per_chunk) - tile0;
+    const int32_t tile0 = sh.u_lo - first.unit_prefix;
+    int32_t left = units_of(len, Tc, pv.tiles_per_chunk, TILE_TOKENS) - tile0;
     int32_t slot = tile0 / pv.tiles_per_chunk;
     int32_t r = (tile0 - slot * pv.tiles_per_chunk) * TILE_TOKENS;
     int32_t nv_c = min(TILE_TOKENS, min(Tc - r, len - (slot * Tc + r)));
@@ -709,16 +714,403 @@ __device__ __forceinline__ void decode_partial_body(const PoolView& pv, const ui
 // whole query rows and the matrix-core accumulators in registers, are compiled without it and do
 // not spill.
 template <int D, int G, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_partial_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_tile_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
-  decode_partial_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
+  decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
 }
 template <int D, int G, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_partial_kernel_wide(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_tile_kernel_wide(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
-  decode_partial_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
+  decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
+}
+
+// ---------------------------------------------------------------------------------------------
+// decode attention, partial pass (split-K), for every other group and chunk size: one wave per equal share
+// of a kv head's units
+//
+// A unit is up to UNIT_TOKENS = 16 consecutive rows of one chunk of one (request, kv head); a tile is
+// up to U units of one request, not necessarily of one chunk. A wave walks its share tile by tile:
+// the next tile's K is asked for as soon as this one's scores are formed, its V as soon as this one's
+// weighted sum is, so that one of the two is on its way at any time.
+//   scores   S^T = K Q^T by 16x16x32 matrix instructions, one unit by up to 16 q heads: A = the unit's
+//      rows (lane 16 g + c: row c, 16 bytes per product), B = the query rows (lane: head c, the same
+//      bytes of it). To load whole cache lines a wave-wide load takes 128 bytes of each of 8 rows instead
+//      of 64 of 16: load j of a half row gives lane (g, c) piece g + 4 (c0 ^ j) of row c with its lowest
+//      bit, c0, replaced by j. Product x takes, per lane, load c0 ^ x: the same piece g + 4 x in every lane,
+//      of row c ^ x, so that its result differs from x = 0's by an exchange of registers only.
+//      Register i of lane (g, c) is then the score of token 4 g + i for head c.
+//   softmax  a lane owns one head (c) and four tokens of every unit: the tile's maximum is lane-local up
+//      to two cross-lane swaps, and the weights are already where the next product wants them: as the sum
+//      of two bf16 values, the next one below the weight and the rest (to 2^-16 of the weight; both
+//      positive, so an infinite V stays infinite), one product each. With the weights rounded to one bf16
+//      value the result is as far from 64 bits as the tile kernels' (2.1e-3 instead of 1.6e-3, the
+//      rounding of the result included), and further where those cut a request more finely.
+//   PV       O^T = V^T P^T, two units at a time: contraction index of lane group g = its four tokens of
+//      either unit. A = V, loaded as whole rows (lane (g, c): dims E c .. E c + E - 1 of rows 4 g + i) and
+//      transposed in registers by v_perm_b32, one product per e = dim % E; B = the weights.
+//      Register i of product e in lane (g, c) is dim E (4 g + i) + e of head c: every per-head quantity
+//      (m, l, the rescaling) sits in the lanes that need it, and a lane ends with 4 E consecutive dims.
+// Nothing goes through LDS. The cost per byte does not depend on the number of q heads up to 16, so every
+// group size up to that is one pass over K and V. Bound by HBM: 48 requests of 6 q heads per kv head (278 MB
+// of K and V) 92.4 -> 51.8 us with the combine pass (the tile kernels took two passes), 64 requests of 16
+// heads of 64 (398 MB) 144 -> 69.8, 16-token chunks (187 MB) 50.8 -> 36.4.
+// Tried on these and on the 8B-shaped layer: two or three tiles in registers (no faster, and what does not
+// fit 256 registers goes through accumulation registers: 2 to 4 % slower); tiles of 64 tokens (pages
+// 37.4); K in 64-byte pieces of 16 rows (16 heads of 64: 77), in whole rows of 4 (no change, more
+// exchanges); an exit between a tile's loads (the compiler then waits for everything in flight).
+// Scores are kept in log2 units (scale_log2 = scale * log2 e).
+// ---------------------------------------------------------------------------------------------
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t words4_t;
+typedef __attribute__((ext_vector_type(2))) uint32_t words2_t;
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef const __attribute__((address_space(1))) char* gptr_t;
+typedef __attribute__((address_space(1))) char* gwptr_t;
+
+constexpr int BUFFER_RAW = 0x00027000;    // last word of a buffer descriptor: raw dwords, range check on the byte offset
+__device__ __forceinline__ f32x4_t mfma16(words4_t a, words4_t b, f32x4_t c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
+}
+// two floats rounded to nearest-even bf16, the first in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
+}
+
+enum : uint32_t { T_FIRST = 1, T_LAST = 2, T_FIN = 4 };   // a tile starts a request here, ends it, ends the share
+// the largest bf16 value below a positive float, as a float's bits; 0 for 0, NaN for NaN
+__device__ __forceinline__ uint32_t bf16_below(float p) {
+  return __builtin_elementwise_sub_sat(__float_as_uint(p), 1u) & 0xffff0000u;
+}
+
+template <int U>
+struct TileInfo {                    // what is known of a tile before its loads are issued (uniform)
+  int32_t n, b, part;                // units, request, partial slot of the request in this wave (-1: finished here)
+  uint32_t flags;                    // T_*
+  int32_t tail;                      // rows of its last unit
+  int32_t nv[U];                     // rows of each unit (0: the tile has no such unit)
+  int32_t r[U];                      // first row of the unit in its chunk
+  uint32_t at[U];                    // its chunk (table entry, or slot of the tensor's own range)
+  const char* base;                  // start of the pool, or of the tensor's range
+};
+
+template <int D, int U, bool APPEND, bool DIRECT>
+__device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
+                                            const char* __restrict__ k_new, const char* __restrict__ v_new,
+                                            float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
+                                            int32_t g_first, int32_t n_heads, const BatchArgs& a) {
+  constexpr int P = D / 32;          // products along a row = 16-byte pieces of K, dwords of a V row, per lane
+  constexpr int ROWB = D * 2, E = D / 16, VB = E * 2;
+  static_assert(U % 2 == 0, "PV takes two units at a time");
+  const int lane = threadIdx.x, c = lane & 15, g16 = lane >> 4;
+  const int32_t Tc = pv.tokens_per_chunk;
+  const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
+
+  const Share sh = locate_share(a, blockIdx.x, lane);
+  const int32_t g = sh.g;
+  const int32_t hq0 = g * pv.group + g_first;        // first q head handled here
+  const int32_t head = min(c, n_heads - 1);          // lanes beyond the last head repeat it and write nothing
+
+  // ---- cursor: the next tile to be asked for ----
+  int32_t cb = sh.b, rem_share = sh.n_units, len, slot, r, rem_req, part;
+  uint32_t first = T_FIRST;
+  TensorWalk walk;
+  {
+    const BatchArgs::Req rq = a.req[cb];
+    len = rq.len;
+    walk = tensor_walk<DIRECT>(pv, rq.tensor);
+    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units;
+    rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
+    if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
+    slot = u0 / pv.units_per_chunk;
+    r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
+    part = rq.n_part == 1 ? -1 : rq.part0 + (sh.w - rq.wave_first);
+  }
+  auto advance = [&](TileInfo<U>& t) __attribute__((always_inline)) {
+    t.n = min(U, min(rem_share, rem_req));
+    t.b = cb;
+    t.part = part;
+    t.flags = first;
+    t.base = DIRECT ? walk.tbase : pv.base;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      if (u == 0 || u < t.n) {
+        t.at[u] = DIRECT ? (uint32_t)slot : (uint32_t)walk.trow[slot];
+        t.r[u] = r;
+        t.nv[u] = min(UNIT_TOKENS, min(Tc - r, len - (slot * Tc + r)));
+        t.tail = t.nv[u];
+        if (u < t.n - 1 || (t.n > 0 && rem_req > t.n)) {   // there is a next unit of this request
+          r += UNIT_TOKENS;
+          if (r >= Tc) { r = 0; slot += 1; }
+        }
+      } else {
+        t.at[u] = t.at[u - 1];
+        t.r[u] = t.r[u - 1];
+        t.nv[u] = 0;
+      }
+    }
+    if (t.n == 0) t.nv[0] = 0;                       // past the end of the share
+    rem_req -= t.n;
+    rem_share -= t.n;
+    first = 0;
+    if (rem_req == 0) {
+      t.flags |= T_LAST;
+      first = T_FIRST;
+    }
+    if (rem_share == 0) t.flags |= T_FIN;
+    if (rem_req == 0 && rem_share > 0) {
+      cb += 1;
+      const BatchArgs::Req rq = a.req[cb];
+      len = rq.len;
+      rem_req = units_of(len, Tc, pv.units_per_chunk);
+      walk = tensor_walk<DIRECT>(pv, rq.tensor);
+      slot = 0;
+      r = 0;
+      part = rq.n_part == 1 ? -1 : rq.part0;
+    }
+  };
+  auto unit_base = [&](const TileInfo<U>& t, int u) __attribute__((always_inline)) {
+    return const_cast<char*>(t.base) + (uint64_t)t.at[u] * pv.chunk_bytes + ((uint64_t)(g * 2) * Tc + t.r[u]) * ROWB;
+  };
+  // the rows of a unit as a buffer of their own
+  auto rows_of = [&](char* base, int32_t rows) __attribute__((always_inline)) {
+    // (uniform values all; said so, because the descriptor has to be in scalar registers)
+    const uint64_t b = (uint64_t)base;
+    const uint64_t bs = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+                        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
+    return __builtin_amdgcn_make_buffer_rsrc((void*)bs, 0, __builtin_amdgcn_readfirstlane(rows * ROWB), BUFFER_RAW);
+  };
+  // how many of them are in the chunk: all but the one that a fused append is about to put there
+  auto there = [&](const TileInfo<U>& t, int u) __attribute__((always_inline)) {
+    return t.nv[u] - (APPEND && (t.flags & T_LAST) && u == t.n - 1 ? 1 : 0);
+  };
+
+  // ---- loads ----
+  // Buffer loads with the unit's rows as their range: rows past its end, and units that the tile does not
+  // have, come back as zeros without a memory access. So the addresses of a lane are the same for every
+  // tile, a wave's last round costs no traffic for the tile after it, V rows that are not there have the
+  // value their weight 0 needs, and the number of loads does not depend on the tile (the waits count them).
+  words4_t k[U][P], qr[P], kn[P / 2];
+  uint32_t v[U][4][P], vn[P];
+  const int c1 = (c >> 1) & 1;
+  // of a unit's K, load j of a half row gives this lane row krow + 8 j, 16 bytes at kpiece(j) of the half
+  const int krow = 4 * (c & 1) + (c >> 2), voff = g16 * ROWB + c * VB;
+  auto kpiece = [&](int32_t j) __attribute__((always_inline)) { return (uint32_t)(g16 + 4 * (c1 ^ j)) * 16; };
+  // Before a tile's own rows, so that waiting for these does not mean waiting for what is asked for later:
+  // with the first tile of a request its query (the one before it has had its last scores formed), and,
+  // fused append, with the last one the new rows. There len counts the new token already, but its row is
+  // still in k_new / v_new; the wave that reaches the end of a request's sequence takes it from there, puts
+  // it where the last tile's loads would have found it, and writes it to the chunk.
+  auto new_row = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    return ((int64_t)(a.q_row0 + t.b) * pv.n_kv_heads + g) * ROWB;
+  };
+  auto load_row = [&](__amdgpu_buffer_rsrc_t rows, int32_t at, uint32_t (&dst)[P]) __attribute__((always_inline)) {
+    if constexpr (P == 4) {
+      const words4_t w = __builtin_amdgcn_raw_buffer_load_b128(rows, at, 0, CPOL_NT);
+      dst[0] = w.x; dst[1] = w.y; dst[2] = w.z; dst[3] = w.w;
+    } else {
+      const words2_t w = __builtin_amdgcn_raw_buffer_load_b64(rows, at, 0, CPOL_NT);
+      dst[0] = w.x; dst[1] = w.y;
+    }
+  };
+  auto issue_k = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    if (t.flags & T_FIRST) {
+      const gptr_t qp = (gptr_t)(q + ((int64_t)(a.q_row0 + t.b) * pv.n_q_heads + hq0 + head) * D) + g16 * 16;
+#pragma unroll
+      for (int p = 0; p < P; p++) qr[p] = *(const __attribute__((address_space(1))) words4_t*)(qp + p * 64);
+    }
+    if (APPEND && (t.flags & T_LAST)) {
+      const gptr_t kp = (gptr_t)(k_new + new_row(t)) + kpiece((t.tail - 1) >> 3 & 1);
+#pragma unroll
+      for (int h = 0; h < P / 2; h++) kn[h] = *(const __attribute__((address_space(1))) words4_t*)(kp + h * 128);
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const auto rows = rows_of(unit_base(t, u), there(t, u));
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+#pragma unroll
+        for (int h = 0; h < P / 2; h++)
+          k[u][2 * h + j] = __builtin_amdgcn_raw_buffer_load_b128(rows, (krow + 8 * j) * ROWB + kpiece(j) + h * 128, 0, CPOL_NT);
+    }
+  };
+  auto issue_v = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    if (APPEND && (t.flags & T_LAST)) load_row(rows_of(const_cast<char*>(v_new) + new_row(t), 1), c * VB, vn);
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const auto rows = rows_of(unit_base(t, u) + plane, there(t, u));
+#pragma unroll
+      for (int i = 0; i < 4; i++) load_row(rows, voff + 4 * i * ROWB, v[u][i]);
+    }
+  };
+
+  // ---- arithmetic ----
+  float m = NEG_BIG, l = 0.f;
+  f32x4_t acc[E], s[U];
+  auto scores = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    if (APPEND && (t.flags & T_LAST)) {
+      // the new token's K row replaces what the loads found in its place, and goes into the chunk (a unit that
+      // the tile does not have has the address of the one before it)
+      const int32_t rl = t.tail - 1;
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int j = 0; j < 2; j++) {
+          const bool mine = u == t.n - 1 && krow + 8 * j == rl;
+#pragma unroll
+          for (int h = 0; h < P / 2; h++) k[u][2 * h + j] = mine ? kn[h] : k[u][2 * h + j];
+        }
+      if (krow == (rl & 7)) {
+        const gwptr_t dst = (gwptr_t)unit_base(t, U - 1) + (uint32_t)(rl * ROWB) + kpiece(rl >> 3);
+#pragma unroll
+        for (int h = 0; h < P / 2; h++) *(__attribute__((address_space(1))) words4_t*)(dst + h * 128) = kn[h];
+      }
+    }
+    const bool odd = c1 != 0;
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      f32x4_t d0 = {0.f, 0.f, 0.f, 0.f}, d1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int h = 0; h < P / 2; h++) {
+        const words4_t k0 = k[u][2 * h], k1 = k[u][2 * h + 1];
+        d0 = mfma16(odd ? k1 : k0, qr[2 * h], d0);
+        d1 = mfma16(odd ? k0 : k1, qr[2 * h + 1], d1);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; i++) s[u][i] = (d0[i] + d1[i ^ 2]) * scale_log2;
+    }
+  };
+  auto weigh = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    if (t.flags & T_FIRST) {
+      m = NEG_BIG;
+      l = 0.f;
+#pragma unroll
+      for (int e = 0; e < E; e++) acc[e] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    }
+    bool full = true;
+#pragma unroll
+    for (int u = 0; u < U; u++) full &= t.nv[u] == UNIT_TOKENS;
+    if (!full) {
+      // scores of rows that are not there
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) s[u][i] = 4 * i + g16 < t.nv[u] ? s[u][i] : -INFINITY;
+    }
+    if (APPEND && (t.flags & T_LAST)) {
+      // the new token's V row
+      const int32_t rl = t.tail - 1;
+#pragma unroll
+      for (int u = 0; u < U; u++)
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+          const bool mine = u == t.n - 1 && 4 * i + g16 == rl;
+#pragma unroll
+          for (int w = 0; w < P; w++) v[u][i][w] = mine ? vn[w] : v[u][i][w];
+        }
+      if (g16 == (rl & 3)) {
+        const gwptr_t dst = (gwptr_t)unit_base(t, U - 1) + plane + (uint32_t)(rl * ROWB + c * VB);
+        if constexpr (P == 4) *(__attribute__((address_space(1))) words4_t*)dst = words4_t{vn[0], vn[1], vn[2], vn[3]};
+        else *(__attribute__((address_space(1))) words2_t*)dst = words2_t{vn[0], vn[1]};
+      }
+    }
+    float mx = fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3]));
+#pragma unroll
+    for (int u = 1; u < U; u++) mx = fmaxf(mx, fmaxf(fmaxf(s[u][0], s[u][1]), fmaxf(s[u][2], s[u][3])));
+    const float mn = fmaxf(m, max_xor32(max_xor16(mx)));
+    if (__builtin_amdgcn_ballot_w64(mn > m)) {       // some head has a new maximum
+      const float alpha = fast_exp2(m - mn);
+      l *= alpha;
+#pragma unroll
+      for (int e = 0; e < E; e++) acc[e] *= alpha;
+      m = mn;
+    }
+    uint32_t pk[U][2], rest[U][2];
+#pragma unroll
+    for (int u = 0; u < U; u++)
+#pragma unroll
+      for (int h = 0; h < 2; h++) {
+        const float p0 = fast_exp2(s[u][2 * h] - m), p1 = fast_exp2(s[u][2 * h + 1] - m);
+        l += p0 + p1;
+        const uint32_t b0 = bf16_below(p0), b1 = bf16_below(p1);
+        pk[u][h] = __builtin_amdgcn_perm(b1, b0, 0x07060302u);
+        rest[u][h] = pack_bf16(p0 - __uint_as_float(b0), p1 - __uint_as_float(b1));
+      }
+#pragma unroll
+    for (int u = 0; u < U; u += 2) {
+      const words4_t pb = {pk[u][0], pk[u][1], pk[u + 1][0], pk[u + 1][1]};
+      const words4_t pr = {rest[u][0], rest[u][1], rest[u + 1][0], rest[u + 1][1]};
+#pragma unroll
+      for (int e = 0; e < E; e++) {
+        const uint32_t sel = (e & 1) ? 0x07060302u : 0x05040100u;
+        const int w = e / 2;
+        const words4_t va = {__builtin_amdgcn_perm(v[u][1][w], v[u][0][w], sel),
+                             __builtin_amdgcn_perm(v[u][3][w], v[u][2][w], sel),
+                             __builtin_amdgcn_perm(v[u + 1][1][w], v[u + 1][0][w], sel),
+                             __builtin_amdgcn_perm(v[u + 1][3][w], v[u + 1][2][w], sel)};
+        acc[e] = mfma16(va, pr, mfma16(va, pb, acc[e]));
+      }
+    }
+  };
+  auto finish = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    const float L = add_xor32(add_xor16(l));
+    if (c >= n_heads) return;
+    if (t.part < 0) {
+      // the whole request lay inside this wave's share: this is the final result. Normalise, round and
+      // write the output rows; no workspace traffic, no second pass for this request
+      const float inv = 1.f / L;
+      uint16_t* o = out + ((int64_t)(a.q_row0 + t.b) * pv.n_q_heads + hq0 + c) * D + g16 * (4 * E);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < E; e += 2)
+          *reinterpret_cast<uint32_t*>(o + i * E + e) = pack_bf16(acc[e][i] * inv, acc[e + 1][i] * inv);
+    } else {
+      // accumulators: one row of D floats per (partial slot, q head), every row a whole number of cache
+      // lines; m and l of all partials sit together behind the rows, two floats each
+      const int64_t row = ((int64_t)g * a.parts_per_head + t.part) * pv.group + g_first + c;
+      float* wout = ws + row * D + g16 * (4 * E);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < E; e += 4)
+          *reinterpret_cast<float4*>(wout + i * E + e) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+      if (g16 == 0)
+        *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(m, L);
+    }
+  };
+
+  // No exit before the round's last load (the share's last round asks for rows it does not use): what is in
+  // flight when a tile is waited for is the same on every path, so the compiler counts the loads exactly.
+  TileInfo<U> t, next;
+  advance(t);
+  issue_k(t);
+  issue_v(t);
+  __builtin_amdgcn_sched_barrier(0);                 // the loads stay where they are asked for
+  advance(next);
+  uint32_t done;
+  do {
+    scores(t);
+    issue_k(next);
+    __builtin_amdgcn_sched_barrier(0);
+    weigh(t);
+    if (t.flags & (T_LAST | T_FIN)) finish(t);       // the request ends here, or the share does
+    done = t.flags & T_FIN;
+    issue_v(next);
+    __builtin_amdgcn_sched_barrier(0);
+    t = next;
+    advance(next);
+  } while (!done);
+}
+
+// Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
+// the accumulation registers, which ordinary instructions cannot read.
+template <int D, int U, bool APPEND, bool DIRECT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
+    PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
+  decode_unit_body<D, U, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -814,7 +1206,7 @@ __global__ __launch_bounds__(256) void read_kernel(const uint4* __restrict__ src
 }
 
 // the K/V rows a decode over this batch reads, with the same work partition and load shape (one
-// wave per share of the same cut, 64-row tiles, 128-bit loads), but no arithmetic
+// wave per share of the same cut, up to 64 rows at a time, 128-bit loads), but no arithmetic
 template <int D, bool DIRECT>
 __global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __restrict__ sink, BatchArgs a) {
   constexpr int LPR = D / 8, RPW = 64 / LPR, NL = 64 / RPW, ROWB = D * 2;
@@ -827,13 +1219,17 @@ __global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __
     const int32_t g = sh.g;
     int32_t cb = sh.b;
     BatchArgs::Req rec = a.req[cb];
-    const int32_t tile0 = sh.t_lo - rec.tile_prefix;
-    int32_t left = tiles_of(rec.len, Tc, pv.tiles_per_chunk) - tile0;
-    int32_t slot = tile0 / pv.tiles_per_chunk;
-    int32_t r = (tile0 - slot * pv.tiles_per_chunk) * TILE_TOKENS;
-    for (int32_t it = 0; it < sh.n_tiles; it++) {
+    const int32_t ut = a.unit_tokens, upc = (Tc + ut - 1) / ut;
+    const int32_t u0 = (sh.u_lo - rec.unit_prefix) * a.step_units;
+    int32_t left = units_of(rec.len, Tc, upc, ut) - u0, todo = sh.n_units;
+    if (a.step_units > 1) todo = min(todo * a.step_units, left);
+    int32_t slot = u0 / upc;
+    int32_t r = (u0 - slot * upc) * ut;
+    while (todo > 0) {
       const TensorWalk walk = tensor_walk<DIRECT>(pv, rec.tensor);
-      const int32_t nv = min(TILE_TOKENS, min(Tc - r, rec.len - (slot * Tc + r)));
+      // up to 64 rows at a time, of one chunk
+      const int32_t n = min(min(todo, left), min(64 / ut, upc - r / ut));
+      const int32_t nv = min(ut * n, min(Tc - r, rec.len - (slot * Tc + r)));
       const char* kb = chunk_addr<DIRECT>(pv, walk, slot) + ((uint64_t)(g * 2) * Tc + r) * ROWB;
       const char* vb = kb + (uint64_t)Tc * ROWB;
       uint4 kr[NL], vr[NL];
@@ -845,18 +1241,17 @@ __global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __
       }
 #pragma unroll
       for (int u = 0; u < NL; u++) x ^= kr[u].x ^ kr[u].y ^ kr[u].z ^ kr[u].w ^ vr[u].x ^ vr[u].y ^ vr[u].z ^ vr[u].w;
-      if (it + 1 < sh.n_tiles) {
-        if (left == 1) {
-          cb += 1;
-          rec = a.req[cb];
-          left = tiles_of(rec.len, Tc, pv.tiles_per_chunk);
-          slot = 0;
-          r = 0;
-        } else {
-          left -= 1;
-          r += TILE_TOKENS;
-          if (r >= Tc) { r = 0; slot += 1; }
-        }
+      todo -= n;
+      left -= n;
+      if (left > 0) {
+        r += ut * n;
+        if (r >= Tc) { r = 0; slot += 1; }
+      } else if (todo > 0) {
+        cb += 1;
+        rec = a.req[cb];
+        left = units_of(rec.len, Tc, upc, ut);
+        slot = 0;
+        r = 0;
       }
     }
   }
@@ -931,23 +1326,22 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
   return 0;
 }
 
-// widest template instance that does not exceed the q heads still to do in a group
-static int group_step(int left) { return left >= 8 ? 8 : left >= 4 ? 4 : left >= 2 ? 2 : 1; }
+// units per tile of the kernel that walks units: 8 KB of K and 8 KB of V for either head size
+template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
 
 template <int D>
-static const void* partial_kernel_ptr(int step) {
-  switch (step) {
-    case 8: return (const void*)decode_partial_kernel_wide<D, 8, true, false>;
-    case 4: return (const void*)decode_partial_kernel_wide<D, 4, true, false>;
-    case 2: return (const void*)decode_partial_kernel<D, 2, true, false>;
-    default: return (const void*)decode_partial_kernel<D, 1, true, false>;
+static const void* partial_kernel_ptr(int group, bool tiles) {
+  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, true, false>;
+  if constexpr (D == 128) {
+    if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false>;
+    if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false>;
   }
+  return group == 2 ? (const void*)decode_tile_kernel<D, 2, true, false> : (const void*)decode_tile_kernel<D, 1, true, false>;
 }
 
-int partial_waves_per_cu(int head_dim, int group) {
-  // the q heads of a group are handled 8, 4, 2 or 1 at a time; plan for the widest instance used
-  const int step = group_step(group);
-  const void* f = head_dim == 128 ? partial_kernel_ptr<128>(step) : partial_kernel_ptr<64>(step);
+int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
+  const bool tiles = tile_kernel(head_dim, group, tokens_per_chunk);
+  const void* f = head_dim == 128 ? partial_kernel_ptr<128>(group, tiles) : partial_kernel_ptr<64>(group, tiles);
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64, 0) != hipSuccess || n < 1) n = 1;
   return n;
@@ -956,56 +1350,50 @@ int partial_waves_per_cu(int head_dim, int group) {
 // ev0 / ev1 (either may be NULL): events that take the kernel's own start and end times (the
 // runtime's extended launch attaches them to the kernel's dispatch, so no marker of its own goes
 // into the stream and the time between them is the kernel's duration)
-template <int D, int G, bool APPEND, bool DIRECT>
-static void launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
-                             void* out, float scale_log2, int32_t g_first, const BatchArgs& a, hipStream_t stream,
-                             hipEvent_t ev0, hipEvent_t ev1) {
+template <typename Kernel, typename... Args>
+static void launch_timed(Kernel kernel, unsigned grid, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, Args... args) {
+  if (ev0 || ev1) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, stream, ev0, ev1, 0, args...);
+  else hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, stream, args...);
+}
+
+template <int D, bool APPEND, bool DIRECT>
+static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
+                            void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
+                            hipEvent_t ev_stop) {
   const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
-  if (ev0 || ev1) {
-    if constexpr (G >= 4)
-      hipExtLaunchKernelGGL((decode_partial_kernel_wide<D, G, APPEND, DIRECT>), dim3(grid), dim3(64), 0, stream, ev0, ev1, 0, pv,
-                            (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, g_first, a);
-    else
-      hipExtLaunchKernelGGL((decode_partial_kernel<D, G, APPEND, DIRECT>), dim3(grid), dim3(64), 0, stream, ev0, ev1, 0, pv,
-                            (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, g_first, a);
-    return;
+  if (a.unit_tokens == TILE_TOKENS) {
+    auto go = [&](auto kernel) {
+      launch_timed(kernel, grid, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
+                   (uint16_t*)out, scale_log2, 0, a);
+    };
+    if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT>);
+    else if (pv.group == 2) go(decode_tile_kernel<D, 2, APPEND, DIRECT>);
+    if constexpr (D == 128) {
+      if (pv.group == 4) go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT>);
+      else if (pv.group == 8) go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT>);
+    }
+    ELLM_HIP_CHECK_LAUNCH();
+    return 0;
   }
-  if constexpr (G >= 4)
-    hipLaunchKernelGGL((decode_partial_kernel_wide<D, G, APPEND, DIRECT>), dim3(grid), dim3(64), 0, stream, pv,
-                       (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, g_first, a);
-  else
-    hipLaunchKernelGGL((decode_partial_kernel<D, G, APPEND, DIRECT>), dim3(grid), dim3(64), 0, stream, pv,
-                       (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, g_first, a);
+  // a group of more than HEADS_PER_PASS q heads is covered by several launches over the same K/V: the
+  // first of them takes the start time, the last one the end time
+  for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
+    const int n = std::min(HEADS_PER_PASS, pv.group - done);
+    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, stream, done == 0 ? ev_start : nullptr,
+                 done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
+                 (uint16_t*)out, scale_log2, done, n, a);
+    ELLM_HIP_CHECK_LAUNCH();
+  }
+  return 0;
 }
 
-template <int D, int G>
-static void launch_partial_t(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
-                             void* out, float scale_log2, int32_t g_first, const BatchArgs& a, hipStream_t stream,
-                             hipEvent_t ev0, hipEvent_t ev1) {
-  if (k_new && pv.vbase) launch_partial_i<D, G, true, true>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a, stream, ev0, ev1);
-  else if (k_new) launch_partial_i<D, G, true, false>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a, stream, ev0, ev1);
-  else if (pv.vbase) launch_partial_i<D, G, false, true>(pv, q, nullptr, nullptr, ws, out, scale_log2, g_first, a, stream, ev0, ev1);
-  else launch_partial_i<D, G, false, false>(pv, q, nullptr, nullptr, ws, out, scale_log2, g_first, a, stream, ev0, ev1);
-}
-
-// a group size that is not 8, 4, 2 or 1 is covered by several launches over the same K/V
 template <int D>
 static int launch_partial_d(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
                             void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
                             hipEvent_t ev_stop) {
-  int done = 0;
-  while (done < pv.group) {
-    const int step = group_step(pv.group - done);
-    // the first launch of the call takes the start time, the last one the end time
-    hipEvent_t ev0 = done == 0 ? ev_start : nullptr, ev1 = done + step >= pv.group ? ev_stop : nullptr;
-    if (step == 8) launch_partial_t<D, 8>(pv, q, k_new, v_new, ws, out, scale_log2, done, a, stream, ev0, ev1);
-    else if (step == 4) launch_partial_t<D, 4>(pv, q, k_new, v_new, ws, out, scale_log2, done, a, stream, ev0, ev1);
-    else if (step == 2) launch_partial_t<D, 2>(pv, q, k_new, v_new, ws, out, scale_log2, done, a, stream, ev0, ev1);
-    else launch_partial_t<D, 1>(pv, q, k_new, v_new, ws, out, scale_log2, done, a, stream, ev0, ev1);
-    ELLM_HIP_CHECK_LAUNCH();
-    done += step;
-  }
-  return 0;
+  auto go = [&](auto launch) { return launch(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop); };
+  if (k_new) return pv.vbase ? go(launch_partial_i<D, true, true>) : go(launch_partial_i<D, true, false>);
+  return pv.vbase ? go(launch_partial_i<D, false, true>) : go(launch_partial_i<D, false, false>);
 }
 
 int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,

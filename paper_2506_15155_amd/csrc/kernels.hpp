@@ -10,7 +10,10 @@ namespace ellm {
 constexpr int MAX_LAUNCH_REQ = 128;   // requests described by one launch's kernel arguments (4 KB in all)
 constexpr int MAX_WAVE_REQ = 512;     // waves per kv head that the request lookup table covers
 constexpr int MAX_PATCH = 448;        // table entries patched by one launch
-constexpr int TILE_TOKENS = 64;       // rows of K (and V) one wave handles at a time
+constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of one chunk a wave handles at a time
+constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
+constexpr int STEP_UNITS = 4;         // units of a request that are worth a wave of their own
+constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walks units handles in one pass over K and V
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
 constexpr int WS_ML = 2;              // floats per partial and q head in the (m, l) region of the workspace
 constexpr size_t STATIC_WS_BYTES = 16u << 20;   // the fixed workspace of the entry point that allocates nothing
@@ -24,17 +27,18 @@ struct PoolView {
   uint32_t chunk_bytes;
   int32_t tokens_per_chunk;
   int32_t tiles_per_chunk;    // ceil(tokens_per_chunk / TILE_TOKENS); a tile never straddles a chunk
+  int32_t units_per_chunk;    // ceil(tokens_per_chunk / UNIT_TOKENS); nor does a unit
   int32_t max_slots;
   int32_t n_q_heads, n_kv_heads, head_dim, group;
 };
 
 // One decode launch: requests [q_row0, q_row0 + n_req) of the caller's batch.
-// For every kv head the tiles of all requests, laid end to end in request order, form one sequence
-// of tiles_per_head tiles, which is dealt out evenly to waves_per_head waves: wave w takes
-// tiles_each tiles, the first tiles_extra waves one more, each from where the wave before it
+// For every kv head the units of all requests, laid end to end in request order, form one sequence
+// of units_per_head units, which is dealt out evenly to waves_per_head waves: wave w takes
+// units_each units, the first units_extra waves one more, each from where the wave before it
 // stopped. A wave whose share runs from one request into the next finishes a result for each; so
 // request b is covered by n_part waves per kv head, numbered from the wave that holds its first
-// tile (wave_first). A request that lies wholly inside one wave's share (n_part == 1) needs no
+// unit (wave_first). A request that lies wholly inside one wave's share (n_part == 1) needs no
 // second pass: that wave normalises and writes the output row itself. Only the others ("split"
 // requests) get partial results in the workspace, part0 + j for the j-th wave, and a combine pass.
 // A launch has one wave for every SIMD of the GPU (a second wave on a SIMD is served markedly
@@ -48,14 +52,17 @@ struct PoolView {
 struct BatchArgs {
   int32_t n_req;
   int32_t q_row0;             // row of the first request in q / out
-  int32_t tiles_per_head;     // tiles of all requests of the launch, for one kv head
-  int32_t waves_per_head;     // <= tiles_per_head
-  int32_t tiles_each, tiles_extra;   // tiles_per_head = waves_per_head * tiles_each + tiles_extra
+  int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
+  int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave gets: up to this
+                              // many units of one request (then "units" in the fields below are such steps)
+  int32_t units_per_head;     // units of all requests of the launch, for one kv head
+  int32_t waves_per_head;     // <= units_per_head
+  int32_t units_each, units_extra;   // units_per_head = waves_per_head * units_each + units_extra
   int32_t parts_per_head;     // partial slots per kv head = sum of n_part over the split requests
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
   int32_t n_split_req;        // requests with n_part > 1: the combine pass runs for these only
-  // request that holds the first tile of wave w of a kv head, one byte each: lets a wave find its
+  // request that holds the first unit of wave w of a kv head, one byte each: lets a wave find its
   // request with one scalar load instead of a search through the prefix entries
   uint32_t wave_req[MAX_WAVE_REQ / 4];
   // the split requests in ascending order, one byte each
@@ -63,9 +70,9 @@ struct BatchArgs {
   // per request, one record, so that a wave gets all of it with one round of scalar loads
   struct Req {
     int32_t len, tensor;
-    int32_t tile_prefix;      // tiles of the requests before this one
-    int32_t wave_first;       // wave that holds this request's first tile
-    int32_t n_part;           // waves that hold tiles of this request
+    int32_t unit_prefix;      // units of the requests before this one
+    int32_t wave_first;       // wave that holds this request's first unit
+    int32_t n_part;           // waves that hold units of this request
     int32_t part0;            // first partial slot of the request within a kv head's slots (split requests)
   } req[MAX_LAUNCH_REQ];
 };
@@ -92,8 +99,22 @@ struct CopyArgs {
   int32_t host_slot[MAX_COPY];
 };
 
-// resident waves of the partial-pass kernel per compute unit (occupancy query), per (head_dim, group)
-int partial_waves_per_cu(int head_dim, int group);
+// Which of the two attention kernels a pool's calls use: the one that walks 64-row tiles of a chunk, or the one
+// that walks 16-row units. The first has no instance for group sizes that are not 1, 2, 4 or 8 (it would
+// read K and V two or three times: 6 heads 92 us against 52, 16 heads of 64 145 against 70) and loads whole
+// tiles, so it pays for chunks that do not fill them. Measured on 32 requests of 1500 to 3500 tokens, 8 kv
+// heads, tiles against units, us: head size 128, 4 q heads per kv head: chunks of 16 tokens 80 / 58, 24:
+// 65 / 58, 40: 55.8 / 57.4, 64: 56.1 / 58.5, 512: 55.7 / 59.2, and alike for 1, 2 and 8 heads; head size
+// 64, 1 head: 24: 44 / 32, 40: 33.0 / 31.8, 48: 30.5 / 31.4, 80: 32.7 / 31.5, 102: 30.4 / 31.8, 2 heads
+// within 1 %; 4 heads: 48: 33.1 / 31.6, 512: 33.5 / 32.0, 8 heads: 39 / 32 and 38 / 33.
+inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
+  const int64_t Tc = tokens_per_chunk, padded = (Tc + TILE_TOKENS - 1) / TILE_TOKENS * TILE_TOKENS;
+  if (head_dim == 128) return (group == 1 || group == 2 || group == 4 || group == 8) && padded * 5 <= Tc * 8;
+  return (group == 1 || group == 2) && padded * 3 <= Tc * 4;
+}
+
+// resident waves of the partial-pass kernel per compute unit (occupancy query)
+int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk);
 
 // each returns 0 or a hipError_t value
 int launch_table_patch(int32_t* table, const PatchArgs& a, hipStream_t stream);
