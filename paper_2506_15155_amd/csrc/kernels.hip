@@ -1070,12 +1070,13 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       // accumulators: one row of D floats per (partial slot, q head), every row a whole number of cache
       // lines; m and l of all partials sit together behind the rows, two floats each
       const int64_t row = ((int64_t)g * a.parts_per_head + t.part) * pv.group + g_first + c;
-      float* wout = ws + row * D + g16 * (4 * E);
+      // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
+      float* wout = ws + row * D + g16 * 4;
 #pragma unroll
       for (int i = 0; i < 4; i++)
 #pragma unroll
         for (int e = 0; e < E; e += 4)
-          *reinterpret_cast<float4*>(wout + i * E + e) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+          *reinterpret_cast<float4*>(wout + (i * E + e) * 4) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
       if (g16 == 0)
         *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(m, L);
     }
@@ -1114,66 +1115,63 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void
 }
 
 // ---------------------------------------------------------------------------------------------
-// combine pass: one wave per (split request, q head). First the common maximum and the normaliser from
-// the (m, l) pairs of all partials, one partial per lane; then the weighted sum of the
-// accumulators, whose loads do not depend on one another.
+// combine pass: one workgroup of W waves per (split request, q head). A row of accumulators is read 16
+// bytes per lane, so the workgroup takes RP = W * 256 / D partials at a time; every lane's rows are asked for
+// before the common maximum is known, so that the pass is one round trip to memory for up to 4 * RP
+// partials. The RP sums of a dim are added up through LDS in a fixed order.
 // ---------------------------------------------------------------------------------------------
-template <int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
-                                                            int32_t n_q_heads, int32_t n_kv_heads, int32_t group,
-                                                            BatchArgs a) {
-  constexpr int DPL = D / 64;        // output dims per lane
-  const int h = blockIdx.y, lane = threadIdx.x;
+constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
+
+template <int D, int W>
+__global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
+                                                                int32_t n_q_heads, int32_t group, BatchArgs a) {
+  constexpr int F = D / 4, RP = W * 64 / F, AHEAD = COMBINE_AHEAD;
+  __shared__ __attribute__((aligned(16))) float4 sums[RP][F];
+  const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
   const int b = (a.split_req[blockIdx.x >> 2] >> ((blockIdx.x & 3) * 8)) & 0xff;   // blockIdx.x-th split request
   const int g = h / group;
   const int n_part = a.req[b].n_part;
   const int64_t row0 = ((int64_t)g * a.parts_per_head + a.req[b].part0) * group + (h - g * group);
-  const float* p0 = ws + row0 * D;                                            // accumulator rows of this head
+  const float4* p = reinterpret_cast<const float4*>(ws + row0 * D) + f;       // accumulator rows of this head
   const float* q0 = ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML;      // their (m, l) pairs
-  const int64_t stride = (int64_t)group * D, qstride = (int64_t)group * WS_ML;
-  float M = NEG_BIG;
+  const int64_t stride = (int64_t)group * F, qstride = (int64_t)group * WS_ML;
+  float4 v[AHEAD];
+  float mv[AHEAD];
+#pragma unroll
+  for (int u = 0; u < AHEAD; u++) {
+    const int j = row + u * RP;
+    mv[u] = -INFINITY;
+    v[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (j < n_part) {
+      mv[u] = q0[j * qstride];
+      v[u] = p[j * stride];
+    }
+  }
+  // the common maximum and the normaliser, by every wave for itself, one partial per lane
+  float M = NEG_BIG, L = 0.f;
   for (int j = lane; j < n_part; j += 64) M = fmaxf(M, q0[j * qstride]);
   M = wave_max(M);
-  float L = 0.f, A[DPL];
-#pragma unroll
-  for (int e = 0; e < DPL; e++) A[e] = 0.f;
-  for (int j0 = 0; j0 < n_part; j0 += 64) {
-    // weight of partial j0 + lane, then every lane walks the block's partials in order
-    const int jl = j0 + lane;
-    float c = 0.f;
-    if (jl < n_part) {
-      c = fast_exp2(q0[jl * qstride] - M);
-      L += q0[jl * qstride + 1] * c;
-    }
-    const int nb = min(64, n_part - j0);
-    const float* p = p0 + j0 * stride + lane * DPL;
-    int j = 0;
-    for (; j + 4 <= nb; j += 4) {
-      float v[4][DPL];
-#pragma unroll
-      for (int u = 0; u < 4; u++)
-#pragma unroll
-        for (int e = 0; e < DPL; e++) v[u][e] = p[(j + u) * stride + e];
-#pragma unroll
-      for (int u = 0; u < 4; u++) {
-        const float cu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c), j + u));
-#pragma unroll
-        for (int e = 0; e < DPL; e++) A[e] += v[u][e] * cu;
-      }
-    }
-    for (; j < nb; j++) {
-      const float cu = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(c), j));
-#pragma unroll
-      for (int e = 0; e < DPL; e++) A[e] += p[j * stride + e] * cu;
-    }
-  }
+  for (int j = lane; j < n_part; j += 64) L += q0[j * qstride + 1] * fast_exp2(q0[j * qstride] - M);
   L = wave_sum(L);
-  uint16_t* o = out + ((int64_t)(a.q_row0 + b) * n_q_heads + h) * D + lane * DPL;
-  if (DPL == 2) {
-    *reinterpret_cast<uint32_t*>(o) = f32_to_bf16_bits(A[0] / L) | (f32_to_bf16_bits(A[DPL - 1] / L) << 16);
-  } else {
-    o[0] = (uint16_t)f32_to_bf16_bits(A[0] / L);
-  }
+  float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const float4& x, float c) __attribute__((always_inline)) {
+    A.x += x.x * c; A.y += x.y * c; A.z += x.z * c; A.w += x.w * c;
+  };
+#pragma unroll
+  for (int u = 0; u < AHEAD; u++)
+    if (row + u * RP < n_part) add(v[u], fast_exp2(mv[u] - M));
+  for (int j = row + AHEAD * RP; j < n_part; j += RP) add(p[j * stride], fast_exp2(q0[j * qstride] - M));
+  sums[row][f] = A;
+  __syncthreads();
+  if (row != 0) return;
+#pragma unroll
+  for (int r = 1; r < RP; r++) add(sums[r][f], 1.f);
+  // which dims these are: rows of the kernel that walks units hold them in the order its lanes store them
+  constexpr int E = D / 16;
+  const int dim = a.unit_tokens == TILE_TOKENS ? 4 * f : E * (4 * (f & 3) + f / E) + (f % E) / 4 * 4;
+  uint16_t* o = out + ((int64_t)(a.q_row0 + b) * n_q_heads + h) * D + dim;
+  *reinterpret_cast<uint2*>(o) = make_uint2(f32_to_bf16_bits(A.x / L) | (f32_to_bf16_bits(A.y / L) << 16),
+                                            f32_to_bf16_bits(A.z / L) | (f32_to_bf16_bits(A.w / L) << 16));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1404,14 +1402,30 @@ int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, 
                             : launch_partial_d<64>(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop);
 }
 
+template <int D, int W>
+static void launch_combine_w(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
+  hipLaunchKernelGGL((decode_combine_kernel<D, W>), dim3(a.n_split_req, pv.n_q_heads), dim3(64 * W), 0, stream, ws,
+                     (uint16_t*)out, pv.n_q_heads, pv.group, a);
+}
+
+// As many waves as take a request's partials (the average over the launch) in one round of loads, in steps
+// of four, but no fewer than four rows at a time: one request of 3250 tokens (51 partials) takes 4.4 us by
+// 16 waves, 5.0 by 4, 10.2 by 1 (7.9 before, one wave walking them); the 8B-shaped step (3 partials on
+// average) 2106 us by 2, 2122 by 4, 2125 by 1 (2116 before); 64 requests of 16 heads of 64 with their
+// attention 67 us by 1, 73 by 4.
+template <int D>
+static void launch_combine_d(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
+  constexpr int per_wave = COMBINE_AHEAD * 256 / D;
+  const int parts = a.parts_per_head / a.n_split_req;
+  if (parts > 4 * per_wave) launch_combine_w<D, 16>(pv, ws, out, a, stream);
+  else if (parts > per_wave) launch_combine_w<D, 4>(pv, ws, out, a, stream);
+  else launch_combine_w<D, D / 64>(pv, ws, out, a, stream);
+}
+
 int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
   if (a.n_req <= 0 || a.n_split_req <= 0) return 0;
-  if (pv.head_dim == 128)
-    hipLaunchKernelGGL(decode_combine_kernel<128>, dim3(a.n_split_req, pv.n_q_heads), dim3(64), 0, stream, ws,
-                       (uint16_t*)out, pv.n_q_heads, pv.n_kv_heads, pv.group, a);
-  else
-    hipLaunchKernelGGL(decode_combine_kernel<64>, dim3(a.n_split_req, pv.n_q_heads), dim3(64), 0, stream, ws,
-                       (uint16_t*)out, pv.n_q_heads, pv.n_kv_heads, pv.group, a);
+  if (pv.head_dim == 128) launch_combine_d<128>(pv, ws, out, a, stream);
+  else launch_combine_d<64>(pv, ws, out, a, stream);
   ELLM_HIP_CHECK_LAUNCH();
   return 0;
 }

@@ -95,3 +95,35 @@ def test_small_batches_are_cut_request_by_request():
         rc, one = B.decode([ids[b]], st.q[[b]])
         assert rc == 0 and torch.equal(one[0], out[b])
     B.close()
+
+
+@pytest.mark.parametrize("parts", [[2, 3, 4], [2, 9, 16, 17, 40], [31, 32, 33, 64, 65, 129, 200]])
+@pytest.mark.parametrize("n_q,dim,tokens", [(4, 128, 128), (3, 128, 128), (1, 64, 128), (5, 64, 48)])
+def test_combine_widths(n_q, dim, tokens, parts):
+    """Few, several and many partial results per request: one, four and sixteen waves add them up, in one
+    round of loads or in more; rows in the order of either attention kernel."""
+    most = 64 * max(parts)
+    cfg = W.Config("c", 9, len(parts), n_q, 1, dim, tokens * 4 * dim, sum(-(-64 * n // tokens) for n in parts) + len(parts) + 2,
+                   most + tokens, "uniform", 1, most)
+    rng = np.random.default_rng(9)
+    B = H.Both(cfg)
+
+    def bits(*shape):
+        return (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    ids = []
+    for n in parts:
+        t = B.create(64 * n)
+        assert B.map(t, 0, -(-64 * n // tokens)) == 0
+        ids.append(t)
+    total = 64 * sum(parts)
+    assert B.append(ids, bits(total, 1, dim), bits(total, 1, dim), [64 * n for n in parts]) == 0
+    q = bits(len(parts), n_q, dim)
+    E.ellm_pool_set_split_tokens(B.pool, 64)
+    rc, out = B.decode(ids, q)
+    rco, ref = B.orc.decode(ids, q)
+    assert rc == 0 and rco == 0
+    H.check_close(out, ref, f"{parts}")
+    rc, again = B.decode(ids, q)
+    assert rc == 0 and torch.equal(out, again)
+    B.close()
