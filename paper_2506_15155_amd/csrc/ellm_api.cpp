@@ -90,9 +90,9 @@ struct ellm_pool {
                                        // directions use their own copy engines and run at the same time
   bool one_allocation = false;         // the pool buffer lies inside one device allocation (asked once)
   char* host_dev = nullptr;            // the host buffer as the GPU addresses it (NULL: it cannot)
-  bool copy_kernels = false;           // offload / fetch by the library's copy kernel (where host_dev is known)
-                                       // instead of the runtime's copy engines: faster alone, but it takes
-                                       // compute units from the kernels it is meant to run beside
+  // offload / fetch by the library's copy kernel (where host_dev is known) or by the runtime's copy engines
+  enum { BY_RULE, BY_ENGINE, BY_KERNEL } copy_by = BY_RULE;
+  bool behind_compute = false;         // the latest migration call to wait for kernels found them unfinished
   ellm::CopyArgs copy_args;            // staging for one launch's list of chunks
   hipStream_t last_stream = nullptr;   // last stream given to append / decode
   bool have_last_stream = false;
@@ -376,7 +376,7 @@ int compute_mark(ellm_pool* p, int64_t need, hipEvent_t* ev, int64_t* covers) {
   return ELLM_OK;
 }
 
-// `waiter` (a side stream) waits for compute call `need`
+// `waiter` (a side stream) waits for compute call `need`; notes whether that was still to be waited for
 int wait_for_compute(ellm_pool* p, hipStream_t waiter, int64_t need, int64_t& waited) {
   if (need <= waited || need <= p->r_compute.done) return ELLM_OK;
   hipEvent_t ev;
@@ -384,6 +384,9 @@ int wait_for_compute(ellm_pool* p, hipStream_t waiter, int64_t need, int64_t& wa
   int rc = compute_mark(p, need, &ev, &covers);
   if (rc) return rc;
   HIP_TRY(hipStreamWaitEvent(waiter, ev, 0), "hipStreamWaitEvent(compute mark)");
+  const hipError_t state = hipEventQuery(ev);
+  if (state != hipSuccess) (void)hipGetLastError();
+  p->behind_compute = state == hipErrorNotReady;
   waited = covers;
   return ELLM_OK;
 }
@@ -490,15 +493,20 @@ size_t move_run(const ellm_pool* p, const std::vector<ellm::Move>& moves, size_t
 
 // Enqueues the copies of an offload (device chunk -> host slot) or a fetch on that direction's side
 // stream: copy calls of the runtime, one per run of neighbouring chunks, which the copy engines carry
-// out beside the kernels; or, if asked for and the GPU can address the host buffer, one launch of the
-// library's copy kernel for all of them. Measured on the 8B-shaped elastic step (3.56 GB each way):
-// the kernel moves 49 / 54 GB/s out / in against 46 / 46, but an attention kernel that runs beside it
-// takes 205-224 us instead of 69-83 (62 alone), and the layer-wise overlapped step is no shorter
-// (114-117 against 109-123 ms); so the copy engines are the default.
+// out beside the kernels; or, where the GPU can address the host buffer, one launch of the library's
+// copy kernel for all of them. The rule: the engines, unless the last migration call that had to wait for
+// kernels found them unfinished. Engines are the faster way on an idle GPU and leave the compute units
+// alone: 27 chunks out and 27 others in, call by call, 1.52 ms against 1.95. But a copy behind an event
+// of another stream that has not happened yet starts 50 to 130 us late, some of the copies become the
+// runtime's own copy kernels, and now and then the calling thread is held for milliseconds: the same
+// swap with passes in flight takes 2.3 to 3.8 ms by engine, 1.87 by kernel, whose waits are between
+// queues. Attention beside the kernel's copies is slower than beside the engines' (8B-shaped elastic step:
+// 205-224 us instead of 69-83), the layer-wise overlapped step as a whole is not (114-117 against 109-123 ms).
 int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) {
   const size_t cb = p->geom.chunk_bytes;
   hipStream_t side = fetch ? p->side_in : p->side_out;
-  if (p->host_dev && p->copy_kernels) {
+  const bool by_kernel = p->copy_by == ellm_pool::BY_RULE ? p->behind_compute : p->copy_by == ellm_pool::BY_KERNEL;
+  if (p->host_dev && by_kernel) {
     for (size_t i = 0; i < moves.size(); i += ellm::MAX_COPY) {
       ellm::CopyArgs& a = p->copy_args;
       a.n = (int32_t)std::min<size_t>(ellm::MAX_COPY, moves.size() - i);
@@ -1316,7 +1324,7 @@ int ellm_debug_fail_mapping(ellm_pool* p, int32_t nth) {
 
 int ellm_debug_set_copy_kernels(ellm_pool* p, int on) {
   if (!p) return set_err(ELLM_ERR_INVALID, "NULL pool");
-  p->copy_kernels = on != 0;
+  p->copy_by = on ? ellm_pool::BY_KERNEL : ellm_pool::BY_ENGINE;
   return ELLM_OK;
 }
 

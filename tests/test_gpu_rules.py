@@ -368,3 +368,55 @@ def test_random_walk_of_every_call_on_the_gpu(pool_mode, seed):
     assert n_ok >= 80 and n_dec >= 10, (n_ok, n_dec)
     print(f"walk seed {seed} ({pool_mode}): {n_ok} of 320 calls accepted, {n_dec} decodes compared")
     B.close()
+
+
+def test_swaps_behind_unfinished_kernels_and_on_an_idle_gpu():
+    """Two sets of requests take turns on the device; passes are issued without waiting (offload and fetch
+    then go by the copy kernel) or with a wait before each (by the copy engines): every pass gives the bits
+    of the first decode of its set."""
+    cfg = W.Config("swap", 9, 4, 8, 2, 128, 512 * (2 * 2 * 128 * 2), 40, 512 * 4, "uniform", 1, 2048, host_slots=32)
+    rng = np.random.default_rng(8)
+    B = H.Both(cfg, max_tensors=8)
+    lens = [2000, 512, 513, 1400]
+    need = [-(-n // 512) for n in lens]
+
+    def bits(*shape):
+        return (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    q = H.dev_bits(bits(4, 8, 128))
+    sets, want = [], []
+    for k in range(2):
+        ids = []
+        for n, s in zip(lens, need):
+            t = B.create(n)
+            assert B.map(t, 0, s) == 0
+            ids.append(t)
+        assert B.append(ids, bits(sum(lens), 2, 128), bits(sum(lens), 2, 128), lens) == 0
+        out = torch.empty_like(q)
+        E.ellm_decode_attention(B.pool, ids, q, out)
+        sets.append(ids)
+        want.append(out)
+    for t, s in zip(sets[1], need):
+        assert B.offload(t, 0, s) == 0
+    E.ellm_pool_sync(B.pool)
+    torch.cuda.synchronize()
+    for wait in (False, True, False):
+        got = []
+        for i in range(6):
+            here, other = sets[i % 2], sets[1 - i % 2]
+            for _ in range(0 if wait else 40):               # enough work for the copies to find it unfinished
+                E.ellm_decode_attention(B.pool, here, q, torch.empty_like(q))
+            for t, s in zip(here, need):
+                assert B.offload(t, 0, s) == 0
+            for t, s in zip(other, need):
+                assert B.fetch(t, 0, s) == 0
+            got.append(torch.empty_like(q))
+            E.ellm_decode_attention(B.pool, other, q, got[-1])
+            if wait:
+                E.ellm_pool_sync(B.pool)
+                torch.cuda.synchronize()
+        torch.cuda.synchronize()
+        for i, out in enumerate(got):
+            assert torch.equal(out, want[1 - i % 2]), (wait, i)
+    B.compare_state()
+    B.close()
