@@ -51,7 +51,7 @@ class _Desc(C.Structure):
                 ("initial_owner", C.c_void_p)]
 
 
-_i32p = C.POINTER(C.c_int32)
+_i32p = C.c_void_p      # arrays and results of 32-bit integers: an address, byref() or a ctypes pointer
 _vp = C.c_void_p
 _sigs = {
     "ellm_pool_create": [C.POINTER(_Desc), C.POINTER(_vp)],
@@ -141,19 +141,22 @@ def _ptr(x) -> int | None:
 
 
 def _i32(a):
+    """(array to keep alive as long as its address is used, its address, its size) of a host array of
+    32-bit integers."""
     if a is None:
         return None, None, 0
-    arr = np.ascontiguousarray(a, dtype=np.int32)
-    return arr, arr.ctypes.data_as(_i32p), arr.size
+    arr = a if type(a) is np.ndarray and a.dtype == np.int32 and a.flags.c_contiguous else np.ascontiguousarray(a, dtype=np.int32)
+    return arr, arr.__array_interface__["data"][0], arr.size
 
 
 def _stream(stream) -> int | None:
-    """hipStream_t of a torch stream (or a raw handle). None selects torch's current stream."""
+    """hipStream_t of a torch stream (or a raw handle). None selects torch's current stream; a process in
+    which torch has not touched the GPU has none but the default one."""
     if stream is None:
         import torch
-        if not torch.cuda.is_available():
+        if not torch.cuda.is_initialized():
             return None
-        return torch.cuda.current_stream().cuda_stream or None
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None
@@ -222,7 +225,7 @@ def ellm_tensor_is_released(pool, tid):
 
 def ellm_kv_premap_ahead(pool, ids, tokens_ahead, flags=0, check=True):
     """Returns the number of chunks mapped (check=True) or (rc, n)."""
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     out = C.c_int32(0)
     rc = lib.ellm_kv_premap_ahead(pool, p, n, int(tokens_ahead), int(flags), C.byref(out))
     if check:
@@ -233,7 +236,7 @@ def ellm_kv_premap_ahead(pool, ids, tokens_ahead, flags=0, check=True):
 
 def ellm_kv_premap_next(pool, ids, flags=0, check=True):
     """Returns the number of chunks mapped (check=True) or (rc, n)."""
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     out = C.c_int32(0)
     rc = lib.ellm_kv_premap_next(pool, p, n, int(flags), C.byref(out))
     if check:
@@ -297,7 +300,7 @@ def ellm_debug_vmm_latency(chunk_bytes, n_chunks, check=True):
 
 
 def ellm_tensor_map_chunks(pool, tid, first_slot, n_slots, chunk_ids=None, flags=0, check=True):
-    _, p, _ = _i32(chunk_ids)
+    keep, p, _ = _i32(chunk_ids)
     return _ret(lib.ellm_tensor_map_chunks(pool, tid, first_slot, n_slots, p, flags), check)
 
 
@@ -306,36 +309,36 @@ def ellm_tensor_unmap_chunks(pool, tid, first_slot, n_slots, check=True):
 
 
 def ellm_pool_transfer(pool, chunk_ids, new_owner, check=True):
-    _, p, n = _i32(chunk_ids)
+    keep, p, n = _i32(chunk_ids)
     return _ret(lib.ellm_pool_transfer(pool, p, n, new_owner), check)
 
 
 def ellm_pool_set_act_busy(pool, chunk_ids, busy, check=True):
-    _, p, n = _i32(chunk_ids)
+    keep, p, n = _i32(chunk_ids)
     return _ret(lib.ellm_pool_set_act_busy(pool, p, n, int(busy)), check)
 
 
 def ellm_kv_append(pool, ids, k_new, v_new, n_new=None, stream=None, check=True):
-    _, p, n = _i32(ids)
-    _, pn, _ = _i32(n_new)
+    keep, p, n = _i32(ids)
+    keep_n, pn, _ = _i32(n_new)
     s = _stream(stream)
     return _ret(lib.ellm_kv_append(pool, p, n, pn, _ptr(k_new), _ptr(v_new), s), check)
 
 
 def ellm_decode_attention(pool, ids, q, out, scale=0.0, stream=None, check=True):
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     s = _stream(stream)
     return _ret(lib.ellm_decode_attention(pool, p, n, _ptr(q), _ptr(out), float(scale), s), check)
 
 
 def ellm_decode_attention_noalloc(pool, ids, q, out, scale=0.0, stream=None, check=True):
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     s = _stream(stream)
     return _ret(lib.ellm_decode_attention_noalloc(pool, p, n, _ptr(q), _ptr(out), float(scale), s), check)
 
 
 def ellm_kv_append_decode(pool, ids, k_new, v_new, q, out, scale=0.0, stream=None, check=True):
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     return _ret(lib.ellm_kv_append_decode(pool, p, n, _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out), float(scale),
                                           _stream(stream)), check)
 
@@ -345,7 +348,7 @@ def ellm_chunk_deflate_to_host(pool, tid, first_slot, n_slots, check=True):
 
 
 def ellm_chunk_inflate_from_host(pool, tid, first_slot, n_slots, chunk_ids=None, check=True):
-    _, p, _ = _i32(chunk_ids)
+    keep, p, _ = _i32(chunk_ids)
     return _ret(lib.ellm_chunk_inflate_from_host(pool, tid, first_slot, n_slots, p), check)
 
 
@@ -475,7 +478,7 @@ def ellm_debug_stream_read(src, nbytes, sink, stream=None, check=True):
 
 
 def ellm_debug_kv_stream_read(pool, ids, sink, stream=None, check=True):
-    _, p, n = _i32(ids)
+    keep, p, n = _i32(ids)
     return _ret(lib.ellm_debug_kv_stream_read(pool, p, n, _ptr(sink), _stream(stream)), check)
 
 
