@@ -809,13 +809,21 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
   return parts;
 }
 
-void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
+// whole: the cut into shares, also where a call would be small enough for one workgroup per block
+void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0,
+                 bool whole = false) {
   const int32_t Tc = p->geom.tokens_per_chunk, n_kv = p->geom.n_kv_heads;
   auto pieces = [&](int64_t len, int32_t most) {      // pieces of up to `most` tokens of one chunk
     const int64_t full = len / Tc, rem = len - full * Tc;
     return full * ((Tc + most - 1) / most) + (rem + most - 1) / most;
   };
-  const bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
+  bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
+  int64_t blocks = 0;                  // what one workgroup of several waves takes, in a launch small enough for that
+  for (int32_t i = 0; i < n_req; i++)
+    blocks += (pieces(p->core->tensor(ids[i])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
+  const bool small = !whole && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
+                     blocks * n_kv <= (blocks > n_req ? ellm::BLOCK_LIMIT_SPLIT : ellm::BLOCK_LIMIT_WHOLE);
+  if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
   int64_t total = 0, steps = 0;
@@ -834,6 +842,10 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   if (p->split_override > 0) {
     const int64_t per = std::max<int64_t>(1, p->split_override / TILE_TOKENS) * (TILE_TOKENS / a.unit_tokens);
     waves = std::max<int64_t>(1, std::min((total + per - 1) / per, total));
+  } else if (small) {
+    a.step_units = ellm::BLOCK_UNITS;
+    for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
+    total = waves = blocks;
   } else {
     waves = std::max<int64_t>(1, std::min(room, total));
     if (!tiles) {
@@ -1122,7 +1134,7 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   int32_t per_wave = 0;
   for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
     const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
-    plan_launch(p, ids + b0, nb, b0, a);
+    plan_launch(p, ids + b0, nb, b0, a, 0, true);
     per_wave = std::max(per_wave, (a.units_each + (a.units_extra > 0 ? 1 : 0)) * a.step_units * a.unit_tokens);
     if (n_split)
       for (int32_t i = 0; i < nb; i++)

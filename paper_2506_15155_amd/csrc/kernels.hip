@@ -795,7 +795,13 @@ struct TileInfo {                    // what is known of a tile before its loads
   const char* base;                  // start of the pool, or of the tensor's range
 };
 
-template <int D, int U, bool APPEND, bool DIRECT>
+// units per tile: 8 KB of K and 8 KB of V for either head size; waves that share a step of BLOCK_UNITS
+template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
+template <int D> constexpr int block_waves = BLOCK_UNITS / tile_units<D>;
+
+// NW == 0: a workgroup is one wave, which walks its share. NW > 0 (small launches): NW waves share a step of
+// NW * U units of one request, one tile each, everything asked for at once, and add up through LDS.
+template <int D, int U, bool APPEND, bool DIRECT, int NW>
 __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                             const char* __restrict__ k_new, const char* __restrict__ v_new,
                                             float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
@@ -803,7 +809,8 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   constexpr int P = D / 32;          // products along a row = 16-byte pieces of K, dwords of a V row, per lane
   constexpr int ROWB = D * 2, E = D / 16, VB = E * 2;
   static_assert(U % 2 == 0, "PV takes two units at a time");
-  const int lane = threadIdx.x, c = lane & 15, g16 = lane >> 4;
+  const int lane = NW ? threadIdx.x & 63 : threadIdx.x, c = lane & 15, g16 = lane >> 4;
+  const int wave = NW ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
@@ -820,9 +827,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     const BatchArgs::Req rq = a.req[cb];
     len = rq.len;
     walk = tensor_walk<DIRECT>(pv, rq.tensor);
-    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units;
+    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + wave * U;
     rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
-    if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
+    if (NW) rem_share = min(U, rem_req);
+    else if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
     slot = u0 / pv.units_per_chunk;
     r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
     part = rq.n_part == 1 ? -1 : rq.part0 + (sh.w - rq.wave_first);
@@ -1082,6 +1090,59 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     }
   };
 
+  if constexpr (NW > 0) {
+    constexpr int F = D / 4, ROW = D + 4;              // a row of a head's accumulators, padded against bank conflicts
+    __shared__ __attribute__((aligned(16))) float sums[NW][HEADS_PER_PASS][ROW];
+    __shared__ float2 ml[NW][HEADS_PER_PASS];
+    if (rem_share > 0) {
+      TileInfo<U> t;
+      advance(t);
+      issue_k(t);
+      issue_v(t);
+      __builtin_amdgcn_sched_barrier(0);
+      scores(t);
+      weigh(t);
+      const float L = add_xor32(add_xor16(l));
+      if (c < n_heads) {
+#pragma unroll
+        for (int i = 0; i < 4; i++)
+#pragma unroll
+          for (int e = 0; e < E; e += 4)
+            *reinterpret_cast<float4*>(&sums[wave][c][g16 * 4 + (i * E + e) * 4]) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+        if (g16 == 0) ml[wave][c] = make_float2(m, L);
+      }
+    } else if (lane < n_heads) {
+      ml[wave][lane] = make_float2(NEG_BIG, 0.f);      // nothing left for this wave: weight 0, its row is not read
+    }
+    __syncthreads();
+    for (int x = threadIdx.x; x < n_heads * F; x += NW * 64) {
+      const int h = x / F, f = x % F;
+      float M = NEG_BIG, L = 0.f;
+#pragma unroll
+      for (int w = 0; w < NW; w++) M = fmaxf(M, ml[w][h].x);
+      float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int w = 0; w < NW; w++) {
+        const float2 p = ml[w][h];
+        if (p.x == NEG_BIG && p.y == 0.f) continue;
+        const float cw = fast_exp2(p.x - M);
+        const float4 v4 = *reinterpret_cast<const float4*>(&sums[w][h][f * 4]);
+        L += p.y * cw;
+        A.x += v4.x * cw; A.y += v4.y * cw; A.z += v4.z * cw; A.w += v4.w * cw;
+      }
+      if (part < 0) {
+        const float inv = 1.f / L;
+        const int dim = E * (4 * (f & 3) + f / E) + (f % E) / 4 * 4;
+        uint16_t* o = out + ((int64_t)(a.q_row0 + cb) * pv.n_q_heads + hq0 + h) * D + dim;
+        *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16(A.x * inv, A.y * inv), pack_bf16(A.z * inv, A.w * inv));
+      } else {
+        const int64_t row = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first + h;
+        *reinterpret_cast<float4*>(ws + row * D + f * 4) = A;
+        if (f == 0) *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(M, L);
+      }
+    }
+    return;
+  }
   // No exit before the round's last load (the share's last round asks for rows it does not use): what is in
   // flight when a tile is waited for is the same on every path, so the compiler counts the loads exactly.
   TileInfo<U> t, next;
@@ -1111,7 +1172,15 @@ template <int D, int U, bool APPEND, bool DIRECT>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
-  decode_unit_body<D, U, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  decode_unit_body<D, U, APPEND, DIRECT, 0>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+}
+// Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
+// of which one launch instead of two is 3 us of host time.
+template <int D, int U, bool APPEND, bool DIRECT>
+__global__ __launch_bounds__(64 * block_waves<D>) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
+    PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
+  decode_unit_body<D, U, APPEND, DIRECT, block_waves<D>>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1324,9 +1393,6 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
   return 0;
 }
 
-// units per tile of the kernel that walks units: 8 KB of K and 8 KB of V for either head size
-template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
-
 template <int D>
 static const void* partial_kernel_ptr(int group, bool tiles) {
   if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, true, false>;
@@ -1349,9 +1415,9 @@ int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
 // runtime's extended launch attaches them to the kernel's dispatch, so no marker of its own goes
 // into the stream and the time between them is the kernel's duration)
 template <typename Kernel, typename... Args>
-static void launch_timed(Kernel kernel, unsigned grid, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, Args... args) {
-  if (ev0 || ev1) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, stream, ev0, ev1, 0, args...);
-  else hipLaunchKernelGGL(kernel, dim3(grid), dim3(64), 0, stream, args...);
+static void launch_timed(Kernel kernel, unsigned grid, unsigned threads, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, Args... args) {
+  if (ev0 || ev1) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, ev0, ev1, 0, args...);
+  else hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, args...);
 }
 
 template <int D, bool APPEND, bool DIRECT>
@@ -1361,7 +1427,7 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
   const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
   if (a.unit_tokens == TILE_TOKENS) {
     auto go = [&](auto kernel) {
-      launch_timed(kernel, grid, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
+      launch_timed(kernel, grid, 64, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
                    (uint16_t*)out, scale_log2, 0, a);
     };
     if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT>);
@@ -1373,11 +1439,17 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }
+  if (a.step_units == BLOCK_UNITS) {
+    launch_timed(decode_block_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64 * block_waves<D>, stream, ev_start, ev_stop, pv,
+                 (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, 0, pv.group, a);
+    ELLM_HIP_CHECK_LAUNCH();
+    return 0;
+  }
   // a group of more than HEADS_PER_PASS q heads is covered by several launches over the same K/V: the
   // first of them takes the start time, the last one the end time
   for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
     const int n = std::min(HEADS_PER_PASS, pv.group - done);
-    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, stream, done == 0 ? ev_start : nullptr,
+    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64, stream, done == 0 ? ev_start : nullptr,
                  done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
                  (uint16_t*)out, scale_log2, done, n, a);
     ELLM_HIP_CHECK_LAUNCH();

@@ -1,4 +1,4 @@
-"""The attention kernel that walks 16-row units: any group size, any chunk size, at the edges of its units,
+"""The attention kernels built of 16-row units (one wave per share; one workgroup per block): any group size, any chunk size, at the edges of its units,
 tiles, shares and head passes, against the fp64 oracle. Unused memory is bf16 NaN, so a row that does not
 belong to a request shows up in the output. Tolerance: the harness's (weights and results are rounded to
 bf16, relative 2^-9 each, on outputs of the size of a N(0, 1) average: 2e-2 at most, 2e-3 on average)."""
@@ -43,10 +43,13 @@ def test_units_and_heads(n_q, n_kv, dim, tokens, most):
     total = int(lens.sum())
     assert B.append(ids, bits(total, n_kv, dim), bits(total, n_kv, dim), list(lens)) == 0
     q, kn, vn = bits(9, n_q, dim), bits(9, n_kv, dim), bits(9, n_kv, dim)
-    rc, out = B.decode(ids, q)
     rco, ref = B.orc.decode(ids, q)
-    assert rc == 0 and rco == 0
-    H.check_close(out, ref, "decode")
+    for split in (0, 192, 64):                # a workgroup per block; waves that walk shares of three tiles, of one
+        E.ellm_pool_set_split_tokens(B.pool, split)
+        rc, out = B.decode(ids, q)
+        assert rc == 0 and rco == 0
+        H.check_close(out, ref, f"decode, split {split}")
+    E.ellm_pool_set_split_tokens(B.pool, 64 * (n_q % 2))
     rc, fused, ref = B.append_decode(ids, kn, vn, q)
     assert rc == 0
     H.check_close(fused, ref, "append + decode")
@@ -73,13 +76,42 @@ def test_infinite_values_stay_with_their_request():
     v[4, 0, 7] = float("inf")                   # last row of the first request
     E.ellm_kv_append(B.pool, ids, k, v, [5, 24, 50])
     q = torch.randn((3, 6, 128), device="cuda").to(torch.bfloat16)
-    out = torch.empty_like(q)
-    E.ellm_decode_attention(B.pool, ids, q, out)
-    assert torch.isposinf(out[0, :, 7]).all()
-    out[0, :, 7] = 1.0
-    assert (out == 1.0).all()
+    for split in (0, 64):
+        E.ellm_pool_set_split_tokens(B.pool, split)
+        out = torch.empty_like(q)
+        E.ellm_decode_attention(B.pool, ids, q, out)
+        assert torch.isposinf(out[0, :, 7]).all()
+        out[0, :, 7] = 1.0
+        assert (out == 1.0).all()
     E.ellm_pool_destroy(B.pool)
     B.orc.close()
+
+
+@pytest.mark.parametrize("n_q,n_kv,dim,lens", [(4, 1, 128, [256] * 256), (4, 1, 128, [257] * 129), (16, 2, 64, [1, 255, 256, 257, 512, 513]),
+                                               (1, 1, 64, [256] * 40), (8, 8, 128, [4096, 4097])])
+def test_block_limits(n_q, n_kv, dim, lens):
+    """Around a block of 256 tokens, and batches at and past the most workgroups that take blocks."""
+    cfg = config(n_q, n_kv, dim, 64, len(lens), max(lens))
+    rng = np.random.default_rng(3)
+    B = H.Both(cfg)
+
+    def bits(*shape):
+        return (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    ids = []
+    for n in lens:
+        t = B.create(n)
+        assert B.map(t, 0, -(-n // 64)) == 0
+        ids.append(t)
+    assert B.append(ids, bits(sum(lens), n_kv, dim), bits(sum(lens), n_kv, dim), lens) == 0
+    q = bits(len(lens), n_q, dim)
+    rc, out = B.decode(ids, q)
+    rco, ref = B.orc.decode(ids, q)
+    assert rc == 0 and rco == 0
+    H.check_close(out, ref, "decode")
+    rc, again = B.decode(ids, q)
+    assert rc == 0 and torch.equal(out, again)
+    B.close()
 
 
 def test_small_batches_are_cut_request_by_request():
