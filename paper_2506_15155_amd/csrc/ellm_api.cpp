@@ -819,9 +819,10 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   };
   bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
   int64_t blocks = 0;                  // what one workgroup of several waves takes, in a launch small enough for that
-  for (int32_t i = 0; i < n_req; i++)
-    blocks += (pieces(p->core->tensor(ids[i])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
-  const bool small = !whole && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
+  int32_t counted = 0;                 // not all of them once it is clear that there are too many
+  for (; counted < n_req && (blocks + n_req - counted) * n_kv <= ellm::BLOCK_LIMIT_WHOLE; counted++)
+    blocks += (pieces(p->core->tensor(ids[counted])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
+  const bool small = counted == n_req && !whole && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
                      blocks * n_kv <= (blocks > n_req ? ellm::BLOCK_LIMIT_SPLIT : ellm::BLOCK_LIMIT_WHOLE);
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;

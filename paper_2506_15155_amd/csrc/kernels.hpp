@@ -47,7 +47,7 @@ struct PoolView {
 // unit (wave_first). A request that lies wholly inside one wave's share (n_part == 1) needs no
 // second pass: that wave normalises and writes the output row itself. Only the others ("split"
 // requests) get partial results in the workspace, part0 + j for the j-th wave, and a combine pass.
-// A launch has one wave for every SIMD of the GPU (a second wave on a SIMD is served markedly
+// A launch that fills the GPU has one wave for every SIMD of it (a second wave on a SIMD is served markedly
 // worse than the first and slows both down): all are resident at once and have the same amount to
 // read, so none waits for a slot and none is left over at the end. The cut is fixed by the plan,
 // so results do not depend on which wave ran when.
@@ -59,8 +59,9 @@ struct BatchArgs {
   int32_t n_req;
   int32_t q_row0;             // row of the first request in q / out
   int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
-  int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave gets: up to this
-                              // many units of one request (then "units" in the fields below are such steps)
+  int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave (STEP_UNITS) or
+                              // workgroup of several waves (BLOCK_UNITS) gets: up to this many units of one
+                              // request (then "units" and "waves" in the fields below are such steps)
   int32_t units_per_head;     // units of all requests of the launch, for one kv head
   int32_t waves_per_head;     // <= units_per_head
   int32_t units_each, units_extra;   // units_per_head = waves_per_head * units_each + units_extra

@@ -88,7 +88,8 @@ def test_infinite_values_stay_with_their_request():
 
 
 @pytest.mark.parametrize("n_q,n_kv,dim,lens", [(4, 1, 128, [256] * 256), (4, 1, 128, [257] * 129), (16, 2, 64, [1, 255, 256, 257, 512, 513]),
-                                               (1, 1, 64, [256] * 40), (8, 8, 128, [4096, 4097])])
+                                               (1, 1, 64, [256] * 40), (8, 8, 128, [4096, 4097]),
+                                               (8, 8, 64, [257] * 20 + [10] * 30), (8, 8, 64, [10] * 30 + [257] * 20)])
 def test_block_limits(n_q, n_kv, dim, lens):
     """Around a block of 256 tokens, and batches at and past the most workgroups that take blocks."""
     cfg = config(n_q, n_kv, dim, 64, len(lens), max(lens))
