@@ -809,9 +809,7 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
   return parts;
 }
 
-// whole: the cut into shares, also where a call would be small enough for one workgroup per block
-void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0,
-                 bool whole = false) {
+void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
   const int32_t Tc = p->geom.tokens_per_chunk, n_kv = p->geom.n_kv_heads;
   auto pieces = [&](int64_t len, int32_t most) {      // pieces of up to `most` tokens of one chunk
     const int64_t full = len / Tc, rem = len - full * Tc;
@@ -822,7 +820,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   int32_t counted = 0;                 // not all of them once it is clear that there are too many
   for (; counted < n_req && (blocks + n_req - counted) * n_kv <= ellm::BLOCK_LIMIT_WHOLE; counted++)
     blocks += (pieces(p->core->tensor(ids[counted])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
-  const bool small = counted == n_req && !whole && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
+  const bool small = counted == n_req && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
                      blocks * n_kv <= (blocks > n_req ? ellm::BLOCK_LIMIT_SPLIT : ellm::BLOCK_LIMIT_WHOLE);
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
@@ -1135,7 +1133,7 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   int32_t per_wave = 0;
   for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
     const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
-    plan_launch(p, ids + b0, nb, b0, a, 0, true);
+    plan_launch(p, ids + b0, nb, b0, a);
     per_wave = std::max(per_wave, (a.units_each + (a.units_extra > 0 ? 1 : 0)) * a.step_units * a.unit_tokens);
     if (n_split)
       for (int32_t i = 0; i < nb; i++)

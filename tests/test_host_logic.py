@@ -417,3 +417,28 @@ def test_bench_refuses_more_than_one_gpu():
                        timeout=120)
     assert r.returncode != 0 and "one GPU" in r.stderr and r.stdout.strip() == ""
 
+
+
+def planned(lens, n_q, n_kv, dim, tokens=512):
+    """(partial results per request, largest share in tokens) of the decode over requests of these lengths, as
+    the library reports them, without a device."""
+    cb = tokens * 4 * n_kv * dim
+    need = [-(-n // tokens) for n in lens]
+    P = E.ellm_pool_create(None, None, cb, n_q, n_kv, dim, len(lens), max(need), flags=1, device_bytes=(sum(need) + 1) * cb)
+    ids = []
+    for n, s in zip(lens, need):
+        ids.append(E.ellm_tensor_create(P, s * tokens))
+        E.ellm_tensor_map_chunks(P, ids[-1], 0, s)
+    E.ellm_kv_append(P, ids, DUMMY, DUMMY, np.asarray(lens, np.int32), stream=0)
+    n_split, most = E.ellm_decode_plan(P, ids)
+    E.ellm_pool_destroy(P)
+    return list(n_split), most
+
+
+def test_plan_reports_the_cut_of_small_batches():
+    """A small batch is decoded by one workgroup per 256 tokens of a request, and that is the cut the plan
+    reports; past the largest batch of that kind, shares of one wave each."""
+    assert planned([200, 256, 257, 512, 1100], 32, 8, 128) == ([1, 1, 2, 2, 5], 256)
+    assert planned([200] * 64, 8, 8, 64) == ([1] * 64, 256)
+    n_split, most = planned([200] * 65, 8, 8, 64)
+    assert most < 256 and max(n_split) > 1
