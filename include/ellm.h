@@ -451,6 +451,9 @@ int ellm_debug_kv_stream_read(ellm_pool* pool, const ellm_tensor_id* ids, int32_
  * wave per SIMD of the GPU; for measurements of the work partition. Results do not depend on it
  * beyond rounding order. */
 int ellm_debug_set_waves(ellm_pool* pool, int32_t percent);
+/* Test hook: launches are planned as for a GPU of n compute units, as a partition of the card has them
+ * (0, the default: as many as the GPU has; without a device 256). INVALID for more than the pool's GPU has. */
+int ellm_debug_set_compute_units(ellm_pool* pool, int32_t n);
 
 /* Measurement only: what the paper's own mechanism costs on this GPU (Sec. 2.1.1, Sec. 3.2: chunks
  * mapped into a reserved virtual range through the driver's virtual-memory calls). Creates

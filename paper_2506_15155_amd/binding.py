@@ -99,6 +99,7 @@ _sigs = {
     "ellm_pool_set_split_tokens": [_vp, C.c_int32],
     "ellm_pool_self_check": [_vp],
     "ellm_debug_set_waves": [_vp, C.c_int32],
+    "ellm_debug_set_compute_units": [_vp, C.c_int32],
     "ellm_debug_copy": [_vp, _vp, C.c_uint64, _vp],
     "ellm_debug_stream_read": [_vp, C.c_uint64, _vp, _vp],
     "ellm_debug_kv_stream_read": [_vp, _i32p, C.c_int32, _vp, _vp],
@@ -484,3 +485,7 @@ def ellm_debug_kv_stream_read(pool, ids, sink, stream=None, check=True):
 
 def ellm_debug_set_waves(pool, percent, check=True):
     return _ret(lib.ellm_debug_set_waves(pool, int(percent)), check)
+
+
+def ellm_debug_set_compute_units(pool, n, check=True):
+    return _ret(lib.ellm_debug_set_compute_units(pool, int(n)), check)

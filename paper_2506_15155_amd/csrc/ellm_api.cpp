@@ -152,6 +152,7 @@ struct ellm_pool {
   std::vector<uint64_t> vmm_tensor_job;      // per tensor: the newest of those
   int32_t split_override = 0;
   int32_t wave_slots = 0;              // waves of a decode launch: one per SIMD of the GPU (0 = not asked yet)
+  int32_t compute_units = 0;           // of the GPU, known with wave_slots
   int32_t waves_percent = 100;         // waves of a launch, as a share of what the GPU holds at once
   int64_t plan_total_units = 0;        // of the launch planned last: units per kv head,
   int64_t plan_waves = 0, plan_slots = 0;   // waves per kv head, partial slots
@@ -218,7 +219,8 @@ int32_t device_simds() {
 
 // Partial slots one decode launch can need under the automatic partition: every wave writes one
 // partial, and one more for every request boundary inside its share; the waves of all kv heads
-// together are at most one per SIMD, and each kv head's sequence has n_req - 1 inner boundaries.
+// together are at most one per SIMD, and each kv head's sequence has n_req - 1 inner boundaries. (A small
+// launch that takes one workgroup per 256 tokens of a request has at most one partial per compute unit.)
 int64_t launch_slot_bound(int32_t simds, int32_t n_kv_heads, int32_t n_req) {
   return (int64_t)simds + (int64_t)n_kv_heads * (std::max(n_req, 1) - 1);
 }
@@ -753,13 +755,16 @@ int ensure_workspace(ellm_pool* p, int64_t n_slots) {
 int32_t wave_slots(ellm_pool* p) {
   if (p->wave_slots > 0) return p->wave_slots;
   int32_t slots = 256 * ellm::SIMDS_PER_CU;
+  p->compute_units = 256;
   if (!p->metadata_only) {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
       slots = cus * std::min(ellm::SIMDS_PER_CU, ellm::partial_waves_per_cu(p->geom.head_dim, p->geom.group, p->geom.tokens_per_chunk));
-    else
+      p->compute_units = cus;
+    } else {
       (void)hipGetLastError();
+    }
   }
   p->wave_slots = slots;
   return slots;
@@ -816,12 +821,13 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     return full * ((Tc + most - 1) / most) + (rem + most - 1) / most;
   };
   bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
+  const int64_t slots = wave_slots(p), cus = p->compute_units;
   int64_t blocks = 0;                  // what one workgroup of several waves takes, in a launch small enough for that
   int32_t counted = 0;                 // not all of them once it is clear that there are too many
-  for (; counted < n_req && (blocks + n_req - counted) * n_kv <= ellm::BLOCK_LIMIT_WHOLE; counted++)
+  for (; counted < n_req && (blocks + n_req - counted) * n_kv <= cus * ellm::BLOCKS_PER_CU_WHOLE; counted++)
     blocks += (pieces(p->core->tensor(ids[counted])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
   const bool small = counted == n_req && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
-                     blocks * n_kv <= (blocks > n_req ? ellm::BLOCK_LIMIT_SPLIT : ellm::BLOCK_LIMIT_WHOLE);
+                     blocks * n_kv <= cus * (blocks > n_req ? ellm::BLOCKS_PER_CU_SPLIT : ellm::BLOCKS_PER_CU_WHOLE);
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
@@ -836,7 +842,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     total += units[i];
     steps += (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
   }
-  const int64_t room = std::max<int64_t>(1, (int64_t)wave_slots(p) * p->waves_percent / 100 / n_kv);
+  const int64_t room = std::max<int64_t>(1, slots * p->waves_percent / 100 / n_kv);
   int64_t waves;
   if (p->split_override > 0) {
     const int64_t per = std::max<int64_t>(1, p->split_override / TILE_TOKENS) * (TILE_TOKENS / a.unit_tokens);
@@ -1342,6 +1348,15 @@ int ellm_debug_set_copy_kernels(ellm_pool* p, int on) {
 int ellm_debug_set_table_kernels(ellm_pool* p, int on) {
   if (!p || !p->vmm) return set_err(ELLM_ERR_INVALID, "set_table_kernels: not a driver-mapped pool");
   p->vmm_table_kernels = on != 0;
+  return ELLM_OK;
+}
+
+int ellm_debug_set_compute_units(ellm_pool* p, int32_t n) {
+  if (!p || n < 0 || n > 4096) return set_err(ELLM_ERR_INVALID, "set_compute_units: bad argument");
+  if (!p->metadata_only && n * ellm::SIMDS_PER_CU > device_simds())
+    return set_err(ELLM_ERR_INVALID, "set_compute_units: more than the GPU has");
+  p->compute_units = n;
+  p->wave_slots = n * ellm::SIMDS_PER_CU;      // 0: asked for again by the next plan
   return ELLM_OK;
 }
 

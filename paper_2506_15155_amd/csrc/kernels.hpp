@@ -14,11 +14,11 @@ constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of on
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
 constexpr int STEP_UNITS = 4;         // units of a request that are worth a wave of their own
 constexpr int BLOCK_UNITS = 16;       // small launches: units of a request that one workgroup of several waves takes
-// Small launches, in workgroups: one for every CU; two where no request needs more than one, so that no
-// combine pass follows. us a call, 8 kv heads of 128, shares / blocks: 32 requests of 200 tokens, 4 q heads
+// Small launches, in workgroups for every CU: one; two where no request needs more than one, so that no
+// combine pass follows. (So a split launch never has more partial results than the GPU has CUs.) With 256 CUs, us a call, 8 kv heads of 128, shares / blocks: 32 requests of 200 tokens, 4 q heads
 // each (256 workgroups) 11.9 / 8.2, one of 8000, 8 heads (256) 15.0 / 11.9, 4 of 2000 (256) 12.0 / 11.8; 64 of
 // 200, heads of 64 (512, none split) 12.5 / 8.7; 8 of 1500 (384, split) 14.6 / 16.0, 16 of 900 (512) 15.2 / 17.1
-constexpr int BLOCK_LIMIT_SPLIT = 256, BLOCK_LIMIT_WHOLE = 512;
+constexpr int BLOCKS_PER_CU_SPLIT = 1, BLOCKS_PER_CU_WHOLE = 2;
 constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walks units handles in one pass over K and V
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
 constexpr int WS_ML = 2;              // floats per partial and q head in the (m, l) region of the workspace

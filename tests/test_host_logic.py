@@ -419,9 +419,9 @@ def test_bench_refuses_more_than_one_gpu():
 
 
 
-def planned(lens, n_q, n_kv, dim, tokens=512):
+def planned(lens, n_q, n_kv, dim, tokens=512, units=0):
     """(partial results per request, largest share in tokens) of the decode over requests of these lengths, as
-    the library reports them, without a device."""
+    the library reports them, without a device (units: on a GPU of so many compute units)."""
     cb = tokens * 4 * n_kv * dim
     need = [-(-n // tokens) for n in lens]
     P = E.ellm_pool_create(None, None, cb, n_q, n_kv, dim, len(lens), max(need), flags=1, device_bytes=(sum(need) + 1) * cb)
@@ -430,6 +430,7 @@ def planned(lens, n_q, n_kv, dim, tokens=512):
         ids.append(E.ellm_tensor_create(P, s * tokens))
         E.ellm_tensor_map_chunks(P, ids[-1], 0, s)
     E.ellm_kv_append(P, ids, DUMMY, DUMMY, np.asarray(lens, np.int32), stream=0)
+    E.ellm_debug_set_compute_units(P, units)
     n_split, most = E.ellm_decode_plan(P, ids)
     E.ellm_pool_destroy(P)
     return list(n_split), most
@@ -442,3 +443,15 @@ def test_plan_reports_the_cut_of_small_batches():
     assert planned([200] * 64, 8, 8, 64) == ([1] * 64, 256)
     n_split, most = planned([200] * 65, 8, 8, 64)
     assert most < 256 and max(n_split) > 1
+
+
+@pytest.mark.parametrize("units", [4, 32, 64, 128, 256])
+@pytest.mark.parametrize("n_q,n_kv,dim", [(64, 8, 128), (8, 8, 64), (6, 2, 128), (40, 40, 128)])
+def test_workspace_bound_on_smaller_gpus(units, n_q, n_kv, dim):
+    """A GPU of fewer compute units (a partition of a card) has a smaller workspace: one partial result per
+    SIMD and one per inner request boundary of every kv head. No plan needs more, around the limit of small
+    batches either."""
+    for lens in ([8000], [8192], [9000], [257], [300] * 2, [513] * 4, [200, 300] * 3, [256] * 40, [2000] * 8, [64, 4000, 64, 4000]):
+        n_split, _ = planned(lens, n_q, n_kv, dim, units=units)
+        slots = n_kv * sum(int(n) for n in n_split if n > 1)
+        assert slots <= 4 * units + n_kv * (len(lens) - 1), (units, lens, n_split)
