@@ -816,18 +816,30 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
 
 void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
   const int32_t Tc = p->geom.tokens_per_chunk, n_kv = p->geom.n_kv_heads;
-  auto pieces = [&](int64_t len, int32_t most) {      // pieces of up to `most` tokens of one chunk
-    const int64_t full = len / Tc, rem = len - full * Tc;
-    return full * ((Tc + most - 1) / most) + (rem + most - 1) / most;
+  // tiles or units (pieces of up to so many tokens of one chunk) of a sequence; a serving loop plans every layer's
+  // call, so the divisions are few: a 64-request plan pays for every nanosecond here 64 times
+  constexpr int32_t UNIT = ellm::UNIT_TOKENS;
+  const int32_t chunk_tiles = (Tc + TILE_TOKENS - 1) / TILE_TOKENS, chunk_units = (Tc + UNIT - 1) / UNIT;
+  auto tiles_in = [&](int64_t len) {
+    const int64_t full = len / Tc;
+    return full * chunk_tiles + (len - full * Tc + TILE_TOKENS - 1) / TILE_TOKENS;
+  };
+  auto units_in = [&](int64_t len) {
+    const int64_t full = len / Tc;
+    return full * chunk_units + (len - full * Tc + UNIT - 1) / UNIT;
   };
   bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
   const int64_t slots = wave_slots(p), cus = p->compute_units;
-  int64_t blocks = 0;                  // what one workgroup of several waves takes, in a launch small enough for that
+  int64_t blocks = 0, longest = 0;     // what workgroups of several waves would take, in a launch small enough for that
   int32_t counted = 0;                 // not all of them once it is clear that there are too many
-  for (; counted < n_req && (blocks + n_req - counted) * n_kv <= cus * ellm::BLOCKS_PER_CU_WHOLE; counted++)
-    blocks += (pieces(p->core->tensor(ids[counted])->len + extra, ellm::UNIT_TOKENS) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
-  const bool small = counted == n_req && p->split_override == 0 && p->waves_percent == 100 && p->geom.group <= ellm::HEADS_PER_PASS &&
-                     blocks * n_kv <= cus * (blocks > n_req ? ellm::BLOCKS_PER_CU_SPLIT : ellm::BLOCKS_PER_CU_WHOLE);
+  for (; counted < n_req && (blocks + n_req - counted) * n_kv <= 2 * cus; counted++) {
+    const int64_t len = p->core->tensor(ids[counted])->len + extra;
+    longest = std::max(longest, len);
+    blocks += (units_in(len) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
+  }
+  const bool one_piece = tiles_in(longest) == 1;
+  const bool small = counted == n_req && p->split_override == 0 && p->waves_percent == 100 &&
+                     ellm::block_launch(p->geom.head_dim, p->geom.group, tiles, one_piece, blocks, n_req, n_kv, (int)cus);
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
@@ -836,7 +848,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   units.resize(n_req);
   for (int32_t i = 0; i < n_req; i++) {
     const int64_t len = p->core->tensor(ids[i])->len + extra;   // extra: tokens of a fused append
-    units[i] = (int32_t)pieces(len, a.unit_tokens);
+    units[i] = (int32_t)(tiles ? tiles_in(len) : units_in(len));
     a.req[i].tensor = ids[i];
     a.req[i].len = (int32_t)len;
     total += units[i];
@@ -862,7 +874,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
       if (std::min(waves, steps) + n_req - 1 > cap) {
         std::vector<int32_t> by64(n_req);
         int64_t n64 = 0;
-        for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)pieces(a.req[i].len, TILE_TOKENS);
+        for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)tiles_in(a.req[i].len);
         coarser = cut_shares(by64, n64, std::min(room, n64), nullptr) <= cap;
       }
       if (coarser) {

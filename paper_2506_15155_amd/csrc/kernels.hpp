@@ -14,11 +14,6 @@ constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of on
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
 constexpr int STEP_UNITS = 4;         // units of a request that are worth a wave of their own
 constexpr int BLOCK_UNITS = 16;       // small launches: units of a request that one workgroup of several waves takes
-// Small launches, in workgroups for every CU: one; two where no request needs more than one, so that no
-// combine pass follows. (So a split launch never has more partial results than the GPU has CUs.) With 256 CUs, us a call, 8 kv heads of 128, shares / blocks: 32 requests of 200 tokens, 4 q heads
-// each (256 workgroups) 11.9 / 8.2, one of 8000, 8 heads (256) 15.0 / 11.9, 4 of 2000 (256) 12.0 / 11.8; 64 of
-// 200, heads of 64 (512, none split) 12.5 / 8.7; 8 of 1500 (384, split) 14.6 / 16.0, 16 of 900 (512) 15.2 / 17.1
-constexpr int BLOCKS_PER_CU_SPLIT = 1, BLOCKS_PER_CU_WHOLE = 2;
 constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walks units handles in one pass over K and V
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
 constexpr int WS_ML = 2;              // floats per partial and q head in the (m, l) region of the workspace
@@ -118,6 +113,41 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
   const int64_t Tc = tokens_per_chunk, padded = (Tc + TILE_TOKENS - 1) / TILE_TOKENS * TILE_TOKENS;
   if (head_dim == 128) return (group == 1 || group == 2 || group == 4 || group == 8) && padded * 5 <= Tc * 8;
   return (group == 1 || group == 2) && padded * 3 <= Tc * 4;
+}
+
+// Which launches take one workgroup of several waves per BLOCK_UNITS units of a request (`blocks` of them per kv
+// head) instead of shares of one wave each; tiles: the pool's shares are cut in tiles; one_piece: no request has
+// more than one tile. Never more workgroups than two for every CU, one where requests are split, so a split
+// launch has at most one partial result per CU. 256 CUs, us a call, blocks / shares:
+//  - Pools whose shares are cut in units: split, 8 kv heads of 64, 4 q heads each: 1 request of 512 tokens
+//    7.7 / 7.8, 4000 8.4 / 8.9; 16 requests of 2000, 2 kv heads of 64, 16 q heads each 9.1 / 10.8. Not split: 64 of 200, 3 q
+//    heads of 128 12.7 / 14.9. Either cut leaves a request's result independent of its neighbours; which cut a
+//    launch has hangs on their number alone up to these limits.
+//  - Tiles, requests of one block each that shares would split: the combine launch is saved. 8 requests of 200
+//    tokens, 8 kv heads of 128, 4 q heads each 5.5 / 8.2; 64 of 200 12.9 / 15.7. One q head, past one for every CU:
+//    64 of 128 tokens 10.5 / 10.0, 8 of 128 with 40 kv heads 9.5 / 9.2.
+//  - Tiles, split requests: the combine pass follows either way, and the blocks' kernel takes longer than the
+//    shares'; fewer partial results pay for that from 12 blocks (3000 tokens) per request on. 8 kv heads of 128:
+//    1 q head each: 1 request of 512 tokens 8.6 / 7.6, 1500 9.5 / 7.8, 3000 10.0 / 9.1, 8000 11.1 / 11.8; 4 q heads:
+//    512 8.8 / 8.4, 1500 9.6 / 9.0, 3000 10.1 / 10.1, 8000 11.2 / 12.9. With 8 q heads of 128 (1 kv head: 512
+//    8.6 / 9.9, 4000 9.8 / 11.0) and 2 of 64 (2: 512 7.4 / 7.7, 4000 8.0 / 8.3) they are the faster way throughout.
+//  - Tiles, where shares split nothing either: one wave a request is enough, and a workgroup whose other waves
+//    have nothing to do only takes longer to start: 64 of 64 tokens, 8 kv heads of 128, 1 q head each 7.9 / 5.6,
+//    heads of 64 5.3 / 5.5 and 8 of 64 4.7 / 4.4. The tile kernel's instances for 4 and 8 q heads start more slowly
+//    still: 8 of 64 tokens, 4 q heads 4.5 / 6.1, 64 of 64 8.0 / 8.2; 2 q heads, 4 kv heads: 8 of 64 4.3 / 5.4, 128 of
+//    64 7.6 / 6.7.
+inline bool block_launch(int head_dim, int group, bool tiles, bool one_piece, int64_t blocks, int n_req, int n_kv, int cus) {
+  const int64_t workgroups = blocks * n_kv, one_each = cus, two_each = 2 * (int64_t)cus;
+  if (group > HEADS_PER_PASS) return false;
+  if (blocks > n_req) {
+    const bool always = !tiles || (head_dim == 64 ? group == 2 : group == 8);
+    return workgroups <= one_each && (always || blocks >= 12 * (int64_t)n_req);
+  }
+  if (tiles && one_piece) {
+    if (head_dim == 64 || group == 1) return false;
+    return workgroups <= (group == 2 ? one_each : two_each);
+  }
+  return workgroups <= (tiles && head_dim == 128 && group == 1 ? one_each : two_each);
 }
 
 // resident waves of the partial-pass kernel per compute unit (occupancy query)

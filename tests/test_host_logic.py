@@ -439,7 +439,7 @@ def planned(lens, n_q, n_kv, dim, tokens=512, units=0):
 def test_plan_reports_the_cut_of_small_batches():
     """A small batch is decoded by one workgroup per 256 tokens of a request, and that is the cut the plan
     reports; past the largest batch of that kind, shares of one wave each."""
-    assert planned([200, 256, 257, 512, 1100], 32, 8, 128) == ([1, 1, 2, 2, 5], 256)
+    assert planned([200, 256, 257, 512, 1100], 64, 8, 128) == ([1, 1, 2, 2, 5], 256)
     assert planned([200] * 64, 8, 8, 64) == ([1] * 64, 256)
     n_split, most = planned([200] * 65, 8, 8, 64)
     assert most < 256 and max(n_split) > 1
@@ -455,3 +455,29 @@ def test_workspace_bound_on_smaller_gpus(units, n_q, n_kv, dim):
         n_split, _ = planned(lens, n_q, n_kv, dim, units=units)
         slots = n_kv * sum(int(n) for n in n_split if n > 1)
         assert slots <= 4 * units + n_kv * (len(lens) - 1), (units, lens, n_split)
+
+
+@pytest.mark.parametrize("n_q,n_kv,dim,tokens,lens,blocks", [
+    # requests of one tile: in tile pools blocks only in place of the kernel's instances that start slowly
+    (8, 8, 128, 512, [64] * 64, False), (24, 8, 128, 512, [64] * 64, True), (40, 40, 128, 102, [64] * 8, False),
+    (8, 8, 64, 512, [64] * 8, False), (8, 4, 128, 512, [64] * 64, True), (8, 4, 128, 512, [64] * 65, False),
+    (32, 8, 128, 512, [64] * 64, True), (32, 8, 128, 512, [64] * 65, False), (32, 8, 128, 16, [64], True),
+    (32, 8, 128, 40, [64], True),
+    # of more than that, up to one block each
+    (8, 8, 128, 512, [64, 65], True), (8, 8, 128, 512, [65] * 32, True), (8, 8, 128, 512, [65] * 33, False),
+    (16, 8, 128, 512, [65] * 64, True), (8, 8, 64, 512, [256] * 64, True), (8, 8, 64, 512, [256] * 65, False),
+    (24, 8, 128, 512, [256], True), (32, 8, 128, 16, [256], True), (34, 2, 128, 512, [100], False),
+    # split requests
+    (24, 8, 128, 512, [257], True), (24, 8, 128, 512, [257] * 17, False),     (8, 8, 128, 512, [257], False), (32, 8, 128, 512, [257] * 4, False), (8, 8, 64, 512, [257], False),
+    (40, 40, 128, 102, [256], False), (16, 8, 64, 512, [257] * 16, True), (16, 8, 64, 512, [257] * 17, False),
+    (64, 8, 128, 512, [257], True), (32, 8, 128, 512, [2816], False), (32, 8, 128, 512, [2817], True),
+    (32, 8, 128, 512, [100, 5700], True), (32, 8, 128, 512, [100, 5600], False), (8, 8, 128, 512, [8192], True),
+    (8, 8, 128, 512, [8193], False)])
+def test_which_launches_take_blocks(n_q, n_kv, dim, tokens, lens, blocks):
+    """A small launch is cut into blocks only where that measured faster than shares of one wave each."""
+    n_split, most = planned(lens, n_q, n_kv, dim, tokens)
+    units = [n // tokens * -(-tokens // 16) + -(-(n % tokens) // 16) for n in lens]
+    cut = [-(-u // 16) for u in units]
+    assert (list(n_split) == cut and most == 256) == blocks
+    if not blocks and max(lens) <= 64 and tokens >= 64:
+        assert most == 64 and max(n_split) == 1         # still one launch, no combine pass
