@@ -166,7 +166,7 @@ struct ellm_pool {
   std::vector<int32_t> n_eff;
   std::vector<ellm::Move> moves;
   std::vector<ellm::BatchArgs> launches;
-  std::vector<int32_t> units_tmp;
+  std::vector<int32_t> units_tmp, by64_tmp;
 };
 
 namespace {
@@ -268,6 +268,7 @@ int ensure_device(ellm_pool* p) {
     p->static_ws_slots = (int64_t)(bytes / slot_bytes(p->geom.group, p->geom.head_dim));
     p->launches.reserve(((size_t)p->geom.max_tensors + ellm::MAX_LAUNCH_REQ - 1) / ellm::MAX_LAUNCH_REQ);
     p->units_tmp.reserve(ellm::MAX_LAUNCH_REQ);
+    p->by64_tmp.reserve(ellm::MAX_LAUNCH_REQ);
   }
   if (p->geom.n_host_slots > 0 || p->vmm) {
     p->chunk_compute.assign(p->geom.n_chunks, 0);
@@ -843,7 +844,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
-  int64_t total = 0, steps = 0;
+  int64_t total = 0, steps = 0, step_parts = 0;   // steps of STEP_UNITS; those of requests of more than one
   std::vector<int32_t>& units = p->units_tmp;
   units.resize(n_req);
   for (int32_t i = 0; i < n_req; i++) {
@@ -852,7 +853,9 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     a.req[i].tensor = ids[i];
     a.req[i].len = (int32_t)len;
     total += units[i];
-    steps += (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
+    const int32_t n_steps = (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
+    steps += n_steps;
+    step_parts += n_steps > 1 ? n_steps : 0;
   }
   const int64_t room = std::max<int64_t>(1, slots * p->waves_percent / 100 / n_kv);
   int64_t waves;
@@ -870,16 +873,19 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
       // fits there; where that cut would fit and this one does not, it is made coarser until it does
       // (for both entry points, which share the cut).
       const int64_t cap = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim)) / n_kv;
+      const bool by_steps = steps <= room;
+      const int64_t need = by_steps ? step_parts : waves + n_req - 1 > cap ? cut_shares(units, total, waves, nullptr) : 0;
       bool coarser = false;
-      if (std::min(waves, steps) + n_req - 1 > cap) {
-        std::vector<int32_t> by64(n_req);
+      if (need > cap) {
+        std::vector<int32_t>& by64 = p->by64_tmp;
+        by64.resize(n_req);
         int64_t n64 = 0;
         for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)tiles_in(a.req[i].len);
         coarser = cut_shares(by64, n64, std::min(room, n64), nullptr) <= cap;
       }
       if (coarser) {
         while (waves > 1 && cut_shares(units, total, waves, nullptr) > cap) waves -= (waves + 15) / 16;
-      } else if (steps <= room) {
+      } else if (by_steps) {
         a.step_units = ellm::STEP_UNITS;
         for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
         total = waves = steps;

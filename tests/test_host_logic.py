@@ -481,3 +481,20 @@ def test_which_launches_take_blocks(n_q, n_kv, dim, tokens, lens, blocks):
     assert (list(n_split) == cut and most == 256) == blocks
     if not blocks and max(lens) <= 64 and tokens >= 64:
         assert most == 64 and max(n_split) == 1         # still one launch, no combine pass
+
+
+@pytest.mark.parametrize("lens,split", [([64] * 128, 1), ([65] * 120, 2), ([256] * 60, 4)])
+def test_a_cut_that_fits_the_fixed_workspace_is_not_made_coarser(lens, split):
+    """64 q heads per kv head: the workspace of the entry point that allocates nothing holds 252 partial
+    results per kv head. One wave per 64 tokens needs none, 240 and 240 of them here."""
+    n_split, most = planned(lens, 128, 2, 128)
+    assert list(n_split) == [split] * len(lens) and most == 64
+
+
+def test_a_cut_that_does_not_fit_the_fixed_workspace_is_made_coarser():
+    """31 q heads, 24-token chunks: that workspace holds 1040 partial results. In 64-token pieces of a chunk
+    (16 a request) the requests end where shares do and need 1024 of them; 31 units a request do not, and 1024
+    shares would need one more for almost every request."""
+    n_split, _ = planned([15 * 24 + 8] * 128, 31, 1, 128, tokens=24)
+    parts = sum(int(n) for n in n_split if n > 1)
+    assert 900 < parts <= 1040

@@ -74,3 +74,31 @@ def test_noalloc_decode_refuses_what_does_not_fit():
     torch.cuda.synchronize()
     assert (out == 0).all()
     E.ellm_pool_destroy(pool)
+
+
+@pytest.mark.parametrize("n", [64, 65, 256])
+def test_noalloc_decode_of_many_short_requests_with_large_groups(n):
+    """64 q heads per kv head, where few partial results fit: requests of one wave each, of two and four."""
+    batch = {64: 128, 65: 120, 256: 60}[n]
+    cfg = W.Config("short", 9, batch, 128, 2, 128, 64 * (2 * 2 * 128 * 2), batch * 5 + 2, 320, "uniform", n, n)
+    rng = np.random.default_rng(4)
+    B = H.Both(cfg)
+    bits = lambda *shape: (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    ids = []
+    for _ in range(batch):
+        ids.append(B.create(n))
+        assert B.map(ids[-1], 0, -(-n // 64)) == 0
+    assert B.append(ids, bits(batch * n, 2, 128), bits(batch * n, 2, 128), [n] * batch) == 0
+    q = bits(batch, 128, 128)
+    rc, want = B.decode(ids, q)
+    rco, ref = B.orc.decode(ids, q)
+    assert rc == 0 and rco == 0
+    H.check_close(want, ref, f"{batch} requests of {n}")
+    qd = H.dev_bits(q)
+    got = torch.full_like(qd, 77)
+    E.ellm_pool_prepare(B.pool)
+    torch.cuda.synchronize()
+    assert E.ellm_decode_attention_noalloc(B.pool, ids, qd, got, check=False) == 0, E.ellm_last_error()
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    B.close()
