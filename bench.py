@@ -603,6 +603,7 @@ def elastic_step(E, torch, W, args, steps=3):
     t_plain = timed(plain)
     us_hand, n_hand = hand_over()
     nbytes = sum(slots(b) for b in sel) * cfg.chunk_bytes * n_layers
+    E.ellm_debug_set_copy_kernels(pool, -1)                      # by the copy engines
     t_off = timed(lambda: [offload_layer(l) for l in range(n_layers)], 1)      # park the selected requests
     t_fetch = timed(lambda: [fetch_layer(l) for l in range(n_layers)], 1)
     t_off2 = timed(lambda: [offload_layer(l) for l in range(n_layers)], 1)     # parked again: the state between steps
@@ -612,12 +613,21 @@ def elastic_step(E, torch, W, args, steps=3):
     t_fetch_k = timed(lambda: [fetch_layer(l) for l in range(n_layers)], 1)
     t_off_k = timed(lambda: [offload_layer(l) for l in range(n_layers)], 1)
     t_block_k = timed(blocking)
-    E.ellm_debug_set_copy_kernels(pool, 0)
-    E.ellm_pool_profile_enable(pool, steps * n_layers)
-    E.ellm_pool_profile_stride(pool, 13)
-    t_layer = timed(layerwise)
-    kern = E.ellm_pool_profile_collect(pool, steps * n_layers)
-    E.ellm_pool_profile_enable(pool, 0)
+
+    def layerwise_profiled():
+        E.ellm_pool_profile_enable(pool, steps * n_layers)
+        E.ellm_pool_profile_stride(pool, 13)
+        t = timed(layerwise)
+        k = E.ellm_pool_profile_collect(pool, steps * n_layers)
+        E.ellm_pool_profile_enable(pool, 0)
+        return t, k
+
+    E.ellm_debug_set_copy_kernels(pool, -1)
+    t_layer_engines, kern_engines = layerwise_profiled()
+    E.ellm_debug_set_copy_kernels(pool, 0)                       # the pool's own rule, as a user's program has it
+    counts0 = E.ellm_pool_get_copy_counts(pool)
+    t_layer, kern = layerwise_profiled()
+    counts1 = E.ellm_pool_get_copy_counts(pool)
     oldest_first[0] = True
     refill_fifo()
     layerwise()                                                  # one step to get the rotation going
@@ -640,6 +650,9 @@ def elastic_step(E, torch, W, args, steps=3):
         "ms_step_no_migration": round(t_plain, 3),
         "ms_step_copies_then_compute": round(t_block, 3), "ms_step_layerwise": round(t_layer, 3),
         "ms_step_layerwise_fetch_into_chunks_free_the_longest": round(t_layer_oldest, 3),
+        "layerwise_calls_by_copy_engine_and_by_copy_kernel": [b - a for a, b in zip(counts0, counts1)],
+        "layerwise_with_copy_engines_only": {"ms_step_layerwise": round(t_layer_engines, 3),
+                                             "attention_kernel_us": round(float(np.mean(kern_engines)) * 1e3, 2) if len(kern_engines) else None},
         "with_copy_kernel_instead_of_copy_engines": {"offload_GBps": round(nbytes / t_off_k / 1e6, 2),
                                                      "fetch_GBps": round(nbytes / t_fetch_k / 1e6, 2),
                                                      "ms_step_copies_then_compute": round(t_block_k, 3)},

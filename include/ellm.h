@@ -484,9 +484,11 @@ int ellm_debug_set_async_mapping(ellm_pool* pool, int on);
 /* Offload and fetch move their chunks with the runtime's copy calls (copy engines, beside the
  * kernels), or, behind kernels that have not finished and where the GPU can address the host buffer,
  * with the library's copy kernel (one launch per call, the GPU reading or writing the pinned host
- * buffer directly). on != 0: always the kernel; 0: always the engines. For measurements; same bytes
- * either way. */
+ * buffer directly). on > 0: always the kernel (where the GPU can address the host buffer); on < 0: always
+ * the engines; 0 (the default) goes back to that rule. For measurements; same bytes either way. */
 int ellm_debug_set_copy_kernels(ellm_pool* pool, int on);
+/* How many offload and fetch calls of the pool moved their chunks each way (either pointer may be NULL). */
+int ellm_pool_get_copy_counts(ellm_pool* pool, int64_t* by_engine, int64_t* by_kernel);
 /* Test hook for the error path of a driver-mapped pool's mapper thread: the nth mapping it is asked
  * for from now on (1 = the next one; 0 = none) is not made and counts as refused by the driver. Every
  * later call that would launch a kernel on the pool, or that waits for the thread, then returns

@@ -89,6 +89,7 @@ _sigs = {
     "ellm_debug_set_table_kernels": [_vp, C.c_int],
     "ellm_debug_set_async_mapping": [_vp, C.c_int],
     "ellm_debug_set_copy_kernels": [_vp, C.c_int],
+    "ellm_pool_get_copy_counts": [_vp, C.POINTER(C.c_int64), C.POINTER(C.c_int64)],
     "ellm_debug_fail_mapping": [_vp, C.c_int32],
     "ellm_pool_get_mapping_wait": [_vp, C.POINTER(C.c_double)],
     "ellm_pool_get_geometry": [_vp, _i32p, _i32p, _i32p, C.POINTER(C.c_uint64)],
@@ -388,7 +389,14 @@ def ellm_debug_set_async_mapping(pool, on, check=True):
 
 
 def ellm_debug_set_copy_kernels(pool, on, check=True):
-    return _ret(lib.ellm_debug_set_copy_kernels(pool, int(bool(on))), check)
+    return _ret(lib.ellm_debug_set_copy_kernels(pool, int(on)), check)
+
+
+def ellm_pool_get_copy_counts(pool):
+    """(offload and fetch calls by the copy engines, by the copy kernel) so far."""
+    engine, kernel = C.c_int64(), C.c_int64()
+    _ret(lib.ellm_pool_get_copy_counts(pool, C.byref(engine), C.byref(kernel)), True)
+    return engine.value, kernel.value
 
 
 def ellm_debug_fail_mapping(pool, nth, check=True):

@@ -92,6 +92,7 @@ struct ellm_pool {
   char* host_dev = nullptr;            // the host buffer as the GPU addresses it (NULL: it cannot)
   // offload / fetch by the library's copy kernel (where host_dev is known) or by the runtime's copy engines
   enum { BY_RULE, BY_ENGINE, BY_KERNEL } copy_by = BY_RULE;
+  int64_t calls_by_engine = 0, calls_by_kernel = 0;
   bool behind_compute = false;         // the latest migration call to wait for kernels found them unfinished
   ellm::CopyArgs copy_args;            // staging for one launch's list of chunks
   hipStream_t last_stream = nullptr;   // last stream given to append / decode
@@ -520,6 +521,7 @@ int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) 
       const int e = ellm::launch_chunk_copy(p->device_base, p->host_dev, (uint32_t)cb, a, !fetch, side);
       if (e) return hip_err((hipError_t)e, fetch ? "copy kernel launch (fetch)" : "copy kernel launch (offload)");
     }
+    p->calls_by_kernel++;
     return ELLM_OK;
   }
   for (size_t i = 0; i < moves.size();) {
@@ -531,6 +533,7 @@ int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) 
     else HIP_TRY(hipMemcpyAsync(host, dev, n * cb, hipMemcpyDeviceToHost, side), "hipMemcpyAsync(offload)");
     i += n;
   }
+  p->calls_by_engine++;
   return ELLM_OK;
 }
 
@@ -1359,7 +1362,14 @@ int ellm_debug_fail_mapping(ellm_pool* p, int32_t nth) {
 
 int ellm_debug_set_copy_kernels(ellm_pool* p, int on) {
   if (!p) return set_err(ELLM_ERR_INVALID, "NULL pool");
-  p->copy_by = on ? ellm_pool::BY_KERNEL : ellm_pool::BY_ENGINE;
+  p->copy_by = on == 0 ? ellm_pool::BY_RULE : on > 0 ? ellm_pool::BY_KERNEL : ellm_pool::BY_ENGINE;
+  return ELLM_OK;
+}
+
+int ellm_pool_get_copy_counts(ellm_pool* p, int64_t* by_engine, int64_t* by_kernel) {
+  if (!p) return set_err(ELLM_ERR_INVALID, "NULL pool");
+  if (by_engine) *by_engine = p->calls_by_engine;
+  if (by_kernel) *by_kernel = p->calls_by_kernel;
   return ELLM_OK;
 }
 

@@ -420,3 +420,43 @@ def test_swaps_behind_unfinished_kernels_and_on_an_idle_gpu():
             assert torch.equal(out, want[1 - i % 2]), (wait, i)
     B.compare_state()
     B.close()
+
+
+def test_copy_path_hook_and_counts():
+    """The hook's three settings: always the copy kernel, always the copy engines, and back to the rule; the
+    pool counts which way each call's chunks went. Same bytes every way."""
+    cfg = W.Config("paths", 9, 2, 8, 2, 128, 512 * (2 * 2 * 128 * 2), 12, 512 * 4, "uniform", 1, 2048, host_slots=8)
+    rng = np.random.default_rng(3)
+    B = H.Both(cfg, keep_twin=True)
+    t = B.create(2000)
+    assert B.map(t, 0, 4) == 0
+    bits = lambda *shape: (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+    assert B.append([t], bits(2000, 2, 128), bits(2000, 2, 128), [2000]) == 0
+    q = H.dev_bits(bits(1, 8, 128))
+    want = torch.empty_like(q)
+    E.ellm_decode_attention(B.pool, [t], q, want)
+    busy = torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")
+
+    def round_trip():
+        before = E.ellm_pool_get_copy_counts(B.pool)
+        for _ in range(20):                                  # milliseconds of work for the offload to find unfinished
+            busy.add_(1)
+        E.ellm_decode_attention(B.pool, [t], q, torch.empty_like(q))
+        assert B.offload(t, 0, 4) == 0 and B.fetch(t, 0, 4) == 0
+        out = torch.empty_like(q)
+        E.ellm_decode_attention(B.pool, [t], q, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        after = E.ellm_pool_get_copy_counts(B.pool)
+        return after[0] - before[0], after[1] - before[1]
+
+    assert sum(round_trip()) == 2
+    E.ellm_debug_set_copy_kernels(B.pool, 1)
+    assert round_trip() == (0, 2)
+    E.ellm_debug_set_copy_kernels(B.pool, -1)
+    assert round_trip() == (2, 0)
+    E.ellm_debug_set_copy_kernels(B.pool, 0)
+    by_engine, by_kernel = round_trip()
+    assert by_kernel >= 1 and by_engine + by_kernel == 2     # the rule again: the offload was behind kernels
+    B.compare_state()
+    B.close()
