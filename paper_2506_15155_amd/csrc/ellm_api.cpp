@@ -93,7 +93,7 @@ struct ellm_pool {
   // offload / fetch by the library's copy kernel (where host_dev is known) or by the runtime's copy engines
   enum { BY_RULE, BY_ENGINE, BY_KERNEL } copy_by = BY_RULE;
   int64_t calls_by_engine = 0, calls_by_kernel = 0;
-  bool behind_compute = false;         // the latest migration call to wait for kernels found them unfinished
+  bool behind_compute = false;         // the migration call being made waits for kernels that have not finished
   ellm::CopyArgs copy_args;            // staging for one launch's list of chunks
   hipStream_t last_stream = nullptr;   // last stream given to append / decode
   bool have_last_stream = false;
@@ -118,6 +118,7 @@ struct ellm_pool {
   // (event r_compute.ev[i % EV_RING]) covers every compute call up to compute_covers[i % EV_RING].
   std::vector<int64_t> compute_covers;
   int64_t compute_marks = 0, compute_covered = 0;
+  int64_t compute_over = 0;            // highest compute call known to be no reason for a copy to wait for long
   std::vector<int64_t> chunk_compute, chunk_in, chunk_out;   // per chunk: seq of the last call of a kind, 0 = none
   std::vector<int64_t> host_in, host_out;                    // per host slot: last fetch that read it, last offload that wrote it
   // what each waiting stream already waits for, per ring (a stream is in order, so waiting for seq n covers all before)
@@ -380,18 +381,40 @@ int compute_mark(ellm_pool* p, int64_t need, hipEvent_t* ev, int64_t* covers) {
   return ELLM_OK;
 }
 
-// `waiter` (a side stream) waits for compute call `need`; notes whether that was still to be waited for
+// Is work unfinished that is in front of event `ev` (NULL: on the compute stream)?
+int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
+  const hipError_t state = ev ? hipEventQuery(ev) : hipStreamQuery(p->last_stream);
+  if (state == hipErrorNotReady) (void)hipGetLastError();
+  else HIP_TRY(state, ev ? "hipEventQuery(compute mark)" : "hipStreamQuery(compute stream)");
+  *yes = state == hipErrorNotReady;
+  return ELLM_OK;
+}
+
+// `waiter` (a side stream) waits for compute call `need`; notes for the copies of the same migration call whether
+// that is still to come
 int wait_for_compute(ellm_pool* p, hipStream_t waiter, int64_t need, int64_t& waited) {
-  if (need <= waited || need <= p->r_compute.done) return ELLM_OK;
+  p->behind_compute = false;
+  if (need <= p->r_compute.done) return ELLM_OK;
+  const bool ask = p->copy_by == ellm_pool::BY_RULE && p->host_dev && need > p->compute_over;
+  const bool marked = need <= p->compute_covered;
+  int rc;
+  if (ask && !marked) {
+    // asked of the stream before a mark goes there: a mark on an idle stream takes a moment to be seen as done
+    if ((rc = unfinished(p, nullptr, &p->behind_compute))) return rc;
+    if (!p->behind_compute) p->compute_over = p->r_compute.seq;
+  }
+  if (need <= waited && !ask) return ELLM_OK;
   hipEvent_t ev;
   int64_t covers;
-  int rc = compute_mark(p, need, &ev, &covers);
-  if (rc) return rc;
-  HIP_TRY(hipStreamWaitEvent(waiter, ev, 0), "hipStreamWaitEvent(compute mark)");
-  const hipError_t state = hipEventQuery(ev);
-  if (state != hipSuccess) (void)hipGetLastError();
-  p->behind_compute = state == hipErrorNotReady;
-  waited = covers;
+  if ((rc = compute_mark(p, need, &ev, &covers))) return rc;
+  if (need > waited) {
+    HIP_TRY(hipStreamWaitEvent(waiter, ev, 0), "hipStreamWaitEvent(compute mark)");
+    waited = covers;
+  }
+  if (ask && marked) {
+    if ((rc = unfinished(p, ev, &p->behind_compute))) return rc;
+    if (!p->behind_compute) p->compute_over = std::max(p->compute_over, covers);
+  }
   return ELLM_OK;
 }
 
@@ -498,14 +521,16 @@ size_t move_run(const ellm_pool* p, const std::vector<ellm::Move>& moves, size_t
 // Enqueues the copies of an offload (device chunk -> host slot) or a fetch on that direction's side
 // stream: copy calls of the runtime, one per run of neighbouring chunks, which the copy engines carry
 // out beside the kernels; or, where the GPU can address the host buffer, one launch of the library's
-// copy kernel for all of them. The rule: the engines, unless the last migration call that had to wait for
-// kernels found them unfinished. Engines are the faster way on an idle GPU and leave the compute units
+// copy kernel for all of them. The rule: the engines, unless the call's copies have to wait for kernels that
+// have not finished. Engines are the faster way on an idle GPU and leave the compute units
 // alone: 27 chunks out and 27 others in, call by call, 1.52 ms against 1.95. But a copy behind an event
 // of another stream that has not happened yet starts 50 to 130 us late, some of the copies become the
 // runtime's own copy kernels, and now and then the calling thread is held for milliseconds: the same
 // swap with passes in flight takes 2.3 to 3.8 ms by engine, 1.87 by kernel, whose waits are between
-// queues. Attention beside the kernel's copies is slower than beside the engines' (8B-shaped elastic step:
-// 205-224 us instead of 69-83), the layer-wise overlapped step as a whole is not (114-117 against 109-123 ms).
+// queues. Attention beside the kernel's copies is slower than beside the engines' (8B-shaped elastic step, layer by
+// layer: 200 us against 64-80), the step as a whole is not (114 ms by the rule, 3040 of 3072 calls by kernel, against
+// 118-149 by engines only); one request swapped for another every tenth step, while the rest decodes, waits for
+// nothing and goes by engine (2.11 ms a step; 2.78 always by kernel).
 int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) {
   const size_t cb = p->geom.chunk_bytes;
   hipStream_t side = fetch ? p->side_in : p->side_out;

@@ -398,13 +398,17 @@ def test_swaps_behind_unfinished_kernels_and_on_an_idle_gpu():
         want.append(out)
     for t, s in zip(sets[1], need):
         assert B.offload(t, 0, s) == 0
+    busy = torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")
     E.ellm_pool_sync(B.pool)
     torch.cuda.synchronize()
     for wait in (False, True, False):
         got = []
+        counts = E.ellm_pool_get_copy_counts(B.pool)
         for i in range(6):
             here, other = sets[i % 2], sets[1 - i % 2]
-            for _ in range(0 if wait else 40):               # enough work for the copies to find it unfinished
+            for _ in range(0 if wait else 10):               # milliseconds of work for the copies to find unfinished
+                busy.add_(1)
+            for _ in range(0 if wait else 40):
                 E.ellm_decode_attention(B.pool, here, q, torch.empty_like(q))
             for t, s in zip(here, need):
                 assert B.offload(t, 0, s) == 0
@@ -418,6 +422,8 @@ def test_swaps_behind_unfinished_kernels_and_on_an_idle_gpu():
         torch.cuda.synchronize()
         for i, out in enumerate(got):
             assert torch.equal(out, want[1 - i % 2]), (wait, i)
+        by_engine, by_kernel = (b - a for a, b in zip(counts, E.ellm_pool_get_copy_counts(B.pool)))
+        assert by_engine + by_kernel == 6 * 8 and (by_kernel == 0) == wait, (by_engine, by_kernel)
     B.compare_state()
     B.close()
 
@@ -460,3 +466,43 @@ def test_copy_path_hook_and_counts():
     assert by_kernel >= 1 and by_engine + by_kernel == 2     # the rule again: the offload was behind kernels
     B.compare_state()
     B.close()
+
+
+def small_pool(n_chunks=12, host_slots=8):
+    """A pool of 512-token chunks of 2 kv heads, one tensor of 2000 tokens in it, decoded once."""
+    cfg = W.Config("paths", 9, 2, 8, 2, 128, 512 * (2 * 2 * 128 * 2), n_chunks, 512 * 4, "uniform", 1, 2048, host_slots=host_slots)
+    B = H.Both(cfg, oracle=False)
+    t = B.create(2000)
+    assert B.map(t, 0, 4) == 0
+    kv = torch.randn(2000, 2, 128, device="cuda").to(torch.bfloat16)
+    q = torch.randn(1, 8, 128, device="cuda").to(torch.bfloat16)
+    want = torch.empty_like(q)
+    E.ellm_kv_append(B.pool, [t], kv, kv, [2000])
+    E.ellm_decode_attention(B.pool, [t], q, want)
+    torch.cuda.synchronize()
+    return B, t, q, want
+
+
+def test_copies_on_an_idle_gpu_after_a_busy_one():
+    """Which way a call's chunks go is decided for that call: after one that was behind kernels, calls that have
+    nothing to wait for any more go by the copy engines, also where they wait for the same kernels."""
+    B, t, q, want = small_pool()
+    busy = torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")
+    for _ in range(20):
+        busy.add_(1)
+    E.ellm_decode_attention(B.pool, [t], q, torch.empty_like(q))
+    assert B.offload(t, 0, 1) == 0 and B.offload(t, 1, 1) == 0
+    assert E.ellm_pool_get_copy_counts(B.pool) == (0, 2)
+    E.ellm_pool_sync(B.pool)
+    torch.cuda.synchronize()
+    assert B.offload(t, 2, 2) == 0 and B.fetch(t, 0, 4) == 0
+    assert E.ellm_pool_get_copy_counts(B.pool) == (2, 2)
+    out = torch.empty_like(q)
+    E.ellm_decode_attention(B.pool, [t], q, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    for first in range(4):                                   # the decode has just finished
+        assert B.offload(t, first, 1) == 0
+    assert E.ellm_pool_get_copy_counts(B.pool) == (6, 2)
+    B.close()
+
