@@ -381,9 +381,21 @@ int compute_mark(ellm_pool* p, int64_t need, hipEvent_t* ev, int64_t* covers) {
   return ELLM_OK;
 }
 
-// Is work unfinished that is in front of event `ev` (NULL: on the compute stream)?
+// Is work unfinished that is in front of event `ev` (NULL: on the compute stream)? While that stream is being
+// captured there is nothing to ask (*yes = false); captures of other streams must not notice the question, which
+// the runtime would otherwise count against them.
 int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
+  *yes = false;
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(p->last_stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();           // the default stream beside a capture that would have to wait for it
+    return ELLM_OK;
+  }
+  if (capture != hipStreamCaptureStatusNone) return ELLM_OK;
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
   const hipError_t state = ev ? hipEventQuery(ev) : hipStreamQuery(p->last_stream);
+  HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
   if (state == hipErrorNotReady) (void)hipGetLastError();
   else HIP_TRY(state, ev ? "hipEventQuery(compute mark)" : "hipStreamQuery(compute stream)");
   *yes = state == hipErrorNotReady;
