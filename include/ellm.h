@@ -128,7 +128,9 @@ typedef struct ellm_pool_desc {
   void*    device_base;      /* device, caller-owned, 256-byte aligned; NULL with METADATA_ONLY and
                                 DRIVER_MAPPED                                                       */
   uint64_t device_bytes;
-  void*    host_base;        /* host, caller-owned, pinned; NULL iff host_bytes < chunk_bytes     */
+  void*    host_base;        /* host, caller-owned, pinned; NULL iff host_bytes < chunk_bytes. Any
+                                address; the library's copy kernel is used only where it is a
+                                multiple of 16 and the GPU can address all of the buffer           */
   uint64_t host_bytes;
   uint32_t chunk_bytes;      /* multiple of 256                                                   */
   uint16_t n_q_heads;
@@ -484,7 +486,7 @@ int ellm_debug_set_async_mapping(ellm_pool* pool, int on);
 /* Offload and fetch move their chunks with the runtime's copy calls (copy engines, beside the
  * kernels), or, behind kernels that have not finished and where the GPU can address the host buffer,
  * with the library's copy kernel (one launch per call, the GPU reading or writing the pinned host
- * buffer directly). on > 0: always the kernel (where the GPU can address the host buffer); on < 0: always
+ * buffer directly). on > 0: always the kernel (where the GPU can address the host buffer, see host_base); on < 0: always
  * the engines; 0 (the default) goes back to that rule. For measurements; same bytes either way. */
 int ellm_debug_set_copy_kernels(ellm_pool* pool, int on);
 /* How many offload and fetch calls of the pool moved their chunks each way (either pointer may be NULL). */

@@ -253,9 +253,15 @@ int ensure_device(ellm_pool* p) {
       (void)hipGetLastError();
   }
   if (p->host_base && p->geom.n_host_slots > 0) {
-    void* seen = nullptr;
-    if (hipHostGetDevicePointer(&seen, p->host_base, 0) == hipSuccess) p->host_dev = (char*)seen;
-    else (void)hipGetLastError();
+    // the copy kernel takes 16 bytes at a time and has no way to fail: the whole buffer has to be there for the GPU
+    const size_t last = (size_t)p->geom.n_host_slots * p->geom.chunk_bytes - 1;
+    void *seen = nullptr, *seen_last = nullptr;
+    if (hipHostGetDevicePointer(&seen, p->host_base, 0) == hipSuccess &&
+        hipHostGetDevicePointer(&seen_last, p->host_base + last, 0) == hipSuccess) {
+      if ((char*)seen_last == (char*)seen + last && ((uintptr_t)seen & 15) == 0) p->host_dev = (char*)seen;
+    } else {
+      (void)hipGetLastError();
+    }
   }
   HIP_TRY(hipStreamCreateWithFlags(&p->side_in, hipStreamNonBlocking), "hipStreamCreate(side)");
   HIP_TRY(hipStreamCreateWithFlags(&p->side_out, hipStreamNonBlocking), "hipStreamCreate(side)");

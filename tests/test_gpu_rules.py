@@ -532,3 +532,38 @@ def test_migration_leaves_a_capture_of_another_stream_alone(busy):
         torch.cuda.synchronize()
         assert (x == 2 * (i + 1)).all()
     B.close()
+
+
+@pytest.mark.parametrize("offset", [0, 8, 16, 4096 + 2])
+def test_host_buffers_at_any_address(offset):
+    """The copy kernel reads and writes 16 bytes at a time; a host buffer that does not begin at a multiple of 16
+    goes by the copy engines, also where the kernel is asked for. One that begins inside a pinned allocation is as
+    good as any."""
+    cfg = W.Config("host", 9, 1, 8, 2, 128, 512 * (2 * 2 * 128 * 2), 6, 512 * 4, "uniform", 1, 2048)
+    dev = torch.zeros(cfg.n_chunks * cfg.chunk_bytes, dtype=torch.uint8, device="cuda")
+    whole = torch.full((5 * cfg.chunk_bytes,), 0x5A, dtype=torch.uint8, pin_memory=True)
+    host = whole[offset:offset + 4 * cfg.chunk_bytes]
+    P = E.ellm_pool_create(dev, host, cfg.chunk_bytes, 8, 2, 128, 1, 4)
+    t = E.ellm_tensor_create(P, 2000)
+    E.ellm_tensor_map_chunks(P, t, 0, 4, np.array([4, 1, 5, 0], np.int32))
+    kv = torch.randn(2000, 2, 128, device="cuda").to(torch.bfloat16)
+    q = torch.randn(1, 8, 128, device="cuda").to(torch.bfloat16)
+    want, out = torch.empty_like(q), torch.empty_like(q)
+    E.ellm_kv_append(P, [t], kv, kv, [2000])
+    E.ellm_decode_attention(P, [t], q, want)
+    E.ellm_debug_set_copy_kernels(P, 1)
+    E.ellm_chunk_deflate_to_host(P, t, 0, 4)
+    E.ellm_pool_sync(P)
+    torch.cuda.synchronize()
+    chunks = dev.view(-1, cfg.chunk_bytes).cpu()
+    assert torch.equal(torch.sort(host.view(-1, cfg.chunk_bytes)[:, :4096].long().sum(1)).values,
+                       torch.sort(chunks[[4, 1, 5, 0], :4096].long().sum(1)).values)
+    assert (whole[:offset] == 0x5A).all() and (whole[offset + 4 * cfg.chunk_bytes:] == 0x5A).all()
+    dev.zero_()
+    torch.cuda.synchronize()                                 # the fetch does not know of it
+    E.ellm_chunk_inflate_from_host(P, t, 0, 4)
+    E.ellm_decode_attention(P, [t], q, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    assert E.ellm_pool_get_copy_counts(P) == ((0, 2) if offset % 16 == 0 else (2, 0))
+    E.ellm_pool_destroy(P)
