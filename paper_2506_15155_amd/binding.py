@@ -51,7 +51,8 @@ class _Desc(C.Structure):
                 ("initial_owner", C.c_void_p)]
 
 
-_i32p = C.c_void_p      # arrays and results of 32-bit integers: an address, byref() or a ctypes pointer
+_i32p = C.POINTER(C.c_int32)
+_i32_at = (C.c_int32 * 1).from_address     # taken where _i32p is declared, and cheaper to make than a pointer
 _vp = C.c_void_p
 _sigs = {
     "ellm_pool_create": [C.POINTER(_Desc), C.POINTER(_vp)],
@@ -143,12 +144,12 @@ def _ptr(x) -> int | None:
 
 
 def _i32(a):
-    """(array to keep alive as long as its address is used, its address, its size) of a host array of
-    32-bit integers."""
+    """(array to keep alive as long as the argument is used, the argument for _i32p, its size) of a host array
+    of 32-bit integers."""
     if a is None:
         return None, None, 0
     arr = a if type(a) is np.ndarray and a.dtype == np.int32 and a.flags.c_contiguous else np.ascontiguousarray(a, dtype=np.int32)
-    return arr, arr.__array_interface__["data"][0], arr.size
+    return arr, _i32_at(arr.__array_interface__["data"][0]), arr.size
 
 
 def _stream(stream) -> int | None:

@@ -498,3 +498,25 @@ def test_a_cut_that_does_not_fit_the_fixed_workspace_is_made_coarser():
     n_split, _ = planned([15 * 24 + 8] * 128, 31, 1, 128, tokens=24)
     parts = sum(int(n) for n in n_split if n > 1)
     assert 900 < parts <= 1040
+
+
+def test_the_binding_refuses_addresses_of_the_wrong_type():
+    """The raw entry points take 32-bit integer arrays and results by typed pointer: 64-bit ones, bytes and bare
+    addresses are refused before anything is called; the wrappers take lists, arrays of any integer type and
+    strided ones, and none."""
+    import ctypes as C
+    P = E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, flags=1, device_bytes=8 << 14)
+    wide = np.zeros(4, np.int64)
+    for bad in (C.byref(C.c_int64()), wide.ctypes.data_as(C.POINTER(C.c_int64)), b"\0" * 16, wide.ctypes.data):
+        with pytest.raises(C.ArgumentError):
+            E.lib.ellm_tensor_create(P, 16, bad)
+        with pytest.raises(C.ArgumentError):
+            E.lib.ellm_decode_plan(P, bad, 1, None, None)
+    out = C.c_int32(-1)
+    assert E.lib.ellm_tensor_create(P, 16, C.byref(out)) == 0 and out.value == 0
+    for ids in ([0], np.array([0]), np.array([[0, 5], [0, 7]], np.int32)[:1, :1], np.zeros(4, np.int32)[::4]):
+        assert E.ellm_kv_premap_ahead(P, ids, 1) in (0, 1)
+    assert E.ellm_kv_premap_ahead(P, [], 1) == 0
+    E.ellm_tensor_map_chunks(P, 0, 1, 0, None)
+    assert E.ellm_tensor_map_chunks(P, 0, 0, 2, np.array([3, 1, 2], np.int64)[:2], check=False) != 0     # slot 0 is mapped
+    E.ellm_pool_destroy(P)
