@@ -153,13 +153,17 @@ def _i32(a):
 
 
 def _stream(stream) -> int | None:
-    """hipStream_t of a torch stream (or a raw handle). None selects torch's current stream; a process in
-    which torch has not touched the GPU has none but the default one."""
+    """hipStream_t of a torch stream (or a raw handle). None selects torch's current stream."""
     if stream is None:
         import torch
-        if not torch.cuda.is_initialized():
+        if torch.cuda.is_initialized():
+            try:        # torch's own short cut to the handle: 0.3 us, against 2 us for the stream object
+                return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+            except AttributeError:
+                pass
+        elif not torch.cuda.is_available():
             return None
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+        return torch.cuda.current_stream().cuda_stream or None
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream or None

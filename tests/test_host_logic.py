@@ -520,3 +520,24 @@ def test_the_binding_refuses_addresses_of_the_wrong_type():
     E.ellm_tensor_map_chunks(P, 0, 1, 0, None)
     assert E.ellm_tensor_map_chunks(P, 0, 0, 2, np.array([3, 1, 2], np.int64)[:2], check=False) != 0     # slot 0 is mapped
     E.ellm_pool_destroy(P)
+
+
+def test_the_current_stream_is_torchs_own_answer(monkeypatch):
+    """A call without a stream goes to torch's current one, whether or not anything has touched the GPU yet in the
+    process, and by torch's documented interface where its internal short cut is not there."""
+    import torch
+    from paper_2506_15155_amd import binding
+
+    class Stream:
+        cuda_stream = 0x1230
+
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: False)
+    assert binding._stream(None) is None and binding._stream(0) is None and binding._stream(7) == 7
+    monkeypatch.setattr(torch.cuda, "is_available", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream(None) == 0x1230                       # not touched yet
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    for name in ("_cuda_getCurrentRawStream", "_cuda_getDevice"):
+        monkeypatch.delattr(torch._C, name, raising=False)
+    assert binding._stream(None) == 0x1230
+    assert binding._stream(Stream) == 0x1230
