@@ -418,6 +418,10 @@ int ellm_pool_get_host_slots(ellm_pool* pool, int32_t* tensor, int32_t* slot);
  * wave or workgroup, in tokens (a multiple of 64, rounded up). For tests of the partition. */
 int ellm_decode_plan(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch,
                      int32_t* n_split, int32_t* split_tokens);
+/* Name of the attention kernel that the first launch of the next decode over these handles runs (with
+ * extra_tokens = 1: of the next ellm_kv_append_decode), or NULL where the call would be refused. For tests
+ * and measurements. */
+const char* ellm_debug_decode_kernel(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, int32_t extra_tokens);
 /* Override the tokens per wave (rounded down to whole 64-token tiles, at least one; 0 = automatic:
  * one wave per SIMD of the GPU). For tests that compare partitions. While an override (this one or
  * ellm_debug_set_waves) is in force, a decode call whose partition needs more partial results than

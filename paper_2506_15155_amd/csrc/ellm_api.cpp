@@ -1215,6 +1215,18 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   return ELLM_OK;
 }
 
+const char* ellm_debug_decode_kernel(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int32_t extra_tokens) {
+  if (!p || batch < 1 || extra_tokens < 0 || extra_tokens > 1) {
+    set_err(ELLM_ERR_INVALID, "debug_decode_kernel: bad argument");
+    return nullptr;
+  }
+  if (core_err(p, p->core->decode_check(ids, batch, extra_tokens))) return nullptr;
+  ellm::BatchArgs a;
+  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
+  if (a.unit_tokens == TILE_TOKENS) return "decode_tile_kernel";
+  return a.step_units == ellm::BLOCK_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
+}
+
 int ellm_pool_set_split_tokens(ellm_pool* p, int32_t split_tokens) {
   if (!p || split_tokens < 0) return set_err(ELLM_ERR_INVALID, "set_split_tokens: bad argument");
   p->split_override = split_tokens;

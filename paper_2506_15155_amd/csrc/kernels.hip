@@ -735,12 +735,13 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 // the next tile's K is asked for as soon as this one's scores are formed, its V as soon as this one's
 // weighted sum is, so that one of the two is on its way at any time.
 //   scores   S^T = K Q^T by 16x16x32 matrix instructions, one unit by up to 16 q heads: A = the unit's
-//      rows (lane 16 g + c: row c, 16 bytes per product), B = the query rows (lane: head c, the same
+//      rows (lane 16 g + c: 16 bytes of one row per product), B = the query rows (lane: head c, the same
 //      bytes of it). To load whole cache lines a wave-wide load takes 128 bytes of each of 8 rows instead
-//      of 64 of 16: load j of a half row gives lane (g, c) piece g + 4 (c0 ^ j) of row c with its lowest
-//      bit, c0, replaced by j. Product x takes, per lane, load c0 ^ x: the same piece g + 4 x in every lane,
-//      of row c ^ x, so that its result differs from x = 0's by an exchange of registers only.
-//      Register i of lane (g, c) is then the score of token 4 g + i for head c.
+//      of 64 of 16: with c1 the second-lowest bit of c, load j of a half row gives lane (g, c) piece
+//      g + 4 (c1 ^ j) of row 4 (c & 1) + (c >> 2) + 8 j. Product x takes, per lane, load c1 ^ x: the same
+//      piece g + 4 x in every lane, of row 4 (c & 1) + (c >> 2) + 8 (c1 ^ x). A's lane c = 4 g + i becomes
+//      register i of lane group g, so product 0 leaves the score of token 4 i + g for head c in register i of
+//      lane (g, c), and product 1 the score of token 4 (i ^ 2) + g: an exchange of registers i and i ^ 2.
 //   softmax  a lane owns one head (c) and four tokens of every unit: the tile's maximum is lane-local up
 //      to two cross-lane swaps, and the weights are already where the next product wants them: as the sum
 //      of two bf16 values, the next one below the weight and the rest (to 2^-16 of the weight; both
@@ -748,11 +749,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 //      value the result is as far from 64 bits as the tile kernels' (2.1e-3 instead of 1.6e-3, the
 //      rounding of the result included), and further where those cut a request more finely.
 //   PV       O^T = V^T P^T, two units at a time: contraction index of lane group g = its four tokens of
-//      either unit. A = V, loaded as whole rows (lane (g, c): dims E c .. E c + E - 1 of rows 4 g + i) and
+//      either unit. A = V, loaded as whole rows (lane (g, c): dims E c .. E c + E - 1 of rows 4 i + g) and
 //      transposed in registers by v_perm_b32, one product per e = dim % E; B = the weights.
 //      Register i of product e in lane (g, c) is dim E (4 g + i) + e of head c: every per-head quantity
 //      (m, l, the rescaling) sits in the lanes that need it, and a lane ends with 4 E consecutive dims.
-// Nothing goes through LDS. The cost per byte does not depend on the number of q heads up to 16, so every
+// Nothing goes through LDS (NW == 0; the waves of a block add up there). The cost per byte does not depend on the number of q heads up to 16, so every
 // group size up to that is one pass over K and V. Bound by HBM: 48 requests of 6 q heads per kv head (278 MB
 // of K and V) 92.4 -> 51.8 us with the combine pass (the tile kernels took two passes), 64 requests of 16
 // heads of 64 (398 MB) 144 -> 69.8, 16-token chunks (187 MB) 50.8 -> 36.4.

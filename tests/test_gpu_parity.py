@@ -97,7 +97,7 @@ def test_reduced_configs_other_partitions(name, split):
 
 @pytest.mark.parametrize("Hq,Hkv,D", [(12, 2, 128), (6, 2, 64), (3, 1, 128), (32, 2, 64), (5, 5, 64)])
 def test_other_group_sizes(Hq, Hkv, D, pool_mode):
-    """Group sizes that are not 1, 2, 4 or 8 are covered by several launches over the same K/V."""
+    """Group sizes that are not 1, 2, 4 or 8: no kernel instance of their own, up to 16 heads in one pass over K/V."""
     cfg = W.Config("g", 9, 5, Hq, Hkv, D, 24 * (2 * Hkv * D * 2), 64, 24 * 12, "uniform", 1, 24 * 12)
     if pool_mode == "driver" and cfg.chunk_bytes % 4096:
         pytest.skip("the driver maps whole 4 KiB pages: this chunk size cannot be a mapping unit")
