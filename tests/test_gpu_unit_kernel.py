@@ -44,7 +44,7 @@ def test_units_and_heads(n_q, n_kv, dim, tokens, most):
     assert B.append(ids, bits(total, n_kv, dim), bits(total, n_kv, dim), list(lens)) == 0
     q, kn, vn = bits(9, n_q, dim), bits(9, n_kv, dim), bits(9, n_kv, dim)
     rco, ref = B.orc.decode(ids, q)
-    for split in (0, 192, 64):                # a workgroup per block; waves that walk shares of three tiles, of one
+    for split in (0, 192, 64):                # as the library cuts it (mostly a workgroup per block); waves that walk shares of three tiles, of one
         E.ellm_pool_set_split_tokens(B.pool, split)
         rc, out = B.decode(ids, q)
         assert rc == 0 and rco == 0
@@ -91,7 +91,7 @@ def test_infinite_values_stay_with_their_request():
                                                (1, 1, 64, [256] * 40), (8, 8, 128, [4096, 4097]),
                                                (8, 8, 64, [257] * 20 + [10] * 30), (8, 8, 64, [10] * 30 + [257] * 20)])
 def test_block_limits(n_q, n_kv, dim, lens):
-    """Around a block of 256 tokens, and batches at and past the most workgroups that take blocks."""
+    """Around a block of 256 tokens, and batches on both sides of the limits up to which blocks are taken."""
     cfg = config(n_q, n_kv, dim, 64, len(lens), max(lens))
     rng = np.random.default_rng(3)
     B = H.Both(cfg)

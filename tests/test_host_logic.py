@@ -541,3 +541,16 @@ def test_the_current_stream_is_torchs_own_answer(monkeypatch):
         monkeypatch.delattr(torch._C, name, raising=False)
     assert binding._stream(None) == 0x1230
     assert binding._stream(Stream) == 0x1230
+
+
+@pytest.mark.parametrize("dim,group,first", [(128, 1, 32), (128, 2, 40), (128, 4, 40), (128, 8, 40), (64, 1, 48), (64, 2, 48)])
+def test_chunks_that_tiles_fill_well_enough(dim, group, first):
+    """From which chunk size on a pool's shares are cut in 64-row tiles instead of 16-row units."""
+    for tokens in range(1, 65):
+        P = E.ellm_pool_create(None, None, tokens * 4 * dim, group, 1, dim, 1, 40, flags=1, device_bytes=41 * tokens * 4 * dim)
+        E.ellm_tensor_create(P, 40 * tokens)
+        E.ellm_tensor_map_chunks(P, 0, 0, 40)
+        E.ellm_kv_append(P, [0], DUMMY, DUMMY, [40 * tokens], stream=0)
+        E.ellm_pool_set_split_tokens(P, 64)
+        assert (E.ellm_debug_decode_kernel(P, [0]) == "decode_tile_kernel") == (tokens >= first), tokens
+        E.ellm_pool_destroy(P)
