@@ -314,7 +314,7 @@ def measure(wl, K, Wm, event_stride=0, use_events=True, preheat_s=0.0):
     if use_events and len(kern_ms):
         avg = float(np.mean(kern_ms))
         ach = partial_bytes / (avg * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": E.ellm_debug_decode_kernel(wl.pool, wl.ids[0], int(wl.fused)), "achieved": round(ach, 1),
+        roofline = {"bound": "hbm", "kernel": E.ellm_debug_decode_kernel(wl.pool, wl.ids[0]), "achieved": round(ach, 1),
                     "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(ach / HBM_PEAK_GBPS, 4), "traffic": None,
                     "avg_launch_us": round(avg * 1e3, 2), "median_launch_us": round(float(np.median(kern_ms)) * 1e3, 2),
                     "launches": int(len(kern_ms)), "algorithmic_bytes_per_launch": int(partial_bytes)}
