@@ -1234,7 +1234,9 @@ __global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __r
   sums[row][f] = A;
   __syncthreads();
   if (row != 0) return;
-#pragma unroll
+  // (eight at a time: all 32 or 64 rows of the widest workgroups at once went through scratch memory, which the
+  // runtime allocates at the launch)
+#pragma unroll 8
   for (int r = 1; r < RP; r++) add(sums[r][f], 1.f);
   // which dims these are: rows of the kernel that walks units hold them in the order its lanes store them
   constexpr int E = D / 16;
@@ -1483,9 +1485,9 @@ static void launch_combine_w(const PoolView& pv, const float* ws, void* out, con
 
 // As many waves as take a request's partials (the average over the launch) in one round of loads, in steps
 // of four, but no fewer than four rows at a time: one request of 3250 tokens (51 partials) takes 4.4 us by
-// 16 waves, 5.0 by 4, 10.2 by 1 (7.9 before, one wave walking them); the 8B-shaped step (3 partials on
-// average) 2106 us by 2, 2122 by 4, 2125 by 1 (2116 before); 64 requests of 16 heads of 64 with their
-// attention 67 us by 1, 73 by 4.
+// 16 waves, 5.0 by 4, 10.2 by 1 (7.9 before, one wave walking them); one of 65536, 1 kv head, 8 q heads of 64
+// (256 partials) 12.4 us a call by 16 (84 before). With few partials the number does not matter: the 8B-shaped step's
+// launch (3 on average) 4.63 us by 2, 4.64 by 1.
 template <int D>
 static void launch_combine_d(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
   constexpr int per_wave = COMBINE_AHEAD * 256 / D;

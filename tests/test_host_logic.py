@@ -554,3 +554,21 @@ def test_chunks_that_tiles_fill_well_enough(dim, group, first):
         E.ellm_pool_set_split_tokens(P, 64)
         assert (E.ellm_debug_decode_kernel(P, [0]) == "decode_tile_kernel") == (tokens >= first), tokens
         E.ellm_pool_destroy(P)
+
+
+def test_no_kernel_needs_scratch_memory(tmp_path):
+    """A kernel with private memory makes the runtime allocate device memory when it is launched, which the entry
+    point that allocates nothing must not, and its launches start late. Read from the notes of the library's own
+    code object."""
+    import subprocess
+    tools = "/opt/rocm/llvm/bin/"
+    bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
+    lib = os.path.join(ROOT, "paper_2506_15155_amd", "libellm.so")
+    subprocess.run([tools + "llvm-objcopy", "--dump-section", ".hip_fatbin=" + bundle, lib, str(tmp_path / "unused")], check=True)
+    subprocess.run([tools + "clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", "--input=" + bundle,
+                    "--output=" + code, "--unbundle"], check=True)
+    notes = subprocess.run([tools + "llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    names, scratch, spills = (re.findall(rf"^    \.{key}: +(\S+)$", notes, flags=re.M) for key in
+                              ("name", "private_segment_fixed_size", "vgpr_spill_count"))
+    assert len(names) == len(scratch) == len(spills) >= 40
+    assert [n for n, a, b in zip(names, scratch, spills) if int(a) or int(b)] == []
