@@ -125,12 +125,15 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 //    heads of 128 12.7 / 14.9. Either cut leaves a request's result independent of its neighbours; which cut a
 //    launch has hangs on their number alone up to these limits.
 //  - Tiles, requests of one block each that shares would split: the combine launch is saved. 8 requests of 200
-//    tokens, 8 kv heads of 128, 4 q heads each 5.5 / 8.2; 64 of 200 12.9 / 15.7. One q head, past one for every CU:
-//    64 of 128 tokens 10.5 / 10.0, 8 of 128 with 40 kv heads 9.5 / 9.2.
+//    tokens, 8 kv heads of 128, 4 q heads each 5.5 / 8.2; 64 of 200 12.9 / 15.7. One q head, past one for every CU: 64
+//    of 80 tokens 8.3 / 9.3, 128 10.4 / 9.4 (two full tiles, where shares are at their best), 160 11.6 / 12.2, 256 14.3 /
+//    14.3, with the fused append 10.8 / 9.8, 12.6 / 12.8, 13.1 / 13.5; 12 of 200 with 40 kv heads 11.9 / 12.4.
 //  - Tiles, split requests: the combine pass follows either way, and the blocks' kernel takes longer than the
 //    shares'; fewer partial results pay for that from 12 blocks (3000 tokens) per request on. 8 kv heads of 128:
 //    1 q head each: 1 request of 512 tokens 8.6 / 7.6, 1500 9.5 / 7.8, 3000 10.0 / 9.1, 8000 11.1 / 11.8; 4 q heads:
-//    512 8.8 / 8.4, 1500 9.6 / 9.0, 3000 10.1 / 10.1, 8000 11.2 / 12.9. With 8 q heads of 128 (1 kv head: 512
+//    512 8.8 / 8.4, 1500 9.6 / 9.0, 3000 10.1 / 10.1, 8000 11.2 / 12.9. With 4 q heads also where there is a workgroup
+//    for most CUs: 4 of 2000 10.5 / 11.2, 6 of 1000 (192) 9.8 / 9.8, with the fused append 10.6 / 11.7, 10.3 / 10.9; 1 q
+//    head: 4 of 2000 10.9 / 10.8, 6 of 1000 10.3 / 9.4. With 8 q heads of 128 (1 kv head: 512
 //    8.6 / 9.9, 4000 9.8 / 11.0) and 2 of 64 (2: 512 7.4 / 7.7, 4000 8.0 / 8.3) they are the faster way throughout.
 //  - Tiles, where shares split nothing either: one wave a request is enough, and a workgroup whose other waves
 //    have nothing to do only takes longer to start: 64 of 64 tokens, 8 kv heads of 128, 1 q head each 7.9 / 5.6,
@@ -142,13 +145,14 @@ inline bool block_launch(int head_dim, int group, bool tiles, bool one_piece, in
   if (group > HEADS_PER_PASS) return false;
   if (blocks > n_req) {
     const bool always = !tiles || (head_dim == 64 ? group == 2 : group == 8);
-    return workgroups <= one_each && (always || blocks >= 12 * (int64_t)n_req);
+    const bool many = head_dim == 128 && group == 4 && workgroups * 4 >= one_each * 3;
+    return workgroups <= one_each && (always || many || blocks >= 12 * (int64_t)n_req);
   }
   if (tiles && one_piece) {
     if (head_dim == 64 || group == 1) return false;
     return workgroups <= (group == 2 ? one_each : two_each);
   }
-  return workgroups <= (tiles && head_dim == 128 && group == 1 ? one_each : two_each);
+  return workgroups <= two_each;
 }
 
 // resident waves of the partial-pass kernel per compute unit (occupancy query)

@@ -464,11 +464,12 @@ def test_workspace_bound_on_smaller_gpus(units, n_q, n_kv, dim):
     (32, 8, 128, 512, [64] * 64, True), (32, 8, 128, 512, [64] * 65, False), (32, 8, 128, 16, [64], True),
     (32, 8, 128, 40, [64], True),
     # of more than that, up to one block each
-    (8, 8, 128, 512, [64, 65], True), (8, 8, 128, 512, [65] * 32, True), (8, 8, 128, 512, [65] * 33, False),
+    (8, 8, 128, 512, [64, 65], True), (8, 8, 128, 512, [65] * 32, True), (8, 8, 128, 512, [65] * 64, True), (8, 8, 128, 512, [65] * 65, False),
     (16, 8, 128, 512, [65] * 64, True), (8, 8, 64, 512, [256] * 64, True), (8, 8, 64, 512, [256] * 65, False),
     (24, 8, 128, 512, [256], True), (32, 8, 128, 16, [256], True), (34, 2, 128, 512, [100], False),
     # split requests
-    (24, 8, 128, 512, [257], True), (24, 8, 128, 512, [257] * 17, False),     (8, 8, 128, 512, [257], False), (32, 8, 128, 512, [257] * 4, False), (8, 8, 64, 512, [257], False),
+    (24, 8, 128, 512, [257], True), (24, 8, 128, 512, [257] * 17, False),     (8, 8, 128, 512, [257], False), (32, 8, 128, 512, [257] * 4, False), (32, 8, 128, 512, [257] * 11, False),
+    (32, 8, 128, 512, [257] * 12, True), (32, 8, 128, 512, [257] * 17, False), (16, 8, 128, 512, [257] * 12, False), (8, 8, 64, 512, [257], False),
     (40, 40, 128, 102, [256], False), (16, 8, 64, 512, [257] * 16, True), (16, 8, 64, 512, [257] * 17, False),
     (64, 8, 128, 512, [257], True), (32, 8, 128, 512, [2816], False), (32, 8, 128, 512, [2817], True),
     (32, 8, 128, 512, [100, 5700], True), (32, 8, 128, 512, [100, 5600], False), (8, 8, 128, 512, [8192], True),
