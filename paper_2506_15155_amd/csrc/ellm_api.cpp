@@ -884,9 +884,9 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     longest = std::max(longest, len);
     blocks += (units_in(len) + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
   }
-  const bool one_piece = tiles_in(longest) == 1;
   const bool small = counted == n_req && p->split_override == 0 && p->waves_percent == 100 &&
-                     ellm::block_launch(p->geom.head_dim, p->geom.group, tiles, one_piece, blocks, n_req, n_kv, (int)cus);
+                     ellm::small_launch(p->geom.group, blocks, n_req, n_kv, (int)cus);
+  const bool by_blocks = small && ellm::takes_blocks(p->geom.head_dim, tiles, tiles_in(longest) == 1, blocks, n_req, n_kv, (int)cus);
   if (small) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
@@ -908,7 +908,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   if (p->split_override > 0) {
     const int64_t per = std::max<int64_t>(1, p->split_override / TILE_TOKENS) * (TILE_TOKENS / a.unit_tokens);
     waves = std::max<int64_t>(1, std::min((total + per - 1) / per, total));
-  } else if (small) {
+  } else if (by_blocks) {
     a.step_units = ellm::BLOCK_UNITS;
     for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
     total = waves = blocks;

@@ -116,43 +116,33 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
   return (group == 1 || group == 2) && padded * 3 <= Tc * 4;
 }
 
-// Which launches take one workgroup of several waves per BLOCK_UNITS units of a request (`blocks` of them per kv
-// head) instead of shares of one wave each; tiles: the pool's shares are cut in tiles; one_piece: no request has
-// more than one tile. Never more workgroups than two for every CU, one where requests are split, so a split
-// launch has at most one partial result per CU. 256 CUs, us a call, blocks / shares:
-//  - Pools whose shares are cut in units: split, 8 kv heads of 64, 4 q heads each: 1 request of 512 tokens
-//    7.7 / 7.8, 4000 8.4 / 8.9; 16 requests of 2000, 2 kv heads of 64, 16 q heads each 9.1 / 10.8. Not split: 64 of 200, 3 q
-//    heads of 128 12.7 / 14.9. Either cut leaves a request's result independent of its neighbours; which cut a
-//    launch has hangs on their number alone up to these limits.
-//  - Tiles, requests of one block each that shares would split: the combine launch is saved. 8 requests of 200
-//    tokens, 8 kv heads of 128, 4 q heads each 5.5 / 8.2; 64 of 200 12.9 / 15.7. One q head, past one for every CU: 64
-//    of 80 tokens 8.3 / 9.3, 128 10.4 / 9.4 (two full tiles, where shares are at their best), 160 11.6 / 12.2, 256 14.3 /
-//    14.3, with the fused append 10.8 / 9.8, 12.6 / 12.8, 13.1 / 13.5; 12 of 200 with 40 kv heads 11.9 / 12.4.
-//  - Tiles, split requests: the combine pass follows either way, and the blocks' kernel takes longer than the
-//    shares'; fewer partial results pay for that from 12 blocks (3000 tokens) per request on. 8 kv heads of 128:
-//    1 q head each: 1 request of 512 tokens 8.6 / 7.6, 1500 9.5 / 7.8, 3000 10.0 / 9.1, 8000 11.1 / 11.8; 4 q heads:
-//    512 8.8 / 8.4, 1500 9.6 / 9.0, 3000 10.1 / 10.1, 8000 11.2 / 12.9. With 4 q heads also where there is a workgroup
-//    for most CUs: 4 of 2000 10.5 / 11.2, 6 of 1000 (192) 9.8 / 9.8, with the fused append 10.6 / 11.7, 10.3 / 10.9; 1 q
-//    head: 4 of 2000 10.9 / 10.8, 6 of 1000 10.3 / 9.4. With 8 q heads of 128 (1 kv head: 512
-//    8.6 / 9.9, 4000 9.8 / 11.0) and 2 of 64 (2: 512 7.4 / 7.7, 4000 8.0 / 8.3) they are the faster way throughout.
-//  - Tiles, where shares split nothing either: one wave a request is enough, and a workgroup whose other waves
-//    have nothing to do only takes longer to start: 64 of 64 tokens, 8 kv heads of 128, 1 q head each 7.9 / 5.6,
-//    heads of 64 5.3 / 5.5 and 8 of 64 4.7 / 4.4. The tile kernel's instances for 4 and 8 q heads start more slowly
-//    still: 8 of 64 tokens, 4 q heads 4.5 / 6.1, 64 of 64 8.0 / 8.2; 2 q heads, 4 kv heads: 8 of 64 4.3 / 5.4, 128 of
-//    64 7.6 / 6.7.
-inline bool block_launch(int head_dim, int group, bool tiles, bool one_piece, int64_t blocks, int n_req, int n_kv, int cus) {
-  const int64_t workgroups = blocks * n_kv, one_each = cus, two_each = 2 * (int64_t)cus;
-  if (group > HEADS_PER_PASS) return false;
-  if (blocks > n_req) {
-    const bool always = !tiles || (head_dim == 64 ? group == 2 : group == 8);
-    const bool many = head_dim == 128 && group == 4 && workgroups * 4 >= one_each * 3;
-    return workgroups <= one_each && (always || many || blocks >= 12 * (int64_t)n_req);
-  }
-  if (tiles && one_piece) {
-    if (head_dim == 64 || group == 1) return false;
-    return workgroups <= (group == 2 ? one_each : two_each);
-  }
-  return workgroups <= two_each;
+// Small launches are cut in units whatever the pool's shares are cut in, and request by request: in blocks (one
+// workgroup of several waves per BLOCK_UNITS units of a request, `blocks` of them per kv head) or in steps (one wave
+// per STEP_UNITS). Small: at most two blocks for every CU, one where requests are split, so a split launch has at most
+// one partial result per SIMD.
+inline bool small_launch(int group, int64_t blocks, int n_req, int n_kv, int cus) {
+  return group <= HEADS_PER_PASS && blocks * n_kv <= cus * (blocks > n_req ? 1 : 2);
+}
+// Which of the two; tiles: the pool's shares are cut in tiles; one_piece: no request has more than one tile. 256 CUs,
+// us a call, blocks / steps / shares of tiles (these with the one-wave combine pass they had then):
+//  - Requests of one block each that steps would split: the combine launch is saved. 8 requests of 200 tokens, 8 kv
+//    heads of 128, 4 q heads each 5.2 / 7.9 / 8.0, 64 of 200 12.4 / 14.4 / 14.3; 1 q head 5.1 / 7.8 / 7.4, 64 of 80
+//    8.3 / - / 9.3, of 128 (two full tiles) 10.2 / 9.8 / 9.9, of 200 12.1 / 13.0 / 13.2.
+//  - Requests that one wave handles: a workgroup whose other waves have nothing to do takes longer to start where a
+//    CU gets two of them. 1 q head of 128: 8 of 64 tokens 4.0 / 4.7 / 4.2, 32 of 64 4.2 / 4.8 / 4.5, 64 of 64 7.7 / 5.2 /
+//    5.4; 4 q heads: 4.1 / 4.7 / 6.1, 4.3 / 4.8 / 6.1, 7.8 / 5.2 / 7.9. Heads of 64: 64 of 64 4.4 / 4.9 / 4.7.
+//  - Split requests: the combine pass follows either way, and the blocks' kernel takes longer; fewer partial results pay
+//    for that from 12 blocks (3000 tokens) per request on, or where almost every CU gets a block. Heads of 128, 8 kv
+//    heads, 4 q heads each: 1 of 512 tokens 8.8 / 8.3 / 8.2, 8 of 300 9.7 / 8.8 / 8.8, 1 of 1500 9.7 / 8.9 / 9.3, 3000 10.0 /
+//    9.9 / 12.6, 8000 10.9 / 12.2 / 20.6, 16 of 512 10.2 / 11.0 / 10.9; 1 q head: 1 of 512 8.6 / 8.3 / 7.5, 8 of 300
+//    9.4 / 8.7 / 7.5, 1 of 1500 9.1 / 8.5 / 8.5, 3000 9.8 / 9.6 / 11.0 (tiles are the faster way for short requests of
+//    one head; their weights are rounded to one bf16 value). Heads of 64: 1 of 512 7.6 / 7.6 / 7.4, 8000 8.6 / 10.8 / 16.
+// Pools whose shares are cut in units always take blocks, which leaves a request's result independent of its neighbours.
+inline bool takes_blocks(int head_dim, bool tiles, bool one_piece, int64_t blocks, int n_req, int n_kv, int cus) {
+  const int64_t workgroups = blocks * n_kv;
+  if (!tiles || head_dim == 64) return true;
+  if (blocks > n_req) return blocks >= 12 * (int64_t)n_req || workgroups * 8 >= (int64_t)cus * 7;
+  return !one_piece || workgroups <= cus;
 }
 
 // resident waves of the partial-pass kernel per compute unit (occupancy query)

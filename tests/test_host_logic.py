@@ -419,7 +419,7 @@ def test_bench_refuses_more_than_one_gpu():
 
 
 
-def planned(lens, n_q, n_kv, dim, tokens=512, units=0):
+def planned(lens, n_q, n_kv, dim, tokens=512, units=0, name=False):
     """(partial results per request, largest share in tokens) of the decode over requests of these lengths, as
     the library reports them, without a device (units: on a GPU of so many compute units)."""
     cb = tokens * 4 * n_kv * dim
@@ -432,14 +432,15 @@ def planned(lens, n_q, n_kv, dim, tokens=512, units=0):
     E.ellm_kv_append(P, ids, DUMMY, DUMMY, np.asarray(lens, np.int32), stream=0)
     E.ellm_debug_set_compute_units(P, units)
     n_split, most = E.ellm_decode_plan(P, ids)
+    kernel = E.ellm_debug_decode_kernel(P, ids)
     E.ellm_pool_destroy(P)
-    return list(n_split), most
+    return (list(n_split), most, kernel) if name else (list(n_split), most)
 
 
 def test_plan_reports_the_cut_of_small_batches():
     """A small batch is decoded by one workgroup per 256 tokens of a request, and that is the cut the plan
     reports; past the largest batch of that kind, shares of one wave each."""
-    assert planned([200, 256, 257, 512, 1100], 64, 8, 128) == ([1, 1, 2, 2, 5], 256)
+    assert planned([200, 256, 257, 512, 1100], 24, 8, 128) == ([1, 1, 2, 2, 5], 256)
     assert planned([200] * 64, 8, 8, 64) == ([1] * 64, 256)
     n_split, most = planned([200] * 65, 8, 8, 64)
     assert most < 256 and max(n_split) > 1
@@ -457,31 +458,42 @@ def test_workspace_bound_on_smaller_gpus(units, n_q, n_kv, dim):
         assert slots <= 4 * units + n_kv * (len(lens) - 1), (units, lens, n_split)
 
 
-@pytest.mark.parametrize("n_q,n_kv,dim,tokens,lens,blocks", [
-    # requests of one tile: in tile pools blocks only in place of the kernel's instances that start slowly
-    (8, 8, 128, 512, [64] * 64, False), (24, 8, 128, 512, [64] * 64, True), (40, 40, 128, 102, [64] * 8, False),
-    (8, 8, 64, 512, [64] * 8, False), (8, 4, 128, 512, [64] * 64, True), (8, 4, 128, 512, [64] * 65, False),
-    (32, 8, 128, 512, [64] * 64, True), (32, 8, 128, 512, [64] * 65, False), (32, 8, 128, 16, [64], True),
-    (32, 8, 128, 40, [64], True),
+@pytest.mark.parametrize("n_q,n_kv,dim,tokens,lens,cut", [
+    # requests of one tile
+    (8, 8, 128, 512, [64] * 32, "block"), (8, 8, 128, 512, [64] * 33, "unit"), (8, 8, 128, 512, [64] * 65, "tile"),
+    (32, 8, 128, 512, [64] * 64, "unit"), (32, 8, 128, 512, [64] * 65, "tile"), (40, 40, 128, 102, [64] * 8, "unit"),
+    (8, 8, 64, 512, [64] * 64, "block"), (24, 8, 128, 512, [64] * 64, "block"), (32, 8, 128, 16, [64] * 64, "block"),
     # of more than that, up to one block each
-    (8, 8, 128, 512, [64, 65], True), (8, 8, 128, 512, [65] * 32, True), (8, 8, 128, 512, [65] * 64, True), (8, 8, 128, 512, [65] * 65, False),
-    (16, 8, 128, 512, [65] * 64, True), (8, 8, 64, 512, [256] * 64, True), (8, 8, 64, 512, [256] * 65, False),
-    (24, 8, 128, 512, [256], True), (32, 8, 128, 16, [256], True), (34, 2, 128, 512, [100], False),
+    (8, 8, 128, 512, [64, 65], "block"), (32, 8, 128, 512, [65] * 64, "block"), (8, 8, 64, 512, [256] * 65, "tile"),
+    (24, 8, 128, 512, [256] * 65, "unit"), (34, 2, 128, 512, [100], "unit"),
     # split requests
-    (24, 8, 128, 512, [257], True), (24, 8, 128, 512, [257] * 17, False),     (8, 8, 128, 512, [257], False), (32, 8, 128, 512, [257] * 4, False), (32, 8, 128, 512, [257] * 11, False),
-    (32, 8, 128, 512, [257] * 12, True), (32, 8, 128, 512, [257] * 17, False), (16, 8, 128, 512, [257] * 12, False), (8, 8, 64, 512, [257], False),
-    (40, 40, 128, 102, [256], False), (16, 8, 64, 512, [257] * 16, True), (16, 8, 64, 512, [257] * 17, False),
-    (64, 8, 128, 512, [257], True), (32, 8, 128, 512, [2816], False), (32, 8, 128, 512, [2817], True),
-    (32, 8, 128, 512, [100, 5700], True), (32, 8, 128, 512, [100, 5600], False), (8, 8, 128, 512, [8192], True),
-    (8, 8, 128, 512, [8193], False)])
-def test_which_launches_take_blocks(n_q, n_kv, dim, tokens, lens, blocks):
-    """A small launch is cut into blocks only where that measured faster than shares of one wave each."""
-    n_split, most = planned(lens, n_q, n_kv, dim, tokens)
+    (8, 8, 128, 512, [257], "unit"), (32, 8, 128, 512, [257] * 4, "unit"), (64, 8, 128, 512, [257], "unit"),
+    (40, 40, 128, 102, [256], "unit"), (40, 40, 128, 102, [256] * 4, "tile"), (8, 8, 64, 512, [257], "block"),
+    (24, 8, 128, 512, [257], "block"), (16, 8, 64, 512, [257] * 17, "tile"), (24, 8, 128, 512, [257] * 17, "unit"),
+    (32, 8, 128, 512, [257] * 13, "unit"), (32, 8, 128, 512, [257] * 14, "block"), (32, 8, 128, 512, [257] * 17, "tile"),
+    (32, 8, 128, 512, [2816], "unit"), (32, 8, 128, 512, [2817], "block"), (8, 8, 128, 512, [8192], "block"),
+    (8, 8, 128, 512, [8193], "tile")])
+def test_cuts_of_small_launches(n_q, n_kv, dim, tokens, lens, cut):
+    """Which kernel a small launch runs, and that it is cut request by request: in blocks of 256 tokens' worth of
+    16-row units, or one wave per 64."""
+    n_split, most, kernel = planned(lens, n_q, n_kv, dim, tokens, name=True)
+    assert kernel == f"decode_{cut}_kernel"
     units = [n // tokens * -(-tokens // 16) + -(-(n % tokens) // 16) for n in lens]
-    cut = [-(-u // 16) for u in units]
-    assert (list(n_split) == cut and most == 256) == blocks
-    if not blocks and max(lens) <= 64 and tokens >= 64:
-        assert most == 64 and max(n_split) == 1         # still one launch, no combine pass
+    if cut == "block":
+        assert n_split == [-(-u // 16) for u in units] and most == 256
+    elif len(lens) * n_kv <= 512 and n_q // n_kv <= 16 and cut == "unit" and sum(units) * n_kv <= 4 * 1024:
+        assert n_split == [-(-u // 4) for u in units] and most == 64
+
+
+def test_no_small_launch_is_further_from_the_exact_result_than_another():
+    """Tiles round a weight to one bf16 value, units carry it as two: every launch below the limits walks units."""
+    for n_q, n_kv, dim, tokens in ((8, 8, 128, 512), (16, 8, 128, 64), (32, 8, 128, 102), (8, 1, 128, 512), (2, 2, 64, 512), (4, 2, 64, 80)):
+        for n in (1, 2, 3, 5, 8, 13, 21, 34, 55, 89):
+            for ln in (1, 17, 63, 64, 65, 200, 256, 257, 300, 511, 700, 1500, 2900, 3100, 8000):
+                units = ln // tokens * -(-tokens // 16) + -(-(ln % tokens) // 16)
+                blocks = n * -(-units // 16)
+                if blocks * n_kv <= (256 if blocks > n else 512):
+                    assert planned([ln] * n, n_q, n_kv, dim, tokens, name=True)[2] != "decode_tile_kernel", (n, ln)
 
 
 @pytest.mark.parametrize("lens,split", [([64] * 128, 1), ([65] * 120, 2), ([256] * 60, 4)])
