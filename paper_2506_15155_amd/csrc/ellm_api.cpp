@@ -118,7 +118,6 @@ struct ellm_pool {
   // (event r_compute.ev[i % EV_RING]) covers every compute call up to compute_covers[i % EV_RING].
   std::vector<int64_t> compute_covers;
   int64_t compute_marks = 0, compute_covered = 0;
-  int64_t compute_over = 0;            // highest compute call known to be no reason for a copy to wait for long
   std::vector<int64_t> chunk_compute, chunk_in, chunk_out;   // per chunk: seq of the last call of a kind, 0 = none
   std::vector<int64_t> host_in, host_out;                    // per host slot: last fetch that read it, last offload that wrote it
   // what each waiting stream already waits for, per ring (a stream is in order, so waiting for seq n covers all before)
@@ -387,9 +386,10 @@ int compute_mark(ellm_pool* p, int64_t need, hipEvent_t* ev, int64_t* covers) {
   return ELLM_OK;
 }
 
-// Is work unfinished that is in front of event `ev` (NULL: on the compute stream)? While that stream is being
-// captured there is nothing to ask (*yes = false); captures of other streams must not notice the question, which
-// the runtime would otherwise count against them.
+// Is the work in front of event `ev`, a mark of the compute stream, unfinished? While that stream is being captured
+// there is nothing to ask (*yes = false); captures of other streams must not notice the question, which the runtime
+// would otherwise count against them. (Half a microsecond in all; asked of the stream itself it would cost 15 where
+// the host has not waited for it, because the runtime then puts a marker there.)
 int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
   *yes = false;
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -400,10 +400,10 @@ int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
   if (capture != hipStreamCaptureStatusNone) return ELLM_OK;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
-  const hipError_t state = ev ? hipEventQuery(ev) : hipStreamQuery(p->last_stream);
+  const hipError_t state = hipEventQuery(ev);
   HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
   if (state == hipErrorNotReady) (void)hipGetLastError();
-  else HIP_TRY(state, ev ? "hipEventQuery(compute mark)" : "hipStreamQuery(compute stream)");
+  else HIP_TRY(state, "hipEventQuery(compute mark)");
   *yes = state == hipErrorNotReady;
   return ELLM_OK;
 }
@@ -413,27 +413,18 @@ int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
 int wait_for_compute(ellm_pool* p, hipStream_t waiter, int64_t need, int64_t& waited) {
   p->behind_compute = false;
   if (need <= p->r_compute.done) return ELLM_OK;
-  const bool ask = p->copy_by == ellm_pool::BY_RULE && p->host_dev && need > p->compute_over;
-  const bool marked = need <= p->compute_covered;
-  int rc;
-  if (ask && !marked) {
-    // asked of the stream before a mark goes there: a mark on an idle stream takes a moment to be seen as done
-    if ((rc = unfinished(p, nullptr, &p->behind_compute))) return rc;
-    if (!p->behind_compute) p->compute_over = p->r_compute.seq;
-  }
+  const bool ask = p->copy_by == ellm_pool::BY_RULE && p->host_dev;
   if (need <= waited && !ask) return ELLM_OK;
   hipEvent_t ev;
   int64_t covers;
-  if ((rc = compute_mark(p, need, &ev, &covers))) return rc;
+  int rc = compute_mark(p, need, &ev, &covers);
+  if (rc) return rc;
   if (need > waited) {
     HIP_TRY(hipStreamWaitEvent(waiter, ev, 0), "hipStreamWaitEvent(compute mark)");
     waited = covers;
   }
-  if (ask && marked) {
-    if ((rc = unfinished(p, ev, &p->behind_compute))) return rc;
-    if (!p->behind_compute) p->compute_over = std::max(p->compute_over, covers);
-  }
-  return ELLM_OK;
+  // (after the wait, which takes the host about as long as a new mark on an idle stream takes to be seen as done)
+  return ask ? unfinished(p, ev, &p->behind_compute) : ELLM_OK;
 }
 
 // a call of ring r's kind has enqueued its work on `stream`: number it and mark its end
