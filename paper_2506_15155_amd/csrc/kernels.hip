@@ -215,8 +215,9 @@ __global__ __launch_bounds__(256) void kv_append_kernel(PoolView pv, const uint4
 // offload / fetch (paper Sec. 2.2.2): whole chunks between the pool and pinned host memory, which the
 // GPU reads and writes directly over PCIe. One launch moves all chunks of a call, wherever they are:
 // per chunk a copy call of the runtime costs about 10 us of a 46 us transfer (2 MiB at a time go at
-// 44-45 GB/s on this machine, one large copy at 57); a kernel that gathers the chunks itself moves
-// them at 55-57 GB/s, and at 45 instead of 39 GB/s per direction when both directions run at once.
+// 44-45 GB/s on this machine, one large copy at 57); a kernel that gathers the chunks itself moves calls of 27
+// chunks at 54 / 57 GB/s out / in (engines 45 / 45) and at 40 per direction when both run at once with nothing to
+// wait for (engines 39), calls of 3 chunks at 49 / 53 and 29 (44 / 44 and 18).
 // WPC workgroups share a chunk; the loads and stores are streaming ones (the data passes through once).
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool, char* __restrict__ host, uint32_t chunk_bytes,
