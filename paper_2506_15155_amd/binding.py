@@ -52,7 +52,7 @@ class _Desc(C.Structure):
 
 
 _i32p = C.POINTER(C.c_int32)
-_i32_at = (C.c_int32 * 1).from_address     # taken where _i32p is declared, and cheaper to make than a pointer
+_i32_one = C.c_int32 * 1        # taken where _i32p is declared, and cheaper to make in place than a pointer
 _vp = C.c_void_p
 _sigs = {
     "ellm_pool_create": [C.POINTER(_Desc), C.POINTER(_vp)],
@@ -151,7 +151,10 @@ def _i32(a):
     if a is None:
         return None, None, 0
     arr = a if type(a) is np.ndarray and a.dtype == np.int32 and a.flags.c_contiguous else np.ascontiguousarray(a, dtype=np.int32)
-    return arr, _i32_at(arr.__array_interface__["data"][0]), arr.size
+    try:
+        return arr, _i32_one.from_buffer(arr), arr.size
+    except (TypeError, ValueError):        # read-only or empty
+        return arr, _i32_one.from_address(arr.ctypes.data), arr.size
 
 
 def _stream(stream) -> int | None:

@@ -529,7 +529,10 @@ def test_the_binding_refuses_addresses_of_the_wrong_type():
     assert E.lib.ellm_tensor_create(P, 16, C.byref(out)) == 0 and out.value == 0
     for ids in ([0], np.array([0]), np.array([[0, 5], [0, 7]], np.int32)[:1, :1], np.zeros(4, np.int32)[::4]):
         assert E.ellm_kv_premap_ahead(P, ids, 1) in (0, 1)
-    assert E.ellm_kv_premap_ahead(P, [], 1) == 0
+    assert E.ellm_kv_premap_ahead(P, [], 1) == 0 and E.ellm_kv_premap_ahead(P, np.zeros((0, 3), np.int32), 1) == 0
+    fixed = np.zeros(1, np.int32)
+    fixed.flags.writeable = False
+    assert E.ellm_kv_premap_ahead(P, fixed, 1) in (0, 1)
     E.ellm_tensor_map_chunks(P, 0, 1, 0, None)
     assert E.ellm_tensor_map_chunks(P, 0, 0, 2, np.array([3, 1, 2], np.int64)[:2], check=False) != 0     # slot 0 is mapped
     E.ellm_pool_destroy(P)
