@@ -568,3 +568,31 @@ def test_host_buffers_at_any_address(offset):
     assert torch.equal(out, want)
     assert E.ellm_pool_get_copy_counts(P) == ((0, 2) if offset % 16 == 0 else (2, 0))
     E.ellm_pool_destroy(P)
+
+
+def test_migration_inside_a_capture_of_its_own_stream():
+    """Decode, offload, fetch and decode captured into one graph: the replay gives the bits of the first decode, and
+    migrations made afterwards, which wait for marks that the capture left behind, are accepted and right."""
+    B, t, q, want = small_pool()
+    assert B.offload(t, 0, 4) == 0 and B.fetch(t, 0, 4) == 0
+    E.ellm_pool_sync(B.pool)
+    torch.cuda.synchronize()
+    out = torch.empty_like(q)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        E.ellm_decode_attention(B.pool, [t], q, out)
+        assert B.offload(t, 0, 2) == 0 and B.offload(t, 2, 2) == 0 and B.fetch(t, 0, 4) == 0
+        E.ellm_decode_attention(B.pool, [t], q, out)
+    out.zero_()
+    graph.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(out, want)
+    for _ in range(3):
+        for s in range(4):
+            assert B.offload(t, s, 1) == 0
+        assert B.fetch(t, 0, 4) == 0
+        out.zero_()
+        E.ellm_decode_attention(B.pool, [t], q, out)
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+    B.close()
