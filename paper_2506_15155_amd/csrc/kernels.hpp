@@ -109,10 +109,11 @@ struct CopyArgs {
 // 65 / 58, 40: 55.8 / 57.4, 64: 56.1 / 58.5, 512: 55.7 / 59.2, and alike for 1, 2 and 8 heads; head size
 // 64, 1 head: 24: 44 / 32, 40: 33.0 / 31.8, 48: 30.5 / 31.4, 80: 32.7 / 31.5, 102: 30.4 / 31.8, 2 heads
 // within 1 %; 4 heads: 48: 33.1 / 31.6, 512: 33.5 / 32.0, 8 heads: 39 / 32 and 38 / 33. With the fused append one
-// head of 128 gains less from units: chunks of 32 tokens 60.2 / 61.4 (without it 57.2 / 58.0), 36: 59.1 / 61.1 (56.5 / 56.5).
+// head of 128 gains nothing from units in chunks of 32 to 39 tokens (32: 60.2 / 61.4, without it 57.2 / 58.0, 36: 59.1 /
+// 61.1, 56.5 / 56.5); they stay there because they carry a weight as two bf16 values, tiles as one.
 inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
   const int64_t Tc = tokens_per_chunk, padded = (Tc + TILE_TOKENS - 1) / TILE_TOKENS * TILE_TOKENS;
-  if (head_dim == 128) return group == 1 ? padded <= Tc * 2 : (group == 2 || group == 4 || group == 8) && padded * 5 <= Tc * 8;
+  if (head_dim == 128) return (group == 1 || group == 2 || group == 4 || group == 8) && padded * 5 <= Tc * 8;
   return (group == 1 || group == 2) && padded * 3 <= Tc * 4;
 }
 

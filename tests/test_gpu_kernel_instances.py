@@ -18,7 +18,7 @@ SHORT = [1, 15, 16, 17, 31, 47, 64, 65, 129, 300]      # around units, tiles, ch
     ("decode_tile_kernel", 2, 2, 64, 48, SHORT, 64), ("decode_tile_kernel", 2, 2, 64, 64, SHORT, 192),
     ("decode_tile_kernel", 4, 2, 64, 64, SHORT, 64), ("decode_tile_kernel", 4, 2, 64, 128, SHORT, 192),
     ("decode_tile_kernel", 1, 1, 128, 40, SHORT, 64), ("decode_tile_kernel", 2, 1, 128, 64, SHORT, 192),
-    ("decode_tile_kernel", 1, 1, 128, 32, SHORT, 192), ("decode_tile_kernel", 3, 3, 128, 72, SHORT, 64),
+    ("decode_unit_kernel", 1, 1, 128, 32, SHORT, 192), ("decode_unit_kernel", 3, 3, 128, 72, SHORT, 64),
     ("decode_tile_kernel", 4, 1, 128, 80, SHORT, 64), ("decode_tile_kernel", 16, 2, 128, 40, SHORT, 192),
     ("decode_unit_kernel", 3, 1, 128, 24, SHORT, 64), ("decode_unit_kernel", 34, 2, 128, 16, SHORT, 192),
     ("decode_unit_kernel", 4, 1, 128, 8, SHORT, 64), ("decode_unit_kernel", 8, 1, 64, 64, SHORT, 192),

@@ -559,7 +559,7 @@ def test_the_current_stream_is_torchs_own_answer(monkeypatch):
     assert binding._stream(Stream) == 0x1230
 
 
-@pytest.mark.parametrize("dim,group,first", [(128, 1, 32), (128, 2, 40), (128, 4, 40), (128, 8, 40), (64, 1, 48), (64, 2, 48)])
+@pytest.mark.parametrize("dim,group,first", [(128, 1, 40), (128, 2, 40), (128, 4, 40), (128, 8, 40), (64, 1, 48), (64, 2, 48)])
 def test_chunks_that_tiles_fill_well_enough(dim, group, first):
     """From which chunk size on a pool's shares are cut in 64-row tiles instead of 16-row units."""
     for tokens in range(1, 65):
