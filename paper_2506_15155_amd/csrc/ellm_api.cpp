@@ -81,6 +81,7 @@ struct ellm_pool {
   // device-side metadata, created by the first call that needs the device
   bool dev_ready = false;
   int32_t* d_table = nullptr;
+  uint32_t* d_merged = nullptr;        // in the same allocation: see PoolView::merged
   float* d_ws = nullptr;               // partial results of one decode launch (see BatchArgs)
   int64_t ws_cap_slots = 0;            // partial slots it holds
   float* static_ws = nullptr;          // this device's copy of the library's fixed workspace
@@ -194,6 +195,7 @@ ellm::PoolView view_of(const ellm_pool* p) {
   v.base = p->device_base;
   v.table = p->d_table;
   v.vbase = (p->vmm && !p->vmm_table_kernels) ? p->d_vbase : nullptr;
+  v.merged = p->d_merged;
   v.chunk_bytes = p->geom.chunk_bytes;
   v.tokens_per_chunk = p->geom.tokens_per_chunk;
   v.tiles_per_chunk = (p->geom.tokens_per_chunk + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
@@ -230,9 +232,13 @@ size_t slot_bytes(int32_t group, int32_t head_dim) { return (size_t)group * (hea
 
 int ensure_device(ellm_pool* p) {
   if (p->dev_ready) return ELLM_OK;
-  const size_t bytes = p->core->table().size() * sizeof(int32_t);
-  HIP_TRY(hipMalloc((void**)&p->d_table, bytes), "hipMalloc(table mirror)");
-  HIP_TRY(hipMemcpy(p->d_table, p->core->table().data(), bytes, hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
+  // the table mirror and, behind it, the counters of partial results, all 0
+  std::vector<int32_t> image = p->core->table();
+  const size_t counters_at = (image.size() + 63) / 64 * 64;
+  image.resize(counters_at + (size_t)p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ * ellm::MERGE_STRIDE, 0);
+  HIP_TRY(hipMalloc((void**)&p->d_table, image.size() * sizeof(int32_t)), "hipMalloc(table mirror)");
+  HIP_TRY(hipMemcpy(p->d_table, image.data(), image.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
+  p->d_merged = (uint32_t*)p->d_table + counters_at;
   (void)p->core->take_dirty();   // the full upload covers everything so far
   // the workspace is sized once, for the largest launch the automatic partition can produce
   p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::MAX_LAUNCH_REQ));
@@ -823,7 +829,7 @@ using ellm::TILE_TOKENS;
 
 // how many partial slots per kv head the cut of sequences of n[i] steps into `waves` shares needs; with
 // a != NULL the cut is written there
-int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a) {
+int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0) {
   const int64_t each = total / waves, more = total - each * waves;
   // wave that holds step x: the first `more` waves hold each + 1 steps, the others each
   auto wave_of = [&](int64_t x) { return x < more * (each + 1) ? x / (each + 1) : more + (x - more * (each + 1)) / each; };
@@ -836,18 +842,19 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
       a->req[i].wave_first = (int32_t)w0;
       a->req[i].n_part = (int32_t)(w1 - w0 + 1);
       a->req[i].part0 = w1 > w0 ? (int32_t)std::min<int64_t>(parts, 0x7fffffff) : 0;
-      if (w1 > w0) a->split_req[n_split >> 2] |= (uint32_t)i << ((n_split & 3) * 8);
+      if (w1 > w0 && w1 - w0 + 1 > merge_parts) {
+        a->split_req[n_split >> 2] |= (uint32_t)i << ((n_split & 3) * 8);
+        n_split++;
+      }
     }
-    if (w1 > w0) {               // a request shared by several waves: partial results and a combine pass
-      parts += w1 - w0 + 1;
-      n_split++;
-    }
+    if (w1 > w0) parts += w1 - w0 + 1;   // a request shared by several waves: partial results
     at += n[i];
   }
   if (a) {
     a->units_each = (int32_t)each;
     a->units_extra = (int32_t)more;
     a->n_split_req = n_split;
+    a->merge_parts = merge_parts;
   }
   return parts;
 }
@@ -930,7 +937,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     }
   }
   std::memset(a.split_req, 0, sizeof(a.split_req));
-  const int64_t parts = cut_shares(units, total, waves, &a);
+  const int64_t parts = cut_shares(units, total, waves, &a, ellm::merge_parts(p->geom.head_dim, p->geom.group, by_blocks));
   a.n_req = n_req;
   a.q_row0 = q_row0;
   a.units_per_head = (int32_t)std::min<int64_t>(total, 0x7fffffff);
@@ -1226,7 +1233,7 @@ int ellm_pool_set_split_tokens(ellm_pool* p, int32_t split_tokens) {
 
 // decode over `ids`; with k_new / v_new the one-token append is fused into the same launches.
 // ws / ws_cap_slots: where the partial results go. The launches of a call run one after the other
-// on one stream, each followed by its combine pass, so all of them use the same workspace.
+// on one stream, so all of them use the same workspace.
 static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, const void* q, const void* k_new,
                        const void* v_new, void* out, float scale, hipStream_t stream, int32_t* n_launched,
                        float* ws_fixed = nullptr, int64_t ws_fixed_slots = 0) {

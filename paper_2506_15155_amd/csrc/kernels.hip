@@ -89,6 +89,12 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef short __attribute__((ext_vector_type(4))) bf16x4_bits_t;     // four bf16 values as the matrix instructions take them
 typedef float __attribute__((ext_vector_type(4))) f32x4_t;
 
+typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+// two floats rounded to nearest-even bf16, the first in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
+}
+
 // c + a.lo * b.lo + a.hi * b.hi on packed bf16 pairs, fp32 accumulate
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float c) {
   return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, a), __builtin_bit_cast(bf16x2_t, b), c, false);
@@ -130,7 +136,22 @@ __device__ __forceinline__ void store_stream16(void* p, uint4 v) {
   __builtin_nontemporal_store(t, reinterpret_cast<u32x4_t*>(p));
 }
 
-constexpr int CPOL_NT = 2;    // cache-policy operand of the load-to-LDS builtin: non-temporal
+// cache-policy operand of the buffer and load-to-LDS builtins: non-temporal; coherent across the GPU (past the L2
+// of the wave's own XCD)
+constexpr int CPOL_NT = 2, CPOL_DEVICE = 16;
+
+typedef __attribute__((ext_vector_type(4))) uint32_t words4_t;
+typedef __attribute__((ext_vector_type(2))) uint32_t words2_t;
+
+// memory from `base` on (the same for all lanes; said so, because the descriptor has to be in scalar registers) as a
+// buffer: loads past its end return zeros, stores past it are dropped
+constexpr int BUFFER_RAW = 0x00027000;    // last word of a buffer descriptor: raw dwords, range check on the byte offset
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* base, int32_t bytes) {
+  const uint64_t b = (uint64_t)base;
+  const uint64_t bs = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
+                      (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
+  return __builtin_amdgcn_make_buffer_rsrc((void*)bs, 0, __builtin_amdgcn_readfirstlane(bytes), BUFFER_RAW);
+}
 
 typedef const __attribute__((address_space(1))) void* global_cptr_t;
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
@@ -282,6 +303,203 @@ __device__ __forceinline__ Share locate_share(const BatchArgs& a, int32_t index,
   return s;
 }
 
+// which four dims of a head piece f of a partial result's row holds: rows keep the dims in the order in which the
+// lanes of the kernel that wrote them store neighbouring pieces
+template <int D>
+__device__ __forceinline__ int32_t partial_dim(int32_t unit_tokens, int32_t f) {
+  constexpr int LPR = D / 8, E = D / 16;
+  return unit_tokens == TILE_TOKENS ? 8 * (f % LPR) + 4 * (f / LPR) : E * (4 * (f & 3) + f / E) + (f % E) / 4 * 4;
+}
+
+// ---------------------------------------------------------------------------------------------
+// Requests that several waves share. The SHARE_WAVES waves of a workgroup (one per SIMD of a CU) walk neighbouring
+// shares; a request that such a wave begins or ends in the middle of has its results of that wave put into LDS, and
+// when all four are done the results of one request are added up there, the requests dealt out to the waves. What
+// lies wholly inside the workgroup is finished by that. A request that reaches into other workgroups leaves one partial
+// result in the workspace, written past the L2 of the XCD, and its workgroup counts itself in once it is there; the last
+// to do so adds up all of them. Which one that is depends on who ends last, but the sum is taken in the order of the
+// partials, so the result does not. Nobody waits for another workgroup, and the counter goes back to 0 by itself
+// (an increment that wraps).
+// This took the place of a combine launch behind every call, 4.6 us of which 3.4 are the launch; a workgroup's chain
+// behind its last wave is 2.5 to 4 us (LDS sum and store 1.2 to 1.6, count 0.4, adding up 1 to 2.4). 8B-shaped step 2087 ->
+// 2003 us, 8 requests of it, 4 layers 67.5 -> 63.7, 48 requests of 6 q heads each 52.2 -> 49.4, 64 of 16 heads of 64 68.2 ->
+// 66.6, chunks of 16 tokens 36.9 -> 33.8. By single waves, without the sum in LDS, it was no faster than the pass: up to 29
+// partials for one wave to add up, 6 us.
+// ---------------------------------------------------------------------------------------------
+__device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t rows, int32_t at, float4 v) {
+  const words4_t w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
+  __builtin_amdgcn_raw_buffer_store_b128(w, rows, at, 0, CPOL_DEVICE);
+}
+__device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t pairs, int32_t at, float2 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(words2_t{__float_as_uint(v.x), __float_as_uint(v.y)}, pairs, at, 0, CPOL_DEVICE);
+}
+// this wave's stores have arrived where every XCD sees them
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
+  asm volatile("" ::: "memory");
+}
+// One more of n_part shares of request b, kv head g, has its results in memory (asked by one lane): how many had before?
+__device__ __forceinline__ uint32_t count_in(const PoolView& pv, int32_t g, int32_t b, int32_t n_part) {
+  return atomicInc(pv.merged + ((int64_t)g * MAX_LAUNCH_REQ + b) * MERGE_STRIDE, (uint32_t)n_part - 1u);
+}
+
+// sums of one 16-byte piece of a head's row over some partials: running maximum, normaliser, weighted sum
+struct Sum { float M, L; float4 A; };
+__device__ __forceinline__ void add(Sum& s, float L, const float4& v, float w) {
+  s.L += L * w;
+  s.A.x += v.x * w; s.A.y += v.y * w; s.A.z += v.z * w; s.A.w += v.w * w;
+}
+__device__ __forceinline__ void rescale(Sum& s, float M) {
+  const float w = fast_exp2(s.M - M);
+  s.M = M;
+  s.L *= w;
+  s.A.x *= w; s.A.y *= w; s.A.z *= w; s.A.w *= w;
+}
+
+// The partials of a request for n_heads q heads of kv head g from head g_first of the group on. Columns: the pieces of
+// the heads' rows in order.
+template <int D>
+struct Partials {
+  static constexpr int F = D / 4;
+  __amdgpu_buffer_rsrc_t rows, pairs;
+  int32_t group;
+  __device__ __forceinline__ Partials(const PoolView& pv, const float* ws, const BatchArgs& a, int32_t part0, int32_t n_part, int32_t g,
+                                      int32_t g_first, int32_t n_heads) : group(pv.group) {
+    const int64_t row0 = ((int64_t)g * a.parts_per_head + part0) * group + g_first;
+    const int32_t n_rows = (n_part - 1) * group + n_heads;
+    rows = buffer_at(ws + row0 * D, n_rows * (D * 4));
+    pairs = buffer_at(ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML, n_rows * (WS_ML * 4));
+    asm volatile("" ::: "memory");     // nothing of this is read before the last one has counted itself in
+  }
+  // columns x, x + step, .. (KB of them) over partials j0 .. j1 - 1, FEW or MANY of them asked for at a time
+  template <int KB, int FEW, int MANY>
+  __device__ __forceinline__ void sum(Sum (&sums)[KB], int32_t x, int32_t step, int32_t j0, int32_t j1) const {
+#pragma unroll
+    for (int k = 0; k < KB; k++) sums[k] = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+    auto some = [&](auto ahead) __attribute__((always_inline)) {
+      constexpr int N = decltype(ahead)::value;
+      words4_t v[KB][N];
+      words2_t ml[KB][N];
+#pragma unroll
+      for (int u = 0; u < N; u++)
+#pragma unroll
+        for (int k = 0; k < KB; k++) {
+          const int32_t xk = x + k * step, row = (j0 + u) * group + xk / F;
+          ml[k][u] = __builtin_amdgcn_raw_buffer_load_b64(pairs, row * (WS_ML * 4), 0, CPOL_DEVICE);
+          v[k][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, row * (D * 4) + xk % F * 16, 0, CPOL_DEVICE);
+        }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int k = 0; k < KB; k++) {
+        float M = sums[k].M;
+#pragma unroll
+        for (int u = 0; u < N; u++) M = j0 + u < j1 ? fmaxf(M, __uint_as_float(ml[k][u].x)) : M;
+        rescale(sums[k], M);
+#pragma unroll
+        for (int u = 0; u < N; u++) {
+          const words4_t t = v[k][u];
+          if (j0 + u < j1)
+            add(sums[k], __uint_as_float(ml[k][u].y), make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)),
+                fast_exp2(__uint_as_float(ml[k][u].x) - M));
+        }
+      }
+    };
+    for (; j0 + FEW < j1; j0 += MANY) some(std::integral_constant<int, MANY>{});
+    if (j0 < j1) some(std::integral_constant<int, FEW>{});
+  }
+};
+
+// column x of request b's output: the four dims that piece x % (D / 4) of the rows holds, of head g_first + x / (D / 4)
+template <int D>
+__device__ __forceinline__ void write_out(const PoolView& pv, uint16_t* __restrict__ out, const BatchArgs& a, int32_t b, int32_t g,
+                                          int32_t g_first, int32_t x, const Sum& s) {
+  constexpr int F = D / 4;
+  const float inv = 1.f / s.L;
+  uint16_t* o = out + ((int64_t)(a.q_row0 + b) * pv.n_q_heads + g * pv.group + g_first + x / F) * D + partial_dim<D>(a.unit_tokens, x % F);
+  *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16(s.A.x * inv, s.A.y * inv), pack_bf16(s.A.z * inv, s.A.w * inv));
+}
+
+// Where a request's partial results are: the workgroups it reaches into, for kv head g, are numbered from 0 on
+struct Parts { int32_t first, n; };    // workgroup of its first wave, how many
+__device__ __forceinline__ Parts parts_of(int32_t wave_first, int32_t n_part, int32_t waves_per_head, int32_t g, bool blocks) {
+  const int32_t w0 = g * waves_per_head + wave_first;
+  if (blocks) return {w0, n_part};     // a workgroup is one of the request's steps
+  return {w0 / SHARE_WAVES, (w0 + n_part - 1) / SHARE_WAVES - w0 / SHARE_WAVES + 1};
+}
+
+// results of the workgroup's waves: slot 2 w of wave w's first request, 2 w + 1 of its last one, if it is another
+template <int D, int HEADS>
+struct Results {
+  float4 rows[2 * SHARE_WAVES][HEADS][D / 4 + 1];    // (padded against bank conflicts)
+  float2 ml[2 * SHARE_WAVES][HEADS];
+  int32_t whose[2 * SHARE_WAVES];      // request and kv head, -1: no result, or one that needs no other
+};
+
+// all waves of the workgroup have ended their shares
+template <int D, int HEADS, int KB, int MANY>
+__device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16_t* __restrict__ out, const BatchArgs& a,
+                                           const Results<D, HEADS>& res, int32_t g_first, int32_t n_heads, int32_t wave, int32_t lane) {
+  constexpr int F = D / 4;
+  __syncthreads();
+  const int32_t whose = lane < 2 * SHARE_WAVES ? res.whose[lane] : -1;
+  uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(whose >= 0);
+  for (int32_t nth = 0; left; nth++) {
+    const int32_t id = __builtin_amdgcn_readlane(whose, __builtin_ctz(left));
+    uint32_t mine = (uint32_t)__builtin_amdgcn_ballot_w64(whose == id);      // the slots of one request
+    left &= ~mine;
+    if (nth % SHARE_WAVES != wave) continue;
+    const int32_t b = id % MAX_LAUNCH_REQ, g = id / MAX_LAUNCH_REQ;
+    const BatchArgs::Req rq = a.req[b];
+    const int32_t n = __builtin_popcount(mine);      // at most one slot of every wave
+    int32_t slot[SHARE_WAVES];
+#pragma unroll
+    for (int i = 0; i < SHARE_WAVES; i++) {
+      slot[i] = mine ? __builtin_ctz(mine) : slot[i ? i - 1 : 0];
+      mine &= mine - 1;
+    }
+    const Parts parts = parts_of(rq.wave_first, rq.n_part, a.waves_per_head, g, false);
+    const int64_t row0 = ((int64_t)g * a.parts_per_head + rq.part0 + ((int32_t)blockIdx.x - parts.first)) * pv.group + g_first;
+    const auto rows = buffer_at(ws + row0 * D, n_heads * (D * 4));
+    const auto pairs = buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4));
+    for (int32_t x = lane; x < n_heads * F; x += 64) {
+      const int32_t h = x / F, f = x % F;
+      float2 ml[SHARE_WAVES];
+      float4 v[SHARE_WAVES];
+#pragma unroll
+      for (int i = 0; i < SHARE_WAVES; i++) {
+        ml[i] = res.ml[slot[i]][h];
+        v[i] = res.rows[slot[i]][h][f];
+      }
+      Sum s = {ml[0].x, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+#pragma unroll
+      for (int i = 1; i < SHARE_WAVES; i++) s.M = fmaxf(s.M, ml[i].x);
+#pragma unroll
+      for (int i = 0; i < SHARE_WAVES; i++)
+        if (i < n) add(s, ml[i].y, v[i], fast_exp2(ml[i].x - s.M));
+      if (n == rq.n_part) {
+        write_out<D>(pv, out, a, b, g, g_first, x, s);
+      } else {
+        store_partial(rows, x * 16, s.A);
+        if (f == 0) store_partial(pairs, h * (WS_ML * 4), make_float2(s.M, s.L));
+      }
+    }
+    if (n == rq.n_part || rq.n_part > a.merge_parts) continue;
+    stores_done();
+    uint32_t before = 0;
+    if (lane == 0) before = count_in(pv, g, b, parts.n);
+    if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)parts.n - 1u) continue;
+    const Partials<D> all(pv, ws, a, rq.part0, parts.n, g, g_first, n_heads);
+    for (int32_t x = lane; x - lane < n_heads * F; x += KB * 64) {
+      Sum s[KB];
+      all.template sum<KB, 4, MANY>(s, x, 64, 0, parts.n);
+#pragma unroll
+      for (int k = 0; k < KB; k++)
+        if (x + k * 64 < n_heads * F) write_out<D>(pv, out, a, b, g, g_first, x + k * 64, s[k]);
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------------------------
 // decode attention, partial pass (split-K), for 1, 2, 4 and 8 q heads per kv head and chunks that whole
 // tiles fill (see tile_kernel): one wave per equal share of a kv head's tiles
@@ -309,6 +527,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
                                                     const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
                                                     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
                                                     int32_t g_first, const BatchArgs& a) {
+  constexpr int NW = SHARE_WAVES;
   constexpr int LPR = D / 8;             // lanes per row = 16-byte pieces per row
   constexpr int RPW = 64 / LPR;          // rows per wave-wide load
   constexpr int NL = 64 / RPW;           // wave-wide loads per 64-row tile and plane
@@ -326,10 +545,14 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
   // one, so that four of its rows at a time are the contraction index of one product; the tile's
   // weights reach it through a small transposed copy in LDS.
   constexpr bool MFMA_PV = (G % 4 == 0);
-  __shared__ __attribute__((aligned(16))) uint16_t sm_p[MFMA_PV ? G * 64 : 8];   // weights [head][token], bf16
-  __shared__ __attribute__((aligned(16))) char sm_k[64 * ROWB];      // the K tile being scored
+  __shared__ __attribute__((aligned(16))) uint16_t sm_p_all[NW][MFMA_PV ? G * 64 : 8];   // weights [head][token], bf16
+  __shared__ __attribute__((aligned(16))) char sm_k_all[NW][64 * ROWB];      // the K tile being scored
+  __shared__ __attribute__((aligned(16))) Results<D, G> results;
 
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint16_t* const sm_p = sm_p_all[wave];
+  char* const sm_k = sm_k_all[wave];
   const int sub = lane % LPR, rg = lane / LPR;
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
@@ -366,7 +589,6 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
     len = nx_.len;                                                                                  \
     left = units_of(len, Tc, pv.tiles_per_chunk, TILE_TOKENS);                                                   \
     c_np = nx_.n_part;                                                                              \
-    c_p0 = nx_.part0;                                                                               \
     walk = tensor_walk<DIRECT>(pv, nx_.tensor);                                                     \
     slot = 0;                                                                                       \
     r = 0;                                                                                          \
@@ -530,8 +752,10 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
     vn = v_new[row16];                                                                              \
   }
 
-  {
-    const Share sh = locate_share(a, blockIdx.x, lane);
+  if (lane < 2) results.whose[2 * wave + lane] = -1;
+  const int32_t index = blockIdx.x * NW + wave;
+  if (index < a.waves_per_head * pv.n_kv_heads) {
+    const Share sh = locate_share(a, index, lane);
     const int32_t g = sh.g, n_tiles = sh.n_units;
     const int hq0 = g * pv.group + g_first;            // first q head handled here
     // cursor: the tile whose K is in LDS or on its way there. cb: its request; len, walk: that
@@ -548,11 +772,9 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
     const char* kb = chunk_addr<DIRECT>(pv, walk, slot) + ((uint64_t)(g * 2) * Tc + r) * ROWB;
     ELLM_LOAD_K_TILE(kb, nv_c)
 
-    // the request being accumulated, and which of its partials this wave writes; b_np, b_p0: how
-    // many waves share the request and where its partial slots start (c_np, c_p0: the same for the
-    // cursor's request, which runs one tile ahead)
-    int32_t b = cb, j = sh.w - first.wave_first;
-    int32_t b_np = first.n_part, b_p0 = first.part0, c_np = b_np, c_p0 = b_p0;
+    // the request being accumulated, and how many waves share it (c_np: the same for the cursor's
+    // request, which runs one tile ahead)
+    int32_t b = cb, b_np = first.n_part, c_np = b_np;
     uint32_t qreg[MFMA_QK ? 1 : G][QR];
     bf16x4_bits_t qa[MFMA_QK ? 2 * LPR : 1];
     uint4 kn, vn;
@@ -641,9 +863,8 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
           l[i] = wave_sum(l[i]);
         }
         if (b_np == 1) {
-          // the whole request lay inside this wave's share: this is the final result. Normalise and
-          // round exactly as the combine pass would for a single partial (weight 1) and write the
-          // output rows; no workspace traffic, no second pass for this request
+          // the whole request lay inside this wave's share: this is the final result. Normalise, round
+          // and write the output rows
           if (rg == 0) {
 #pragma unroll
             for (int i = 0; i < G; i++) {
@@ -657,31 +878,27 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
             }
           }
         } else {
-          // accumulators: one row of D floats per (partial slot, q head), every row a whole number of
-          // cache lines; m and l of all partials sit together behind the rows, two floats each
-          const int64_t row0 = ((int64_t)g * a.parts_per_head + b_p0 + j) * pv.group + g_first;
-          float* wout = ws + row0 * D;
-          float* wml = ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML;
+          // one of several waves of the request: its results meet the others' in LDS
+          // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
+          const int32_t to = 2 * wave + (b == sh.b ? 0 : 1);
           if (rg == 0) {
 #pragma unroll
-            for (int i = 0; i < G; i++) {
-              float4* dst = reinterpret_cast<float4*>(wout + i * D + sub * 8);
-              dst[0] = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-              dst[1] = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
-            }
+            for (int i = 0; i < G; i++)
+#pragma unroll
+              for (int h = 0; h < 2; h++)
+                results.rows[to][i][h * LPR + sub] = make_float4(acc[i][4 * h], acc[i][4 * h + 1], acc[i][4 * h + 2], acc[i][4 * h + 3]);
             float mm = m[0], ll = l[0];       // lane `sub` writes head sub's pair
 #pragma unroll
             for (int i = 1; i < G; i++)
               if (sub == i) { mm = m[i]; ll = l[i]; }
-            if (sub < G) *reinterpret_cast<float2*>(wml + sub * WS_ML) = make_float2(mm, ll);
+            if (sub < G) results.ml[to][sub] = make_float2(mm, ll);
+            if (sub == 0) results.whose[to] = g * MAX_LAUNCH_REQ + b;
           }
         }
         if (more) {
           // the cursor is already in the next request, whose first tile this wave holds
           b = cb;
-          j = 0;
           b_np = c_np;
-          b_p0 = c_p0;
           ELLM_LOAD_Q(b)
           ELLM_LOAD_NEW_ROW(b)
           q_settled = false;
@@ -699,6 +916,8 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
       }
     }
   }
+  constexpr int KB = (G * D / 4 + 63) / 64;
+  end_shares<D, G, KB, KB == 1 ? 16 : 32 / KB>(pv, ws, out, a, results, g_first, G, wave, lane);
 #undef ELLM_LOAD_Q
 #undef ELLM_LOAD_NEW_ROW
 #undef ELLM_LOAD_TILE
@@ -715,13 +934,13 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
 // whole query rows and the matrix-core accumulators in registers, are compiled without it and do
 // not spill.
 template <int D, int G, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void decode_tile_kernel(
+__global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void decode_tile_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
   decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
 }
 template <int D, int G, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_tile_kernel_wide(
+__global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_tile_kernel_wide(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
   decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
@@ -756,7 +975,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 //      (m, l, the rescaling) sits in the lanes that need it, and a lane ends with 4 E consecutive dims.
 // Nothing goes through LDS (NW == 0; the waves of a block add up there). The cost per byte does not depend on the number of q heads up to 16, so every
 // group size up to that is one pass over K and V. Bound by HBM: 48 requests of 6 q heads per kv head (278 MB
-// of K and V) 92.4 -> 51.8 us with the combine pass (the tile kernels took two passes), 64 requests of 16
+// of K and V) 92.4 -> 51.8 us with a combine pass (the tile kernels read K and V twice), 64 requests of 16
 // heads of 64 (398 MB) 144 -> 69.8, 16-token chunks (187 MB) 50.8 -> 36.4.
 // Tried on these and on the 8B-shaped layer: two or three tiles in registers (no faster, and what does not
 // fit 256 registers goes through accumulation registers: 2 to 4 % slower); tiles of 64 tokens (pages
@@ -765,19 +984,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(1, 1))) void
 // Scores are kept in log2 units (scale_log2 = scale * log2 e).
 // ---------------------------------------------------------------------------------------------
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) uint32_t words4_t;
-typedef __attribute__((ext_vector_type(2))) uint32_t words2_t;
-typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef const __attribute__((address_space(1))) char* gptr_t;
 typedef __attribute__((address_space(1))) char* gwptr_t;
 
-constexpr int BUFFER_RAW = 0x00027000;    // last word of a buffer descriptor: raw dwords, range check on the byte offset
 __device__ __forceinline__ f32x4_t mfma16(words4_t a, words4_t b, f32x4_t c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b), c, 0, 0, 0);
-}
-// two floats rounded to nearest-even bf16, the first in the low half
-__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
-  return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t{a, b}), bf16x2_t));
 }
 
 enum : uint32_t { T_FIRST = 1, T_LAST = 2, T_FIN = 4 };   // a tile starts a request here, ends it, ends the share
@@ -811,12 +1022,13 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   constexpr int P = D / 32;          // products along a row = 16-byte pieces of K, dwords of a V row, per lane
   constexpr int ROWB = D * 2, E = D / 16, VB = E * 2;
   static_assert(U % 2 == 0, "PV takes two units at a time");
-  const int lane = NW ? threadIdx.x & 63 : threadIdx.x, c = lane & 15, g16 = lane >> 4;
-  const int wave = NW ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const int lane = threadIdx.x & 63, c = lane & 15, g16 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
-  const Share sh = locate_share(a, blockIdx.x, lane);
+  const int32_t index = NW ? blockIdx.x : blockIdx.x * SHARE_WAVES + wave;
+  const Share sh = locate_share(a, NW ? index : min(index, a.waves_per_head * pv.n_kv_heads - 1), lane);
   const int32_t g = sh.g;
   const int32_t hq0 = g * pv.group + g_first;        // first q head handled here
   const int32_t head = min(c, n_heads - 1);          // lanes beyond the last head repeat it and write nothing
@@ -825,17 +1037,18 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   int32_t cb = sh.b, rem_share = sh.n_units, len, slot, r, rem_req, part;
   uint32_t first = T_FIRST;
   TensorWalk walk;
+  const BatchArgs::Req first_rq = a.req[cb];
   {
-    const BatchArgs::Req rq = a.req[cb];
+    const BatchArgs::Req& rq = first_rq;
     len = rq.len;
     walk = tensor_walk<DIRECT>(pv, rq.tensor);
-    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + wave * U;
+    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + (NW ? wave * U : 0);
     rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
     if (NW) rem_share = min(U, rem_req);
     else if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
     slot = u0 / pv.units_per_chunk;
     r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
-    part = rq.n_part == 1 ? -1 : rq.part0 + (sh.w - rq.wave_first);
+    part = rq.n_part == 1 ? -1 : rq.part0 + (sh.w - rq.wave_first);    // (which slot: only where a workgroup is a step)
   }
   auto advance = [&](TileInfo<U>& t) __attribute__((always_inline)) {
     t.n = min(U, min(rem_share, rem_req));
@@ -885,11 +1098,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   };
   // the rows of a unit as a buffer of their own
   auto rows_of = [&](char* base, int32_t rows) __attribute__((always_inline)) {
-    // (uniform values all; said so, because the descriptor has to be in scalar registers)
-    const uint64_t b = (uint64_t)base;
-    const uint64_t bs = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b) |
-                        (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32)) << 32;
-    return __builtin_amdgcn_make_buffer_rsrc((void*)bs, 0, __builtin_amdgcn_readfirstlane(rows * ROWB), BUFFER_RAW);
+    return buffer_at(base, rows * ROWB);
   };
   // how many of them are in the chunk: all but the one that a fused append is about to put there
   auto there = [&](const TileInfo<U>& t, int u) __attribute__((always_inline)) {
@@ -1063,35 +1272,6 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       }
     }
   };
-  auto finish = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
-    const float L = add_xor32(add_xor16(l));
-    if (c >= n_heads) return;
-    if (t.part < 0) {
-      // the whole request lay inside this wave's share: this is the final result. Normalise, round and
-      // write the output rows; no workspace traffic, no second pass for this request
-      const float inv = 1.f / L;
-      uint16_t* o = out + ((int64_t)(a.q_row0 + t.b) * pv.n_q_heads + hq0 + c) * D + g16 * (4 * E);
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int e = 0; e < E; e += 2)
-          *reinterpret_cast<uint32_t*>(o + i * E + e) = pack_bf16(acc[e][i] * inv, acc[e + 1][i] * inv);
-    } else {
-      // accumulators: one row of D floats per (partial slot, q head), every row a whole number of cache
-      // lines; m and l of all partials sit together behind the rows, two floats each
-      const int64_t row = ((int64_t)g * a.parts_per_head + t.part) * pv.group + g_first + c;
-      // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
-      float* wout = ws + row * D + g16 * 4;
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int e = 0; e < E; e += 4)
-          *reinterpret_cast<float4*>(wout + (i * E + e) * 4) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
-      if (g16 == 0)
-        *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(m, L);
-    }
-  };
-
   if constexpr (NW > 0) {
     constexpr int F = D / 4, ROW = D + 4;              // a row of a head's accumulators, padded against bank conflicts
     __shared__ __attribute__((aligned(16))) float sums[NW][HEADS_PER_PASS][ROW];
@@ -1119,59 +1299,116 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     __syncthreads();
     for (int x = threadIdx.x; x < n_heads * F; x += NW * 64) {
       const int h = x / F, f = x % F;
-      float M = NEG_BIG, L = 0.f;
+      Sum s = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
 #pragma unroll
-      for (int w = 0; w < NW; w++) M = fmaxf(M, ml[w][h].x);
-      float4 A = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int w = 0; w < NW; w++) s.M = fmaxf(s.M, ml[w][h].x);
 #pragma unroll
       for (int w = 0; w < NW; w++) {
         const float2 p = ml[w][h];
         if (p.x == NEG_BIG && p.y == 0.f) continue;
-        const float cw = fast_exp2(p.x - M);
-        const float4 v4 = *reinterpret_cast<const float4*>(&sums[w][h][f * 4]);
-        L += p.y * cw;
-        A.x += v4.x * cw; A.y += v4.y * cw; A.z += v4.z * cw; A.w += v4.w * cw;
+        add(s, p.y, *reinterpret_cast<const float4*>(&sums[w][h][f * 4]), fast_exp2(p.x - s.M));
       }
       if (part < 0) {
-        const float inv = 1.f / L;
-        const int dim = E * (4 * (f & 3) + f / E) + (f % E) / 4 * 4;
-        uint16_t* o = out + ((int64_t)(a.q_row0 + cb) * pv.n_q_heads + hq0 + h) * D + dim;
-        *reinterpret_cast<uint2*>(o) = make_uint2(pack_bf16(A.x * inv, A.y * inv), pack_bf16(A.z * inv, A.w * inv));
+        write_out<D>(pv, out, a, cb, g, g_first, x, s);
       } else {
-        const int64_t row = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first + h;
-        *reinterpret_cast<float4*>(ws + row * D + f * 4) = A;
-        if (f == 0) *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(M, L);
+        const int64_t row0 = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first;
+        store_partial(buffer_at(ws + row0 * D, n_heads * (D * 4)), x * 16, s.A);
+        if (f == 0)
+          store_partial(buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4)), h * (WS_ML * 4), make_float2(s.M, s.L));
       }
     }
+    const int32_t n_part = first_rq.n_part;
+    if (n_part == 1 || n_part > a.merge_parts) return;
+    // one of several blocks of its request: the last of them to get here adds their results up. The waves that one
+    // column each would leave idle take a part of the partials; these meet in LDS.
+    __shared__ uint32_t before;
+    stores_done();
+    __syncthreads();
+    if (threadIdx.x == 0) before = count_in(pv, g, cb, n_part);
+    __syncthreads();
+    if (before != (uint32_t)n_part - 1u) return;
+    const Partials<D> all(pv, ws, a, first_rq.part0, n_part, g, g_first, n_heads);
+    const int32_t wide = (n_heads * F + 63) / 64, ways = NW / wide;      // waves that the columns take (at most NW), times
+    const int32_t way = wave / wide, each = (n_part + ways - 1) / ways;
+    const int32_t x = (wave - way * wide) * 64 + lane;
+    const bool mine = way < ways && x < n_heads * F;
+    Sum s[1];
+    if (way < ways) all.template sum<1, 4, 8>(s, x, 0, way * each, min(n_part, (way + 1) * each));
+    if (ways > 1) {
+      if (mine) {
+        *reinterpret_cast<float4*>(&sums[way][x / F][x % F * 4]) = s[0].A;
+        if (x % F == 0) ml[way][x / F] = make_float2(s[0].M, s[0].L);
+      }
+      __syncthreads();
+      if (mine && way == 0)
+        for (int32_t i = 1; i < ways; i++) {
+          const float2 p = ml[i][x / F];
+          const float M = fmaxf(s[0].M, p.x);
+          rescale(s[0], M);
+          add(s[0], p.y, *reinterpret_cast<const float4*>(&sums[i][x / F][x % F * 4]), fast_exp2(p.x - M));
+        }
+    }
+    if (mine && way == 0) write_out<D>(pv, out, a, cb, g, g_first, x, s[0]);
     return;
   }
+  __shared__ __attribute__((aligned(16))) Results<D, HEADS_PER_PASS> results;
+  if (lane < 2) results.whose[2 * wave + lane] = -1;
+  auto finish = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
+    const float L = add_xor32(add_xor16(l));
+    if (c >= n_heads) return;
+    if (t.part < 0) {
+      // the whole request lay inside this wave's share: this is the final result. Normalise, round and
+      // write the output rows
+      const float inv = 1.f / L;
+      uint16_t* o = out + ((int64_t)(a.q_row0 + t.b) * pv.n_q_heads + hq0 + c) * D + g16 * (4 * E);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < E; e += 2)
+          *reinterpret_cast<uint32_t*>(o + i * E + e) = pack_bf16(acc[e][i] * inv, acc[e + 1][i] * inv);
+    } else {
+      // one of several waves of the request: its results meet the others' in LDS
+      // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
+      const int32_t to = 2 * wave + (t.b == sh.b ? 0 : 1);
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < E; e += 4)
+          results.rows[to][c][g16 + i * E + e] = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+      if (g16 == 0) results.ml[to][c] = make_float2(m, L);
+      if (lane == 0) results.whose[to] = g * MAX_LAUNCH_REQ + t.b;
+    }
+  };
   // No exit before the round's last load (the share's last round asks for rows it does not use): what is in
   // flight when a tile is waited for is the same on every path, so the compiler counts the loads exactly.
-  TileInfo<U> t, next;
-  advance(t);
-  issue_k(t);
-  issue_v(t);
-  __builtin_amdgcn_sched_barrier(0);                 // the loads stay where they are asked for
-  advance(next);
-  uint32_t done;
-  do {
-    scores(t);
-    issue_k(next);
-    __builtin_amdgcn_sched_barrier(0);
-    weigh(t);
-    if (t.flags & (T_LAST | T_FIN)) finish(t);       // the request ends here, or the share does
-    done = t.flags & T_FIN;
-    issue_v(next);
-    __builtin_amdgcn_sched_barrier(0);
-    t = next;
+  if (index < a.waves_per_head * pv.n_kv_heads) {
+    TileInfo<U> t, next;
+    advance(t);
+    issue_k(t);
+    issue_v(t);
+    __builtin_amdgcn_sched_barrier(0);               // the loads stay where they are asked for
     advance(next);
-  } while (!done);
+    uint32_t done;
+    do {
+      scores(t);
+      issue_k(next);
+      __builtin_amdgcn_sched_barrier(0);
+      weigh(t);
+      if (t.flags & (T_LAST | T_FIN)) finish(t);     // the request ends here, or the share does
+      done = t.flags & T_FIN;
+      issue_v(next);
+      __builtin_amdgcn_sched_barrier(0);
+      t = next;
+      advance(next);
+    } while (!done);
+  }
+  end_shares<D, HEADS_PER_PASS, 2, 8>(pv, ws, out, a, results, g_first, n_heads, wave, lane);
 }
 
 // Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
 // the accumulation registers, which ordinary instructions cannot read.
 template <int D, int U, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
+__global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
   decode_unit_body<D, U, APPEND, DIRECT, 0>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
@@ -1186,22 +1423,25 @@ __global__ __launch_bounds__(64 * block_waves<D>) __attribute__((amdgpu_waves_pe
 }
 
 // ---------------------------------------------------------------------------------------------
-// combine pass: one workgroup of W waves per (split request, q head). A row of accumulators is read 16
-// bytes per lane, so the workgroup takes RP = W * 256 / D partials at a time; every lane's rows are asked for
-// before the common maximum is known, so that the pass is one round trip to memory for up to 4 * RP
-// partials. The RP sums of a dim are added up through LDS in a fixed order.
+// combine pass, for the requests whose partial results are too many for one workgroup (merge_parts): one workgroup
+// per (such request, q head). A row of accumulators is read 16 bytes per lane, so the workgroup takes RP = 16
+// partials at a time; every lane's rows are asked for before the common maximum is known, so that the pass is one round
+// trip to memory for up to 64 partials. The RP sums of a dim are added up through LDS in a fixed order. Twice as many
+// waves are slower below 64 partials (32: 11.7 a call, 11.2; of heads of 64 36: 9.5, 8.4), faster for many (256 of heads
+// of 64: 19.5, 21.5).
 // ---------------------------------------------------------------------------------------------
 constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
+template <int D> constexpr int combine_waves = D / 16;
 
-template <int D, int W>
-__global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
+template <int D>
+__global__ __launch_bounds__(64 * combine_waves<D>) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
                                                                 int32_t n_q_heads, int32_t group, BatchArgs a) {
-  constexpr int F = D / 4, RP = W * 64 / F, AHEAD = COMBINE_AHEAD;
+  constexpr int F = D / 4, RP = combine_waves<D> * 64 / F, AHEAD = COMBINE_AHEAD;
   __shared__ __attribute__((aligned(16))) float4 sums[RP][F];
   const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
   const int b = (a.split_req[blockIdx.x >> 2] >> ((blockIdx.x & 3) * 8)) & 0xff;   // blockIdx.x-th split request
   const int g = h / group;
-  const int n_part = a.req[b].n_part;
+  const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.step_units == BLOCK_UNITS).n;
   const int64_t row0 = ((int64_t)g * a.parts_per_head + a.req[b].part0) * group + (h - g * group);
   const float4* p = reinterpret_cast<const float4*>(ws + row0 * D) + f;       // accumulator rows of this head
   const float* q0 = ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML;      // their (m, l) pairs
@@ -1235,14 +1475,10 @@ __global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __r
   sums[row][f] = A;
   __syncthreads();
   if (row != 0) return;
-  // (eight at a time: all 32 or 64 rows of the widest workgroups at once went through scratch memory, which the
-  // runtime allocates at the launch)
+  // (eight at a time: all rows at once went through scratch memory, which the runtime allocates at the launch)
 #pragma unroll 8
   for (int r = 1; r < RP; r++) add(sums[r][f], 1.f);
-  // which dims these are: rows of the kernel that walks units hold them in the order its lanes store them
-  constexpr int E = D / 16;
-  const int dim = a.unit_tokens == TILE_TOKENS ? 4 * f : E * (4 * (f & 3) + f / E) + (f % E) / 4 * 4;
-  uint16_t* o = out + ((int64_t)(a.q_row0 + b) * n_q_heads + h) * D + dim;
+  uint16_t* o = out + ((int64_t)(a.q_row0 + b) * n_q_heads + h) * D + partial_dim<D>(a.unit_tokens, f);
   *reinterpret_cast<uint2*>(o) = make_uint2(f32_to_bf16_bits(A.x / L) | (f32_to_bf16_bits(A.y / L) << 16),
                                             f32_to_bf16_bits(A.z / L) | (f32_to_bf16_bits(A.w / L) << 16));
 }
@@ -1411,8 +1647,8 @@ int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
   const bool tiles = tile_kernel(head_dim, group, tokens_per_chunk);
   const void* f = head_dim == 128 ? partial_kernel_ptr<128>(group, tiles) : partial_kernel_ptr<64>(group, tiles);
   int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64, 0) != hipSuccess || n < 1) n = 1;
-  return n;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * SHARE_WAVES, 0) != hipSuccess || n < 1) n = 1;
+  return n * SHARE_WAVES;
 }
 
 // ev0 / ev1 (either may be NULL): events that take the kernel's own start and end times (the
@@ -1428,10 +1664,10 @@ template <int D, bool APPEND, bool DIRECT>
 static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
                             void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
                             hipEvent_t ev_stop) {
-  const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
+  const unsigned waves = (unsigned)(a.waves_per_head * pv.n_kv_heads), grid = (waves + SHARE_WAVES - 1) / SHARE_WAVES;
   if (a.unit_tokens == TILE_TOKENS) {
     auto go = [&](auto kernel) {
-      launch_timed(kernel, grid, 64, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
+      launch_timed(kernel, grid, 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
                    (uint16_t*)out, scale_log2, 0, a);
     };
     if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT>);
@@ -1444,7 +1680,7 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     return 0;
   }
   if (a.step_units == BLOCK_UNITS) {
-    launch_timed(decode_block_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64 * block_waves<D>, stream, ev_start, ev_stop, pv,
+    launch_timed(decode_block_kernel<D, tile_units<D>, APPEND, DIRECT>, waves, 64 * block_waves<D>, stream, ev_start, ev_stop, pv,
                  (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, 0, pv.group, a);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
@@ -1453,7 +1689,7 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
   // first of them takes the start time, the last one the end time
   for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
     const int n = std::min(HEADS_PER_PASS, pv.group - done);
-    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64, stream, done == 0 ? ev_start : nullptr,
+    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64 * SHARE_WAVES, stream, done == 0 ? ev_start : nullptr,
                  done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
                  (uint16_t*)out, scale_log2, done, n, a);
     ELLM_HIP_CHECK_LAUNCH();
@@ -1478,30 +1714,13 @@ int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, 
                             : launch_partial_d<64>(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop);
 }
 
-template <int D, int W>
-static void launch_combine_w(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL((decode_combine_kernel<D, W>), dim3(a.n_split_req, pv.n_q_heads), dim3(64 * W), 0, stream, ws,
-                     (uint16_t*)out, pv.n_q_heads, pv.group, a);
-}
-
-// As many waves as take a request's partials (the average over the launch) in one round of loads, in steps
-// of four, but no fewer than four rows at a time: one request of 3250 tokens (51 partials) takes 4.4 us by
-// 16 waves, 5.0 by 4, 10.2 by 1 (7.9 before, one wave walking them); one of 65536, 1 kv head, 8 q heads of 64
-// (256 partials) 12.4 us a call by 16 (84 before). With few partials the number does not matter: the 8B-shaped step's
-// launch (3 on average) 4.63 us by 2, 4.64 by 1.
-template <int D>
-static void launch_combine_d(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
-  constexpr int per_wave = COMBINE_AHEAD * 256 / D;
-  const int parts = a.parts_per_head / a.n_split_req;
-  if (parts > 4 * per_wave) launch_combine_w<D, 16>(pv, ws, out, a, stream);
-  else if (parts > per_wave) launch_combine_w<D, 4>(pv, ws, out, a, stream);
-  else launch_combine_w<D, D / 64>(pv, ws, out, a, stream);
-}
-
 int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
   if (a.n_req <= 0 || a.n_split_req <= 0) return 0;
-  if (pv.head_dim == 128) launch_combine_d<128>(pv, ws, out, a, stream);
-  else launch_combine_d<64>(pv, ws, out, a, stream);
+  const dim3 grid(a.n_split_req, pv.n_q_heads), block(pv.head_dim * 4);
+  if (pv.head_dim == 128)
+    hipLaunchKernelGGL(decode_combine_kernel<128>, grid, block, 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
+  else
+    hipLaunchKernelGGL(decode_combine_kernel<64>, grid, block, 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
   ELLM_HIP_CHECK_LAUNCH();
   return 0;
 }

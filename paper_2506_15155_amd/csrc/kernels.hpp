@@ -1,5 +1,6 @@
 // Argument blocks and launchers shared by the C-ABI layer and the HIP kernels.
 #pragma once
+#include <algorithm>
 #include <cstddef>
 #include <cstdint>
 
@@ -16,7 +17,9 @@ constexpr int STEP_UNITS = 4;         // units of a request that are worth a wav
 constexpr int BLOCK_UNITS = 16;       // small launches: units of a request that one workgroup of several waves takes
 constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walks units handles in one pass over K and V
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
+constexpr int SHARE_WAVES = SIMDS_PER_CU;   // waves of a workgroup that walk a share each
 constexpr int WS_ML = 2;              // floats per partial and q head in the (m, l) region of the workspace
+constexpr int MERGE_STRIDE = 16;      // words from one of the counters of partial results to the next: 64 bytes
 constexpr size_t STATIC_WS_BYTES = 16u << 20;   // the fixed workspace of the entry point that allocates nothing
 
 // what a kernel needs to turn (tensor, token) into an address
@@ -25,6 +28,8 @@ struct PoolView {
   const int32_t* table;       // device mirror of the chunk tables, [max_tensors][max_slots]
   const uint64_t* vbase;      // NULL: kernels go through the table. Else: per tensor, the start of its virtual
                               // address range, into which the driver has mapped its chunks; kernels read that
+  uint32_t* merged;           // [kv head][MAX_LAUNCH_REQ] counters, 0 between launches: workgroups whose partial result
+                              // of a request is in the workspace
   uint32_t chunk_bytes;
   int32_t tokens_per_chunk;
   int32_t tiles_per_chunk;    // ceil(tokens_per_chunk / TILE_TOKENS); a tile never straddles a chunk
@@ -39,9 +44,11 @@ struct PoolView {
 // units_each units, the first units_extra waves one more, each from where the wave before it
 // stopped. A wave whose share runs from one request into the next finishes a result for each; so
 // request b is covered by n_part waves per kv head, numbered from the wave that holds its first
-// unit (wave_first). A request that lies wholly inside one wave's share (n_part == 1) needs no
-// second pass: that wave normalises and writes the output row itself. Only the others ("split"
-// requests) get partial results in the workspace, part0 + j for the j-th wave, and a combine pass.
+// unit (wave_first). A request that lies wholly inside one wave's share (n_part == 1) is finished by that wave, which
+// normalises and writes the output row itself. The others ("split" requests) are added up: SHARE_WAVES neighbouring
+// waves are a workgroup, whose results of a request meet in LDS; a request that reaches into several workgroups gets one
+// partial result from each, part0 + j from the j-th, and the workgroup that ends last, or the combine pass where there
+// are many, adds those up (merge_parts()).
 // A launch that fills the GPU has one wave for every SIMD of it (a second wave on a SIMD is served markedly
 // worse than the first and slows both down): all are resident at once and have the same amount to
 // read, so none waits for a slot and none is left over at the end. The cut is fixed by the plan,
@@ -60,14 +67,16 @@ struct BatchArgs {
   int32_t units_per_head;     // units of all requests of the launch, for one kv head
   int32_t waves_per_head;     // <= units_per_head
   int32_t units_each, units_extra;   // units_per_head = waves_per_head * units_each + units_extra
-  int32_t parts_per_head;     // partial slots per kv head = sum of n_part over the split requests
+  int32_t parts_per_head;     // partial slots per kv head = sum of n_part over the split requests (where workgroups are
+                              // waves of several shares, a request uses no more than it spans workgroups)
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
-  int32_t n_split_req;        // requests with n_part > 1: the combine pass runs for these only
+  int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last
+  int32_t n_split_req;        // requests with more: the combine pass runs for these only
   // request that holds the first unit of wave w of a kv head, one byte each: lets a wave find its
   // request with one scalar load instead of a search through the prefix entries
   uint32_t wave_req[MAX_WAVE_REQ / 4];
-  // the split requests in ascending order, one byte each
+  // the requests for the combine pass in ascending order, one byte each
   uint32_t split_req[MAX_LAUNCH_REQ / 4];
   // per request, one record, so that a wave gets all of it with one round of scalar loads
   struct Req {
@@ -115,6 +124,21 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
   const int64_t Tc = tokens_per_chunk, padded = (Tc + TILE_TOKENS - 1) / TILE_TOKENS * TILE_TOKENS;
   if (head_dim == 128) return (group == 1 || group == 2 || group == 4 || group == 8) && padded * 5 <= Tc * 8;
   return (group == 1 || group == 2) && padded * 3 <= Tc * 4;
+}
+
+// Up to how many waves (blocks: steps) a request may be shared by for its partial results, one per workgroup, to be
+// added up by the workgroup that ends last. The others go to the combine pass: a launch of its own, 4 to 5 us, but a
+// workgroup for each q head. us, added up by the last / by the pass:
+//  - Where shares are walked one wave reads them all, 16 KB in a round trip: up to 64 KB. 8 kv heads of 128, one request of
+//    20000 to 100000 tokens (32 workgroups), 1 q head each (16 KB) 65.5 / 66.6, 4 (64 KB) 21.8 / 22.6, 8 (128 KB) 72.3 /
+//    70.2, 16 (256 KB) 81 / 70.8; 4 kv heads (64 workgroups), 4 q heads each (128 KB) 30.2 / 28.3, 8: 36.9 / 29.6.
+//  - The waves of a block share them, as many as one column of the heads does not take: up to 8 for each of those ways, one
+//    round trip. Heads of 128, one request, 4 q heads each (4 ways): 13 blocks 9.1 / 9.7, 31: 11.9 / 12.3; 8 (2 ways): 16
+//    10.1 / 10.3, 32 10.7 / 10.0; 16 (1 way): 8 9.8 / 10.1, 16 11.2 / 10.9, 31 15.2 / 13.0.
+inline int merge_parts(int head_dim, int group, bool blocks) {
+  if (!blocks) return (64 << 10) * SHARE_WAVES / (group * head_dim * 4);
+  const int waves = head_dim / 16, wide = (group * head_dim / 4 + 63) / 64;      // of a block; that one column takes
+  return 8 * std::max(1, waves / wide);
 }
 
 // Small launches are cut in units whatever the pool's shares are cut in, and request by request: in blocks (one
