@@ -222,8 +222,8 @@ int32_t device_simds() {
 
 // Partial slots one decode launch can need under the automatic partition: every wave writes one
 // partial, and one more for every request boundary inside its share; the waves of all kv heads
-// together are at most one per SIMD, and each kv head's sequence has n_req - 1 inner boundaries. (A small
-// launch that takes one workgroup per 256 tokens of a request has at most one partial per compute unit.)
+// together are at most one per SIMD, and each kv head's sequence has n_req - 1 inner boundaries. (A launch
+// that is cut in blocks has at most one partial per compute unit.)
 int64_t launch_slot_bound(int32_t simds, int32_t n_kv_heads, int32_t n_req) {
   return (int64_t)simds + (int64_t)n_kv_heads * (std::max(n_req, 1) - 1);
 }
@@ -820,7 +820,8 @@ int32_t wave_slots(ellm_pool* p) {
 // all are resident from the start, and a wave whose share crosses from one request into the next
 // finishes a result for each. A launch that has no STEP_UNITS units for each of them is cut at every
 // STEP_UNITS-th unit of each request instead, one wave each: a smaller share is not worth its partial
-// result (its first loads take as long), and the cut of a request does not depend on its neighbours.
+// result (its first loads take as long), and the cut of a request does not depend on its neighbours. Launches that are
+// small enough for it go by workgroups of several waves (small_launch(), wide_launch()).
 // The cut depends only on the batch's lengths, the pool geometry and the device's wave capacity, never
 // on physical chunk ids or on which wave runs when: every rounding is reproducible and invariant
 // under remapping.
@@ -859,6 +860,36 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
   return parts;
 }
 
+// Units of a request that each workgroup of a wide launch takes: the fewest that leave no more workgroups than CUs; 0 if
+// the launch is not one. *blocks: workgroups per kv head.
+int32_t wide_block(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t extra, int32_t cus, int64_t* blocks) {
+  const int32_t Tc = p->geom.tokens_per_chunk, room = cus / p->geom.n_kv_heads;
+  const int32_t chunk_units = (Tc + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
+  std::vector<int32_t>& units = p->units_tmp;
+  units.resize(n_req);
+  int64_t total = 0;
+  for (int32_t i = 0; i < n_req; i++) {
+    const int64_t len = p->core->tensor(ids[i])->len + extra, full = len / Tc;
+    const int64_t n = full * chunk_units + (len - full * Tc + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
+    total += n;
+    if (total > (int64_t)ellm::WIDE_UNITS * room) return 0;      // (most launches: known after a few requests)
+    units[i] = (int32_t)n;
+  }
+  if (!ellm::wide_launch(p->geom.group, total, n_req, room)) return 0;
+  for (int32_t b = (int32_t)((total + room - 1) / room); b <= ellm::WIDE_UNITS; b++) {
+    int64_t n = 0;
+    int32_t parts = 0;
+    for (int32_t u : units) {
+      parts = std::max(parts, (u + b - 1) / b);
+      n += (u + b - 1) / b;
+    }
+    if (n > room) continue;
+    *blocks = n;
+    return parts <= ellm::WIDE_PARTS ? b : 0;
+  }
+  return 0;
+}
+
 void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0, ellm::BatchArgs& a, int32_t extra = 0) {
   const int32_t Tc = p->geom.tokens_per_chunk, n_kv = p->geom.n_kv_heads;
   // tiles or units (pieces of up to so many tokens of one chunk) of a sequence; a serving loop plans every layer's
@@ -886,6 +917,10 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
                      ellm::small_launch(p->geom.group, blocks, n_req, n_kv, (int)cus);
   const bool by_blocks = small && ellm::takes_blocks(p->geom.head_dim, tiles, tiles_in(longest) == 1, blocks, n_req, n_kv, (int)cus);
   if (small) tiles = false;
+  int32_t block_units = by_blocks ? ellm::BLOCK_UNITS : 0;
+  if (!small && p->split_override == 0 && p->waves_percent == 100)
+    block_units = wide_block(p, ids, n_req, extra, (int)cus, &blocks);
+  if (block_units) tiles = false;
   a.unit_tokens = tiles ? TILE_TOKENS : ellm::UNIT_TOKENS;
   a.step_units = 1;
   int64_t total = 0, steps = 0, step_parts = 0;   // steps of STEP_UNITS; those of requests of more than one
@@ -906,9 +941,9 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   if (p->split_override > 0) {
     const int64_t per = std::max<int64_t>(1, p->split_override / TILE_TOKENS) * (TILE_TOKENS / a.unit_tokens);
     waves = std::max<int64_t>(1, std::min((total + per - 1) / per, total));
-  } else if (by_blocks) {
-    a.step_units = ellm::BLOCK_UNITS;
-    for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::BLOCK_UNITS - 1) / ellm::BLOCK_UNITS;
+  } else if (block_units) {
+    a.step_units = block_units;
+    for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + block_units - 1) / block_units;
     total = waves = blocks;
   } else {
     waves = std::max<int64_t>(1, std::min(room, total));
@@ -937,7 +972,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     }
   }
   std::memset(a.split_req, 0, sizeof(a.split_req));
-  const int64_t parts = cut_shares(units, total, waves, &a, ellm::merge_parts(p->geom.head_dim, p->geom.group, by_blocks));
+  const int64_t parts = cut_shares(units, total, waves, &a, ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0));
   a.n_req = n_req;
   a.q_row0 = q_row0;
   a.units_per_head = (int32_t)std::min<int64_t>(total, 0x7fffffff);
@@ -1222,7 +1257,7 @@ const char* ellm_debug_decode_kernel(ellm_pool* p, const ellm_tensor_id* ids, in
   ellm::BatchArgs a;
   plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
   if (a.unit_tokens == TILE_TOKENS) return "decode_tile_kernel";
-  return a.step_units == ellm::BLOCK_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
+  return a.step_units > ellm::STEP_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
 }
 
 int ellm_pool_set_split_tokens(ellm_pool* p, int32_t split_tokens) {

@@ -1008,12 +1008,11 @@ struct TileInfo {                    // what is known of a tile before its loads
   const char* base;                  // start of the pool, or of the tensor's range
 };
 
-// units per tile: 8 KB of K and 8 KB of V for either head size; waves that share a step of BLOCK_UNITS
+// units per tile: 8 KB of K and 8 KB of V for either head size
 template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
-template <int D> constexpr int block_waves = BLOCK_UNITS / tile_units<D>;
 
-// NW == 0: a workgroup is one wave, which walks its share. NW > 0 (small launches): NW waves share a step of
-// NW * U units of one request, one tile each, everything asked for at once, and add up through LDS.
+// NW == 0: a wave walks its share. NW > 0 (small launches): NW waves share a step of up to NW * U units of one
+// request, one tile each, everything asked for at once, and add up through LDS.
 template <int D, int U, bool APPEND, bool DIRECT, int NW>
 __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                             const char* __restrict__ k_new, const char* __restrict__ v_new,
@@ -1042,9 +1041,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     const BatchArgs::Req& rq = first_rq;
     len = rq.len;
     walk = tensor_walk<DIRECT>(pv, rq.tensor);
-    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + (NW ? wave * U : 0);
+    const int32_t mine = NW ? wave * a.step_units / NW : 0;     // (at most U apart from one wave to the next)
+    const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + mine;
     rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
-    if (NW) rem_share = min(U, rem_req);
+    if (NW) rem_share = min((wave + 1) * a.step_units / NW - mine, rem_req);
     else if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
     slot = u0 / pv.units_per_chunk;
     r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
@@ -1414,12 +1414,13 @@ __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_e
   decode_unit_body<D, U, APPEND, DIRECT, 0>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
-// of which one launch instead of two is 3 us of host time.
-template <int D, int U, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64 * block_waves<D>) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
+// of which one launch instead of two is 3 us of host time. Launches of 50 MB of K and V, in wide blocks with four units
+// a wave: 8 requests of 4 q heads per kv head of 128, 4 layers of map-ahead, append and decode 63.2 -> 57.0 us.
+template <int D, int U, int NW, bool APPEND, bool DIRECT>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
-  decode_unit_body<D, U, APPEND, DIRECT, block_waves<D>>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  decode_unit_body<D, U, APPEND, DIRECT, NW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1441,7 +1442,7 @@ __global__ __launch_bounds__(64 * combine_waves<D>) void decode_combine_kernel(c
   const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
   const int b = (a.split_req[blockIdx.x >> 2] >> ((blockIdx.x & 3) * 8)) & 0xff;   // blockIdx.x-th split request
   const int g = h / group;
-  const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.step_units == BLOCK_UNITS).n;
+  const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.step_units > STEP_UNITS).n;
   const int64_t row0 = ((int64_t)g * a.parts_per_head + a.req[b].part0) * group + (h - g * group);
   const float4* p = reinterpret_cast<const float4*>(ws + row0 * D) + f;       // accumulator rows of this head
   const float* q0 = ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML;      // their (m, l) pairs
@@ -1679,9 +1680,13 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }
-  if (a.step_units == BLOCK_UNITS) {
-    launch_timed(decode_block_kernel<D, tile_units<D>, APPEND, DIRECT>, waves, 64 * block_waves<D>, stream, ev_start, ev_stop, pv,
-                 (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, 0, pv.group, a);
+  if (a.step_units > STEP_UNITS) {
+    auto go = [&](auto kernel, unsigned n_waves) {
+      launch_timed(kernel, waves, 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
+                   (uint16_t*)out, scale_log2, 0, pv.group, a);
+    };
+    if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, tile_units<D>, BLOCK_UNITS / tile_units<D>, APPEND, DIRECT>, BLOCK_UNITS / tile_units<D>);
+    else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT>, WIDE_WAVES);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }

@@ -15,6 +15,8 @@ constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of on
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
 constexpr int STEP_UNITS = 4;         // units of a request that are worth a wave of their own
 constexpr int BLOCK_UNITS = 16;       // small launches: units of a request that one workgroup of several waves takes
+constexpr int WIDE_UNITS = 32;        // launches up to twice as large: the most units that a workgroup takes,
+constexpr int WIDE_WAVES = 8;         // and its waves
 constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walks units handles in one pass over K and V
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
 constexpr int SHARE_WAVES = SIMDS_PER_CU;   // waves of a workgroup that walk a share each
@@ -62,8 +64,8 @@ struct BatchArgs {
   int32_t q_row0;             // row of the first request in q / out
   int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
   int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave (STEP_UNITS) or
-                              // workgroup of several waves (BLOCK_UNITS) gets: up to this many units of one
-                              // request (then "units" and "waves" in the fields below are such steps)
+                              // workgroup of several waves (up to WIDE_UNITS) gets: up to this many units of
+                              // one request (then "units" and "waves" in the fields below are such steps)
   int32_t units_per_head;     // units of all requests of the launch, for one kv head
   int32_t waves_per_head;     // <= units_per_head
   int32_t units_each, units_extra;   // units_per_head = waves_per_head * units_each + units_extra
@@ -168,6 +170,20 @@ inline bool takes_blocks(int head_dim, bool tiles, bool one_piece, int64_t block
   if (!tiles || head_dim == 64) return true;
   if (blocks > n_req) return blocks >= 12 * (int64_t)n_req || workgroups * 8 >= (int64_t)cus * 7;
   return !one_piece || workgroups <= cus;
+}
+
+// Launches past those in which one workgroup per CU can still have everything in flight at once, whichever way the pool's
+// shares are cut: blocks again, but of as many units (17 to WIDE_UNITS) as leave no more of them than CUs. Shares of such
+// launches are one or two tiles a wave, one after the other. Shares / blocks, us a call, 8 kv heads of 128: 8 requests of 800
+// to 1200 tokens, 4 q heads each 11.0 / 10.1, of 1400 to 1700 12.4 / 11.8, of 1700 to 2000 14.3 / 13.2, 16 of 700 to 900
+// 12.4 / 11.8, 30 of 300 to 400 12.3 / 9.3; 4 of 3000 to 4000, 8 q heads each 18.0 / 13.4, 1 q head 13.4 / 13.4; 6 q heads, 8 of
+// 1500 to 2000 14.3 / 12.7. Heads of 64, 4 q heads, 8 of 1500 to 2000 10.4 / 8.8, 1 q head 9.5 / 8.9; twice as many units a
+// wave are no gain there (16 of 1500 to 2000, 4 q heads 14.2 / 13.5, 1 q head 12.6 / 13.7). Up to 12 units for every CU (17
+// of 257 tokens 9.0 / 7.9), and where a request has more than WIDE_PARTS blocks (1 of 15000 15.6 / 13.5, 9000 13.9 / 10.8),
+// blocks would be faster too; shares are the way there that tests hold on to.
+constexpr int WIDE_PARTS = 16;
+inline bool wide_launch(int group, int64_t units, int n_req, int room) {      // room: CUs for each kv head
+  return group <= HEADS_PER_PASS && n_req <= room && units > 12 * (int64_t)room && units <= (int64_t)WIDE_UNITS * room;
 }
 
 // resident waves of the partial-pass kernel per compute unit (occupancy query)
