@@ -235,7 +235,8 @@ int ensure_device(ellm_pool* p) {
   // the table mirror and, behind it, the counters of partial results, all 0
   std::vector<int32_t> image = p->core->table();
   const size_t counters_at = (image.size() + 63) / 64 * 64;
-  image.resize(counters_at + (size_t)p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ * ellm::MERGE_STRIDE, 0);
+  const int32_t lines = std::max(p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
+  image.resize(counters_at + (size_t)lines * ellm::MERGE_STRIDE, 0);
   HIP_TRY(hipMalloc((void**)&p->d_table, image.size() * sizeof(int32_t)), "hipMalloc(table mirror)");
   HIP_TRY(hipMemcpy(p->d_table, image.data(), image.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   p->d_merged = (uint32_t*)p->d_table + counters_at;

@@ -354,9 +354,10 @@ __device__ __forceinline__ void stores_done() {
   __builtin_amdgcn_s_waitcnt(waitcnt_vm(0));
   asm volatile("" ::: "memory");
 }
-// One more of n_part shares of request b, kv head g, has its results in memory (asked by one lane): how many had before?
-__device__ __forceinline__ uint32_t count_in(const PoolView& pv, int32_t g, int32_t b, int32_t n_part) {
-  return atomicInc(pv.merged + ((int64_t)g * MAX_LAUNCH_REQ + b) * MERGE_STRIDE, (uint32_t)n_part - 1u);
+// One more of n_part workgroups has its results in memory (asked by one lane): how many had before? `line`: of the counters,
+// `k`: which in that line.
+__device__ __forceinline__ uint32_t count_in(const PoolView& pv, int32_t line, int32_t k, int32_t n_part) {
+  return atomicInc(pv.merged + (int64_t)line * MERGE_STRIDE + k, (uint32_t)n_part - 1u);
 }
 
 // sums of one 16-byte piece of a head's row over some partials: running maximum, normaliser, weighted sum
@@ -451,6 +452,17 @@ struct Results {
   int32_t whose[2 * SHARE_WAVES];      // request and kv head, -1: no result, or one that needs no other
 };
 
+// column x of a request's result of this workgroup becomes partial result `part` of the request
+template <int D>
+__device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, const BatchArgs& a, int32_t part, int32_t g, int32_t g_first,
+                                              int32_t n_heads, int32_t x, const Sum& s) {
+  constexpr int F = D / 4;
+  const int64_t row0 = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first;
+  store_partial(buffer_at(ws + row0 * D, n_heads * (D * 4)), x * 16, s.A);
+  if (x % F == 0)
+    store_partial(buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4)), x / F * (WS_ML * 4), make_float2(s.M, s.L));
+}
+
 // all waves of the workgroup have ended their shares
 template <int D, int HEADS, int KB, int MANY>
 __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16_t* __restrict__ out, const BatchArgs& a,
@@ -502,7 +514,7 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
     if (n == rq.n_part || rq.n_part > a.merge_parts) continue;
     stores_done();
     uint32_t before = 0;
-    if (lane == 0) before = count_in(pv, g, b, parts.n);
+    if (lane == 0) before = count_in(pv, g * MAX_LAUNCH_REQ + b, 0, parts.n);
     if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)parts.n - 1u) continue;
     const Partials<D> all(pv, ws, a, rq.part0, parts.n, g, g_first, n_heads);
     for (int32_t x = lane; x - lane < n_heads * F; x += KB * 64) {
@@ -1314,9 +1326,15 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       ml[wave][lane] = make_float2(NEG_BIG, 0.f);      // nothing left for this wave: weight 0, its row is not read
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < n_heads * F; x += NW * 64) {
-      const int h = x / F, f = x % F;
-      Sum s = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+    // Every wave takes 64 columns (pieces of the heads' rows in order), in all blocks of a request the same ones, which need
+    // no other wave from here on: they are stored, counted in and, by the last, added up by themselves. (All threads
+    // together before, with two more barriers around the count and a sum through LDS: one request of 13 blocks 8.66 -> 8.25 us a
+    // call, wide blocks 56.0 -> 52.8 for 8 requests, 4 layers. Shares gained nothing from it: no barriers there to save.)
+    const int32_t n_cols = n_heads * F, x = threadIdx.x, h = x / F, f = x % F;
+    static_assert(HEADS_PER_PASS * F <= NW * 64, "a thread for every column");
+    if (wave * 64 >= n_cols) return;
+    Sum s = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
+    if (x < n_cols) {
 #pragma unroll
       for (int w = 0; w < NW; w++) s.M = fmaxf(s.M, ml[w][h].x);
 #pragma unroll
@@ -1325,47 +1343,21 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
         if (p.x == NEG_BIG && p.y == 0.f) continue;
         add(s, p.y, *reinterpret_cast<const float4*>(&sums[w][h][f * 4]), fast_exp2(p.x - s.M));
       }
-      if (part < 0) {
-        write_out<D>(pv, out, a, cb, g, g_first, x, s);
-      } else {
-        const int64_t row0 = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first;
-        store_partial(buffer_at(ws + row0 * D, n_heads * (D * 4)), x * 16, s.A);
-        if (f == 0)
-          store_partial(buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4)), h * (WS_ML * 4), make_float2(s.M, s.L));
-      }
+      if (part < 0) write_out<D>(pv, out, a, cb, g, g_first, x, s);
+      else leave_partial<D>(pv, ws, a, part, g, g_first, n_heads, x, s);
     }
+    // one of several blocks of its request: the last of them to get here adds their results up
     const int32_t n_part = first_rq.n_part;
     if (n_part == 1 || n_part > a.merge_parts) return;
-    // one of several blocks of its request: the last of them to get here adds their results up. The waves that one
-    // column each would leave idle take a part of the partials; these meet in LDS.
-    __shared__ uint32_t before;
     stores_done();
-    __syncthreads();
-    if (threadIdx.x == 0) before = count_in(pv, g, cb, n_part);
-    __syncthreads();
-    if (before != (uint32_t)n_part - 1u) return;
+    uint32_t before = 0;
+    // counting in one line takes turns (12 ns each; 8 times 8 for 16 heads in 8 blocks): as many lines as there are blocks
+    if (lane == 0) before = count_in(pv, g * a.waves_per_head + first_rq.wave_first + wave % n_part, wave, n_part);
+    if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)n_part - 1u) return;
     const Partials<D> all(pv, ws, a, first_rq.part0, n_part, g, g_first, n_heads);
-    const int32_t wide = (n_heads * F + 63) / 64, ways = NW / wide;      // waves that the columns take (at most NW), times
-    const int32_t way = wave / wide, each = (n_part + ways - 1) / ways;
-    const int32_t x = (wave - way * wide) * 64 + lane;
-    const bool mine = way < ways && x < n_heads * F;
-    Sum s[1];
-    if (way < ways) all.template sum<1, 4, 8>(s, x, 0, way * each, min(n_part, (way + 1) * each));
-    if (ways > 1) {
-      if (mine) {
-        *reinterpret_cast<float4*>(&sums[way][x / F][x % F * 4]) = s[0].A;
-        if (x % F == 0) ml[way][x / F] = make_float2(s[0].M, s[0].L);
-      }
-      __syncthreads();
-      if (mine && way == 0)
-        for (int32_t i = 1; i < ways; i++) {
-          const float2 p = ml[i][x / F];
-          const float M = fmaxf(s[0].M, p.x);
-          rescale(s[0], M);
-          add(s[0], p.y, *reinterpret_cast<const float4*>(&sums[i][x / F][x % F * 4]), fast_exp2(p.x - M));
-        }
-    }
-    if (mine && way == 0) write_out<D>(pv, out, a, cb, g, g_first, x, s[0]);
+    Sum all_of[1];
+    all.template sum<1, 8, 16>(all_of, x, 0, 0, n_part);
+    if (x < n_cols) write_out<D>(pv, out, a, cb, g, g_first, x, all_of[0]);
     return;
   }
   __shared__ __attribute__((aligned(16))) Results<D, HEADS_PER_PASS> results;
@@ -1433,7 +1425,7 @@ __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_e
 }
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
 // of which one launch instead of two is 3 us of host time. Launches of 50 MB of K and V, in wide blocks with four units
-// a wave: 8 requests of 4 q heads per kv head of 128, 4 layers of map-ahead, append and decode 63.2 -> 57.0 us.
+// a wave: 8 requests of 4 q heads per kv head of 128, 4 layers of map-ahead, append and decode 63.2 -> 57.0 us a pass.
 template <int D, int U, int NW, bool APPEND, bool DIRECT>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,

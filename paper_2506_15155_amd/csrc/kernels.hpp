@@ -21,7 +21,7 @@ constexpr int HEADS_PER_PASS = 16;    // q heads of a group the kernel that walk
 constexpr int SIMDS_PER_CU = 4;       // a decode launch runs one wave on each SIMD
 constexpr int SHARE_WAVES = SIMDS_PER_CU;   // waves of a workgroup that walk a share each
 constexpr int WS_ML = 2;              // floats per partial and q head in the (m, l) region of the workspace
-constexpr int MERGE_STRIDE = 16;      // words from one of the counters of partial results to the next: 64 bytes
+constexpr int MERGE_STRIDE = 16;      // words of a line of counters of partial results: 64 bytes
 constexpr size_t STATIC_WS_BYTES = 16u << 20;   // the fixed workspace of the entry point that allocates nothing
 
 // what a kernel needs to turn (tensor, token) into an address
@@ -30,8 +30,8 @@ struct PoolView {
   const int32_t* table;       // device mirror of the chunk tables, [max_tensors][max_slots]
   const uint64_t* vbase;      // NULL: kernels go through the table. Else: per tensor, the start of its virtual
                               // address range, into which the driver has mapped its chunks; kernels read that
-  uint32_t* merged;           // [kv head][MAX_LAUNCH_REQ] counters, 0 between launches: workgroups whose partial result
-                              // of a request is in the workspace
+  uint32_t* merged;           // lines of counters, 0 between launches: workgroups whose partial result of a request is in
+                              // the workspace. Line kv head * MAX_LAUNCH_REQ + request; of blocks, the blocks' own numbers
   uint32_t chunk_bytes;
   int32_t tokens_per_chunk;
   int32_t tiles_per_chunk;    // ceil(tokens_per_chunk / TILE_TOKENS); a tile never straddles a chunk
