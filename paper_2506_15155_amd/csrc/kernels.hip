@@ -272,7 +272,8 @@ __device__ __forceinline__ int32_t units_of(int32_t len, int32_t Tc, int32_t uni
 
 // request whose units include unit number pos of a kv head's sequence: the last b with
 // unit_prefix[b] <= pos (wave-uniform result)
-__device__ __forceinline__ int find_request(const BatchArgs& a, int pos, int lane) {
+template <class Args>
+__device__ __forceinline__ int find_request(const Args& a, int pos, int lane) {
   int cnt = 0;
   for (int base = 0; base < a.n_req; base += 64) {
     const int i = base + lane;
@@ -287,9 +288,10 @@ __device__ __forceinline__ int find_request(const BatchArgs& a, int pos, int lan
 // steps find theirs in the L2. Wide blocks 57.2 -> 56.0 us for 8 requests, 4 layers, one request by blocks 8.79 -> 8.67, shares
 // of units 34.04 -> 33.63 (chunks of 16 tokens) and 49.06 -> 48.68 (6 q heads per kv head); the tile kernel was slower with it
 // (2000 -> 2014 a step of 32 layers).
+template <class Args>
 __device__ __forceinline__ uint32_t touch_arguments(int lane) {
-  constexpr uint32_t BYTES = sizeof(PoolView) + sizeof(BatchArgs);      // of every attention kernel, and some pointers
-  static_assert(BYTES + 64 > 60 * 64 && BYTES <= 64 * 64, "one line per lane");
+  constexpr uint32_t BYTES = sizeof(PoolView) + sizeof(Args);           // of every attention kernel, and some pointers
+  static_assert(BYTES <= 64 * 64, "one line per lane");
   const auto* at = (const __attribute__((address_space(1))) char*)(uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
   const uint32_t line = (uint32_t)lane * 64u;
   return *(const __attribute__((address_space(1))) uint32_t*)(at + (line < BYTES ? line : 0u));
@@ -306,7 +308,8 @@ struct Share { int32_t g, w, u_lo, n_units, b; };
 // request can go out, and while the memory system is saturated more than that, so the look-up is
 // written to need few levels: the launch header, then one word of the request table, then
 // everything about the request at once.
-__device__ __forceinline__ Share locate_share(const BatchArgs& a, int32_t index, int lane) {
+template <class Args>
+__device__ __forceinline__ Share locate_share(const Args& a, int32_t index, int lane) {
   Share s;
   const int32_t W = a.waves_per_head, each = a.units_each, extra = a.units_extra;
   s.g = index / W;
@@ -380,7 +383,8 @@ struct Partials {
   static constexpr int F = D / 4;
   __amdgpu_buffer_rsrc_t rows, pairs;
   int32_t group;
-  __device__ __forceinline__ Partials(const PoolView& pv, const float* ws, const BatchArgs& a, int32_t part0, int32_t n_part, int32_t g,
+  template <class Args>
+  __device__ __forceinline__ Partials(const PoolView& pv, const float* ws, const Args& a, int32_t part0, int32_t n_part, int32_t g,
                                       int32_t g_first, int32_t n_heads) : group(pv.group) {
     const int64_t row0 = ((int64_t)g * a.parts_per_head + part0) * group + g_first;
     const int32_t n_rows = (n_part - 1) * group + n_heads;
@@ -427,8 +431,8 @@ struct Partials {
 };
 
 // column x of request b's output: the four dims that piece x % (D / 4) of the rows holds, of head g_first + x / (D / 4)
-template <int D>
-__device__ __forceinline__ void write_out(const PoolView& pv, uint16_t* __restrict__ out, const BatchArgs& a, int32_t b, int32_t g,
+template <int D, class Args>
+__device__ __forceinline__ void write_out(const PoolView& pv, uint16_t* __restrict__ out, const Args& a, int32_t b, int32_t g,
                                           int32_t g_first, int32_t x, const Sum& s) {
   constexpr int F = D / 4;
   const float inv = 1.f / s.L;
@@ -453,8 +457,8 @@ struct Results {
 };
 
 // column x of a request's result of this workgroup becomes partial result `part` of the request
-template <int D>
-__device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, const BatchArgs& a, int32_t part, int32_t g, int32_t g_first,
+template <int D, class Args>
+__device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, const Args& a, int32_t part, int32_t g, int32_t g_first,
                                               int32_t n_heads, int32_t x, const Sum& s) {
   constexpr int F = D / 4;
   const int64_t row0 = ((int64_t)g * a.parts_per_head + part) * pv.group + g_first;
@@ -464,8 +468,8 @@ __device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, con
 }
 
 // all waves of the workgroup have ended their shares
-template <int D, int HEADS, int KB, int MANY>
-__device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16_t* __restrict__ out, const BatchArgs& a,
+template <int D, int HEADS, int KB, int MANY, class Args>
+__device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16_t* __restrict__ out, const Args& a,
                                            const Results<D, HEADS>& res, int32_t g_first, int32_t n_heads, int32_t wave, int32_t lane) {
   constexpr int F = D / 4;
   __syncthreads();
@@ -477,7 +481,7 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
     left &= ~mine;
     if (nth % SHARE_WAVES != wave) continue;
     const int32_t b = id % MAX_LAUNCH_REQ, g = id / MAX_LAUNCH_REQ;
-    const BatchArgs::Req rq = a.req[b];
+    const typename Args::Req rq = a.req[b];
     const int32_t n = __builtin_popcount(mine);      // at most one slot of every wave
     int32_t slot[SHARE_WAVES];
 #pragma unroll
@@ -1040,17 +1044,17 @@ template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
 
 // NW == 0: a wave walks its share. NW > 0 (small launches): NW waves share a step of up to NW * U units of one
 // request, one tile each, everything asked for at once, and add up through LDS.
-template <int D, int U, bool APPEND, bool DIRECT, int NW>
+template <int D, int U, bool APPEND, bool DIRECT, int NW, class Args>
 __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                             const char* __restrict__ k_new, const char* __restrict__ v_new,
                                             float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
-                                            int32_t g_first, int32_t n_heads, const BatchArgs& a) {
+                                            int32_t g_first, int32_t n_heads, const Args& a) {
   constexpr int P = D / 32;          // products along a row = 16-byte pieces of K, dwords of a V row, per lane
   constexpr int ROWB = D * 2, E = D / 16, VB = E * 2;
   static_assert(U % 2 == 0, "PV takes two units at a time");
   const int lane = threadIdx.x & 63, c = lane & 15, g16 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t touch = wave == 0 ? touch_arguments(lane) : 0u;
+  const uint32_t touch = wave == 0 ? touch_arguments<Args>(lane) : 0u;
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
@@ -1064,15 +1068,16 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   int32_t cb = sh.b, rem_share = sh.n_units, len, slot, r, rem_req, part;
   uint32_t first = T_FIRST;
   TensorWalk walk;
-  const BatchArgs::Req first_rq = a.req[cb];
+  const typename Args::Req first_rq = a.req[cb];
   {
-    const BatchArgs::Req& rq = first_rq;
+    const typename Args::Req& rq = first_rq;
     len = rq.len;
     walk = tensor_walk<DIRECT>(pv, rq.tensor);
-    const int32_t mine = NW ? wave * a.step_units / NW : 0;     // (at most U apart from one wave to the next)
+    constexpr int32_t STEP_WAVES = NW ? NW : 1;
+    const int32_t mine = NW ? wave * a.step_units / STEP_WAVES : 0;     // (at most U apart from one wave to the next)
     const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + mine;
     rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
-    if (NW) rem_share = min((wave + 1) * a.step_units / NW - mine, rem_req);
+    if (NW) rem_share = min((wave + 1) * a.step_units / STEP_WAVES - mine, rem_req);
     else if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
     slot = u0 / pv.units_per_chunk;
     r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
@@ -1112,7 +1117,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     if (rem_share == 0) t.flags |= T_FIN;
     if (rem_req == 0 && rem_share > 0) {
       cb += 1;
-      const BatchArgs::Req rq = a.req[cb];
+      const typename Args::Req rq = a.req[cb];
       len = rq.len;
       rem_req = units_of(len, Tc, pv.units_per_chunk);
       walk = tensor_walk<DIRECT>(pv, rq.tensor);
@@ -1426,10 +1431,10 @@ __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_e
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
 // of which one launch instead of two is 3 us of host time. Launches of 50 MB of K and V, in wide blocks with four units
 // a wave: 8 requests of 4 q heads per kv head of 128, 4 layers of map-ahead, append and decode 63.2 -> 57.0 us a pass.
-template <int D, int U, int NW, bool APPEND, bool DIRECT>
+template <int D, int U, int NW, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
-    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, Args a) {
   decode_unit_body<D, U, APPEND, DIRECT, NW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 
@@ -1671,6 +1676,20 @@ static void launch_timed(Kernel kernel, unsigned grid, unsigned threads, hipStre
   else hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, args...);
 }
 
+// the same launch, described for the kernels that take few requests (the combine pass, which reads split_req, is not one)
+static FewArgs few_of(const BatchArgs& a) {
+  FewArgs f;
+  f.n_req = a.n_req; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens; f.step_units = a.step_units;
+  f.units_per_head = a.units_per_head; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
+  f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.use_wave_req = a.use_wave_req;
+  f.merge_parts = a.merge_parts; f.n_split_req = a.n_split_req;
+  std::copy_n(a.wave_req, FewArgs::MAX_WAVE / 4, f.wave_req);
+  std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
+  for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};
+  for (int i = 0; i < a.n_req; i++) f.req[i] = {a.req[i].len, a.req[i].tensor, a.req[i].unit_prefix, a.req[i].wave_first, a.req[i].n_part, a.req[i].part0};
+  return f;
+}
+
 template <int D, bool APPEND, bool DIRECT>
 static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
                             void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
@@ -1691,12 +1710,18 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     return 0;
   }
   if (a.step_units > STEP_UNITS) {
-    auto go = [&](auto kernel, unsigned n_waves) {
+    auto go = [&](auto kernel, unsigned n_waves, const auto& args) {
       launch_timed(kernel, waves, 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
-                   (uint16_t*)out, scale_log2, 0, pv.group, a);
+                   (uint16_t*)out, scale_log2, 0, pv.group, args);
     };
-    if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, tile_units<D>, BLOCK_UNITS / tile_units<D>, APPEND, DIRECT>, BLOCK_UNITS / tile_units<D>);
-    else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT>, WIDE_WAVES);
+    auto in_blocks = [&](const auto& args) {
+      using Args = std::decay_t<decltype(args)>;
+      constexpr int U = tile_units<D>, NW = BLOCK_UNITS / U;
+      if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
+      else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
+    };
+    if (a.n_req <= FewArgs::MAX_REQ && a.waves_per_head <= FewArgs::MAX_WAVE) in_blocks(few_of(a));
+    else in_blocks(a);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }
