@@ -239,8 +239,13 @@ __global__ __launch_bounds__(256) void kv_append_kernel(PoolView pv, const uint4
 // 44-45 GB/s on this machine, one large copy at 57); a kernel that gathers the chunks itself moves calls of 27
 // chunks at 54 / 57 GB/s out / in (engines 45 / 45) and at 40 per direction when both run at once with nothing to
 // wait for (engines 39), calls of 3 chunks at 49 / 53 and 29 (44 / 44 and 18).
-// WPC workgroups share a chunk; the loads and stores are streaming ones (the data passes through once).
+// WPC workgroups share a chunk; the loads and stores are streaming ones (the data passes through once), one of each a
+// lane at a time: while calls of both directions run beside each other, what an offload has in flight holds up the
+// fetch's reads. Requests of 1 to 5 chunks swapped for others, 27 chunks each way, us: 4 loads a lane, 64 workgroups for a
+// call 1893; 1 load, 64: 1819, 128: 1839, 192: 1829, 64 for an offload and 128 for a fetch 1702 to 1748, the other way round
+// 1920, 64 and 256: 1773, 32 and 128: 1747. One direction alone goes at 50 to 54 GB/s in all of these.
 // ---------------------------------------------------------------------------------------------
+constexpr int OFFLOAD_WORKGROUPS = 64, FETCH_WORKGROUPS = 128;
 __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool, char* __restrict__ host, uint32_t chunk_bytes,
                                                          int32_t wpc, int32_t to_host, CopyArgs a) {
   const int32_t c = blockIdx.x / wpc, part = blockIdx.x - c * wpc;
@@ -250,15 +255,7 @@ __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool
   const uint4* src = reinterpret_cast<const uint4*>(to_host ? dev_p : host_p);
   uint4* dst = reinterpret_cast<uint4*>(to_host ? host_p : dev_p);
   const uint32_t nv = chunk_bytes / 16;                 // chunk_bytes is a multiple of 256
-  for (uint32_t i = (uint32_t)part * 1024u + threadIdx.x; i < nv; i += (uint32_t)wpc * 1024u) {
-    uint4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; u++)
-      if (i + u * 256 < nv) v[u] = load_stream16(src + i + u * 256);
-#pragma unroll
-    for (int u = 0; u < 4; u++)
-      if (i + u * 256 < nv) store_stream16(dst + i + u * 256, v[u]);
-  }
+  for (uint32_t i = (uint32_t)part * 256u + threadIdx.x; i < nv; i += (uint32_t)wpc * 256u) store_stream16(dst + i, load_stream16(src + i));
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1639,10 +1636,9 @@ int launch_kv_append(const PoolView& pv, const void* k_new, const void* v_new, c
 
 int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, hipStream_t stream) {
   if (a.n <= 0) return 0;
-  // enough workgroups in flight to fill the link also when a call moves few chunks; a workgroup should
-  // still have at least 64 KiB to move
-  int wpc = std::max(1, std::min(16, 64 / a.n));
-  wpc = std::max(1, std::min<int>(wpc, (int)(chunk_bytes / (64u << 10))));
+  // a workgroup should still have 16 KiB to move
+  int wpc = std::max(1, (to_host ? OFFLOAD_WORKGROUPS : FETCH_WORKGROUPS) / a.n);
+  wpc = std::max(1, std::min<int>(wpc, (int)(chunk_bytes / (16u << 10))));
   hipLaunchKernelGGL(chunk_copy_kernel, dim3((unsigned)(a.n * wpc)), dim3(256), 0, stream, pool, host, chunk_bytes, wpc,
                      to_host ? 1 : 0, a);
   ELLM_HIP_CHECK_LAUNCH();
