@@ -140,13 +140,13 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 //  - Where shares are walked one wave reads them all, 16 KB in a round trip: up to 64 KB. 8 kv heads of 128, one request of
 //    20000 to 100000 tokens (32 workgroups), 1 q head each (16 KB) 65.5 / 66.6, 4 (64 KB) 21.8 / 22.6, 8 (128 KB) 72.3 /
 //    70.2, 16 (256 KB) 81 / 70.8; 4 kv heads (64 workgroups), 4 q heads each (128 KB) 30.2 / 28.3, 8: 36.9 / 29.6.
-//  - The waves of a block share them, as many as one column of the heads does not take: up to 8 for each of those ways, one
-//    round trip. Heads of 128, one request, 4 q heads each (4 ways): 13 blocks 9.1 / 9.7, 31: 11.9 / 12.3; 8 (2 ways): 16
-//    10.1 / 10.3, 32 10.7 / 10.0; 16 (1 way): 8 9.8 / 10.1, 16 11.2 / 10.9, 31 15.2 / 13.0.
+//  - The waves of a block take 64 columns each, 16 partials in a round trip: up to 192 KB. One request: 8 kv heads of 128, 31
+//    blocks of 4 q heads each (62 KB) 9.7 / 11.7, of 6 (93 KB) 10.1 / 11.9, of 8 (124 KB) 10.6 / 12.0, of 16 (248 KB) 12.9 / 12.4; 16
+//    blocks of 16 (128 KB) 9.8 / 11.6; 4 kv heads, 59 of 4 (118 KB) 11.1 / 12.1, of 8 (236 KB) 12.6 / 12.3; heads of 64, 31 of 16
+//    (124 KB) 9.0 / 11.5.
 inline int merge_parts(int head_dim, int group, bool blocks) {
-  if (!blocks) return (64 << 10) * SHARE_WAVES / (group * head_dim * 4);
-  const int waves = head_dim / 16, wide = (group * head_dim / 4 + 63) / 64;      // of a block; that one column takes
-  return 8 * std::max(1, waves / wide);
+  const int row = group * head_dim * 4;      // bytes of a partial result
+  return blocks ? (192 << 10) / row : (64 << 10) * SHARE_WAVES / row;
 }
 
 // Small launches are cut in units whatever the pool's shares are cut in, and request by request: in blocks (one

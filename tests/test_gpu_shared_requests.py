@@ -13,9 +13,7 @@ pytestmark = pytest.mark.gpu
 
 def merge_parts(dim, group, blocks):
     """The library's line between the two, as its sources state it."""
-    if not blocks:
-        return (64 << 10) * 4 // (group * dim * 4)
-    return 8 * max(1, dim // 16 // -(-(group * dim // 4) // 64))
+    return (192 << 10 if blocks else (64 << 10) * 4) // (group * dim * 4)
 
 
 # n_kv: workgroups that begin in one kv head and end in the next (3, 5); waves that are no whole number of workgroups (1)
@@ -23,8 +21,8 @@ def merge_parts(dim, group, blocks):
     ("decode_tile_kernel", 3, 1, 128, 128, 9), ("decode_tile_kernel", 1, 4, 128, 128, 129), ("decode_tile_kernel", 5, 4, 128, 64, 9),
     ("decode_tile_kernel", 3, 8, 128, 128, 65), ("decode_tile_kernel", 1, 2, 64, 128, 9), ("decode_unit_kernel", 3, 16, 128, 48, 33),
     ("decode_unit_kernel", 1, 6, 128, 24, 86), ("decode_unit_kernel", 5, 3, 64, 64, 9), ("decode_unit_kernel", 1, 34, 64, 64, 31),
-    ("decode_block_kernel", 1, 4, 128, 128, 33), ("decode_block_kernel", 3, 8, 128, 128, 17), ("decode_block_kernel", 1, 16, 128, 48, 9),
-    ("decode_block_kernel", 2, 6, 64, 64, 17)])
+    ("decode_block_kernel", 1, 4, 128, 128, 97), ("decode_block_kernel", 2, 8, 128, 128, 49), ("decode_block_kernel", 3, 16, 128, 48, 25),
+    ("decode_block_kernel", 1, 6, 128, 64, 65), ("decode_block_kernel", 2, 16, 64, 64, 49)])
 def test_sums_of_shared_requests(kernel, n_kv, group, dim, tokens, most):
     """Requests of 1 to 9 waves, in an order that puts their ends at every place in a workgroup, and of as many as are
     added up without the combine pass, and one more. The oracle's output; the same bits from every replay of a graph, with
@@ -34,7 +32,7 @@ def test_sums_of_shared_requests(kernel, n_kv, group, dim, tokens, most):
     at_line = most == line + 1
     assert at_line or most == 9 and line > 9
     step = 256 if blocks else 64
-    parts = [most, most - 1, most] if blocks else [1, 2, 3, 1, 4, 5, 1, 1, 7, 8, 9, 2, 6] + ([most - 1, most] if at_line else [])
+    parts = [most, most - 1] if blocks else [1, 2, 3, 1, 4, 5, 1, 1, 7, 8, 9, 2, 6] + ([most - 1, most] if at_line else [])
     lens = [step * n - (5 * i) % 11 for i, n in enumerate(parts)]
     need = [-(-n // tokens) for n in lens]
     cfg = W.Config("s", 9, len(lens), n_kv * group, n_kv, dim, tokens * 4 * n_kv * dim, sum(need) + 2, max(need) * tokens, "uniform", 1, max(lens))
