@@ -229,10 +229,26 @@ class Workload:
         self.steps_done += 1
 
     def n_split_items(self):
-        """Partial results per kv head that a launch writes to the workspace and the combine pass reads:
-        requests that lie inside one wave's share have none."""
+        """Partial results per kv head that a launch writes to the workspace and reads back (on average), the largest share in
+        tokens, requests that several waves share. Requests that lie inside one workgroup (four neighbouring waves' shares;
+        where requests are cut in blocks, a block) have no partial result, the others one for each they reach into."""
         n_split, S = self.E.ellm_decode_plan(self.pool, self.ids[0])
-        return int(n_split[n_split > 1].sum()), int(S), int((n_split > 1).sum())
+        kernel = self.E.ellm_debug_decode_kernel(self.pool, self.ids[0])
+        split = n_split > 1
+        if kernel == "decode_block_kernel":
+            return int(n_split[split].sum()), int(S), int(split.sum())
+        unit = 64 if kernel == "decode_tile_kernel" else 16
+        Tc, n_kv = self.cfg.tokens_per_chunk, self.cfg.n_kv_heads
+        units = np.asarray(self.lens) // Tc * -(-Tc // unit) + -(-(np.asarray(self.lens) % Tc) // unit)
+        first = np.cumsum(units) - units
+        waves = min(self.torch.cuda.get_device_properties(0).multi_processor_count * 4 // n_kv, int(units.sum()))
+        each, extra = divmod(int(units.sum()), waves)
+        w0 = np.where(first < extra * (each + 1), first // (each + 1), extra + (first - extra * (each + 1)) // each)
+        parts = 0
+        for g in range(n_kv):
+            reached = (g * waves + w0 + n_split - 1) // 4 - (g * waves + w0) // 4 + 1
+            parts += int(reached[reached > 1].sum())
+        return round(parts / n_kv), int(S), int(split.sum())
 
     def close(self):
         self.torch.cuda.synchronize()
@@ -289,11 +305,10 @@ def measure(wl, K, Wm, event_stride=0, use_events=True, preheat_s=0.0):
     ab = W.algorithmic_bytes(cfg, lens_mid, n_items)
     step_bytes = ab["total"] * wl.n_layers
     value = step_bytes / (ms_per_step * 1e-3) / 1e9
-    # the attention kernel reads K/V, q and table entries, writes the partials of the split requests and the
-    # output rows of the others; fused, it also reads the new token's K/V rows and writes them into their chunks
-    B, Hq, D = cfg.batch, cfg.n_q_heads, cfg.head_dim
-    direct_out = (B - n_split_req) * Hq * D * 2
-    partial_bytes = ab["kv"] + ab["q_out"] // 2 + ab["table"] + ab["partials"] // 2 + direct_out + (ab["append"] if wl.fused else 0)
+    # the attention kernel reads K/V, q and table entries, writes the output rows, and writes and reads back the partial
+    # results; fused, it also reads the new token's K/V rows and writes them into their chunks
+    B = cfg.batch
+    partial_bytes = ab["kv"] + ab["q_out"] + ab["table"] + ab["partials"] + (ab["append"] if wl.fused else 0)
     res = {
         "value": round(value, 1), "unit": "GB/s", "pct_of_peak": round(100.0 * value / HBM_PEAK_GBPS, 2),
         "ms_per_step": round(ms_per_step, 4), "steps": K, "warmup": Wm, "layers": wl.n_layers,
@@ -307,7 +322,7 @@ def measure(wl, K, Wm, event_stride=0, use_events=True, preheat_s=0.0):
         "value_without_partials": round((step_bytes - ab["partials"] * wl.n_layers) / (ms_per_step * 1e-3) / 1e9, 1),
         "value_kv_only": round(ab["kv"] * wl.n_layers / (ms_per_step * 1e-3) / 1e9, 1),
         "mean_context": round(float(lens_mid.mean()), 1), "split_tokens": S,
-        "partials_per_kv_head": n_items, "requests_finished_by_the_attention_kernel": B - n_split_req,
+        "partials_per_kv_head": n_items, "requests_finished_by_one_wave": B - n_split_req,
         "algorithmic_bytes_per_step": int(step_bytes),
     }
     roofline = None
@@ -588,7 +603,7 @@ def elastic_step(E, torch, W, args, steps=3):
     for _ in range(2):
         wl.step()
     # invariance: decode without appending, round-trip a quarter of the requests through the host, decode again
-    q0, B_ = wl.q[0], cfg.batch
+    q0 = wl.q[0]
     before = torch.empty_like(wl.out[0])
     after = torch.empty_like(wl.out[0])
     E.ellm_decode_attention(pool, ids[0], q0, before)
@@ -636,10 +651,9 @@ def elastic_step(E, torch, W, args, steps=3):
     for l in range(n_layers):          # leave everything resident
         fetch_layer(l)
     sync()
-    n_items, _, n_split_req = wl.n_split_items()
+    n_items, _, _ = wl.n_split_items()
     ab = W.algorithmic_bytes(cfg, wl.lens, n_items)
-    partial_bytes = (ab["kv"] + ab["q_out"] // 2 + ab["table"] + ab["partials"] // 2 + ab["append"]
-                     + (B_ - n_split_req) * cfg.n_q_heads * cfg.head_dim * 2)
+    partial_bytes = ab["kv"] + ab["q_out"] + ab["table"] + ab["partials"] + ab["append"]
     res = {
         "workload": f"llama8b shapes, {n_layers} layers, every 4th request ({len(sel)} of {B}) offloaded to pinned host and fetched "
                     f"between steps, 30 % of the idle activation chunks handed to the KV side before each step",
@@ -943,7 +957,7 @@ def main():
         "value_without_partials": head["value_without_partials"], "value_kv_only": head["value_kv_only"],
         "config": {"workload": desc, "global_batch": B, "layers": n_layers, "split_tokens": head["split_tokens"],
                    "partials_per_kv_head": head["partials_per_kv_head"],
-                   "requests_finished_by_the_attention_kernel": head["requests_finished_by_the_attention_kernel"],
+                   "requests_finished_by_one_wave": head["requests_finished_by_one_wave"],
                    "algorithmic_bytes_per_step": head["algorithmic_bytes_per_step"], "pool_chunks": n_chunks_head},
         "roofline": roofline, "cpu_baseline": cpu, "parity": parity,
     }

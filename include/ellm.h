@@ -412,9 +412,9 @@ int ellm_pool_get_owner_state(ellm_pool* pool, uint8_t* owner, uint8_t* state,
 /* Per host slot (host arrays of n_host_slots, any may be NULL): the (tensor, slot) stored, else -1. */
 int ellm_pool_get_host_slots(ellm_pool* pool, int32_t* tensor, int32_t* slot);
 /* The partition the next decode over these handles would use: n_split[b] (host array of batch) is
- * the number of partial results of each (request b, kv head) pair, i.e. the number of waves whose
- * share of the kv head's tiles holds tiles of the request or, in a batch small enough for one
- * workgroup per 256 tokens of a request, the number of those; *split_tokens is the largest share of a
+ * the number of pieces of each (request b, kv head) pair, i.e. the number of waves whose share of the kv
+ * head's tiles holds tiles of the request or, in a batch small enough for one workgroup per 256 (a little
+ * larger: up to 512) tokens of a request, the number of those; *split_tokens is the largest share of a
  * wave or workgroup, in tokens (a multiple of 64, rounded up). For tests of the partition. */
 int ellm_decode_plan(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch,
                      int32_t* n_split, int32_t* split_tokens);
