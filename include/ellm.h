@@ -170,6 +170,12 @@ uint64_t ellm_workspace_bytes(const ellm_pool_desc* desc, int32_t max_batch);
  * migration call. The only call besides that first one that allocates device memory. No-op on a
  * metadata-only pool. Errors: HIP. */
 int ellm_pool_prepare(ellm_pool* pool, void* stream);
+/* Put the counters of partial results (see ellm_decode_attention) back to 0, on `stream`, behind the pool's append /
+ * decode calls so far and before those to come. Needed only after calls have overlapped that must not; the caller
+ * sees to it that no replay of a graph that holds decode calls of the pool is in flight. Does not wait for the device. No-op
+ * before the pool has its device-side metadata. Errors: INVALID while `stream` or the stream of the
+ * pool's last call is being captured; HIP. */
+int ellm_pool_reset_counters(ellm_pool* pool, void* stream);
 
 /* Reserve a virtual tensor of max_tokens tokens (Sec. 2.1.1: virtual range = maximum context,
  * no physical chunk yet). n_slots = ceil(max_tokens / T_c). Returns the lowest unused handle.
@@ -299,7 +305,13 @@ int ellm_kv_append(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, co
  *   under remapping.
  * Checks: batch < 0, NULL q / out, non-finite scale -> INVALID; per request in order: bad handle ->
  * INVALID, len == 0 -> EMPTY; slots 0 .. ceil(len / T_c) - 1 ascending: empty -> UNMAPPED, on host
- * -> NOT_RESIDENT. Enqueued on `stream`; returns without waiting. */
+ * -> NOT_RESIDENT. Enqueued on `stream`; returns without waiting.
+ * The partial results of requests that are split are kept in the pool's workspace and counted, in device memory of the
+ * pool, as they arrive; between calls every counter is 0. The calls of a pool are ordered among each other by the library,
+ * on whatever streams they come, but replays of graphs that hold such calls are not: a replay must not overlap another
+ * replay or call on the same pool of this entry point or ellm_kv_append_decode (ellm_decode_attention_noalloc keeps
+ * both apart from these). Where that happens all the same, the outputs of both are undefined and counters may stay
+ * off 0, which makes the outputs of later calls wrong as well, until ellm_pool_reset_counters. */
 int ellm_decode_attention(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, const void* q,
                           void* out, float scale, void* stream);
 
@@ -316,7 +328,10 @@ int ellm_decode_attention(ellm_pool* pool, const ellm_tensor_id* ids, int32_t ba
  * runs on holds one such workspace from load to process end, shared by all pools and all calls of
  * this entry point on that GPU: calls that overlap in time on one GPU (two streams, two pools)
  * race on it and must be ordered by the caller. Nothing in it needs clearing between calls: every
- * slot a call reads, the same call has written before. */
+ * slot a call reads, the same call has written before. The counters of partial results are the pool's, in a
+ * set of their own for this entry point: a captured call of it may be replayed while calls of the other
+ * entry points run on the same pool. Overlapping calls of this entry point on one pool can leave
+ * them off 0, with the consequences and the remedy that ellm_decode_attention names. */
 #define ELLM_NOALLOC_WORKSPACE_BYTES (16u << 20)
 int ellm_decode_attention_noalloc(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, const void* q,
                                   void* out, float scale, void* stream);
@@ -460,6 +475,9 @@ int ellm_debug_set_waves(ellm_pool* pool, int32_t percent);
 /* Test hook: launches are planned as for a GPU of n compute units, as a partition of the card has them
  * (0, the default: as many as the GPU has; without a device 256). INVALID for more than the pool's GPU has. */
 int ellm_debug_set_compute_units(ellm_pool* pool, int32_t n);
+/* Test hook: every counter of partial results (see ellm_decode_attention) set to value, ordered like
+ * ellm_pool_reset_counters' 0. INVALID before the pool has its device-side metadata. */
+int ellm_debug_set_counters(ellm_pool* pool, uint32_t value, void* stream);
 
 /* Measurement only: what the paper's own mechanism costs on this GPU (Sec. 2.1.1, Sec. 3.2: chunks
  * mapped into a reserved virtual range through the driver's virtual-memory calls). Creates

@@ -102,6 +102,8 @@ _sigs = {
     "ellm_pool_self_check": [_vp],
     "ellm_debug_set_waves": [_vp, C.c_int32],
     "ellm_debug_set_compute_units": [_vp, C.c_int32],
+    "ellm_pool_reset_counters": [_vp, _vp],
+    "ellm_debug_set_counters": [_vp, C.c_uint32, _vp],
     "ellm_debug_copy": [_vp, _vp, C.c_uint64, _vp],
     "ellm_debug_stream_read": [_vp, C.c_uint64, _vp, _vp],
     "ellm_debug_kv_stream_read": [_vp, _i32p, C.c_int32, _vp, _vp],
@@ -515,3 +517,11 @@ def ellm_debug_set_waves(pool, percent, check=True):
 
 def ellm_debug_set_compute_units(pool, n, check=True):
     return _ret(lib.ellm_debug_set_compute_units(pool, int(n)), check)
+
+
+def ellm_pool_reset_counters(pool, stream=None, check=True):
+    return _ret(lib.ellm_pool_reset_counters(pool, _stream(stream)), check)
+
+
+def ellm_debug_set_counters(pool, value, stream=None, check=True):
+    return _ret(lib.ellm_debug_set_counters(pool, int(value), _stream(stream)), check)

@@ -81,7 +81,8 @@ struct ellm_pool {
   // device-side metadata, created by the first call that needs the device
   bool dev_ready = false;
   int32_t* d_table = nullptr;
-  uint32_t* d_merged = nullptr;        // in the same allocation: see PoolView::merged
+  uint32_t* d_merged = nullptr;        // in the same allocation: two sets of counters (see PoolView::merged) of merged_words
+  size_t merged_words = 0;             // words each, one set for each workspace a launch's partial results can be in
   float* d_ws = nullptr;               // partial results of one decode launch (see BatchArgs)
   int64_t ws_cap_slots = 0;            // partial slots it holds
   float* static_ws = nullptr;          // this device's copy of the library's fixed workspace
@@ -190,12 +191,14 @@ int core_changed(ellm_pool* p, int rc) {
   return p->vmm ? vmm_sync(p) : ELLM_OK;
 }
 
-ellm::PoolView view_of(const ellm_pool* p) {
+// fixed_ws: for a launch whose partial results are in the library's fixed workspace. A captured call of the entry point
+// that uses it may be replayed while another entry point's launch runs on the same pool: they share nothing they write.
+ellm::PoolView view_of(const ellm_pool* p, bool fixed_ws = false) {
   ellm::PoolView v;
   v.base = p->device_base;
   v.table = p->d_table;
   v.vbase = (p->vmm && !p->vmm_table_kernels) ? p->d_vbase : nullptr;
-  v.merged = p->d_merged;
+  v.merged = p->d_merged + (fixed_ws ? p->merged_words : 0);
   v.chunk_bytes = p->geom.chunk_bytes;
   v.tokens_per_chunk = p->geom.tokens_per_chunk;
   v.tiles_per_chunk = (p->geom.tokens_per_chunk + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
@@ -232,11 +235,12 @@ size_t slot_bytes(int32_t group, int32_t head_dim) { return (size_t)group * (hea
 
 int ensure_device(ellm_pool* p) {
   if (p->dev_ready) return ELLM_OK;
-  // the table mirror and, behind it, the counters of partial results, all 0
+  // the table mirror and, behind it, the two sets of counters of partial results, all 0
   std::vector<int32_t> image = p->core->table();
   const size_t counters_at = (image.size() + 63) / 64 * 64;
   const int32_t lines = std::max(p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
-  image.resize(counters_at + (size_t)lines * ellm::MERGE_STRIDE, 0);
+  p->merged_words = (size_t)lines * ellm::MERGE_STRIDE;
+  image.resize(counters_at + 2 * p->merged_words, 0);
   HIP_TRY(hipMalloc((void**)&p->d_table, image.size() * sizeof(int32_t)), "hipMalloc(table mirror)");
   HIP_TRY(hipMemcpy(p->d_table, image.data(), image.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   p->d_merged = (uint32_t*)p->d_table + counters_at;
@@ -301,6 +305,39 @@ int ensure_device(ellm_pool* p) {
   }
   p->dev_ready = true;
   return ELLM_OK;
+}
+
+// the append / decode calls of a pool are one sequence: what comes next runs on `stream`, behind them
+int follow_on(ellm_pool* p, hipStream_t stream) {
+  if (!p->have_last_stream || stream == p->last_stream) return ELLM_OK;
+  HIP_TRY(hipEventRecord(p->ev_switch, p->last_stream), "hipEventRecord(stream change)");
+  HIP_TRY(hipStreamWaitEvent(stream, p->ev_switch, 0), "hipStreamWaitEvent(stream change)");
+  p->compute_waits_in = p->compute_waits_out = 0;   // what the old stream waited for, the new one has yet to
+  return ELLM_OK;
+}
+
+// true also where the runtime will not say (the default stream beside a capture that would have to wait for it)
+bool being_captured(hipStream_t stream) {
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  return capture != hipStreamCaptureStatusNone;
+}
+
+// Every counter of partial results to `value`, between the decode calls before and after. Launches leave them at 0; only
+// launches that overlap where they must not (replays of graphs, which the pool does not see) can leave others. Not to
+// be recorded into a capture: replayed later, it would not be between calls any more.
+int set_counters(ellm_pool* p, uint32_t value, hipStream_t stream) {
+  if (being_captured(stream) || (p->have_last_stream && being_captured(p->last_stream)))
+    return set_err(ELLM_ERR_INVALID, "reset_counters: not while a stream of the pool's calls is being captured");
+  int rc = follow_on(p, stream);
+  if (rc) return rc;
+  p->last_stream = stream;
+  p->have_last_stream = true;
+  const int e = ellm::launch_fill(p->d_merged, value, 2 * p->merged_words, stream);
+  return e ? hip_err((hipError_t)e, "counter fill launch") : ELLM_OK;
 }
 
 // push host-side table changes to the device mirror, ordered on `stream`: the changed entries
@@ -399,12 +436,7 @@ int compute_mark(ellm_pool* p, int64_t need, hipEvent_t* ev, int64_t* covers) {
 // the host has not waited for it, because the runtime then puts a marker there.)
 int unfinished(ellm_pool* p, hipEvent_t ev, bool* yes) {
   *yes = false;
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(p->last_stream, &capture) != hipSuccess) {
-    (void)hipGetLastError();           // the default stream beside a capture that would have to wait for it
-    return ELLM_OK;
-  }
-  if (capture != hipStreamCaptureStatusNone) return ELLM_OK;
+  if (being_captured(p->last_stream)) return ELLM_OK;
   hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
   HIP_TRY(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode");
   const hipError_t state = hipEventQuery(ev);
@@ -450,11 +482,7 @@ int enter_compute(ellm_pool* p, hipStream_t stream, const int32_t* ids, int32_t 
   int rc = ensure_device(p);
   if (rc) return rc;
   if (p->vmm && (rc = vmm_wait_slots(p, ids, batch, extra))) return rc;
-  if (p->have_last_stream && stream != p->last_stream) {
-    HIP_TRY(hipEventRecord(p->ev_switch, p->last_stream), "hipEventRecord(stream change)");
-    HIP_TRY(hipStreamWaitEvent(stream, p->ev_switch, 0), "hipStreamWaitEvent(stream change)");
-    p->compute_waits_in = p->compute_waits_out = 0;   // what the old stream waited for, the new one has yet to
-  }
+  if ((rc = follow_on(p, stream))) return rc;
   if (tracks_chunks(p) && (p->r_in.seq > p->compute_waits_in || p->r_out.seq > p->compute_waits_out)) {
     int64_t need_in = 0, need_out = 0;
     for (int32_t b = 0; b < batch; b++) {
@@ -1297,7 +1325,7 @@ static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, c
   if (scale == 0.f) scale = 1.0f / std::sqrt((float)p->geom.head_dim);
   const float scale_log2 = scale * 1.4426950408889634f;
 
-  const ellm::PoolView pv = view_of(p);
+  const ellm::PoolView pv = view_of(p, ws_fixed != nullptr);
   int err = ELLM_OK;
   for (const ellm::BatchArgs& a : launches) {
     bool prof = (size_t)(p->prof_used + 1) * 2 <= p->prof_ev.size();
@@ -1412,6 +1440,16 @@ int ellm_pool_prepare(ellm_pool* p, void* stream) {
   int rc = ensure_device(p);
   if (rc) return rc;
   return flush_table(p, (hipStream_t)stream);
+}
+
+int ellm_pool_reset_counters(ellm_pool* p, void* stream) {
+  if (!p) return set_err(ELLM_ERR_INVALID, "NULL pool");
+  return p->dev_ready ? set_counters(p, 0, (hipStream_t)stream) : ELLM_OK;
+}
+
+int ellm_debug_set_counters(ellm_pool* p, uint32_t value, void* stream) {
+  if (!p || !p->dev_ready) return set_err(ELLM_ERR_INVALID, "set_counters: the pool has no counters on a device yet");
+  return set_counters(p, value, (hipStream_t)stream);
 }
 
 int ellm_pool_get_device_base(ellm_pool* p, void** base) {

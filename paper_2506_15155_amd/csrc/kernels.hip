@@ -189,6 +189,11 @@ constexpr int waitcnt_vm(int n) { return (n & 15) | ((n >> 4) << 14) | 0x0F70; }
 
 constexpr float NEG_BIG = -1.0e30f;   // finite stand-in for "no score yet"; exp2(NEG_BIG - x) == 0
 
+__global__ __launch_bounds__(256) void fill_kernel(uint32_t* words, uint32_t value, size_t n) {
+  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) words[i] = value;
+}
+
 // ---------------------------------------------------------------------------------------------
 // table patch: device_table[idx[i]] = val[i]
 // ---------------------------------------------------------------------------------------------
@@ -1617,6 +1622,13 @@ int static_workspace(float** ptr, size_t* bytes) {
 int launch_table_patch(int32_t* table, const PatchArgs& a, hipStream_t stream) {
   if (a.n <= 0) return 0;
   hipLaunchKernelGGL(table_patch_kernel, dim3((a.n + 255) / 256), dim3(256), 0, stream, table, a);
+  ELLM_HIP_CHECK_LAUNCH();
+  return 0;
+}
+
+int launch_fill(uint32_t* words, uint32_t value, size_t n, hipStream_t stream) {
+  if (n == 0) return 0;
+  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, words, value, n);
   ELLM_HIP_CHECK_LAUNCH();
   return 0;
 }

@@ -31,7 +31,8 @@ struct PoolView {
   const uint64_t* vbase;      // NULL: kernels go through the table. Else: per tensor, the start of its virtual
                               // address range, into which the driver has mapped its chunks; kernels read that
   uint32_t* merged;           // lines of counters, 0 between launches: workgroups whose partial result of a request is in
-                              // the workspace. Line kv head * MAX_LAUNCH_REQ + request; of blocks, the blocks' own numbers
+                              // the workspace. Line kv head * MAX_LAUNCH_REQ + request; of blocks, the blocks' own numbers.
+                              // A set for each workspace: launches that may overlap count in different ones
   uint32_t chunk_bytes;
   int32_t tokens_per_chunk;
   int32_t tiles_per_chunk;    // ceil(tokens_per_chunk / TILE_TOKENS); a tile never straddles a chunk
@@ -197,6 +198,7 @@ int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk);
 
 // each returns 0 or a hipError_t value
 int launch_table_patch(int32_t* table, const PatchArgs& a, hipStream_t stream);
+int launch_fill(uint32_t* words, uint32_t value, size_t n, hipStream_t stream);
 int launch_kv_append(const PoolView& pv, const void* k_new, const void* v_new, const AppendArgs& a,
                      hipStream_t stream);
 // Whole chunks between the pool (chunk c at pool + c * chunk_bytes) and the host buffer as the GPU
