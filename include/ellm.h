@@ -437,6 +437,9 @@ int ellm_decode_plan(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch,
  * extra_tokens = 1: of the next ellm_kv_append_decode), or NULL where the call would be refused. For tests
  * and measurements. */
 const char* ellm_debug_decode_kernel(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, int32_t extra_tokens);
+/* How many requests of that launch are split and have their partial results added up by a launch of its own behind it; those of
+ * the other split requests are added up by the attention kernel itself. Errors as of the call. For tests. */
+int ellm_debug_combined_requests(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, int32_t extra_tokens);
 /* Override the tokens per wave (rounded down to whole 64-token tiles, at least one; 0 = automatic:
  * one wave per SIMD of the GPU). For tests that compare partitions. While an override (this one or
  * ellm_debug_set_waves) is in force, a decode call whose partition needs more partial results than

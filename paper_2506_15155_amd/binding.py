@@ -102,6 +102,7 @@ _sigs = {
     "ellm_pool_self_check": [_vp],
     "ellm_debug_set_waves": [_vp, C.c_int32],
     "ellm_debug_set_compute_units": [_vp, C.c_int32],
+    "ellm_debug_combined_requests": [_vp, _i32p, C.c_int32, C.c_int32],
     "ellm_pool_reset_counters": [_vp, _vp],
     "ellm_debug_set_counters": [_vp, C.c_uint32, _vp],
     "ellm_debug_copy": [_vp, _vp, C.c_uint64, _vp],
@@ -472,6 +473,11 @@ def ellm_debug_decode_kernel(pool, ids, extra_tokens=0):
     if name is None:
         raise EllmError(-1, ellm_last_error())
     return name.decode()
+
+
+def ellm_debug_combined_requests(pool, ids, extra_tokens=0, check=True):
+    keep, p, n = _i32(ids)
+    return _ret(lib.ellm_debug_combined_requests(pool, p, n, int(extra_tokens)), check)
 
 
 def ellm_pool_set_split_tokens(pool, split_tokens, check=True):

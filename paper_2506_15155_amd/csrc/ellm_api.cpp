@@ -858,13 +858,13 @@ int32_t wave_slots(ellm_pool* p) {
 using ellm::TILE_TOKENS;
 
 // how many partial slots per kv head the cut of sequences of n[i] steps into `waves` shares needs; with
-// a != NULL the cut is written there
+// a != NULL the cut is written there. Either all shared requests go to the combine pass or, where all have up to merge_parts
+// parts, none does
 int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0) {
   const int64_t each = total / waves, more = total - each * waves;
   // wave that holds step x: the first `more` waves hold each + 1 steps, the others each
   auto wave_of = [&](int64_t x) { return x < more * (each + 1) ? x / (each + 1) : more + (x - more * (each + 1)) / each; };
-  int64_t at = 0, parts = 0;
-  int32_t n_split = 0;
+  int64_t at = 0, parts = 0, most = 0;
   for (size_t i = 0; i < n.size(); i++) {
     const int64_t w0 = wave_of(at), w1 = wave_of(at + n[i] - 1);
     if (a) {
@@ -872,19 +872,21 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
       a->req[i].wave_first = (int32_t)w0;
       a->req[i].n_part = (int32_t)(w1 - w0 + 1);
       a->req[i].part0 = w1 > w0 ? (int32_t)std::min<int64_t>(parts, 0x7fffffff) : 0;
-      if (w1 > w0 && w1 - w0 + 1 > merge_parts) {
-        a->split_req[n_split >> 2] |= (uint32_t)i << ((n_split & 3) * 8);
-        n_split++;
-      }
     }
+    most = std::max(most, w1 - w0 + 1);
     if (w1 > w0) parts += w1 - w0 + 1;   // a request shared by several waves: partial results
     at += n[i];
   }
   if (a) {
     a->units_each = (int32_t)each;
     a->units_extra = (int32_t)more;
-    a->n_split_req = n_split;
-    a->merge_parts = merge_parts;
+    a->merge_parts = most > merge_parts ? 0 : merge_parts;
+    a->n_split_req = 0;
+    for (size_t i = 0; i < n.size(); i++)
+      if (a->req[i].n_part > std::max(1, a->merge_parts)) {
+        a->split_req[a->n_split_req >> 2] |= (uint32_t)i << ((a->n_split_req & 3) * 8);
+        a->n_split_req++;
+      }
   }
   return parts;
 }
@@ -1001,7 +1003,9 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
     }
   }
   std::memset(a.split_req, 0, sizeof(a.split_req));
-  const int64_t parts = cut_shares(units, total, waves, &a, ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0));
+  const int32_t merge_parts = ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0);
+  const int64_t parts = cut_shares(units, total, waves, &a, merge_parts);
+  a.in_order_parts = block_units ? merge_parts : 0;
   a.n_req = n_req;
   a.q_row0 = q_row0;
   a.units_per_head = (int32_t)std::min<int64_t>(total, 0x7fffffff);
@@ -1287,6 +1291,15 @@ const char* ellm_debug_decode_kernel(ellm_pool* p, const ellm_tensor_id* ids, in
   plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
   if (a.unit_tokens == TILE_TOKENS) return "decode_tile_kernel";
   return a.step_units > ellm::STEP_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
+}
+
+int ellm_debug_combined_requests(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int32_t extra_tokens) {
+  if (!p || batch < 1 || extra_tokens < 0 || extra_tokens > 1) return set_err(ELLM_ERR_INVALID, "debug_combined_requests: bad argument");
+  int rc = core_err(p, p->core->decode_check(ids, batch, extra_tokens));
+  if (rc) return rc;
+  ellm::BatchArgs a;
+  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
+  return a.n_split_req;
 }
 
 int ellm_pool_set_split_tokens(ellm_pool* p, int32_t split_tokens) {

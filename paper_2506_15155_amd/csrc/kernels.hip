@@ -491,6 +491,8 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
       slot[i] = mine ? __builtin_ctz(mine) : slot[i ? i - 1 : 0];
       mine &= mine - 1;
     }
+    // (a request for the combine pass goes there also where no other workgroup has a part of it)
+    const bool whole = n == rq.n_part && rq.n_part <= a.merge_parts;
     const Parts parts = parts_of(rq.wave_first, rq.n_part, a.waves_per_head, g, false);
     const int64_t row0 = ((int64_t)g * a.parts_per_head + rq.part0 + ((int32_t)blockIdx.x - parts.first)) * pv.group + g_first;
     const auto rows = buffer_at(ws + row0 * D, n_heads * (D * 4));
@@ -510,14 +512,14 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
 #pragma unroll
       for (int i = 0; i < SHARE_WAVES; i++)
         if (i < n) add(s, ml[i].y, v[i], fast_exp2(ml[i].x - s.M));
-      if (n == rq.n_part) {
+      if (whole) {
         write_out<D>(pv, out, a, b, g, g_first, x, s);
       } else {
         store_partial(rows, x * 16, s.A);
         if (f == 0) store_partial(pairs, h * (WS_ML * 4), make_float2(s.M, s.L));
       }
     }
-    if (n == rq.n_part || rq.n_part > a.merge_parts) continue;
+    if (whole || rq.n_part > a.merge_parts) continue;
     stores_done();
     uint32_t before = 0;
     if (lane == 0) before = count_in(pv, g * MAX_LAUNCH_REQ + b, 0, parts.n);
@@ -1446,7 +1448,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // partials at a time; every lane's rows are asked for before the common maximum is known, so that the pass is one round
 // trip to memory for up to 64 partials. The RP sums of a dim are added up through LDS in a fixed order. Twice as many
 // waves are slower below 64 partials (32: 11.7 a call, 11.2; of heads of 64 36: 9.5, 8.4), faster for many (256 of heads
-// of 64: 19.5, 21.5).
+// of 64: 19.5, 21.5). In a launch in blocks a request that the attention kernel would have added up, were it not for
+// another request, is added up in that kernel's order: its bits do not depend on its neighbours.
 // ---------------------------------------------------------------------------------------------
 constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
 template <int D> constexpr int combine_waves = D / 16;
@@ -1460,6 +1463,17 @@ __global__ __launch_bounds__(64 * combine_waves<D>) void decode_combine_kernel(c
   const int b = (a.split_req[blockIdx.x >> 2] >> ((blockIdx.x & 3) * 8)) & 0xff;   // blockIdx.x-th split request
   const int g = h / group;
   const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.step_units > STEP_UNITS).n;
+  if (n_part <= a.in_order_parts) {
+    PoolView pv;
+    pv.n_q_heads = n_q_heads;
+    pv.group = group;
+    if (threadIdx.x >= F) return;
+    const Partials<D> all(pv, ws, a, a.req[b].part0, n_part, g, h - g * group, 1);
+    Sum s[1];
+    all.template sum<1, 8, 16>(s, f, 0, 0, n_part);
+    write_out<D>(pv, out, a, b, g, h - g * group, f, s[0]);
+    return;
+  }
   const int64_t row0 = ((int64_t)g * a.parts_per_head + a.req[b].part0) * group + (h - g * group);
   const float4* p = reinterpret_cast<const float4*>(ws + row0 * D) + f;       // accumulator rows of this head
   const float* q0 = ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML;      // their (m, l) pairs
@@ -1690,7 +1704,7 @@ static FewArgs few_of(const BatchArgs& a) {
   f.n_req = a.n_req; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens; f.step_units = a.step_units;
   f.units_per_head = a.units_per_head; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
   f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.use_wave_req = a.use_wave_req;
-  f.merge_parts = a.merge_parts; f.n_split_req = a.n_split_req;
+  f.merge_parts = a.merge_parts; f.in_order_parts = a.in_order_parts; f.n_split_req = a.n_split_req;
   std::copy_n(a.wave_req, FewArgs::MAX_WAVE / 4, f.wave_req);
   std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
   for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};

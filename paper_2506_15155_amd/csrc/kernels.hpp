@@ -76,7 +76,9 @@ struct BatchArgsOf {
                               // waves of several shares, a request uses no more than it spans workgroups)
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
-  int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last
+  int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last;
+                              // 0 where any request has more than merge_parts()
+  int32_t in_order_parts;     // requests of up to so many partials the combine pass adds up in that kernel's order
   int32_t n_split_req;        // requests with more: the combine pass runs for these only
   // request that holds the first unit of wave w of a kv head, one byte each: lets a wave find its
   // request with one scalar load instead of a search through the prefix entries
@@ -137,7 +139,11 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 
 // Up to how many waves (blocks: steps) a request may be shared by for its partial results, one per workgroup, to be
 // added up by the workgroup that ends last. The others go to the combine pass: a launch of its own, 4 to 5 us, but a
-// workgroup for each q head. us, added up by the last / by the pass:
+// workgroup for each q head. Where one request of a launch goes there, all do: beside a combine launch the others' sums at the
+// end of the attention kernel save nothing and take 2 to 4 us. us a call, both ways in one launch / the pass for all: 1 kv head of
+// 128, 4 q heads, 10 requests of 5400 to 16200 tokens (shares of 15 to 38 workgroups) 19.1 / 15.6, 8 heads of 64, 11 of 2100 to 6400
+// 15.6 / 12.0, 16 heads of 128, 11 of 6500 to 19400 36.9 / 30.8; 12 heads, 6 of 2000 to 9000 (8 to 36 blocks) 14.6 / 10.4.
+// us, added up by the last / by the pass, of launches in which all requests go one way:
 //  - Where shares are walked one wave reads them all, 16 KB in a round trip: up to 64 KB. 8 kv heads of 128, one request of
 //    20000 to 100000 tokens (32 workgroups), 1 q head each (16 KB) 65.5 / 66.6, 4 (64 KB) 21.8 / 22.6, 8 (128 KB) 72.3 /
 //    70.2, 16 (256 KB) 81 / 70.8; 4 kv heads (64 workgroups), 4 q heads each (128 KB) 30.2 / 28.3, 8: 36.9 / 29.6.

@@ -1,0 +1,98 @@
+"""The split requests of a launch are added up by the attention kernel, or all of them by the combine pass: either way where one
+of them has just as many partial results as the kernel takes, and one more."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_15155_amd as E
+import workloads as W
+from tests import gpu_harness as H
+
+DUMMY = 0x1000
+
+
+def line(dim, group, blocks):
+    """Parts of a request that the attention kernel adds up at most, as the library's sources state it."""
+    return (192 << 10 if blocks else (64 << 10) * 4) // (group * dim * 4)
+
+
+def test_all_or_none_go_to_the_combine_pass():
+    """Without a device: how many requests of a launch the combine pass gets, over random batches."""
+    rng = np.random.default_rng(8)
+    seen = {True: 0, False: 0}
+    for _ in range(300):
+        n_kv, group, dim = int(rng.choice([1, 1, 2, 4, 8])), int(rng.choice([1, 4, 8, 12, 16])), int(rng.choice([64, 128]))
+        tokens, n = int(rng.choice([16, 24, 102, 512])), int(rng.integers(1, 40))
+        mean = float(np.exp(rng.uniform(np.log(50), np.log(12000))))
+        lens = [int(x) for x in np.maximum(1, rng.lognormal(np.log(mean), 0.8, n))]
+        need = [-(-x // tokens) for x in lens]
+        cb = tokens * 4 * n_kv * dim
+        P = E.ellm_pool_create(None, None, cb, n_kv * group, n_kv, dim, n, max(need), flags=1, device_bytes=(sum(need) + 1) * cb)
+        ids = []
+        for x, s in zip(lens, need):
+            ids.append(E.ellm_tensor_create(P, s * tokens))
+            E.ellm_tensor_map_chunks(P, ids[-1], 0, s)
+        E.ellm_kv_append(P, ids, DUMMY, DUMMY, np.asarray(lens, np.int32), stream=0)
+        n_split, _ = E.ellm_decode_plan(P, ids)
+        blocks = E.ellm_debug_decode_kernel(P, ids) == "decode_block_kernel"
+        got = E.ellm_debug_combined_requests(P, ids)
+        E.ellm_pool_destroy(P)
+        over = bool(n_split.max() > line(dim, group, blocks))
+        seen[over] += 1
+        assert got == (int((n_split > 1).sum()) if over else 0), (lens, n_kv, group, dim)
+    assert min(seen.values()) > 30
+
+
+def load(n_kv, group, dim, tokens, lens, seed):
+    need = [-(-n // tokens) for n in lens]
+    cfg = W.Config("o", 9, len(lens), n_kv * group, n_kv, dim, tokens * 4 * n_kv * dim, sum(need) + 2, max(need) * tokens, "uniform", 1, max(lens))
+    rng = np.random.default_rng(seed)
+    B = H.Both(cfg)
+
+    def bits(*shape):
+        return (rng.standard_normal(shape).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16)
+
+    ids = []
+    for n, s in zip(lens, need):
+        ids.append(B.create(n))
+        assert B.map(ids[-1], 0, s) == 0
+    assert B.append(ids, bits(sum(lens), n_kv, dim), bits(sum(lens), n_kv, dim), lens) == 0
+    return B, ids, bits(len(lens), n_kv * group, dim)
+
+
+# (one kv head of 16 or of 34 heads: a request inside one workgroup is on the combine pass's list as well)
+@pytest.mark.gpu
+@pytest.mark.parametrize("over", [0, 1])
+@pytest.mark.parametrize("kernel,n_kv,group,dim,tokens", [
+    ("decode_tile_kernel", 3, 8, 128, 128), ("decode_tile_kernel", 1, 4, 128, 128), ("decode_unit_kernel", 3, 16, 128, 48),
+    ("decode_unit_kernel", 1, 34, 64, 64), ("decode_block_kernel", 2, 8, 128, 128), ("decode_block_kernel", 1, 12, 128, 64),
+    ("decode_block_kernel", 1, 16, 64, 64)])
+def test_either_way(kernel, n_kv, group, dim, tokens, over):
+    blocks = kernel == "decode_block_kernel"
+    most = line(dim, group, blocks) + over
+    step = 256 if blocks else 64
+    parts = [2, most, 1, 6, 4] if blocks else [1, 2, 3, 1, 4, most, 5, 2]
+    lens = [step * n - (5 * i) % 11 for i, n in enumerate(parts)]
+    B, ids, q = load(n_kv, group, dim, tokens, lens, 12)
+    if not blocks:
+        E.ellm_pool_set_split_tokens(B.pool, 64)
+    assert E.ellm_debug_decode_kernel(B.pool, ids) == kernel
+    n_split, _ = E.ellm_decode_plan(B.pool, ids)
+    combined = E.ellm_debug_combined_requests(B.pool, ids)
+    if list(n_split) == parts and group <= 16:
+        assert combined == (sum(n > 1 for n in parts) if over else 0)
+    rc, out = B.decode(ids, q)
+    rco, ref = B.orc.decode(ids, q)
+    assert rc == 0 and rco == 0
+    H.check_close(out, ref, f"{parts}")
+    for _ in range(3):
+        rc, again = B.decode(ids, q)
+        assert rc == 0 and torch.equal(again, out)
+    if blocks and (group > 8 or dim == 64):
+        # (pools whose small launches always go by blocks) what the request that is over the line changes for the others
+        # is who adds them up, not the bits
+        for b in (0, 2, 3, 4):
+            rc, one = B.decode([ids[b]], q[[b]])
+            assert rc == 0 and torch.equal(one[0], out[b])
+            assert E.ellm_debug_combined_requests(B.pool, [ids[b]]) == 0
+    B.close()
