@@ -444,9 +444,9 @@ __device__ __forceinline__ void write_out(const PoolView& pv, uint16_t* __restri
 
 // Where a request's partial results are: the workgroups it reaches into, for kv head g, are numbered from 0 on
 struct Parts { int32_t first, n; };    // workgroup of its first wave, how many
-__device__ __forceinline__ Parts parts_of(int32_t wave_first, int32_t n_part, int32_t waves_per_head, int32_t g, bool blocks) {
+__device__ __forceinline__ Parts parts_of(int32_t wave_first, int32_t n_part, int32_t waves_per_head, int32_t g, int32_t wg_waves) {
   const int32_t w0 = g * waves_per_head + wave_first;
-  if (blocks) return {w0, n_part};     // a workgroup is one of the request's steps
+  if (wg_waves == 1) return {w0, n_part};     // a workgroup is one of the request's steps
   return {w0 / SHARE_WAVES, (w0 + n_part - 1) / SHARE_WAVES - w0 / SHARE_WAVES + 1};
 }
 
@@ -493,7 +493,7 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
     }
     // (a request for the combine pass goes there also where no other workgroup has a part of it)
     const bool whole = n == rq.n_part && rq.n_part <= a.merge_parts;
-    const Parts parts = parts_of(rq.wave_first, rq.n_part, a.waves_per_head, g, false);
+    const Parts parts = parts_of(rq.wave_first, rq.n_part, a.waves_per_head, g, SHARE_WAVES);
     const int64_t row0 = ((int64_t)g * a.parts_per_head + rq.part0 + ((int32_t)blockIdx.x - parts.first)) * pv.group + g_first;
     const auto rows = buffer_at(ws + row0 * D, n_heads * (D * 4));
     const auto pairs = buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4));
@@ -1046,9 +1046,9 @@ struct TileInfo {                    // what is known of a tile before its loads
 // units per tile: 8 KB of K and 8 KB of V for either head size
 template <int D> constexpr int tile_units = D == 128 ? 2 : 4;
 
-// NW == 0: a wave walks its share. NW > 0 (small launches): NW waves share a step of up to NW * U units of one
+// NW == 0: a wave walks its share, SW of them are a workgroup; SW == 1: single_waves(). NW > 0 (small launches): NW waves share a step of up to NW * U units of one
 // request, one tile each, everything asked for at once, and add up through LDS.
-template <int D, int U, bool APPEND, bool DIRECT, int NW, class Args>
+template <int D, int U, bool APPEND, bool DIRECT, int NW, int SW, class Args>
 __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                             const char* __restrict__ k_new, const char* __restrict__ v_new,
                                             float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
@@ -1062,7 +1062,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
-  const int32_t index = NW ? blockIdx.x : blockIdx.x * SHARE_WAVES + wave;
+  const int32_t index = NW ? blockIdx.x : blockIdx.x * SW + wave;
   const Share sh = locate_share(a, NW ? index : min(index, a.waves_per_head * pv.n_kv_heads - 1), lane);
   const int32_t g = sh.g;
   const int32_t hq0 = g * pv.group + g_first;        // first q head handled here
@@ -1369,8 +1369,8 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     if (x < n_cols) write_out<D>(pv, out, a, cb, g, g_first, x, all_of[0]);
     return;
   }
-  __shared__ __attribute__((aligned(16))) Results<D, HEADS_PER_PASS> results;
-  if (lane < 2) results.whose[2 * wave + lane] = -1;
+  __shared__ __attribute__((aligned(16))) Results<D, SW == 1 ? 1 : HEADS_PER_PASS> results;     // (SW == 1: not used)
+  if (SW > 1 && lane < 2) results.whose[2 * wave + lane] = -1;
   auto finish = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
     const float L = add_xor32(add_xor16(l));
     if (c >= n_heads) return;
@@ -1384,6 +1384,17 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
 #pragma unroll
         for (int e = 0; e < E; e += 2)
           *reinterpret_cast<uint32_t*>(o + i * E + e) = pack_bf16(acc[e][i] * inv, acc[e + 1][i] * inv);
+    } else if constexpr (SW == 1) {
+      // one of several waves of the request: a partial result
+      // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
+      const int64_t row = ((int64_t)g * a.parts_per_head + t.part) * pv.group + g_first + c;
+      float* to = ws + row * D + g16 * 4;
+#pragma unroll
+      for (int i = 0; i < 4; i++)
+#pragma unroll
+        for (int e = 0; e < E; e += 4)
+          *reinterpret_cast<float4*>(to + (i * E + e) * 4) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
+      if (g16 == 0) *reinterpret_cast<float2*>(ws + (int64_t)a.ws_slots * pv.group * D + row * WS_ML) = make_float2(m, L);
     } else {
       // one of several waves of the request: its results meet the others' in LDS
       // (dims in the order in which the lanes of a row store neighbouring 16-byte pieces)
@@ -1421,16 +1432,16 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       advance(next);
     } while (!done);
   }
-  end_shares<D, HEADS_PER_PASS, 2, 8>(pv, ws, out, a, results, g_first, n_heads, wave, lane);
+  if constexpr (SW > 1) end_shares<D, HEADS_PER_PASS, 2, 8>(pv, ws, out, a, results, g_first, n_heads, wave, lane);
 }
 
 // Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
 // the accumulation registers, which ordinary instructions cannot read.
-template <int D, int U, bool APPEND, bool DIRECT>
-__global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
+template <int D, int U, int SW, bool APPEND, bool DIRECT>
+__global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
-  decode_unit_body<D, U, APPEND, DIRECT, 0>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  decode_unit_body<D, U, APPEND, DIRECT, 0, SW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
 // of which one launch instead of two is 3 us of host time. Launches of 50 MB of K and V, in wide blocks with four units
@@ -1439,7 +1450,7 @@ template <int D, int U, int NW, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, Args a) {
-  decode_unit_body<D, U, APPEND, DIRECT, NW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  decode_unit_body<D, U, APPEND, DIRECT, NW, 1>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1449,21 +1460,21 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // trip to memory for up to 64 partials. The RP sums of a dim are added up through LDS in a fixed order. Twice as many
 // waves are slower below 64 partials (32: 11.7 a call, 11.2; of heads of 64 36: 9.5, 8.4), faster for many (256 of heads
 // of 64: 19.5, 21.5). In a launch in blocks a request that the attention kernel would have added up, were it not for
-// another request, is added up in that kernel's order: its bits do not depend on its neighbours.
+// another request, is added up in that kernel's order: its bits do not depend on its neighbours (IN_ORDER; its registers are as many
+// as 16 partials ahead take, which launches of many workgroups do not have to pay).
 // ---------------------------------------------------------------------------------------------
 constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
-template <int D> constexpr int combine_waves = D / 16;
 
-template <int D>
-__global__ __launch_bounds__(64 * combine_waves<D>) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
+template <int D, int W, bool IN_ORDER = false>
+__global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
                                                                 int32_t n_q_heads, int32_t group, BatchArgs a) {
-  constexpr int F = D / 4, RP = combine_waves<D> * 64 / F, AHEAD = COMBINE_AHEAD;
+  constexpr int F = D / 4, RP = W * 64 / F, AHEAD = COMBINE_AHEAD;
   __shared__ __attribute__((aligned(16))) float4 sums[RP][F];
   const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
   const int b = (a.split_req[blockIdx.x >> 2] >> ((blockIdx.x & 3) * 8)) & 0xff;   // blockIdx.x-th split request
   const int g = h / group;
-  const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.step_units > STEP_UNITS).n;
-  if (n_part <= a.in_order_parts) {
+  const int n_part = parts_of(a.req[b].wave_first, a.req[b].n_part, a.waves_per_head, g, a.wg_waves).n;
+  if (IN_ORDER && n_part <= a.in_order_parts) {
     PoolView pv;
     pv.n_q_heads = n_q_heads;
     pv.group = group;
@@ -1673,7 +1684,7 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
 
 template <int D>
 static const void* partial_kernel_ptr(int group, bool tiles) {
-  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, true, false>;
+  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, true, false>;
   if constexpr (D == 128) {
     if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false>;
     if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false>;
@@ -1704,7 +1715,7 @@ static FewArgs few_of(const BatchArgs& a) {
   f.n_req = a.n_req; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens; f.step_units = a.step_units;
   f.units_per_head = a.units_per_head; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
   f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.use_wave_req = a.use_wave_req;
-  f.merge_parts = a.merge_parts; f.in_order_parts = a.in_order_parts; f.n_split_req = a.n_split_req;
+  f.wg_waves = a.wg_waves; f.merge_parts = a.merge_parts; f.in_order_parts = a.in_order_parts; f.n_split_req = a.n_split_req;
   std::copy_n(a.wave_req, FewArgs::MAX_WAVE / 4, f.wave_req);
   std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
   for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};
@@ -1751,9 +1762,12 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
   // first of them takes the start time, the last one the end time
   for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
     const int n = std::min(HEADS_PER_PASS, pv.group - done);
-    launch_timed(decode_unit_kernel<D, tile_units<D>, APPEND, DIRECT>, grid, 64 * SHARE_WAVES, stream, done == 0 ? ev_start : nullptr,
-                 done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
-                 (uint16_t*)out, scale_log2, done, n, a);
+    auto go = [&](auto kernel, unsigned n_wg, unsigned threads) {
+      launch_timed(kernel, n_wg, threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q,
+                   (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, done, n, a);
+    };
+    if (a.wg_waves == 1) go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT>, waves, 64);
+    else go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT>, grid, 64 * SHARE_WAVES);
     ELLM_HIP_CHECK_LAUNCH();
   }
   return 0;
@@ -1778,11 +1792,15 @@ int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, 
 
 int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
   if (a.n_req <= 0 || a.n_split_req <= 0) return 0;
-  const dim3 grid(a.n_split_req, pv.n_q_heads), block(pv.head_dim * 4);
-  if (pv.head_dim == 128)
-    hipLaunchKernelGGL(decode_combine_kernel<128>, grid, block, 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
-  else
-    hipLaunchKernelGGL(decode_combine_kernel<64>, grid, block, 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
+  // where every wave leaves partials there can be few of them each for many requests: as many waves as these fill
+  const bool single = a.wg_waves == 1 && a.step_units <= STEP_UNITS;
+  const int fill = single ? a.parts_per_head / a.n_split_req * pv.head_dim / (COMBINE_AHEAD * 256) : 4;    // by 1, by 4, more
+  auto go = [&](auto kernel, unsigned waves) {
+    hipLaunchKernelGGL(kernel, dim3(a.n_split_req, pv.n_q_heads), dim3(64 * waves), 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
+  };
+  if (a.in_order_parts) pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, true>, 8) : go(decode_combine_kernel<64, 4, true>, 4);
+  else if (pv.head_dim == 128) fill < 1 ? go(decode_combine_kernel<128, 2>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4>, 4) : go(decode_combine_kernel<128, 8>, 8);
+  else fill < 1 ? go(decode_combine_kernel<64, 1>, 1) : go(decode_combine_kernel<64, 4>, 4);
   ELLM_HIP_CHECK_LAUNCH();
   return 0;
 }

@@ -76,6 +76,7 @@ struct BatchArgsOf {
                               // waves of several shares, a request uses no more than it spans workgroups)
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
+  int32_t wg_waves;           // waves of a workgroup that each have a share of their own (SHARE_WAVES), or 1
   int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last;
                               // 0 where any request has more than merge_parts()
   int32_t in_order_parts;     // requests of up to so many partials the combine pass adds up in that kernel's order
@@ -151,9 +152,22 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 //    blocks of 4 q heads each (62 KB) 9.7 / 11.7, of 6 (93 KB) 10.1 / 11.9, of 8 (124 KB) 10.6 / 12.0, of 16 (248 KB) 12.9 / 12.4; 16
 //    blocks of 16 (128 KB) 9.8 / 11.6; 4 kv heads, 59 of 4 (118 KB) 11.1 / 12.1, of 8 (236 KB) 12.6 / 12.3; heads of 64, 31 of 16
 //    (124 KB) 9.0 / 11.5.
+//  - A group of more than HEADS_PER_PASS q heads takes several launches over the same units, each with these sums at its
+//    end: up to 16 waves. us a call, in every launch / the pass: 4 kv heads of 64, 20 q heads each, 8 requests of
+//    2100 to 6400 tokens (16 to 48 waves) 25.1 / 21.7, of 128, 32 q heads, 14 of 1000 to 3100 (18 waves) 39.7 / 33.9, 128 of 300 to 600
+//    (2 or 3) 54.6 / 85.
 inline int merge_parts(int head_dim, int group, bool blocks) {
   const int row = group * head_dim * 4;      // bytes of a partial result
-  return blocks ? (192 << 10) / row : (64 << 10) * SHARE_WAVES / row;
+  if (blocks) return (192 << 10) / row;
+  return std::min((64 << 10) * SHARE_WAVES / row, group > HEADS_PER_PASS ? 4 * SHARE_WAVES : 1 << 30);
+}
+// Such launches do without sums in the kernel where a wave has few units (more, where many requests end inside waves): a
+// workgroup is one wave, and every wave leaves a partial result of its own for one combine pass behind the last launch. us
+// a call, sums in every launch / this: steps: 16 requests of 200 to 400 tokens, 1 kv head of 128, 64 q heads 47.3 / 22.1, 44 of 58 to 175,
+// 33 heads 31.2 / 17.4, 4 kv heads, 40 heads, 5 of 270 to 800 36.6 / 18.5; 8 kv heads, 32 heads, 114 of 31 to 93 (5 units a wave) 44.0 / 33.7; 2 kv
+// heads, 16 of 2000 to 4000 (6 units a wave, few requests) 28.1 / 32.0.
+inline bool single_waves(int group, bool blocks, int64_t units, int64_t waves, int n_req) {
+  return group > HEADS_PER_PASS && !blocks && units < STEP_UNITS * waves + 2 * n_req;
 }
 
 // Small launches are cut in units whatever the pool's shares are cut in, and request by request: in blocks (one

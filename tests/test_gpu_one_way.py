@@ -96,3 +96,41 @@ def test_either_way(kernel, n_kv, group, dim, tokens, over):
             assert rc == 0 and torch.equal(one[0], out[b])
             assert E.ellm_debug_combined_requests(B.pool, [ids[b]]) == 0
     B.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("group,dim,n_kv,split,most,combined", [
+    (34, 64, 1, 64, 12, True), (20, 128, 3, 64, 9, True),          # a workgroup is one wave
+    (34, 64, 3, 128, 16, False), (20, 128, 1, 128, 16, False), (64, 128, 1, 128, 8, False),
+    (34, 64, 1, 128, 17, True), (17, 128, 3, 128, 17, True), (64, 128, 2, 128, 9, True),
+    (34, 64, 2, 0, 0, True), (48, 128, 1, 0, 0, True)])             # single steps, as cut by the library
+def test_groups_of_several_launches(group, dim, n_kv, split, most, combined):
+    """More q heads per kv head than one launch handles: few units a wave, with a partial result from each, and shares,
+    added up in every launch or by the pass; the same bits from replays of a graph with another batch behind."""
+    parts = [1, 2, most, 3, 1, 5, most - 1, 2] if split else [1, 3, 2, 5, 9, 30]
+    per = split or 64
+    lens = [per * n - (7 * i) % 13 for i, n in enumerate(parts)]
+    B, ids, q = load(n_kv, group, dim, 64, lens, 4)
+    if split:
+        E.ellm_pool_set_split_tokens(B.pool, split)
+    assert E.ellm_debug_decode_kernel(B.pool, ids) == "decode_unit_kernel"
+    n_split, _ = E.ellm_decode_plan(B.pool, ids)
+    assert E.ellm_debug_combined_requests(B.pool, ids) == (int((n_split > 1).sum()) if combined else 0)
+    rc, out = B.decode(ids, q)
+    rco, ref = B.orc.decode(ids, q)
+    assert rc == 0 and rco == 0
+    H.check_close(out, ref, f"{parts}")
+    qd, got, other = H.dev_bits(q), torch.empty_like(out), torch.empty_like(out)
+    stream, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    stream.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(stream):
+        with torch.cuda.graph(graph, stream=stream):
+            E.ellm_decode_attention(B.pool, ids, qd, got)
+            E.ellm_decode_attention(B.pool, ids[::-1], qd, other)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        got.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, out)
+    B.close()
