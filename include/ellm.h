@@ -516,6 +516,9 @@ int ellm_debug_set_async_mapping(ellm_pool* pool, int on);
 int ellm_debug_set_copy_kernels(ellm_pool* pool, int on);
 /* How many offload and fetch calls of the pool moved their chunks each way (either pointer may be NULL). */
 int ellm_pool_get_copy_counts(ellm_pool* pool, int64_t* by_engine, int64_t* by_kernel);
+/* 1: the pool's offloads by kernel leave memory traffic to attention that runs beside them, because the append or decode call
+ * after the last copies did not wait for the newest of them (of the fetches, if there were any); else 0. For tests. */
+int ellm_debug_compute_beside_copies(ellm_pool* pool);
 /* Test hook for the error path of a driver-mapped pool's mapper thread: the nth mapping it is asked
  * for from now on (1 = the next one; 0 = none) is not made and counts as refused by the driver. Every
  * later call that would launch a kernel on the pool, or that waits for the thread, then returns

@@ -103,6 +103,7 @@ _sigs = {
     "ellm_debug_set_waves": [_vp, C.c_int32],
     "ellm_debug_set_compute_units": [_vp, C.c_int32],
     "ellm_debug_combined_requests": [_vp, _i32p, C.c_int32, C.c_int32],
+    "ellm_debug_compute_beside_copies": [_vp],
     "ellm_pool_reset_counters": [_vp, _vp],
     "ellm_debug_set_counters": [_vp, C.c_uint32, _vp],
     "ellm_debug_copy": [_vp, _vp, C.c_uint64, _vp],
@@ -523,6 +524,10 @@ def ellm_debug_set_waves(pool, percent, check=True):
 
 def ellm_debug_set_compute_units(pool, n, check=True):
     return _ret(lib.ellm_debug_set_compute_units(pool, int(n)), check)
+
+
+def ellm_debug_compute_beside_copies(pool):
+    return bool(_ret(lib.ellm_debug_compute_beside_copies(pool), True))
 
 
 def ellm_pool_reset_counters(pool, stream=None, check=True):

@@ -126,6 +126,10 @@ struct ellm_pool {
   int64_t compute_waits_in = 0, compute_waits_out = 0;
   int64_t in_waits_compute = 0, in_waits_out = 0;
   int64_t out_waits_compute = 0, out_waits_in = 0;
+  // Does the program compute beside its copies? After the copies that came last, the next append / decode call did not wait
+  // for the newest of them (fetches, if there were any)
+  bool compute_beside_copies = false;
+  int64_t judged_in = 0, judged_out = 0;                     // copies that this takes into account
   // Per tensor: the newest fetch / offload that touched one of its chunks, valid while its table
   // row is unchanged (a copy that touches a chunk of a tensor always changes that tensor's row), so
   // that a compute call walks a tensor's slots once per change and not once per call.
@@ -483,8 +487,8 @@ int enter_compute(ellm_pool* p, hipStream_t stream, const int32_t* ids, int32_t 
   if (rc) return rc;
   if (p->vmm && (rc = vmm_wait_slots(p, ids, batch, extra))) return rc;
   if ((rc = follow_on(p, stream))) return rc;
+  int64_t need_in = 0, need_out = 0;
   if (tracks_chunks(p) && (p->r_in.seq > p->compute_waits_in || p->r_out.seq > p->compute_waits_out)) {
-    int64_t need_in = 0, need_out = 0;
     for (int32_t b = 0; b < batch; b++) {
       ellm_pool::CopySeen& cs = p->copy_seen[ids[b]];
       const uint32_t ver = p->core->row_version(ids[b]);
@@ -506,6 +510,12 @@ int enter_compute(ellm_pool* p, hipStream_t stream, const int32_t* ids, int32_t 
     if ((rc = wait_for(stream, p->r_in, need_in, p->compute_waits_in))) return rc;
     if ((rc = wait_for(stream, p->r_out, need_out, p->compute_waits_out))) return rc;
   }
+  if (p->r_in.seq > p->judged_in)
+    p->compute_beside_copies = p->r_in.seq > std::max({need_in, p->compute_waits_in, p->r_in.done});
+  else if (p->r_out.seq > p->judged_out)
+    p->compute_beside_copies = p->r_out.seq > std::max({need_out, p->compute_waits_out, p->r_out.done});
+  p->judged_in = p->r_in.seq;
+  p->judged_out = p->r_out.seq;
   rc = flush_table(p, stream);
   if (rc) return rc;
   p->last_stream = stream;
@@ -570,10 +580,10 @@ size_t move_run(const ellm_pool* p, const std::vector<ellm::Move>& moves, size_t
 // alone: 27 chunks out and 27 others in, call by call, 1.52 ms against 1.95. But a copy behind an event
 // of another stream that has not happened yet starts 50 to 130 us late, some of the copies become the
 // runtime's own copy kernels, and now and then the calling thread is held for milliseconds: the same
-// swap with passes in flight takes 2.3 to 3.8 ms by engine, 1.87 by kernel, whose waits are between
-// queues. Attention beside the kernel's copies is slower than beside the engines' (8B-shaped elastic step, layer by
-// layer: 200 us against 64-80), the step as a whole is not (114 ms by the rule, 3040 of 3072 calls by kernel, against
-// 118-149 by engines only); one request swapped for another every tenth step, while the rest decodes, waits for
+// swap with passes in flight takes 2.3 to 3.8 ms by engine, 1.71 by kernel, whose waits are between
+// queues. Attention beside the kernel's copies is no slower than beside the engines' where few workgroups write to host memory
+// (OFFLOAD_WORKGROUPS_BESIDE; 8B-shaped elastic step, layer by layer: 66 us against 64-84), and the step is faster (108 ms by the
+// rule, 3040 of 3072 calls by kernel, against 131-142 by engines only); one request swapped for another every tenth step, while the rest decodes, waits for
 // nothing and goes by engine (2.11 ms a step; 2.78 always by kernel).
 int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) {
   const size_t cb = p->geom.chunk_bytes;
@@ -587,7 +597,8 @@ int copy_chunks(ellm_pool* p, const std::vector<ellm::Move>& moves, bool fetch) 
         a.chunk[k] = moves[i + k].chunk;
         a.host_slot[k] = moves[i + k].host_slot;
       }
-      const int e = ellm::launch_chunk_copy(p->device_base, p->host_dev, (uint32_t)cb, a, !fetch, side);
+      const int wgs = fetch ? ellm::FETCH_WORKGROUPS : p->compute_beside_copies ? ellm::OFFLOAD_WORKGROUPS_BESIDE : ellm::OFFLOAD_WORKGROUPS;
+      const int e = ellm::launch_chunk_copy(p->device_base, p->host_dev, (uint32_t)cb, a, !fetch, wgs, side);
       if (e) return hip_err((hipError_t)e, fetch ? "copy kernel launch (fetch)" : "copy kernel launch (offload)");
     }
     p->calls_by_kernel++;
@@ -1513,6 +1524,11 @@ int ellm_pool_get_copy_counts(ellm_pool* p, int64_t* by_engine, int64_t* by_kern
   if (by_engine) *by_engine = p->calls_by_engine;
   if (by_kernel) *by_kernel = p->calls_by_kernel;
   return ELLM_OK;
+}
+
+int ellm_debug_compute_beside_copies(ellm_pool* p) {
+  if (!p) return set_err(ELLM_ERR_INVALID, "NULL pool");
+  return p->compute_beside_copies ? 1 : 0;
 }
 
 int ellm_debug_set_table_kernels(ellm_pool* p, int on) {

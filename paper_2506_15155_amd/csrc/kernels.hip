@@ -242,15 +242,14 @@ __global__ __launch_bounds__(256) void kv_append_kernel(PoolView pv, const uint4
 // GPU reads and writes directly over PCIe. One launch moves all chunks of a call, wherever they are:
 // per chunk a copy call of the runtime costs about 10 us of a 46 us transfer (2 MiB at a time go at
 // 44-45 GB/s on this machine, one large copy at 57); a kernel that gathers the chunks itself moves calls of 27
-// chunks at 54 / 57 GB/s out / in (engines 45 / 45) and at 40 per direction when both run at once with nothing to
-// wait for (engines 39), calls of 3 chunks at 49 / 53 and 29 (44 / 44 and 18).
+// chunks at 55 / 56 GB/s out / in, the host's wait for their end included (engines 45 / 45). Both directions at once, call by
+// call with nothing to wait for, 31 each, calls of 3 chunks 28 (engines 48, and 12 to 25).
 // WPC workgroups share a chunk; the loads and stores are streaming ones (the data passes through once), one of each a
 // lane at a time: while calls of both directions run beside each other, what an offload has in flight holds up the
 // fetch's reads. Requests of 1 to 5 chunks swapped for others, 27 chunks each way, us: 4 loads a lane, 64 workgroups for a
 // call 1893; 1 load, 64: 1819, 128: 1839, 192: 1829, 64 for an offload and 128 for a fetch 1702 to 1748, the other way round
-// 1920, 64 and 256: 1773, 32 and 128: 1747. One direction alone goes at 50 to 54 GB/s in all of these.
+// 1920, 64 and 256: 1773, 32 and 128: 1747. One direction alone goes at 50 to 56 GB/s in all of these.
 // ---------------------------------------------------------------------------------------------
-constexpr int OFFLOAD_WORKGROUPS = 64, FETCH_WORKGROUPS = 128;
 __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool, char* __restrict__ host, uint32_t chunk_bytes,
                                                          int32_t wpc, int32_t to_host, CopyArgs a) {
   const int32_t c = blockIdx.x / wpc, part = blockIdx.x - c * wpc;
@@ -1671,10 +1670,10 @@ int launch_kv_append(const PoolView& pv, const void* k_new, const void* v_new, c
   return 0;
 }
 
-int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, hipStream_t stream) {
+int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, int workgroups, hipStream_t stream) {
   if (a.n <= 0) return 0;
   // a workgroup should still have 16 KiB to move
-  int wpc = std::max(1, (to_host ? OFFLOAD_WORKGROUPS : FETCH_WORKGROUPS) / a.n);
+  int wpc = std::max(1, workgroups / a.n);
   wpc = std::max(1, std::min<int>(wpc, (int)(chunk_bytes / (16u << 10))));
   hipLaunchKernelGGL(chunk_copy_kernel, dim3((unsigned)(a.n * wpc)), dim3(256), 0, stream, pool, host, chunk_bytes, wpc,
                      to_host ? 1 : 0, a);

@@ -122,6 +122,14 @@ struct CopyArgs {
   int32_t host_slot[MAX_COPY];
 };
 
+// Workgroups of a call's copy kernel. While copies of both directions run, 64 for an offload and 128 for a fetch are the fastest,
+// but the writes to host memory that an offload has under way hold up all other traffic of the GPU. Where attention runs beside
+// copies the offload takes 32 (for how that is known see ellm_pool::compute_beside_copies): 16 requests swapped for others layer by
+// layer under the attention of an 8B-shaped model, an attention launch (60 us alone) / the step: 64 workgroups 265 to 340 us /
+// 113 ms, 32: 68 us / 108 ms, 48 and 96 for the fetch 280 to 330, 32 and 64: 94 to 120. With copies always under way: offloads alone
+// 240 / 158 us, fetches alone (128) 213, both 300 / 184. Swaps that nothing runs beside, 8 requests for 8, 27 chunks: 1714 us, 32: 1760.
+constexpr int OFFLOAD_WORKGROUPS = 64, OFFLOAD_WORKGROUPS_BESIDE = 32, FETCH_WORKGROUPS = 128;
+
 // Which of the two attention kernels a pool's calls use: the one that walks 64-row tiles of a chunk, or the one
 // that walks 16-row units. The first has no instance for group sizes that are not 1, 2, 4 or 8 (it would
 // read K and V two or three times: 6 heads 92 us against 52, 16 heads of 64 145 against 70) and loads whole
@@ -223,7 +231,7 @@ int launch_kv_append(const PoolView& pv, const void* k_new, const void* v_new, c
                      hipStream_t stream);
 // Whole chunks between the pool (chunk c at pool + c * chunk_bytes) and the host buffer as the GPU
 // sees it (slot s at host + s * chunk_bytes); to_host: offload, else fetch.
-int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, hipStream_t stream);
+int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, int workgroups, hipStream_t stream);
 // k_new / v_new non-NULL: fused append. a.len then counts one token per request whose K/V row
 // ([request][kv head][dim], rows q_row0 .. of the caller's batch) is still in k_new / v_new; the
 // kernel uses it from there and writes it into the chunk.
