@@ -891,13 +891,16 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
   if (a) {
     a->units_each = (int32_t)each;
     a->units_extra = (int32_t)more;
-    a->merge_parts = most > merge_parts ? 0 : merge_parts;
+    a->merge_parts = merge_parts;
     a->n_split_req = 0;
-    for (size_t i = 0; i < n.size(); i++)
-      if (a->req[i].n_part > std::max(1, a->merge_parts)) {
-        a->split_req[a->n_split_req >> 2] |= (uint32_t)i << ((a->n_split_req & 3) * 8);
-        a->n_split_req++;
-      }
+    if (most > merge_parts) {
+      a->merge_parts = 0;
+      for (size_t i = 0; i < n.size(); i++)
+        if (a->req[i].n_part > 1) {
+          a->split_req[a->n_split_req >> 2] |= (uint32_t)i << ((a->n_split_req & 3) * 8);
+          a->n_split_req++;
+        }
+    }
   }
   return parts;
 }
@@ -907,6 +910,7 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
 int32_t wide_block(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t extra, int32_t cus, int64_t* blocks) {
   const int32_t Tc = p->geom.tokens_per_chunk, room = cus / p->geom.n_kv_heads;
   const int32_t chunk_units = (Tc + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
+  if (!ellm::wide_batch(p->geom.group, n_req, room)) return 0;
   std::vector<int32_t>& units = p->units_tmp;
   units.resize(n_req);
   int64_t total = 0;
@@ -917,7 +921,7 @@ int32_t wide_block(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t extr
     if (total > (int64_t)ellm::WIDE_UNITS * room) return 0;      // (most launches: known after a few requests)
     units[i] = (int32_t)n;
   }
-  if (!ellm::wide_launch(p->geom.group, total, n_req, room)) return 0;
+  if (!ellm::wide_launch(total, room)) return 0;
   for (int32_t b = (int32_t)((total + room - 1) / room); b <= ellm::WIDE_UNITS; b++) {
     int64_t n = 0;
     int32_t parts = 0;

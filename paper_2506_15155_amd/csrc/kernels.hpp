@@ -217,9 +217,8 @@ inline bool takes_blocks(int head_dim, bool tiles, bool one_piece, int64_t block
 // of 257 tokens 9.0 / 7.9), and where a request has more than WIDE_PARTS blocks (1 of 15000 15.6 / 13.5, 9000 13.9 / 10.8),
 // blocks would be faster too; shares are the way there that tests hold on to.
 constexpr int WIDE_PARTS = 16;
-inline bool wide_launch(int group, int64_t units, int n_req, int room) {      // room: CUs for each kv head
-  return group <= HEADS_PER_PASS && n_req <= room && units > 12 * (int64_t)room && units <= (int64_t)WIDE_UNITS * room;
-}
+inline bool wide_batch(int group, int n_req, int room) { return group <= HEADS_PER_PASS && n_req <= room; }   // room: CUs for each kv head
+inline bool wide_launch(int64_t units, int room) { return units > 12 * (int64_t)room && units <= (int64_t)WIDE_UNITS * room; }
 
 // resident waves of the partial-pass kernel per compute unit (occupancy query)
 int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk);
