@@ -1019,7 +1019,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   }
   std::memset(a.split_req, 0, sizeof(a.split_req));
   const bool single = ellm::single_waves(p->geom.group, block_units > 0, total * a.step_units, waves, n_req);
-  const int32_t merge_parts = single ? 0 : ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0);
+  const int32_t merge_parts = single ? 0 : ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0, tiles);
   a.wg_waves = block_units || single ? 1 : ellm::SHARE_WAVES;
   const int64_t parts = cut_shares(units, total, waves, &a, merge_parts);
   a.in_order_parts = block_units ? merge_parts : 0;

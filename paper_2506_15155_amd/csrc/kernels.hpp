@@ -153,9 +153,12 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 // 128, 4 q heads, 10 requests of 5400 to 16200 tokens (shares of 15 to 38 workgroups) 19.1 / 15.6, 8 heads of 64, 11 of 2100 to 6400
 // 15.6 / 12.0, 16 heads of 128, 11 of 6500 to 19400 36.9 / 30.8; 12 heads, 6 of 2000 to 9000 (8 to 36 blocks) 14.6 / 10.4.
 // us, added up by the last / by the pass, of launches in which all requests go one way:
-//  - Where shares are walked one wave reads them all, 16 KB in a round trip: up to 64 KB. 8 kv heads of 128, one request of
+//  - Where shares are walked one wave reads them all, in tiles 16 to 32 KB in a round trip: up to 64 KB. 8 kv heads of 128, one request of
 //    20000 to 100000 tokens (32 workgroups), 1 q head each (16 KB) 65.5 / 66.6, 4 (64 KB) 21.8 / 22.6, 8 (128 KB) 72.3 /
 //    70.2, 16 (256 KB) 81 / 70.8; 4 kv heads (64 workgroups), 4 q heads each (128 KB) 30.2 / 28.3, 8: 36.9 / 29.6.
+//    In units 16 KB of two heads in a round trip: up to 32 KB. 16-token chunks, 2 kv heads of 128, 8 q heads each, 9 of 10000 (56 KB) 21.3 /
+//    19.8, of 12486 (60 KB) 25.2 / 23.7, 14 of 12000 (40 KB) 32.4 / 31.8, 4 kv heads, 16 each, 12 of 6000 (48 KB) 31.3 / 30.4, 24 of 6000
+//    (32 KB) 52.4 / 53.8; heads of 64, 6 each, 4 of 12800 to 38300 (27 to 60 KB) 18.0 / 15.4, 8 each, 9 of 12000 (30 KB) 14.0 / 14.6.
 //  - The waves of a block take 64 columns each, 16 partials in a round trip: up to 192 KB. One request: 8 kv heads of 128, 31
 //    blocks of 4 q heads each (62 KB) 9.7 / 11.7, of 6 (93 KB) 10.1 / 11.9, of 8 (124 KB) 10.6 / 12.0, of 16 (248 KB) 12.9 / 12.4; 16
 //    blocks of 16 (128 KB) 9.8 / 11.6; 4 kv heads, 59 of 4 (118 KB) 11.1 / 12.1, of 8 (236 KB) 12.6 / 12.3; heads of 64, 31 of 16
@@ -164,10 +167,10 @@ inline bool tile_kernel(int head_dim, int group, int tokens_per_chunk) {
 //    end: up to 16 waves. us a call, in every launch / the pass: 4 kv heads of 64, 20 q heads each, 8 requests of
 //    2100 to 6400 tokens (16 to 48 waves) 25.1 / 21.7, of 128, 32 q heads, 14 of 1000 to 3100 (18 waves) 39.7 / 33.9, 128 of 300 to 600
 //    (2 or 3) 54.6 / 85.
-inline int merge_parts(int head_dim, int group, bool blocks) {
-  const int row = group * head_dim * 4;      // bytes of a partial result
+inline int merge_parts(int head_dim, int group, bool blocks, bool tiles) {
+  const int row = std::min(group, HEADS_PER_PASS) * head_dim * 4;      // bytes of a partial result in one launch
   if (blocks) return (192 << 10) / row;
-  return std::min((64 << 10) * SHARE_WAVES / row, group > HEADS_PER_PASS ? 4 * SHARE_WAVES : 1 << 30);
+  return std::min((tiles ? 64 << 10 : 32 << 10) * SHARE_WAVES / row, group > HEADS_PER_PASS ? 4 * SHARE_WAVES : 1 << 30);
 }
 // Such launches do without sums in the kernel where a wave has few units (more, where many requests end inside waves): a
 // workgroup is one wave, and every wave leaves a partial result of its own for one combine pass behind the last launch. us

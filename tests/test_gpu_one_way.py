@@ -11,9 +11,10 @@ from tests import gpu_harness as H
 DUMMY = 0x1000
 
 
-def line(dim, group, blocks):
+def line(dim, group, kernel):
     """Parts of a request that the attention kernel adds up at most, as the library's sources state it."""
-    return (192 << 10 if blocks else (64 << 10) * 4) // (group * dim * 4)
+    kb = {"decode_block_kernel": 192, "decode_tile_kernel": 64 * 4, "decode_unit_kernel": 32 * 4}[kernel]
+    return min((kb << 10) // (min(group, 16) * dim * 4), 16 if group > 16 else 1 << 30)
 
 
 def test_all_or_none_go_to_the_combine_pass():
@@ -34,10 +35,10 @@ def test_all_or_none_go_to_the_combine_pass():
             E.ellm_tensor_map_chunks(P, ids[-1], 0, s)
         E.ellm_kv_append(P, ids, DUMMY, DUMMY, np.asarray(lens, np.int32), stream=0)
         n_split, _ = E.ellm_decode_plan(P, ids)
-        blocks = E.ellm_debug_decode_kernel(P, ids) == "decode_block_kernel"
+        kernel = E.ellm_debug_decode_kernel(P, ids)
         got = E.ellm_debug_combined_requests(P, ids)
         E.ellm_pool_destroy(P)
-        over = bool(n_split.max() > line(dim, group, blocks))
+        over = bool(n_split.max() > line(dim, group, kernel))
         seen[over] += 1
         assert got == (int((n_split > 1).sum()) if over else 0), (lens, n_kv, group, dim)
     assert min(seen.values()) > 30
@@ -69,7 +70,7 @@ def load(n_kv, group, dim, tokens, lens, seed):
     ("decode_block_kernel", 1, 16, 64, 64)])
 def test_either_way(kernel, n_kv, group, dim, tokens, over):
     blocks = kernel == "decode_block_kernel"
-    most = line(dim, group, blocks) + over
+    most = line(dim, group, kernel) + over
     step = 256 if blocks else 64
     parts = [2, most, 1, 6, 4] if blocks else [1, 2, 3, 1, 4, most, 5, 2]
     lens = [step * n - (5 * i) % 11 for i, n in enumerate(parts)]
@@ -101,8 +102,8 @@ def test_either_way(kernel, n_kv, group, dim, tokens, over):
 @pytest.mark.gpu
 @pytest.mark.parametrize("group,dim,n_kv,split,most,combined", [
     (34, 64, 1, 64, 12, True), (20, 128, 3, 64, 9, True),          # a workgroup is one wave
-    (34, 64, 3, 128, 16, False), (20, 128, 1, 128, 16, False), (64, 128, 1, 128, 8, False),
-    (34, 64, 1, 128, 17, True), (17, 128, 3, 128, 17, True), (64, 128, 2, 128, 9, True),
+    (34, 64, 3, 128, 16, False), (20, 128, 1, 128, 16, False), (64, 128, 1, 128, 16, False),
+    (34, 64, 1, 128, 17, True), (17, 128, 3, 128, 17, True), (64, 128, 2, 128, 17, True),
     (34, 64, 2, 0, 0, True), (48, 128, 1, 0, 0, True)])             # single steps, as cut by the library
 def test_groups_of_several_launches(group, dim, n_kv, split, most, combined):
     """More q heads per kv head than one launch handles: few units a wave, with a partial result from each, and shares,

@@ -11,24 +11,25 @@ from tests import gpu_harness as H
 pytestmark = pytest.mark.gpu
 
 
-def merge_parts(dim, group, blocks):
+def merge_parts(dim, group, kernel):
     """The library's line between the two, as its sources state it."""
-    return (192 << 10 if blocks else (64 << 10) * 4) // (group * dim * 4)
+    kb = {"decode_block_kernel": 192, "decode_tile_kernel": 64 * 4, "decode_unit_kernel": 32 * 4}[kernel]
+    return min((kb << 10) // (min(group, 16) * dim * 4), 16 if group > 16 else 1 << 30)
 
 
 # n_kv: workgroups that begin in one kv head and end in the next (3, 5); waves that are no whole number of workgroups (1)
 @pytest.mark.parametrize("kernel,n_kv,group,dim,tokens,most", [
     ("decode_tile_kernel", 3, 1, 128, 128, 9), ("decode_tile_kernel", 1, 4, 128, 128, 129), ("decode_tile_kernel", 5, 4, 128, 64, 9),
-    ("decode_tile_kernel", 3, 8, 128, 128, 65), ("decode_tile_kernel", 1, 2, 64, 128, 9), ("decode_unit_kernel", 3, 16, 128, 48, 33),
-    ("decode_unit_kernel", 1, 6, 128, 24, 86), ("decode_unit_kernel", 5, 3, 64, 64, 9), ("decode_unit_kernel", 1, 34, 64, 64, 31),
+    ("decode_tile_kernel", 3, 8, 128, 128, 65), ("decode_tile_kernel", 1, 2, 64, 128, 9), ("decode_unit_kernel", 3, 16, 128, 48, 17),
+    ("decode_unit_kernel", 1, 6, 128, 24, 43), ("decode_unit_kernel", 5, 3, 64, 64, 9), ("decode_unit_kernel", 1, 34, 64, 64, 17),
     ("decode_block_kernel", 1, 4, 128, 128, 97), ("decode_block_kernel", 2, 8, 128, 128, 49), ("decode_block_kernel", 3, 16, 128, 48, 25),
     ("decode_block_kernel", 1, 6, 128, 64, 65), ("decode_block_kernel", 2, 16, 64, 64, 49)])
 def test_sums_of_shared_requests(kernel, n_kv, group, dim, tokens, most):
-    """Requests of 1 to 9 waves, in an order that puts their ends at every place in a workgroup, and of as many as are
-    added up without the combine pass, and one more. The oracle's output; the same bits from every replay of a graph, with
+    """Requests of 1 to 9 waves, in an order that puts their ends at every place in a workgroup, with or without one of
+    just too many to be added up without the combine pass, which then adds up all of them. The oracle's output; the same bits from every replay of a graph, with
     other batches decoded in between (counters that did not go back to 0 would give the sums to the wrong workgroup)."""
     blocks = kernel == "decode_block_kernel"
-    line = merge_parts(dim, group, blocks)
+    line = merge_parts(dim, group, kernel)
     at_line = most == line + 1
     assert at_line or most == 9 and line > 9
     step = 256 if blocks else 64
@@ -54,6 +55,7 @@ def test_sums_of_shared_requests(kernel, n_kv, group, dim, tokens, most):
     if dim == 128 and tokens in (64, 128):
         assert list(n_split) == parts
     assert not at_line or (n_split.max() > line and (n_split > 1).sum() > (n_split > line).sum())
+    assert E.ellm_debug_combined_requests(B.pool, ids) == ((n_split > 1).sum() if at_line or group > 16 else 0)
     q = bits(len(lens), cfg.n_q_heads, dim)
     rc, want = B.decode(ids, q)
     rco, ref = B.orc.decode(ids, q)
