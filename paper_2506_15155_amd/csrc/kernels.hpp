@@ -76,10 +76,8 @@ struct BatchArgsOf {
                               // waves of several shares, a request uses no more than it spans workgroups)
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
-  int32_t wg_waves;           // waves of a workgroup that each have a share of their own (SHARE_WAVES), or 1
   int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last;
                               // 0 where any request has more than merge_parts()
-  int32_t in_order_parts;     // requests of up to so many partials the combine pass adds up in that kernel's order
   int32_t n_split_req;        // requests with more: the combine pass runs for these only
   // request that holds the first unit of wave w of a kv head, one byte each: lets a wave find its
   // request with one scalar load instead of a search through the prefix entries
@@ -94,6 +92,9 @@ struct BatchArgsOf {
     int32_t n_part;           // waves that hold units of this request
     int32_t part0;            // first partial slot of the request within a kv head's slots (split requests)
   } req[REQS];
+  // for the combine pass:
+  int32_t wg_waves;           // waves of a workgroup that each have a share of their own (SHARE_WAVES), or 1
+  int32_t in_order_parts;     // requests of up to so many partials are added up in the attention kernel's order
 };
 using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ, MAX_WAVE_REQ>;
 // what a launch in blocks of few requests hands to its kernel instead: the host writes the arguments to device memory for
