@@ -16,7 +16,12 @@ pytestmark = pytest.mark.gpu
     (4, 1, 128, 512, [16 * 17 * 3 - 1], 3, 17), (8, 2, 128, 512, [400, 17, 900, 630], 9, 19),
     (4, 1, 128, 512, [16 * 17 * 2 - 15], 2, 17), (6, 1, 128, 512, [1000, 337, 300], 5, 22), (1, 1, 128, 40, [1500, 1, 700], 7, 29),
     (16, 1, 128, 64, [512 * 3 - 1, 510], 4, 32), (8, 1, 128, 24, [700, 800, 12], 6, 30), (3, 3, 64, 16, [500, 500, 1], 4, 32),
-    (4, 1, 64, 512, [512 * 4 - 1, 496], 5, 32), (16, 1, 64, 64, [900, 2000, 100], 8, 29), (32, 8, 128, 512, [3000, 900], 9, 29)])
+    (4, 1, 64, 512, [512 * 4 - 1, 496], 5, 32), (16, 1, 64, 64, [900, 2000, 100], 8, 29), (32, 8, 128, 512, [3000, 900], 9, 29),
+    # as many requests, and blocks per kv head, as the small argument table takes, and one more of either
+    (4, 1, 128, 512, [272] * 16, 20, 17), (4, 1, 128, 512, [272] * 17, 21, 17), (12, 2, 64, 64, [270] * 16, 18, 17), (12, 2, 64, 64, [270] * 17, 19, 17),
+    (4, 1, 128, 512, [5120, 5119, 5111, 5105], 64, 20), (4, 1, 128, 512, [4160, 4159, 4151, 4145, 4160], 65, 20),
+    (16, 1, 64, 64, [5120, 5119, 5111, 5105], 64, 20), (16, 1, 64, 64, [4160, 4159, 4151, 4145, 4160], 65, 20),
+    (6, 3, 128, 128, [400, 420, 350, 117] * 10, 64, 22), (32, 8, 64, 512, [350] * 30, 32, 22)])
 def test_wide_blocks(pool_mode, n_q, n_kv, dim, tokens, lens, room, units):
     n = len(lens)
     need = [-(-(x + 1) // tokens) for x in lens]

@@ -21,10 +21,10 @@ def expected(units, n_kv, cus):
 
 def test_wide_blocks_of_random_batches():
     rng = np.random.default_rng(4)
-    wide = 0
-    for _ in range(400):
+    wide = many = 0
+    for _ in range(600):
         n_kv, group, dim = int(rng.choice([1, 2, 5, 8])), int(rng.choice([1, 3, 4, 8, 16])), int(rng.choice([64, 128]))
-        tokens, cus, n = int(rng.choice([16, 24, 102, 512])), int(rng.choice([8, 17, 64, 256])), int(rng.integers(1, 12))
+        tokens, cus, n = int(rng.choice([16, 24, 102, 512])), int(rng.choice([8, 17, 64, 256])), int(rng.integers(1, 12) if rng.random() < 0.6 else rng.integers(12, 60))
         room = cus // n_kv
         if room == 0:
             continue
@@ -52,7 +52,8 @@ def test_wide_blocks_of_random_batches():
             assert kernel != "decode_block_kernel", (lens, n_kv, cus)
             continue
         wide += 1
+        many += len(lens) > 16 or int(n_split.sum()) > 64      # more than the small argument table takes
         assert 16 < b <= 32 and kernel == "decode_block_kernel"
         assert list(n_split) == [-(-u // b) for u in units] and most == -(-b // 4) * 64
         assert n_kv * int(n_split.sum()) <= cus
-    assert wide > 60
+    assert wide > 60 and many > 10
