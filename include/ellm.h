@@ -158,9 +158,9 @@ int ellm_pool_destroy(ellm_pool* pool);
 /* Bytes of device workspace a pool of this geometry allocates for the partial results of split
  * decode attention (Sec. 5 "Efficient Kernels": the sequence is split and partial softmax results
  * are combined), for batches of up to max_batch requests: a decode launch covers at most 128
- * requests and runs one wave per SIMD of the GPU; every wave writes at most one partial result per
- * request its share touches, so a launch needs at most SIMDs + n_kv_heads * (min(max_batch, 128) - 1)
- * partial slots of G * (head_dim + 2) floats, and the launches of one call reuse the same slots.
+ * requests and runs one wave per SIMD of the GPU; every wave has room for one partial result per
+ * request its share touches (most workgroups write one for all their waves), so a launch takes at most
+ * SIMDs + n_kv_heads * (min(max_batch, 128) - 1) partial slots of G * (head_dim + 2) floats, and the launches of one call reuse the same slots.
  * Uses the current HIP device's SIMD count (a nominal 1024 without a device). Only the head
  * counts and head_dim of desc are read. 0 for a bad argument. */
 uint64_t ellm_workspace_bytes(const ellm_pool_desc* desc, int32_t max_batch);
@@ -299,7 +299,7 @@ int ellm_kv_append(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, co
  *   For q head h, kv head g = h / G:  s_t = scale * <q_h, K_t,g>,  w = softmax_t(s),
  *   out_h = sum_t w_t * V_t,g  for t = 0 .. len-1, no mask. scale = 0 selects 1/sqrt(head_dim).
  *   fp32 accumulation (softmax weights are rounded to bf16 before they multiply V and before they
- *   are summed), output rounded to nearest-even bf16. Split over the sequence with a partition
+ *   are summed, or, in some kernels, multiply V as two bf16 values), output rounded to nearest-even bf16. Split over the sequence with a partition
  *   that depends only on the lengths in the batch, the pool geometry and the device's wave
  *   capacity, never on physical chunk ids, so results are bitwise reproducible and invariant
  *   under remapping.

@@ -227,10 +227,12 @@ int32_t device_simds() {
   return 256 * ellm::SIMDS_PER_CU;
 }
 
-// Partial slots one decode launch can need under the automatic partition: every wave writes one
-// partial, and one more for every request boundary inside its share; the waves of all kv heads
+// Partial slots one decode launch can reserve under the automatic partition: one for every wave, and one
+// more for every request boundary inside its share; the waves of all kv heads
 // together are at most one per SIMD, and each kv head's sequence has n_req - 1 inner boundaries. (A launch
-// that is cut in blocks has at most one partial per compute unit.)
+// that is cut in blocks has at most one partial per compute unit. Where workgroups are four waves with shares they
+// write one partial for all four, so up to three quarters of the reserved slots stay unused: the bound is the
+// documented one, and the cut that has to fit the fixed workspace counts the same way.)
 int64_t launch_slot_bound(int32_t simds, int32_t n_kv_heads, int32_t n_req) {
   return (int64_t)simds + (int64_t)n_kv_heads * (std::max(n_req, 1) - 1);
 }

@@ -300,7 +300,7 @@ __device__ __forceinline__ uint32_t touch_arguments(int lane) {
 // the value is of no use; its register is free from here on
 __device__ __forceinline__ void touched(uint32_t v) { asm volatile("" :: "v"(v)); }
 
-// what a workgroup (one wave) handles: kv head g, wave w of that head, n_units steps of the head's
+// what a wave (in blocks: a workgroup) handles: kv head g, wave w of that head, n_units steps of the head's
 // sequence from step u_lo on, the first of which belongs to request b. A step is a unit (a tile in the
 // kernel that walks tiles) or, where every wave gets one step, up to step_units units of one request
 struct Share { int32_t g, w, u_lo, n_units, b; };
@@ -1007,7 +1007,7 @@ __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_e
 //      transposed in registers by v_perm_b32, one product per e = dim % E; B = the weights.
 //      Register i of product e in lane (g, c) is dim E (4 g + i) + e of head c: every per-head quantity
 //      (m, l, the rescaling) sits in the lanes that need it, and a lane ends with 4 E consecutive dims.
-// Nothing goes through LDS (NW == 0; the waves of a block add up there). The cost per byte does not depend on the number of q heads up to 16, so every
+// K, V and the weights do not go through LDS (results that several waves share do). The cost per byte does not depend on the number of q heads up to 16, so every
 // group size up to that is one pass over K and V. Bound by HBM: 48 requests of 6 q heads per kv head (278 MB
 // of K and V) 92.4 -> 51.8 us with a combine pass (the tile kernels read K and V twice), 64 requests of 16
 // heads of 64 (398 MB) 144 -> 69.8, 16-token chunks (187 MB) 50.8 -> 36.4.

@@ -51,7 +51,8 @@ struct PoolView {
 // normalises and writes the output row itself. The others ("split" requests) are added up: SHARE_WAVES neighbouring
 // waves are a workgroup, whose results of a request meet in LDS; a request that reaches into several workgroups gets one
 // partial result from each, part0 + j from the j-th, and the workgroup that ends last, or the combine pass where there
-// are many, adds those up (merge_parts()).
+// are many, adds those up (merge_parts()). Short launches of more than HEADS_PER_PASS heads have workgroups of one wave, and a
+// partial result from each (single_waves()).
 // A launch that fills the GPU has one wave for every SIMD of it (a second wave on a SIMD is served markedly
 // worse than the first and slows both down): all are resident at once and have the same amount to
 // read, so none waits for a slot and none is left over at the end. The cut is fixed by the plan,
@@ -98,7 +99,7 @@ struct BatchArgsOf {
 };
 using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ, MAX_WAVE_REQ>;
 // what a launch in blocks of few requests hands to its kernel instead: the host writes the arguments to device memory for
-// each launch; 0.6 KB instead of 4 take it 0.4 us less (4 requests of up to 256 tokens 7.67 -> 7.37 us a call)
+// each launch; with 0.6 KB instead of 4 a call of 4 requests of up to 256 tokens takes 7.37 us instead of 7.67
 using FewArgs = BatchArgsOf<16, 64>;
 
 struct AppendArgs {
@@ -189,20 +190,20 @@ inline bool single_waves(int group, bool blocks, int64_t units, int64_t waves, i
 inline bool small_launch(int group, int64_t blocks, int n_req, int n_kv, int cus) {
   return group <= HEADS_PER_PASS && blocks * n_kv <= cus * (blocks > n_req ? 1 : 2);
 }
-// Which of the two; tiles: the pool's shares are cut in tiles; one_piece: no request has more than one tile. 256 CUs,
-// us a call, blocks / steps / shares of tiles (these with the one-wave combine pass they had then):
-//  - Requests of one block each that steps would split: the combine launch is saved. 8 requests of 200 tokens, 8 kv
-//    heads of 128, 4 q heads each 5.2 / 7.9 / 8.0, 64 of 200 12.4 / 14.4 / 14.3; 1 q head 5.1 / 7.8 / 7.4, 64 of 80
-//    8.3 / - / 9.3, of 128 (two full tiles) 10.2 / 9.8 / 9.9, of 200 12.1 / 13.0 / 13.2.
+// Which of the two; tiles: the pool's shares are cut in tiles; one_piece: no request has more than one tile. The lines were
+// drawn when every split request was followed by a combine launch, which blocks of whole requests saved and fewer partial
+// results made shorter; those below 12 blocks (3000 tokens) per request went by steps, unless almost every CU got a block. 256
+// CUs, 8 kv heads of 128, us a call of the present kernels in a replayed graph, blocks / steps / shares of tiles:
+//  - Requests of one block each: 8 of 200 tokens, 4 q heads each 4.8 / 5.9 / 6.0, 64 of 200 12.1 / 12.3 / 10.5; 1 q head 5.2 / 5.7 / 5.0,
+//    64 of 80 7.8 / 6.1 / 6.1, of 128 (two full tiles) 10.2 / 7.7 / 7.9, of 200 12.0 / 11.6 / 9.7.
 //  - Requests that one wave handles: a workgroup whose other waves have nothing to do takes longer to start where a
-//    CU gets two of them. 1 q head of 128: 8 of 64 tokens 4.0 / 4.7 / 4.2, 32 of 64 4.2 / 4.8 / 4.5, 64 of 64 7.7 / 5.2 /
-//    5.4; 4 q heads: 4.1 / 4.7 / 6.1, 4.3 / 4.8 / 6.1, 7.8 / 5.2 / 7.9. Heads of 64: 64 of 64 4.4 / 4.9 / 4.7.
-//  - Split requests: the combine pass follows either way, and the blocks' kernel takes longer; fewer partial results pay
-//    for that from 12 blocks (3000 tokens) per request on, or where almost every CU gets a block. Heads of 128, 8 kv
-//    heads, 4 q heads each: 1 of 512 tokens 8.8 / 8.3 / 8.2, 8 of 300 9.7 / 8.8 / 8.8, 1 of 1500 9.7 / 8.9 / 9.3, 3000 10.0 /
-//    9.9 / 12.6, 8000 10.9 / 12.2 / 20.6, 16 of 512 10.2 / 11.0 / 10.9; 1 q head: 1 of 512 8.6 / 8.3 / 7.5, 8 of 300
-//    9.4 / 8.7 / 7.5, 1 of 1500 9.1 / 8.5 / 8.5, 3000 9.8 / 9.6 / 11.0 (tiles are the faster way for short requests of
-//    one head; their weights are rounded to one bf16 value). Heads of 64: 1 of 512 7.6 / 7.6 / 7.4, 8000 8.6 / 10.8 / 16.
+//    CU gets two of them. 1 q head: 8 of 64 tokens 3.6 / 4.7 / 4.3, 32 of 64 3.9 / 5.2 / 5.0, 64 of 64 7.1 / 5.1 / 4.8; 4 q heads: 3.7 /
+//    4.9 / 5.9, 3.9 / 5.3 / 6.6, 7.1 / 5.3 / 6.4. Heads of 64: 64 of 64 3.8 / 4.5 / 3.9.
+//  - Split requests: 4 q heads: 1 of 512 tokens 6.5 / 7.2 / 7.2, 8 of 300 7.4 / 8.1 / 8.5, 1 of 1500 7.3 / 8.0 / 9.0, 3000 7.9 / 9.0 / 9.4, 8000
+//    9.2 / 10.7 / 11.6, 16 of 512 8.6 / 8.9 / 9.8; 1 q head: 1 of 512 6.4 / 7.1 / 6.0, 8 of 300 7.3 / 7.7 / 7.1, 1 of 1500 7.3 / 7.8 / 7.5, 3000
+//    7.9 / 8.9 / 7.9 (tiles are as fast for requests of one head; their weights are rounded to one bf16 value). Heads of 64:
+//    1 of 512 5.5 / 6.6 / 5.2, 8000 7.4 / 10.3 / 8.3.
+// So blocks would be the faster way for all split requests of 4 heads, and no longer are for 64 requests of two or more tiles.
 // Pools whose shares are cut in units always take blocks, which leaves a request's result independent of its neighbours.
 inline bool takes_blocks(int head_dim, bool tiles, bool one_piece, int64_t blocks, int n_req, int n_kv, int cus) {
   const int64_t workgroups = blocks * n_kv;
@@ -219,7 +220,7 @@ inline bool takes_blocks(int head_dim, bool tiles, bool one_piece, int64_t block
 // 1500 to 2000 14.3 / 12.7. Heads of 64, 4 q heads, 8 of 1500 to 2000 10.4 / 8.8, 1 q head 9.5 / 8.9; twice as many units a
 // wave are no gain there (16 of 1500 to 2000, 4 q heads 14.2 / 13.5, 1 q head 12.6 / 13.7). Up to 12 units for every CU (17
 // of 257 tokens 9.0 / 7.9), and where a request has more than WIDE_PARTS blocks (1 of 15000 15.6 / 13.5, 9000 13.9 / 10.8),
-// blocks would be faster too; shares are the way there that tests hold on to.
+// blocks would be faster too: these two lines are not drawn by the figures but stand where tests/test_host_logic.py has shares.
 constexpr int WIDE_PARTS = 16;
 inline bool wide_batch(int group, int n_req, int room) { return group <= HEADS_PER_PASS && n_req <= room; }   // room: CUs for each kv head
 inline bool wide_launch(int64_t units, int room) { return units > 12 * (int64_t)room && units <= (int64_t)WIDE_UNITS * room; }
