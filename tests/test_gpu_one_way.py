@@ -45,7 +45,7 @@ def test_all_or_none_go_to_the_combine_pass():
 
 
 def load(n_kv, group, dim, tokens, lens, seed):
-    need = [-(-n // tokens) for n in lens]
+    need = [-(-(n + 1) // tokens) for n in lens]
     cfg = W.Config("o", 9, len(lens), n_kv * group, n_kv, dim, tokens * 4 * n_kv * dim, sum(need) + 2, max(need) * tokens, "uniform", 1, max(lens))
     rng = np.random.default_rng(seed)
     B = H.Both(cfg)
@@ -55,7 +55,7 @@ def load(n_kv, group, dim, tokens, lens, seed):
 
     ids = []
     for n, s in zip(lens, need):
-        ids.append(B.create(n))
+        ids.append(B.create(n + 1))
         assert B.map(ids[-1], 0, s) == 0
     assert B.append(ids, bits(sum(lens), n_kv, dim), bits(sum(lens), n_kv, dim), lens) == 0
     return B, ids, bits(len(lens), n_kv * group, dim)
@@ -105,9 +105,9 @@ def test_either_way(kernel, n_kv, group, dim, tokens, over):
     (34, 64, 3, 128, 16, False), (20, 128, 1, 128, 16, False), (64, 128, 1, 128, 16, False),
     (34, 64, 1, 128, 17, True), (17, 128, 3, 128, 17, True), (64, 128, 2, 128, 17, True),
     (34, 64, 2, 0, 0, True), (48, 128, 1, 0, 0, True)])             # single steps, as cut by the library
-def test_groups_of_several_launches(group, dim, n_kv, split, most, combined):
+def test_groups_of_several_launches(pool_mode, group, dim, n_kv, split, most, combined):
     """More q heads per kv head than one launch handles: few units a wave, with a partial result from each, and shares,
-    added up in every launch or by the pass; the same bits from replays of a graph with another batch behind."""
+    added up in every launch or by the pass; the same bits from replays of a graph with another batch behind; the fused call gives the bits of the separate ones."""
     parts = [1, 2, most, 3, 1, 5, most - 1, 2] if split else [1, 3, 2, 5, 9, 30]
     per = split or 64
     lens = [per * n - (7 * i) % 13 for i, n in enumerate(parts)]
@@ -134,4 +134,11 @@ def test_groups_of_several_launches(group, dim, n_kv, split, most, combined):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(got, out)
+    rng = np.random.default_rng(6)
+    k, v = ((rng.standard_normal((len(lens), n_kv, dim)).astype(np.float32).view(np.uint32) >> 16).astype(np.uint16) for _ in range(2))
+    rc, fused, ref = B.append_decode(ids, k, v, q)
+    assert rc == 0
+    H.check_close(fused, ref, "append + decode")
+    rc, again = B.decode(ids, q)
+    assert rc == 0 and torch.equal(fused, again)
     B.close()
