@@ -513,14 +513,16 @@ def test_migration_leaves_a_capture_of_another_stream_alone(busy):
     """Offload and fetch are accepted while another stream is being captured (in the mode that counts every
     thread's calls), and that graph is whole afterwards."""
     B, t, q, want = small_pool()
-    side, x, work = torch.cuda.Stream(), torch.zeros(1 << 10, device="cuda"), torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")
+    # (two streams in a row: torch hands its 32 out in turn, so one that it made earlier by itself may be `side`)
+    side, captured = torch.cuda.Stream(), torch.cuda.Stream()
+    x, work = torch.zeros(1 << 10, device="cuda"), torch.zeros(1 << 29, dtype=torch.uint8, device="cuda")
     torch.cuda.synchronize()
     with torch.cuda.stream(side):
         for _ in range(20 if busy else 0):
             work.add_(1)
     E.ellm_decode_attention(B.pool, [t], q, torch.empty_like(q), stream=side)
     graph = torch.cuda.CUDAGraph()
-    with torch.cuda.graph(graph, capture_error_mode="global"):
+    with torch.cuda.graph(graph, stream=captured, capture_error_mode="global"):
         x.add_(1)
         assert B.offload(t, 0, 2) == 0 and B.offload(t, 2, 2) == 0 and B.fetch(t, 0, 4) == 0
         x.add_(1)
