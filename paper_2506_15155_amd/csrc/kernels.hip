@@ -1331,7 +1331,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
         if (g16 == 0) ml[wave][c] = make_float2(m, L);
       }
     } else if (lane < n_heads) {
-      ml[wave][lane] = make_float2(NEG_BIG, 0.f);      // nothing left for this wave: weight 0, its row is not read
+      ml[wave][lane] = make_float2(-INFINITY, 0.f);    // nothing left for this wave: its row is not read
     }
     __syncthreads();
     // Every wave takes 64 columns (pieces of the heads' rows in order), in all blocks of a request the same ones, which need
@@ -1348,7 +1348,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
 #pragma unroll
       for (int w = 0; w < NW; w++) {
         const float2 p = ml[w][h];
-        if (p.x == NEG_BIG && p.y == 0.f) continue;
+        if (p.x < NEG_BIG) continue;                   // (a sum of 0 is not nothing: scores of -inf, beside which an infinite V is NaN)
         add(s, p.y, *reinterpret_cast<const float4*>(&sums[w][h][f * 4]), fast_exp2(p.x - s.M));
       }
       if (part < 0) write_out<D>(pv, out, a, cb, g, g_first, x, s);

@@ -53,3 +53,39 @@ def test_wide_blocks(pool_mode, n_q, n_kv, dim, tokens, lens, room, units):
     rc, again = B.decode(ids, q)
     assert rc == 0 and torch.equal(fused, again)
     B.close()
+
+
+@pytest.mark.parametrize("n_q,n_kv,dim,tokens,lens,kernel", [
+    (32, 8, 128, 512, [3500, 3400, 3300, 3600], "decode_block_kernel"), (12, 1, 128, 64, [6000, 900], "decode_block_kernel"),
+    (8, 2, 64, 64, [3000, 40], "decode_block_kernel"), (32, 8, 128, 512, [1500, 2500, 800] * 16, "decode_tile_kernel"),
+    (12, 2, 64, 64, [9000, 900] * 30, "decode_unit_kernel")])
+def test_infinite_v_beside_scores_of_minus_infinity(n_q, n_kv, dim, tokens, lens, kernel):
+    """The first tokens of a request have scores of -inf only, whole waves of them, and one an infinite V: 0 * inf, as the
+    softmax has it, in the column it stands in and nowhere else."""
+    n, need = len(lens), [-(-x // tokens) for x in lens]
+    cb = tokens * 4 * n_kv * dim
+    dev = torch.zeros((sum(need) + 1) * cb, dtype=torch.uint8, device="cuda")
+    P = E.ellm_pool_create(dev, None, cb, n_q, n_kv, dim, n, max(need))
+    ids = []
+    for s in need:
+        ids.append(E.ellm_tensor_create(P, s * tokens))
+        E.ellm_tensor_map_chunks(P, ids[-1], 0, s)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q = torch.randn(n, n_q, dim, device="cuda", generator=g).to(torch.bfloat16)
+    k, v = (torch.randn(sum(lens), n_kv, dim, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    q[0] = q[0].abs() + 0.1
+    k[:700] = -float("inf")
+    v[300, 0, 1] = float("inf")
+    E.ellm_kv_append(P, ids, k, v, np.asarray(lens, np.int32))
+    assert E.ellm_debug_decode_kernel(P, ids) == kernel
+    out = torch.empty_like(q)
+    E.ellm_decode_attention(P, ids, q, out)
+    want = torch.zeros(n_q, dim, dtype=torch.bool, device="cuda")
+    want[:n_q // n_kv, 1] = True
+    assert torch.equal(out[0].isnan(), want) and out[1:].isfinite().all()
+    kk, vv = k[700:lens[0]].double(), v[700:lens[0]].double()
+    for h in range(n_q):
+        w = torch.softmax((kk[:, h // (n_q // n_kv)] * q[0, h].double()).sum(-1) / dim ** 0.5, 0)
+        ref = (w[:, None] * vv[:, h // (n_q // n_kv)]).sum(0)
+        assert (out[0, h].double() - ref)[~want[h]].abs().max() <= H.MAX_ABS
+    E.ellm_pool_destroy(P)
