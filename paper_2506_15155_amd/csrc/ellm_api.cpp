@@ -242,14 +242,17 @@ size_t slot_bytes(int32_t group, int32_t head_dim) { return (size_t)group * (hea
 int ensure_device(ellm_pool* p) {
   if (p->dev_ready) return ELLM_OK;
   // the table mirror and, behind it, the two sets of counters of partial results, all 0
-  std::vector<int32_t> image = p->core->table();
-  const size_t counters_at = (image.size() + 63) / 64 * 64;
-  const int32_t lines = std::max(p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
-  p->merged_words = (size_t)lines * ellm::MERGE_STRIDE;
-  image.resize(counters_at + 2 * p->merged_words, 0);
-  HIP_TRY(hipMalloc((void**)&p->d_table, image.size() * sizeof(int32_t)), "hipMalloc(table mirror)");
-  HIP_TRY(hipMemcpy(p->d_table, image.data(), image.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
+  const std::vector<int32_t>& table = p->core->table();
+  const size_t counters_at = (table.size() + 63) / 64 * 64;
+  const size_t lines = std::max((size_t)p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, (size_t)device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
+  p->merged_words = lines * ellm::MERGE_STRIDE;
+  HIP_TRY(hipMalloc((void**)&p->d_table, (counters_at + 2 * p->merged_words) * sizeof(int32_t)), "hipMalloc(table mirror)");
+  HIP_TRY(hipMemcpy(p->d_table, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   p->d_merged = (uint32_t*)p->d_table + counters_at;
+  const std::vector<uint32_t> zeros(std::min<size_t>(2 * p->merged_words, 1 << 18), 0);
+  for (size_t i = 0; i < 2 * p->merged_words; i += zeros.size())
+    HIP_TRY(hipMemcpy(p->d_merged + i, zeros.data(), std::min(zeros.size(), 2 * p->merged_words - i) * sizeof(uint32_t), hipMemcpyHostToDevice),
+            "hipMemcpy(counters)");
   (void)p->core->take_dirty();   // the full upload covers everything so far
   // the workspace is sized once, for the largest launch the automatic partition can produce
   p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::MAX_LAUNCH_REQ));
