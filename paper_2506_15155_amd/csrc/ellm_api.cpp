@@ -247,12 +247,11 @@ int ensure_device(ellm_pool* p) {
   const size_t lines = std::max((size_t)p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, (size_t)device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
   p->merged_words = lines * ellm::MERGE_STRIDE;
   HIP_TRY(hipMalloc((void**)&p->d_table, (counters_at + 2 * p->merged_words) * sizeof(int32_t)), "hipMalloc(table mirror)");
-  HIP_TRY(hipMemcpy(p->d_table, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   p->d_merged = (uint32_t*)p->d_table + counters_at;
-  const std::vector<uint32_t> zeros(std::min<size_t>(2 * p->merged_words, 1 << 18), 0);
-  for (size_t i = 0; i < 2 * p->merged_words; i += zeros.size())
-    HIP_TRY(hipMemcpy(p->d_merged + i, zeros.data(), std::min(zeros.size(), 2 * p->merged_words - i) * sizeof(uint32_t), hipMemcpyHostToDevice),
-            "hipMemcpy(counters)");
+  // the counters by a kernel on the default stream, which the copy of the table comes after and the host waits for
+  const int e = ellm::launch_fill(p->d_merged, 0, 2 * p->merged_words, nullptr);
+  if (e) return hip_err((hipError_t)e, "counter fill launch");
+  HIP_TRY(hipMemcpy(p->d_table, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   (void)p->core->take_dirty();   // the full upload covers everything so far
   // the workspace is sized once, for the largest launch the automatic partition can produce
   p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::MAX_LAUNCH_REQ));
