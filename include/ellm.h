@@ -30,7 +30,8 @@
  * call that works in several launches (more than 128 requests) has then done the work of the
  * launches before it, completely, and nothing of the rest (see ellm_kv_append).
  *
- * Device memory of the library: the mirror of the chunk tables and the workspace for partial
+ * Device memory of the library: the mirror of the chunk tables (behind it the counters of partial
+ * results, see ellm_decode_attention) and the workspace for partial
  * attention results, both allocated once by the first call that needs the device (or by
  * ellm_pool_prepare) and freed by ellm_pool_destroy; ellm_workspace_bytes tells the size of the
  * second. After that first call ellm_kv_append, ellm_decode_attention and ellm_kv_append_decode
