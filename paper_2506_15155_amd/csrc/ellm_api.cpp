@@ -212,6 +212,9 @@ ellm::PoolView view_of(const ellm_pool* p, bool fixed_ws = false) {
   v.n_kv_heads = p->geom.n_kv_heads;
   v.head_dim = p->geom.head_dim;
   v.group = p->geom.group;
+  v.by_chunk = ellm::divisor(v.tokens_per_chunk);
+  v.by_tiles = ellm::divisor(v.tiles_per_chunk);
+  v.by_units = ellm::divisor(v.units_per_chunk);
   return v;
 }
 
@@ -1033,16 +1036,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   a.waves_per_head = (int32_t)std::min<int64_t>(waves, 0x7fffffff);
   a.parts_per_head = (int32_t)std::min<int64_t>(parts, 0x7fffffff);
   a.ws_slots = (int32_t)std::min<int64_t>(parts * n_kv, 0x7fffffff);
-  a.use_wave_req = waves <= ellm::MAX_WAVE_REQ ? 1 : 0;
-  if (a.use_wave_req) {
-    std::memset(a.wave_req, 0, sizeof(a.wave_req));
-    int32_t i = 0;
-    for (int64_t w = 0; w < waves; w++) {
-      const int64_t lo = w * a.units_each + std::min<int64_t>(w, a.units_extra);
-      while (a.req[i].unit_prefix + (int64_t)units[i] <= lo) i++;
-      a.wave_req[w >> 2] |= (uint32_t)i << ((w & 3) * 8);
-    }
-  }
+  a.by_waves = ellm::divisor(a.waves_per_head);
   p->plan_total_units = total;
   p->plan_waves = waves;
   p->plan_slots = parts * n_kv;

@@ -266,59 +266,67 @@ __global__ __launch_bounds__(256) void chunk_copy_kernel(char* __restrict__ pool
 // work partition shared by the partial pass, the combine pass and the calibration kernel
 // ---------------------------------------------------------------------------------------------
 // number of units (tiles) of a sequence of len tokens (neither straddles a chunk)
-__device__ __forceinline__ int32_t units_of(int32_t len, int32_t Tc, int32_t units_per_chunk, int32_t unit_tokens = UNIT_TOKENS) {
-  const int32_t full = len / Tc, rest = len - full * Tc;
+__device__ __forceinline__ int32_t units_of(int32_t len, const PoolView& pv, int32_t units_per_chunk, int32_t unit_tokens = UNIT_TOKENS) {
+  const int32_t Tc = pv.tokens_per_chunk, full = divide(len, pv.by_chunk), rest = len - full * Tc;
   return full * units_per_chunk + (rest + unit_tokens - 1) / unit_tokens;
 }
 
-// request whose units include unit number pos of a kv head's sequence: the last b with
-// unit_prefix[b] <= pos (wave-uniform result)
-template <class Args>
-__device__ __forceinline__ int find_request(const Args& a, int pos, int lane) {
-  int cnt = 0;
-  for (int base = 0; base < a.n_req; base += 64) {
-    const int i = base + lane;
-    const bool below = i < a.n_req && a.req[i].unit_prefix <= pos;
-    cnt += __popcll(__ballot(below));
-  }
-  return __builtin_amdgcn_readfirstlane(cnt - 1);
+// Kernel arguments that a wave needs early. Named in one place, they are asked for together when it starts; left to
+// itself the compiler puts loads of them behind waits for other loads and behind branches, and no cache holds them yet.
+// (eight to an asm statement: across such statements loads are not made into wider ones)
+template <class A, class B, class C, class D, class E, class F, class G, class H>
+__device__ __forceinline__ void wanted(A a, B b, C c, D d, E e, F f, G g, H h) {
+  asm volatile("" :: "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h));
 }
 
-// The launch's arguments are 4 KB that no cache holds yet, and a wave goes through them in three dependent steps (header,
-// which request, its record). The first wave of a workgroup asks for every line of them at once, so that the later
-// steps find theirs in the L2. Wide blocks 57.2 -> 56.0 us for 8 requests, 4 layers, one request by blocks 8.79 -> 8.67, shares
-// of units 34.04 -> 33.63 (chunks of 16 tokens) and 49.06 -> 48.68 (6 q heads per kv head); the tile kernel was slower with it
-// (2000 -> 2014 a step of 32 layers).
+// The records of a launch's requests, spread over the lanes of a wave: lane l has those of requests l, l + 64, .. Where a
+// wave begins used to be found in three dependent steps (header, a table of the waves' requests, the record), about a third
+// of a microsecond each from the L2 and more from memory, which no cache holds the arguments of. Now all records are asked for
+// at once, together with the header, when the wave starts. One request of 3300 tokens 8.25 -> 7.99 us a call, 8 requests, 4
+// layers 52.3 -> 51.6, four short ones 7.38 -> 7.11; shares no different (8B-shaped step 1992, 1994).
 template <class Args>
-__device__ __forceinline__ uint32_t touch_arguments(int lane) {
-  constexpr uint32_t BYTES = sizeof(PoolView) + sizeof(Args);           // of every attention kernel, and some pointers
-  static_assert(BYTES <= 64 * 64, "one line per lane");
-  const auto* at = (const __attribute__((address_space(1))) char*)(uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-  const uint32_t line = (uint32_t)lane * 64u;
-  return *(const __attribute__((address_space(1))) uint32_t*)(at + (line < BYTES ? line : 0u));
-}
-// the value is of no use; its register is free from here on
-__device__ __forceinline__ void touched(uint32_t v) { asm volatile("" :: "v"(v)); }
+struct Records {
+  static constexpr int N = (Args::MAX_REQ + 63) / 64;
+  typename Args::Req rec[N];
+  __device__ __forceinline__ Records(const Args& a, int lane) {
+#pragma unroll
+    for (int k = 0; k < N; k++) rec[k] = a.req[min(64 * k + lane, Args::MAX_REQ - 1)];
+  }
+  // request whose units include unit number pos of a kv head's sequence: the last b with unit_prefix[b] <= pos
+  __device__ __forceinline__ int32_t find(int32_t n_req, int32_t pos, int lane) const {
+    int32_t cnt = 0;
+#pragma unroll
+    for (int k = 0; k < N; k++) cnt += __popcll(__builtin_amdgcn_ballot_w64(64 * k + lane < n_req && rec[k].unit_prefix <= pos));
+    return cnt - 1;
+  }
+  __device__ __forceinline__ typename Args::Req of(int32_t b) const {      // b: the same in all lanes
+    auto get = [&](auto field) __attribute__((always_inline)) {
+      int32_t v = rec[0].*field;
+#pragma unroll
+      for (int k = 1; k < N; k++) v = b >= 64 * k ? rec[k].*field : v;
+      return __builtin_amdgcn_readlane(v, b & 63);
+    };
+    using R = typename Args::Req;
+    return {get(&R::len), get(&R::tensor), get(&R::unit_prefix), get(&R::wave_first), get(&R::n_part), get(&R::part0)};
+  }
+};
 
 // what a wave (in blocks: a workgroup) handles: kv head g, wave w of that head, n_units steps of the head's
 // sequence from step u_lo on, the first of which belongs to request b. A step is a unit (a tile in the
 // kernel that walks tiles) or, where every wave gets one step, up to step_units units of one request
-struct Share { int32_t g, w, u_lo, n_units, b; };
-
-// Every level of dependent scalar loads costs a wave about a microsecond before its first K/V
-// request can go out, and while the memory system is saturated more than that, so the look-up is
-// written to need few levels: the launch header, then one word of the request table, then
-// everything about the request at once.
 template <class Args>
-__device__ __forceinline__ Share locate_share(const Args& a, int32_t index, int lane) {
-  Share s;
+struct Share { int32_t g, w, u_lo, n_units, b; typename Args::Req first; };
+
+template <class Args>
+__device__ __forceinline__ Share<Args> locate_share(const Args& a, const Records<Args>& records, int32_t index, int lane) {
+  Share<Args> s;
   const int32_t W = a.waves_per_head, each = a.units_each, extra = a.units_extra;
-  s.g = index / W;
+  s.g = divide(index, a.by_waves);
   s.w = index - s.g * W;
   s.u_lo = s.w * each + min(s.w, extra);
   s.n_units = each + (s.w < extra ? 1 : 0);
-  if (a.use_wave_req) s.b = (a.wave_req[s.w >> 2] >> ((s.w & 3) * 8)) & 0xff;
-  else s.b = find_request(a, s.u_lo, lane);
+  s.b = records.find(a.n_req, s.u_lo, lane);
+  s.first = records.of(s.b);
   return s;
 }
 
@@ -585,6 +593,10 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const Records<BatchArgs> records(a, lane);
+  wanted(a.n_req, a.waves_per_head, a.units_each, a.units_extra, a.by_waves.mul, a.by_waves.shift, a.q_row0, g_first);
+  wanted(pv.chunk_bytes, pv.tokens_per_chunk, pv.tiles_per_chunk, pv.max_slots, pv.n_q_heads, pv.n_kv_heads, pv.group, q);
+  wanted(pv.base, pv.table, pv.vbase, k_new, pv.by_chunk.mul, pv.by_chunk.shift, pv.by_tiles.mul, pv.by_tiles.shift);
   uint16_t* const sm_p = sm_p_all[wave];
   char* const sm_k = sm_k_all[wave];
   const int sub = lane % LPR, rg = lane / LPR;
@@ -621,7 +633,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
     cb += 1;                                                                                        \
     const BatchArgs::Req nx_ = a.req[cb];                                                           \
     len = nx_.len;                                                                                  \
-    left = units_of(len, Tc, pv.tiles_per_chunk, TILE_TOKENS);                                                   \
+    left = units_of(len, pv, pv.tiles_per_chunk, TILE_TOKENS);                                                   \
     c_np = nx_.n_part;                                                                              \
     walk = tensor_walk<DIRECT>(pv, nx_.tensor);                                                     \
     slot = 0;                                                                                       \
@@ -789,18 +801,18 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
   if (lane < 2) results.whose[2 * wave + lane] = -1;
   const int32_t index = blockIdx.x * NW + wave;
   if (index < a.waves_per_head * pv.n_kv_heads) {
-    const Share sh = locate_share(a, index, lane);
+    const Share<BatchArgs> sh = locate_share(a, records, index, lane);
     const int32_t g = sh.g, n_tiles = sh.n_units;
     const int hq0 = g * pv.group + g_first;            // first q head handled here
     // cursor: the tile whose K is in LDS or on its way there. cb: its request; len, walk: that
     // request's length and its table row or base address (read-only for the kernel's lifetime: uniform loads)
     int32_t cb = sh.b;
-    const BatchArgs::Req first = a.req[cb];
+    const BatchArgs::Req& first = sh.first;
     int32_t len = first.len;
     TensorWalk walk = tensor_walk<DIRECT>(pv, first.tensor);
     const int32_t tile0 = sh.u_lo - first.unit_prefix;
-    int32_t left = units_of(len, Tc, pv.tiles_per_chunk, TILE_TOKENS) - tile0;
-    int32_t slot = tile0 / pv.tiles_per_chunk;
+    int32_t left = units_of(len, pv, pv.tiles_per_chunk, TILE_TOKENS) - tile0;
+    int32_t slot = divide(tile0, pv.by_tiles);
     int32_t r = (tile0 - slot * pv.tiles_per_chunk) * TILE_TOKENS;
     int32_t nv_c = min(TILE_TOKENS, min(Tc - r, len - (slot * Tc + r)));
     const char* kb = chunk_addr<DIRECT>(pv, walk, slot) + ((uint64_t)(g * 2) * Tc + r) * ROWB;
@@ -1057,12 +1069,15 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   static_assert(U % 2 == 0, "PV takes two units at a time");
   const int lane = threadIdx.x & 63, c = lane & 15, g16 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t touch = wave == 0 ? touch_arguments<Args>(lane) : 0u;
+  const Records<Args> records(a, lane);
+  wanted(a.n_req, a.waves_per_head, a.units_each, a.units_extra, a.by_waves.mul, a.by_waves.shift, a.step_units, a.q_row0);
+  wanted(pv.chunk_bytes, pv.tokens_per_chunk, pv.units_per_chunk, pv.max_slots, pv.n_q_heads, pv.n_kv_heads, pv.group, g_first);
+  wanted(pv.base, pv.table, pv.vbase, q, pv.by_chunk.mul, pv.by_chunk.shift, pv.by_units.mul, pv.by_units.shift);
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
   const int32_t index = NW ? blockIdx.x : blockIdx.x * SW + wave;
-  const Share sh = locate_share(a, NW ? index : min(index, a.waves_per_head * pv.n_kv_heads - 1), lane);
+  const Share<Args> sh = locate_share(a, records, NW ? index : min(index, a.waves_per_head * pv.n_kv_heads - 1), lane);
   const int32_t g = sh.g;
   const int32_t hq0 = g * pv.group + g_first;        // first q head handled here
   const int32_t head = min(c, n_heads - 1);          // lanes beyond the last head repeat it and write nothing
@@ -1071,7 +1086,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   int32_t cb = sh.b, rem_share = sh.n_units, len, slot, r, rem_req, part;
   uint32_t first = T_FIRST;
   TensorWalk walk;
-  const typename Args::Req first_rq = a.req[cb];
+  const typename Args::Req& first_rq = sh.first;
   {
     const typename Args::Req& rq = first_rq;
     len = rq.len;
@@ -1079,10 +1094,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     constexpr int32_t STEP_WAVES = NW ? NW : 1;
     const int32_t mine = NW ? wave * a.step_units / STEP_WAVES : 0;     // (at most U apart from one wave to the next)
     const int32_t u0 = (sh.u_lo - rq.unit_prefix) * a.step_units + mine;
-    rem_req = units_of(len, Tc, pv.units_per_chunk) - u0;
+    rem_req = units_of(len, pv, pv.units_per_chunk) - u0;
     if (NW) rem_share = min((wave + 1) * a.step_units / STEP_WAVES - mine, rem_req);
     else if (a.step_units > 1) rem_share = min(rem_share * a.step_units, rem_req);
-    slot = u0 / pv.units_per_chunk;
+    slot = divide(u0, pv.by_units);
     r = (u0 - slot * pv.units_per_chunk) * UNIT_TOKENS;
     part = rq.n_part == 1 ? -1 : rq.part0 + (sh.w - rq.wave_first);    // (which slot: only where a workgroup is a step)
   }
@@ -1092,23 +1107,22 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     t.part = part;
     t.flags = first;
     t.base = DIRECT ? walk.tbase : pv.base;
+    // (which table entries are wanted is known before any of them is asked for: their loads are on the way together)
+    int32_t in_slot[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      if (u == 0 || u < t.n) {
-        t.at[u] = DIRECT ? (uint32_t)slot : (uint32_t)walk.trow[slot];
-        t.r[u] = r;
-        t.nv[u] = min(UNIT_TOKENS, min(Tc - r, len - (slot * Tc + r)));
-        t.tail = t.nv[u];
-        if (u < t.n - 1 || (t.n > 0 && rem_req > t.n)) {   // there is a next unit of this request
-          r += UNIT_TOKENS;
-          if (r >= Tc) { r = 0; slot += 1; }
-        }
-      } else {
-        t.at[u] = t.at[u - 1];
-        t.r[u] = t.r[u - 1];
-        t.nv[u] = 0;
+      const bool there = u == 0 || u < t.n;
+      in_slot[u] = there ? slot : in_slot[u ? u - 1 : 0];
+      t.r[u] = there ? r : t.r[u ? u - 1 : 0];
+      t.nv[u] = there ? min(UNIT_TOKENS, min(Tc - r, len - (slot * Tc + r))) : 0;
+      t.tail = there ? t.nv[u] : t.tail;
+      if (u < t.n - 1 || (u < t.n && rem_req > t.n)) {     // there is a next unit of this request
+        r += UNIT_TOKENS;
+        if (r >= Tc) { r = 0; slot += 1; }
       }
     }
+#pragma unroll
+    for (int u = 0; u < U; u++) t.at[u] = DIRECT ? (uint32_t)in_slot[u] : (uint32_t)walk.trow[in_slot[u]];
     if (t.n == 0) t.nv[0] = 0;                       // past the end of the share
     rem_req -= t.n;
     rem_share -= t.n;
@@ -1122,7 +1136,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       cb += 1;
       const typename Args::Req rq = a.req[cb];
       len = rq.len;
-      rem_req = units_of(len, Tc, pv.units_per_chunk);
+      rem_req = units_of(len, pv, pv.units_per_chunk);
       walk = tensor_walk<DIRECT>(pv, rq.tensor);
       slot = 0;
       r = 0;
@@ -1318,7 +1332,6 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       issue_k(t);
       issue_v(t);
       __builtin_amdgcn_sched_barrier(0);
-      touched(touch);
       scores(t);
       weigh(t);
       const float L = add_xor32(add_xor16(l));
@@ -1415,7 +1428,6 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     issue_k(t);
     issue_v(t);
     __builtin_amdgcn_sched_barrier(0);               // the loads stay where they are asked for
-    touched(touch);
     advance(next);
     uint32_t done;
     do {
@@ -1564,13 +1576,13 @@ __global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __
   const int32_t Tc = pv.tokens_per_chunk;
   uint32_t x = 0;
   {
-    const Share sh = locate_share(a, blockIdx.x, lane);
+    const Share<BatchArgs> sh = locate_share(a, Records<BatchArgs>(a, lane), blockIdx.x, lane);
     const int32_t g = sh.g;
     int32_t cb = sh.b;
-    BatchArgs::Req rec = a.req[cb];
+    BatchArgs::Req rec = sh.first;
     const int32_t ut = a.unit_tokens, upc = (Tc + ut - 1) / ut;
     const int32_t u0 = (sh.u_lo - rec.unit_prefix) * a.step_units;
-    int32_t left = units_of(rec.len, Tc, upc, ut) - u0, todo = sh.n_units;
+    int32_t left = units_of(rec.len, pv, upc, ut) - u0, todo = sh.n_units;
     if (a.step_units > 1) todo = min(todo * a.step_units, left);
     int32_t slot = u0 / upc;
     int32_t r = (u0 - slot * upc) * ut;
@@ -1598,7 +1610,7 @@ __global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __
       } else if (todo > 0) {
         cb += 1;
         rec = a.req[cb];
-        left = units_of(rec.len, Tc, upc, ut);
+        left = units_of(rec.len, pv, upc, ut);
         slot = 0;
         r = 0;
       }
@@ -1713,9 +1725,8 @@ static FewArgs few_of(const BatchArgs& a) {
   FewArgs f;
   f.n_req = a.n_req; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens; f.step_units = a.step_units;
   f.units_per_head = a.units_per_head; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
-  f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.use_wave_req = a.use_wave_req;
+  f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.by_waves = a.by_waves;
   f.wg_waves = a.wg_waves; f.merge_parts = a.merge_parts; f.in_order_parts = a.in_order_parts; f.n_split_req = a.n_split_req;
-  std::copy_n(a.wave_req, FewArgs::MAX_WAVE / 4, f.wave_req);
   std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
   for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};
   for (int i = 0; i < a.n_req; i++) f.req[i] = {a.req[i].len, a.req[i].tensor, a.req[i].unit_prefix, a.req[i].wave_first, a.req[i].n_part, a.req[i].part0};
@@ -1752,7 +1763,7 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
       if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
       else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
     };
-    if (a.n_req <= FewArgs::MAX_REQ && a.waves_per_head <= FewArgs::MAX_WAVE) in_blocks(few_of(a));
+    if (a.n_req <= FewArgs::MAX_REQ) in_blocks(few_of(a));
     else in_blocks(a);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;

@@ -6,10 +6,11 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include "divide.hpp"
+
 namespace ellm {
 
-constexpr int MAX_LAUNCH_REQ = 128;   // requests described by one launch's kernel arguments (4 KB in all)
-constexpr int MAX_WAVE_REQ = 512;     // waves per kv head that the request lookup table covers
+constexpr int MAX_LAUNCH_REQ = 128;   // requests described by one launch's kernel arguments (3.2 KB in all)
 constexpr int MAX_PATCH = 448;        // table entries patched by one launch
 constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of one chunk a wave handles at a time
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
@@ -39,6 +40,7 @@ struct PoolView {
   int32_t units_per_chunk;    // ceil(tokens_per_chunk / UNIT_TOKENS); nor does a unit
   int32_t max_slots;
   int32_t n_q_heads, n_kv_heads, head_dim, group;
+  Divisor by_chunk, by_tiles, by_units;   // division by tokens_per_chunk, tiles_per_chunk, units_per_chunk
 };
 
 // One decode launch: requests [q_row0, q_row0 + n_req) of the caller's batch.
@@ -61,31 +63,29 @@ struct PoolView {
 // Workspace of a launch, from the pointer the launch is given: accumulator rows
 // [kv head][partial slot of the head][q head of the group][D] fp32 (ws_slots = n_kv_heads *
 // parts_per_head slots in all), then the (m, l) pairs in the same order, WS_ML floats each.
-template <int REQS, int WAVES>
+template <int REQS>
 struct BatchArgsOf {
-  static constexpr int MAX_REQ = REQS, MAX_WAVE = WAVES;
+  static constexpr int MAX_REQ = REQS;
+  // (first what a wave needs before anything else: one load of eight words)
   int32_t n_req;
-  int32_t q_row0;             // row of the first request in q / out
-  int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
-  int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave (STEP_UNITS) or
-                              // workgroup of several waves (up to WIDE_UNITS) gets: up to this many units of
-                              // one request (then "units" and "waves" in the fields below are such steps)
-  int32_t units_per_head;     // units of all requests of the launch, for one kv head
   int32_t waves_per_head;     // <= units_per_head
   int32_t units_each, units_extra;   // units_per_head = waves_per_head * units_each + units_extra
+  Divisor by_waves;           // division by waves_per_head
+  int32_t step_units;         // 1; or, in a launch too small to fill the GPU, what every wave (STEP_UNITS) or
+                              // workgroup of several waves (up to WIDE_UNITS) gets: up to this many units of
+                              // one request (then "units" and "waves" in the fields around are such steps)
+  int32_t q_row0;             // row of the first request in q / out
+  int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
+  int32_t units_per_head;     // units of all requests of the launch, for one kv head
   int32_t parts_per_head;     // partial slots per kv head = sum of n_part over the split requests (where workgroups are
                               // waves of several shares, a request uses no more than it spans workgroups)
   int32_t ws_slots;           // n_kv_heads * parts_per_head
-  int32_t use_wave_req;       // wave_req is filled in (waves_per_head <= MAX_WAVE_REQ)
   int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last;
                               // 0 where any request has more than merge_parts()
   int32_t n_split_req;        // requests with more: the combine pass runs for these only
-  // request that holds the first unit of wave w of a kv head, one byte each: lets a wave find its
-  // request with one scalar load instead of a search through the prefix entries
-  uint32_t wave_req[WAVES / 4];
   // the requests for the combine pass in ascending order, one byte each
   uint32_t split_req[REQS / 4];
-  // per request, one record, so that a wave gets all of it with one round of scalar loads
+  // per request, one record: a wave gets all of them with one round of loads (Records in kernels.hip)
   struct Req {
     int32_t len, tensor;
     int32_t unit_prefix;      // units of the requests before this one
@@ -97,10 +97,10 @@ struct BatchArgsOf {
   int32_t wg_waves;           // waves of a workgroup that each have a share of their own (SHARE_WAVES), or 1
   int32_t in_order_parts;     // requests of up to so many partials are added up in the attention kernel's order
 };
-using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ, MAX_WAVE_REQ>;
+using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ>;
 // what a launch in blocks of few requests hands to its kernel instead: the host writes the arguments to device memory for
-// each launch; with 0.6 KB instead of 4 a call of 4 requests of up to 256 tokens takes 7.37 us instead of 7.67
-using FewArgs = BatchArgsOf<16, 64>;
+// each launch; with 0.6 KB instead of 4 a call of 4 requests of up to 256 tokens took 7.37 us instead of 7.67 (0.5 and 3.2 KB now)
+using FewArgs = BatchArgsOf<16>;
 
 struct AppendArgs {
   int32_t n_req, total_new;
