@@ -6,6 +6,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PROGRAM = r"""
 #include "divide.hpp"
 #include <cstdio>
+#include <initializer_list>
 int main() {
   int64_t wrong = 0, n_checked = 0;
   auto check = [&](int32_t n, int32_t d) { n_checked++; if (n >= 0 && ellm::divide(n, ellm::divisor(d)) != n / d) wrong++; };
