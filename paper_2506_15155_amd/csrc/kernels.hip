@@ -279,6 +279,13 @@ __device__ __forceinline__ void wanted(A a, B b, C c, D d, E e, F f, G g, H h) {
   asm volatile("" :: "s"(a), "s"(b), "s"(c), "s"(d), "s"(e), "s"(f), "s"(g), "s"(h));
 }
 
+// A kernel argument as a value of its own, which is not loaded again later and from which nothing is derived earlier
+template <class T>
+__device__ __forceinline__ T held(T v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
+
 // The records of a launch's requests, spread over the lanes of a wave: lane l has those of requests l, l + 64, .. Where a
 // wave begins used to be found in three dependent steps (header, a table of the waves' requests, the record), about a third
 // of a microsecond each from the L2 and more from memory, which no cache holds the arguments of. Now all records are asked for
@@ -347,11 +354,11 @@ __device__ __forceinline__ int32_t partial_dim(int32_t unit_tokens, int32_t f) {
 // to do so adds up all of them. Which one that is depends on who ends last, but the sum is taken in the order of the
 // partials, so the result does not. Nobody waits for another workgroup, and the counter goes back to 0 by itself
 // (an increment that wraps).
-// This took the place of a combine launch behind every call, 4.6 us of which 3.4 are the launch; a workgroup's chain
-// behind its last wave is 2.5 to 4 us (LDS sum and store 1.2 to 1.6, count 0.4, adding up 1 to 2.4). 8B-shaped step 2087 ->
+// This took the place of a combine launch behind every call, 4.6 us of which 3.4 are the launch: 8B-shaped step 2087 ->
 // 2003 us, 8 requests of it, 4 layers 67.5 -> 63.7, 48 requests of 6 q heads each 52.2 -> 49.4, 64 of 16 heads of 64 68.2 ->
 // 66.6, chunks of 16 tokens 36.9 -> 33.8. By single waves, without the sum in LDS, it was no faster than the pass: up to 29
-// partials for one wave to add up, 6 us.
+// partials for one wave to add up, 6 us. A workgroup's chain behind its last wave is 2.2 to 3.3 us now (where the results go 0.6, LDS
+// sum 0.3 and store 0.3, count 0.3, adding up 0.7 to 1.5).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ void store_partial(__amdgpu_buffer_rsrc_t rows, int32_t at, float4 v) {
   const words4_t w = {__float_as_uint(v.x), __float_as_uint(v.y), __float_as_uint(v.z), __float_as_uint(v.w)};
@@ -392,18 +399,18 @@ struct Partials {
   static constexpr int F = D / 4;
   __amdgpu_buffer_rsrc_t rows, pairs;
   int32_t group;
-  template <class Args>
-  __device__ __forceinline__ Partials(const PoolView& pv, const float* ws, const Args& a, int32_t part0, int32_t n_part, int32_t g,
-                                      int32_t g_first, int32_t n_heads) : group(pv.group) {
-    const int64_t row0 = ((int64_t)g * a.parts_per_head + part0) * group + g_first;
+  // slot0: the first one's slot; ws_slots: all slots of the workspace
+  __device__ __forceinline__ Partials(const float* ws, int32_t ws_slots, int64_t slot0, int32_t n_part, int32_t group, int32_t g_first,
+                                      int32_t n_heads) : group(group) {
+    const int64_t row0 = slot0 * group + g_first;
     const int32_t n_rows = (n_part - 1) * group + n_heads;
     rows = buffer_at(ws + row0 * D, n_rows * (D * 4));
-    pairs = buffer_at(ws + (int64_t)a.ws_slots * group * D + row0 * WS_ML, n_rows * (WS_ML * 4));
-    asm volatile("" ::: "memory");     // nothing of this is read before the last one has counted itself in
+    pairs = buffer_at(ws + (int64_t)ws_slots * group * D + row0 * WS_ML, n_rows * (WS_ML * 4));
   }
   // columns x, x + step, .. (KB of them) over partials j0 .. j1 - 1, FEW or MANY of them asked for at a time
   template <int KB, int FEW, int MANY>
   __device__ __forceinline__ void sum(Sum (&sums)[KB], int32_t x, int32_t step, int32_t j0, int32_t j1) const {
+    asm volatile("" ::: "memory");     // nothing of this is read before the last one has counted itself in
 #pragma unroll
     for (int k = 0; k < KB; k++) sums[k] = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
     auto some = [&](auto ahead) __attribute__((always_inline)) {
@@ -414,9 +421,10 @@ struct Partials {
       for (int u = 0; u < N; u++)
 #pragma unroll
         for (int k = 0; k < KB; k++) {
-          const int32_t xk = x + k * step, row = (j0 + u) * group + xk / F;
-          ml[k][u] = __builtin_amdgcn_raw_buffer_load_b64(pairs, row * (WS_ML * 4), 0, CPOL_DEVICE);
-          v[k][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, row * (D * 4) + xk % F * 16, 0, CPOL_DEVICE);
+          // (the same row for every u: what differs between them is the same for all lanes)
+          const int32_t xk = x + k * step, row = xk / F, more = (j0 + u) * group;
+          ml[k][u] = __builtin_amdgcn_raw_buffer_load_b64(pairs, row * (WS_ML * 4), more * (WS_ML * 4), CPOL_DEVICE);
+          v[k][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, row * (D * 4) + xk % F * 16, more * (D * 4), CPOL_DEVICE);
         }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -427,10 +435,10 @@ struct Partials {
         rescale(sums[k], M);
 #pragma unroll
         for (int u = 0; u < N; u++) {
+          // (a row that is not there came back as zeros; a branch around each would make a chain of them)
           const words4_t t = v[k][u];
-          if (j0 + u < j1)
-            add(sums[k], __uint_as_float(ml[k][u].y), make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)),
-                fast_exp2(__uint_as_float(ml[k][u].x) - M));
+          add(sums[k], __uint_as_float(ml[k][u].y), make_float4(__uint_as_float(t.x), __uint_as_float(t.y), __uint_as_float(t.z), __uint_as_float(t.w)),
+              j0 + u < j1 ? fast_exp2(__uint_as_float(ml[k][u].x) - M) : 0.f);
         }
       }
     };
@@ -460,9 +468,18 @@ __device__ __forceinline__ Parts parts_of(int32_t wave_first, int32_t n_part, in
 // results of the workgroup's waves: slot 2 w of wave w's first request, 2 w + 1 of its last one, if it is another
 template <int D, int HEADS>
 struct Results {
-  float4 rows[2 * SHARE_WAVES][HEADS][D / 4 + 1];    // (padded against bank conflicts)
-  float2 ml[2 * SHARE_WAVES][HEADS];
-  int32_t whose[2 * SHARE_WAVES];      // request and kv head, -1: no result, or one that needs no other
+  static constexpr int SLOTS = 2 * SHARE_WAVES, NONE = SLOTS;      // slot NONE: what takes part in a sum and adds nothing
+  float4 rows[SLOTS + 1][HEADS][D / 4 + 1];    // (padded against bank conflicts)
+  float2 ml[SLOTS + 1][HEADS];
+  int32_t whose[SLOTS];      // request and kv head, -1: no result, or one that needs no other
+  // by all waves, a slot in whose each, before their first results
+  __device__ __forceinline__ void clear(int32_t wave, int32_t lane) {
+    if (lane < 2) whose[2 * wave + lane] = -1;
+    for (int32_t h = wave; h < HEADS; h += SHARE_WAVES) {
+      if (lane < D / 4) rows[NONE][h][lane] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (lane == 0) ml[NONE][h] = make_float2(-INFINITY, 0.f);
+    }
+  }
 };
 
 // column x of a request's result of this workgroup becomes partial result `part` of the request
@@ -476,36 +493,54 @@ __device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, con
     store_partial(buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4)), x / F * (WS_ML * 4), make_float2(s.M, s.L));
 }
 
-// all waves of the workgroup have ended their shares
-template <int D, int HEADS, int KB, int MANY, class Args>
-__device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16_t* __restrict__ out, const Args& a,
+// All waves of the workgroup have ended their shares. What follows is a chain of latencies with nothing beside it, so what
+// it needs is in registers (`records`, the arguments) before the barrier, LDS is read without a branch, and the heads of a
+// request are dealt out to the waves, in up to four pieces that are stored, counted in and added up each by itself: one
+// request, four waves; two, two waves each; more, a wave each. (A piece is whole heads: their (m, l) pairs belong to it.) With one
+// wave for a request and branches around the parts of each sum: 48 requests of 6 q heads each 49.95 -> 49.3 us, 64 of 16
+// heads of 64 66.4 -> 65.7, chunks of 16 tokens 33.6 -> 33.3, the 8B-shaped step 1995 -> 1985.
+template <int D, int HEADS, class Args>
+__device__ __forceinline__ void end_shares(const PoolView& pv, float* ws_, uint16_t* __restrict__ out, const Args& a, const Records<Args>& records,
                                            const Results<D, HEADS>& res, int32_t g_first, int32_t n_heads, int32_t wave, int32_t lane) {
-  constexpr int F = D / 4;
+  constexpr int F = D / 4, SLOTS = Results<D, HEADS>::SLOTS, NONE = Results<D, HEADS>::NONE;
+  float* const ws = held(ws_);
+  const int32_t waves_per_head = held(a.waves_per_head), parts_per_head = held(a.parts_per_head), ws_slots = held(a.ws_slots),
+                merge_parts = held(a.merge_parts);
   __syncthreads();
-  const int32_t whose = lane < 2 * SHARE_WAVES ? res.whose[lane] : -1;
-  uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(whose >= 0);
+  const int32_t whose = res.whose[lane % SLOTS];
+  uint32_t left = (uint32_t)__builtin_amdgcn_ballot_w64(whose >= 0) & ((1u << SLOTS) - 1u);
+  int32_t n_requests = 0;
+  for (uint32_t l = left; l; n_requests++)
+    l &= ~(uint32_t)__builtin_amdgcn_ballot_w64(whose == __builtin_amdgcn_readlane(whose, __builtin_ctz(l)));
+  // pieces of 1, 2 or 4 heads; those that a wave has: piece p0 on, n_pieces of them
+  const int32_t shift = n_heads <= 4 ? 0 : n_heads <= 8 ? 1 : 2, pieces = (n_heads + (1 << shift) - 1) >> shift;
+  const int32_t each = n_requests == 1 ? 1 : n_requests == 2 ? 2 : 4, p0 = n_requests == 1 ? wave : n_requests == 2 ? wave & ~1 : 0;
+  const int32_t n_pieces = min(each, pieces - p0), h0 = p0 << shift, h1 = min(n_heads, (p0 + each) << shift);
+  if (n_pieces <= 0) return;
   for (int32_t nth = 0; left; nth++) {
     const int32_t id = __builtin_amdgcn_readlane(whose, __builtin_ctz(left));
-    uint32_t mine = (uint32_t)__builtin_amdgcn_ballot_w64(whose == id);      // the slots of one request
+    uint32_t mine = (uint32_t)__builtin_amdgcn_ballot_w64(whose == id) & ((1u << SLOTS) - 1u);      // the slots of one request
     left &= ~mine;
-    if (nth % SHARE_WAVES != wave) continue;
-    const int32_t b = id % MAX_LAUNCH_REQ, g = id / MAX_LAUNCH_REQ;
-    const typename Args::Req rq = a.req[b];
+    if (n_requests == 2 ? nth != (wave & 1) : n_requests > 2 && nth % SHARE_WAVES != wave) continue;
+    const int32_t b = id % MAX_LAUNCH_REQ, g = id / MAX_LAUNCH_REQ, group = held(pv.group);
+    const typename Args::Req rq = records.of(b);
     const int32_t n = __builtin_popcount(mine);      // at most one slot of every wave
     int32_t slot[SHARE_WAVES];
 #pragma unroll
     for (int i = 0; i < SHARE_WAVES; i++) {
-      slot[i] = mine ? __builtin_ctz(mine) : slot[i ? i - 1 : 0];
+      slot[i] = mine ? __builtin_ctz(mine) : NONE;
       mine &= mine - 1;
     }
     // (a request for the combine pass goes there also where no other workgroup has a part of it)
-    const bool whole = n == rq.n_part && rq.n_part <= a.merge_parts;
-    const Parts parts = parts_of(rq.wave_first, rq.n_part, a.waves_per_head, g, SHARE_WAVES);
-    const int64_t row0 = ((int64_t)g * a.parts_per_head + rq.part0 + ((int32_t)blockIdx.x - parts.first)) * pv.group + g_first;
-    const auto rows = buffer_at(ws + row0 * D, n_heads * (D * 4));
-    const auto pairs = buffer_at(ws + (int64_t)a.ws_slots * pv.group * D + row0 * WS_ML, n_heads * (WS_ML * 4));
-    for (int32_t x = lane; x < n_heads * F; x += 64) {
-      const int32_t h = x / F, f = x % F;
+    const bool whole = n == rq.n_part && rq.n_part <= merge_parts;
+    const Parts parts = parts_of(rq.wave_first, rq.n_part, waves_per_head, g, SHARE_WAVES);
+    const int64_t slot0 = (int64_t)g * parts_per_head + rq.part0;
+    const int64_t row0 = (slot0 + ((int32_t)blockIdx.x - parts.first)) * group + g_first;
+    // (stores past this wave's heads are dropped by the buffers' range)
+    const auto rows = buffer_at(ws + row0 * D, h1 * (D * 4));
+    const auto pairs = buffer_at(ws + (int64_t)ws_slots * group * D + row0 * WS_ML, h1 * (WS_ML * 4));
+    for (int32_t x = h0 * F + lane; x - lane < h1 * F; x += 64) {
+      const int32_t h = min(x / F, HEADS - 1), f = x % F;
       float2 ml[SHARE_WAVES];
       float4 v[SHARE_WAVES];
 #pragma unroll
@@ -517,27 +552,37 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws, uint16
 #pragma unroll
       for (int i = 1; i < SHARE_WAVES; i++) s.M = fmaxf(s.M, ml[i].x);
 #pragma unroll
-      for (int i = 0; i < SHARE_WAVES; i++)
-        if (i < n) add(s, ml[i].y, v[i], fast_exp2(ml[i].x - s.M));
+      for (int i = 0; i < SHARE_WAVES; i++) add(s, ml[i].y, v[i], fast_exp2(ml[i].x - s.M));
       if (whole) {
-        write_out<D>(pv, out, a, b, g, g_first, x, s);
+        if (x < h1 * F) write_out<D>(pv, out, a, b, g, g_first, x, s);
       } else {
         store_partial(rows, x * 16, s.A);
-        if (f == 0) store_partial(pairs, h * (WS_ML * 4), make_float2(s.M, s.L));
+        if (f == 0) store_partial(pairs, x / F * (WS_ML * 4), make_float2(s.M, s.L));
       }
     }
-    if (whole || rq.n_part > a.merge_parts) continue;
+    if (whole || rq.n_part > merge_parts) continue;
     stores_done();
     uint32_t before = 0;
-    if (lane == 0) before = count_in(pv, g * MAX_LAUNCH_REQ + b, 0, parts.n);
-    if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)parts.n - 1u) continue;
-    const Partials<D> all(pv, ws, a, rq.part0, parts.n, g, g_first, n_heads);
-    for (int32_t x = lane; x - lane < n_heads * F; x += KB * 64) {
-      Sum s[KB];
-      all.template sum<KB, 4, MANY>(s, x, 64, 0, parts.n);
-#pragma unroll
-      for (int k = 0; k < KB; k++)
-        if (x + k * 64 < n_heads * F) write_out<D>(pv, out, a, b, g, g_first, x + k * 64, s[k]);
+    if (lane < n_pieces) before = count_in(pv, g * MAX_LAUNCH_REQ + b, p0 + lane, parts.n);
+    const Partials<D> all(ws, ws_slots, slot0, parts.n, held(pv.group), g_first, h1);
+    // (all of a wave's pieces or none, as a rule)
+    const uint32_t last = (uint32_t)__builtin_amdgcn_ballot_w64(lane < n_pieces && before == (uint32_t)parts.n - 1u);
+    if (!last) continue;
+    auto done = [&](int32_t x, const Sum& s) __attribute__((always_inline)) {
+      if (x < h1 * F && (last >> ((x / F >> shift) - p0) & 1u)) write_out<D>(pv, out, a, b, g, g_first, x, s);
+    };
+    const int32_t x = h0 * F + lane;
+    if ((h1 - h0) * F <= 64) {
+      Sum s[1];
+      all.template sum<1, 4, 16>(s, x, 0, 0, parts.n);
+      done(x, s[0]);
+    } else {
+      for (int32_t at = x; at - lane < h1 * F; at += 128) {
+        Sum s[2];
+        all.template sum<2, 4, 8>(s, at, 64, 0, parts.n);
+        done(at, s[0]);
+        done(at + 64, s[1]);
+      }
     }
   }
 }
@@ -798,7 +843,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
     vn = v_new[row16];                                                                              \
   }
 
-  if (lane < 2) results.whose[2 * wave + lane] = -1;
+  results.clear(wave, lane);             // (behind the first loads it is slower: LDS writes wait for loads to LDS)
   const int32_t index = blockIdx.x * NW + wave;
   if (index < a.waves_per_head * pv.n_kv_heads) {
     const Share<BatchArgs> sh = locate_share(a, records, index, lane);
@@ -962,8 +1007,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
       }
     }
   }
-  constexpr int KB = (G * D / 4 + 63) / 64;
-  end_shares<D, G, KB, KB == 1 ? 16 : 32 / KB>(pv, ws, out, a, results, g_first, G, wave, lane);
+  end_shares<D, G>(pv, ws, out, a, records, results, g_first, G, wave, lane);
 #undef ELLM_LOAD_Q
 #undef ELLM_LOAD_NEW_ROW
 #undef ELLM_LOAD_TILE
@@ -1343,8 +1387,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
             *reinterpret_cast<float4*>(&sums[wave][c][g16 * 4 + (i * E + e) * 4]) = make_float4(acc[e][i], acc[e + 1][i], acc[e + 2][i], acc[e + 3][i]);
         if (g16 == 0) ml[wave][c] = make_float2(m, L);
       }
-    } else if (lane < n_heads) {
-      ml[wave][lane] = make_float2(-INFINITY, 0.f);    // nothing left for this wave: its row is not read
+    } else {
+      // nothing left for this wave: zeros, whose weight is 0
+      if (lane < n_heads) ml[wave][lane] = make_float2(-INFINITY, 0.f);
+      for (int i = lane; i < n_heads * F; i += 64) *reinterpret_cast<float4*>(&sums[wave][i / F][i % F * 4]) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
     __syncthreads();
     // Every wave takes 64 columns (pieces of the heads' rows in order), in all blocks of a request the same ones, which need
@@ -1356,14 +1402,19 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     if (wave * 64 >= n_cols) return;
     Sum s = {NEG_BIG, 0.f, make_float4(0.f, 0.f, 0.f, 0.f)};
     if (x < n_cols) {
-#pragma unroll
-      for (int w = 0; w < NW; w++) s.M = fmaxf(s.M, ml[w][h].x);
+      // (all rows are read before the first is added, and none is skipped: a branch around each makes a chain of LDS
+      // latencies, 0.7 us where this takes 0.45; one request of 3300 tokens 7.99 -> 7.5 us a call with the same in Partials::sum)
+      float2 p[NW];
+      float4 v4[NW];
 #pragma unroll
       for (int w = 0; w < NW; w++) {
-        const float2 p = ml[w][h];
-        if (p.x < NEG_BIG) continue;                   // (a sum of 0 is not nothing: scores of -inf, beside which an infinite V is NaN)
-        add(s, p.y, *reinterpret_cast<const float4*>(&sums[w][h][f * 4]), fast_exp2(p.x - s.M));
+        p[w] = ml[w][h];
+        v4[w] = *reinterpret_cast<const float4*>(&sums[w][h][f * 4]);
       }
+#pragma unroll
+      for (int w = 0; w < NW; w++) s.M = fmaxf(s.M, p[w].x);
+#pragma unroll
+      for (int w = 0; w < NW; w++) add(s, p[w].y, v4[w], fast_exp2(p[w].x - s.M));
       if (part < 0) write_out<D>(pv, out, a, cb, g, g_first, x, s);
       else leave_partial<D>(pv, ws, a, part, g, g_first, n_heads, x, s);
     }
@@ -1374,15 +1425,14 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     uint32_t before = 0;
     // counting in one line takes turns (12 ns each; 8 times 8 for 16 heads in 8 blocks): as many lines as there are blocks
     if (lane == 0) before = count_in(pv, g * a.waves_per_head + first_rq.wave_first + wave % n_part, wave, n_part);
+    const Partials<D> all(ws, a.ws_slots, (int64_t)g * a.parts_per_head + first_rq.part0, n_part, held(pv.group), g_first, n_heads);
     if (__builtin_amdgcn_readfirstlane(before) != (uint32_t)n_part - 1u) return;
-    const Partials<D> all(pv, ws, a, first_rq.part0, n_part, g, g_first, n_heads);
     Sum all_of[1];
     all.template sum<1, 8, 16>(all_of, x, 0, 0, n_part);
     if (x < n_cols) write_out<D>(pv, out, a, cb, g, g_first, x, all_of[0]);
     return;
   }
   __shared__ __attribute__((aligned(16))) Results<D, SW == 1 ? 1 : HEADS_PER_PASS> results;     // (SW == 1: not used)
-  if (SW > 1 && lane < 2) results.whose[2 * wave + lane] = -1;
   auto finish = [&](const TileInfo<U>& t) __attribute__((always_inline)) {
     const float L = add_xor32(add_xor16(l));
     if (c >= n_heads) return;
@@ -1428,6 +1478,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     issue_k(t);
     issue_v(t);
     __builtin_amdgcn_sched_barrier(0);               // the loads stay where they are asked for
+    if constexpr (SW > 1) results.clear(wave, lane);
     advance(next);
     uint32_t done;
     do {
@@ -1442,8 +1493,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
       t = next;
       advance(next);
     } while (!done);
+  } else if constexpr (SW > 1) {
+    results.clear(wave, lane);
   }
-  if constexpr (SW > 1) end_shares<D, HEADS_PER_PASS, 2, 8>(pv, ws, out, a, results, g_first, n_heads, wave, lane);
+  if constexpr (SW > 1) end_shares<D, HEADS_PER_PASS>(pv, ws, out, a, records, results, g_first, n_heads, wave, lane);
 }
 
 // Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
@@ -1490,7 +1543,7 @@ __global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __r
     pv.n_q_heads = n_q_heads;
     pv.group = group;
     if (threadIdx.x >= F) return;
-    const Partials<D> all(pv, ws, a, a.req[b].part0, n_part, g, h - g * group, 1);
+    const Partials<D> all(ws, a.ws_slots, (int64_t)g * a.parts_per_head + a.req[b].part0, n_part, group, h - g * group, 1);
     Sum s[1];
     all.template sum<1, 8, 16>(s, f, 0, 0, n_part);
     write_out<D>(pv, out, a, b, g, h - g * group, f, s[0]);
