@@ -257,7 +257,7 @@ int ensure_device(ellm_pool* p) {
   HIP_TRY(hipMemcpy(p->d_table, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   (void)p->core->take_dirty();   // the full upload covers everything so far
   // the workspace is sized once, for the largest launch the automatic partition can produce
-  p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::MAX_LAUNCH_REQ));
+  p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::GROUP_REQ));
   HIP_TRY(hipMalloc((void**)&p->d_ws, (size_t)p->ws_cap_slots * slot_bytes(p->geom.group, p->geom.head_dim)), "hipMalloc(workspace)");
   if (p->vmm) {
     const size_t vb = (size_t)p->geom.max_tensors * sizeof(uint64_t);
@@ -295,7 +295,7 @@ int ensure_device(ellm_pool* p) {
     const int e = ellm::static_workspace(&p->static_ws, &bytes);
     if (e) return hip_err((hipError_t)e, "hipGetSymbolAddress(fixed workspace)");
     p->static_ws_slots = (int64_t)(bytes / slot_bytes(p->geom.group, p->geom.head_dim));
-    p->launches.reserve(((size_t)p->geom.max_tensors + ellm::MAX_LAUNCH_REQ - 1) / ellm::MAX_LAUNCH_REQ);
+    p->launches.reserve(((size_t)p->geom.max_tensors + ellm::GROUP_REQ - 1) / ellm::GROUP_REQ + 1);
     p->units_tmp.reserve(ellm::MAX_LAUNCH_REQ);
     p->by64_tmp.reserve(ellm::MAX_LAUNCH_REQ);
   }
@@ -861,7 +861,7 @@ int32_t wave_slots(ellm_pool* p) {
   return slots;
 }
 
-// The partition of one launch (at most MAX_LAUNCH_REQ requests). For each kv head the units (up to
+// The partition of one launch (at most MAX_LAUNCH_REQ requests, see plan_next). For each kv head the units (up to
 // UNIT_TOKENS tokens of one chunk) of all requests form one sequence, dealt out evenly to as many waves
 // as the GPU has SIMDs (all kv heads together): every wave reads the same amount to within one unit,
 // all are resident from the start, and a wave whose share crosses from one request into the next
@@ -877,8 +877,9 @@ using ellm::TILE_TOKENS;
 
 // how many partial slots per kv head the cut of sequences of n[i] steps into `waves` shares needs; with
 // a != NULL the cut is written there. Either all shared requests go to the combine pass or, where all have up to merge_parts
-// parts, none does
-int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0) {
+// parts, none does. by_workgroup: slots for the partial results that workgroups of SHARE_WAVES waves leave, and not one for each
+// wave, which is how the workspace's documented size counts
+int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0, bool by_workgroup = false) {
   const int64_t each = total / waves, more = total - each * waves;
   // wave that holds step x: the first `more` waves hold each + 1 steps, the others each
   auto wave_of = [&](int64_t x) { return x < more * (each + 1) ? x / (each + 1) : more + (x - more * (each + 1)) / each; };
@@ -892,7 +893,13 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
       a->req[i].part0 = w1 > w0 ? (int32_t)std::min<int64_t>(parts, 0x7fffffff) : 0;
     }
     most = std::max(most, w1 - w0 + 1);
-    if (w1 > w0) parts += w1 - w0 + 1;   // a request shared by several waves: partial results
+    if (w1 > w0) {   // a request shared by several waves: partial results
+      constexpr int64_t S = ellm::SHARE_WAVES;
+      const int64_t n_part = w1 - w0 + 1;
+      if (!by_workgroup) parts += n_part;
+      else if (waves % S == 0) parts += w1 / S - w0 / S + 1;
+      else parts += std::min(n_part, (n_part + S - 2) / S + 1);    // the most workgroups that they can lie in
+    }
     at += n[i];
   }
   if (a) {
@@ -959,6 +966,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   };
   bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
   const int64_t slots = wave_slots(p), cus = p->compute_units;
+  const bool by_workgroup = n_req > ellm::GROUP_REQ;
   int64_t blocks = 0, longest = 0;     // what workgroups of several waves would take, in a launch small enough for that
   int32_t counted = 0;                 // not all of them once it is clear that there are too many
   for (; counted < n_req && (blocks + n_req - counted) * n_kv <= 2 * cus; counted++) {
@@ -1006,17 +1014,17 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
       // (for both entry points, which share the cut).
       const int64_t cap = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim)) / n_kv;
       const bool by_steps = steps <= room;
-      const int64_t need = by_steps ? step_parts : waves + n_req - 1 > cap ? cut_shares(units, total, waves, nullptr) : 0;
+      const int64_t need = by_steps ? step_parts : waves + n_req - 1 > cap ? cut_shares(units, total, waves, nullptr, 0, by_workgroup) : 0;
       bool coarser = false;
       if (need > cap) {
         std::vector<int32_t>& by64 = p->by64_tmp;
         by64.resize(n_req);
         int64_t n64 = 0;
         for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)tiles_in(a.req[i].len);
-        coarser = cut_shares(by64, n64, std::min(room, n64), nullptr) <= cap;
+        coarser = cut_shares(by64, n64, std::min(room, n64), nullptr, 0, by_workgroup) <= cap;
       }
       if (coarser) {
-        while (waves > 1 && cut_shares(units, total, waves, nullptr) > cap) waves -= (waves + 15) / 16;
+        while (waves > 1 && cut_shares(units, total, waves, nullptr, 0, by_workgroup) > cap) waves -= (waves + 15) / 16;
       } else if (by_steps) {
         a.step_units = ellm::STEP_UNITS;
         for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
@@ -1028,7 +1036,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   const bool single = ellm::single_waves(p->geom.group, block_units > 0, total * a.step_units, waves, n_req);
   const int32_t merge_parts = single ? 0 : ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0, tiles);
   a.wg_waves = block_units || single ? 1 : ellm::SHARE_WAVES;
-  const int64_t parts = cut_shares(units, total, waves, &a, merge_parts);
+  const int64_t parts = cut_shares(units, total, waves, &a, merge_parts, by_workgroup && a.wg_waves > 1);
   a.in_order_parts = block_units ? merge_parts : 0;
   a.n_req = n_req;
   a.q_row0 = q_row0;
@@ -1040,6 +1048,26 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   p->plan_total_units = total;
   p->plan_waves = waves;
   p->plan_slots = parts * n_kv;
+}
+
+// The next launch of a batch of which b0 requests have been planned: how many requests it takes. Launches are of up to
+// GROUP_REQ requests; a batch of up to twice as many is one launch if its partial results fit where those of the others
+// fit (the workspace, and the fixed one: both entry points share the cut). A second launch is a second time for the first
+// chunk to arrive and for the last waves to end. us a call, two launches / one: 200 requests of 64 to 8192 tokens, 4 q heads each, 8
+// kv heads of 128, 190.6 / 182.8, of 100 to 300, 1 q head 37.1 / 29.4; 150 of 1000 to 3000, 4 kv heads 105.1 / 97.1; 197 of 22 to 111, 16 kv
+// heads, 6 q heads each 35.8 / 27.2; 136 of 3 to 156, 1 kv head, in blocks 11.6 / 9.3. Groups of more than HEADS_PER_PASS q heads, whose
+// waves leave a partial result each, and cuts set by hand stay at GROUP_REQ.
+int32_t plan_next(ellm_pool* p, const int32_t* ids, int32_t batch, int32_t b0, ellm::BatchArgs& a, int32_t extra = 0) {
+  if (batch > ellm::GROUP_REQ && batch <= ellm::MAX_LAUNCH_REQ && p->geom.group <= ellm::HEADS_PER_PASS && p->split_override == 0 &&
+      p->waves_percent == 100 && b0 == 0) {
+    plan_launch(p, ids, batch, 0, a, extra);
+    const int64_t fixed = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim));
+    if (p->plan_slots <= std::min(fixed, launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::GROUP_REQ))))
+      return batch;
+  }
+  const int32_t n = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
+  plan_launch(p, ids + b0, n, b0, a, extra);
+  return n;
 }
 
 // a debug hook can make the n-th launch from now fail as if the runtime had refused it
@@ -1182,7 +1210,7 @@ int ellm_kv_append(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, const
   int32_t most_new = 0;
   for (int32_t b = 0; b < batch; b++) most_new = std::max(most_new, n_new ? n_new[b] : 1);
   if (!p->metadata_only && (rc = enter_compute(p, stream, ids, batch, most_new))) return rc;
-  // One launch per group of MAX_LAUNCH_REQ requests; a group's lengths advance as soon as its launch
+  // One launch per group of GROUP_REQ requests; a group's lengths advance as soon as its launch
   // has been accepted, so rows written and lengths agree at every point, also when the runtime
   // refuses a later launch.
   const size_t tok_bytes = (size_t)p->geom.n_kv_heads * p->geom.head_dim * 2;
@@ -1190,8 +1218,8 @@ int ellm_kv_append(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, const
   int64_t row0 = 0;
   int err = ELLM_OK;
   int32_t done = 0;
-  for (int32_t b0 = 0; b0 < batch && !err; b0 += ellm::MAX_LAUNCH_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
+  for (int32_t b0 = 0; b0 < batch && !err; b0 += ellm::GROUP_REQ) {
+    const int32_t nb = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
     a.n_req = nb;
     int32_t t = 0;
     for (int32_t i = 0; i < nb; i++) {
@@ -1282,9 +1310,8 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   if (rc) return rc;
   ellm::BatchArgs a;
   int32_t per_wave = 0;
-  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
-    plan_launch(p, ids + b0, nb, b0, a);
+  for (int32_t b0 = 0, nb; b0 < batch; b0 += nb) {
+    nb = plan_next(p, ids, batch, b0, a);
     per_wave = std::max(per_wave, (a.units_each + (a.units_extra > 0 ? 1 : 0)) * a.step_units * a.unit_tokens);
     if (n_split)
       for (int32_t i = 0; i < nb; i++)
@@ -1303,7 +1330,7 @@ const char* ellm_debug_decode_kernel(ellm_pool* p, const ellm_tensor_id* ids, in
   }
   if (core_err(p, p->core->decode_check(ids, batch, extra_tokens))) return nullptr;
   ellm::BatchArgs a;
-  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
+  plan_next(p, ids, batch, 0, a, extra_tokens);
   if (a.unit_tokens == TILE_TOKENS) return "decode_tile_kernel";
   return a.step_units > ellm::STEP_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
 }
@@ -1313,7 +1340,7 @@ int ellm_debug_combined_requests(ellm_pool* p, const ellm_tensor_id* ids, int32_
   int rc = core_err(p, p->core->decode_check(ids, batch, extra_tokens));
   if (rc) return rc;
   ellm::BatchArgs a;
-  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
+  plan_next(p, ids, batch, 0, a, extra_tokens);
   return a.n_split_req;
 }
 
@@ -1335,13 +1362,21 @@ static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, c
   std::vector<ellm::BatchArgs>& launches = p->launches;
   launches.clear();
   int64_t most_slots = 0;
-  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
+  for (int32_t b0 = 0, nb; b0 < batch; b0 += nb) {
     launches.emplace_back();
-    plan_launch(p, ids + b0, nb, b0, launches.back(), extra);
+    nb = plan_next(p, ids, batch, b0, launches.back(), extra);
     if (p->plan_total_units > 0x7fffffffll || p->plan_waves * p->geom.n_kv_heads > 0x7fffffffll || p->plan_slots > 0x7fffffffll)
       return set_err(ELLM_ERR_RANGE, "decode_attention: too much work for one call");
     most_slots = std::max(most_slots, p->plan_slots);
+  }
+  // (what the fixed workspace takes is what it would take in launches of GROUP_REQ requests)
+  if (ws_fixed && launches[0].n_req > ellm::GROUP_REQ && launch_slot_bound(device_simds(), p->geom.n_kv_heads, ellm::GROUP_REQ) > ws_fixed_slots) {
+    ellm::BatchArgs& a = launches.emplace_back();
+    for (int32_t b0 = 0; b0 < batch; b0 += ellm::GROUP_REQ) {
+      plan_launch(p, ids + b0, std::min<int32_t>(ellm::GROUP_REQ, batch - b0), b0, a, extra);
+      most_slots = std::max(most_slots, p->plan_slots);
+    }
+    launches.pop_back();
   }
   if (ws_fixed && most_slots > ws_fixed_slots)
     return set_err(ELLM_ERR_RANGE, "decode_attention_noalloc: the batch needs more partial results than the fixed "
@@ -1457,7 +1492,7 @@ uint64_t ellm_workspace_bytes(const ellm_pool_desc* d, int32_t max_batch) {
   if (!d || max_batch < 1 || !d->n_kv_heads || !d->n_q_heads || d->n_q_heads % d->n_kv_heads ||
       (d->head_dim != 64 && d->head_dim != 128))
     return 0;
-  const int32_t n_req = std::min<int32_t>(max_batch, ellm::MAX_LAUNCH_REQ);
+  const int32_t n_req = std::min<int32_t>(max_batch, ellm::GROUP_REQ);
   return (uint64_t)launch_slot_bound(device_simds(), d->n_kv_heads, n_req) *
          slot_bytes(d->n_q_heads / d->n_kv_heads, d->head_dim);
 }
@@ -1662,8 +1697,8 @@ int ellm_debug_kv_stream_read(ellm_pool* p, const ellm_tensor_id* ids, int32_t b
   if (rc) return rc;
   const ellm::PoolView pv = view_of(p);
   ellm::BatchArgs a;
-  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
+  for (int32_t b0 = 0; b0 < batch; b0 += ellm::GROUP_REQ) {
+    const int32_t nb = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
     plan_launch(p, ids + b0, nb, b0, a);
     int e = ellm::launch_kv_stream(pv, (uint32_t*)sink, a, stream);
     if (e) return hip_err((hipError_t)e, "kv stream launch");

@@ -293,28 +293,39 @@ __device__ __forceinline__ T held(T v) {
 // layers 52.3 -> 51.6, four short ones 7.38 -> 7.11; shares no different (8B-shaped step 1992, 1994).
 template <class Args>
 struct Records {
+  using Req = typename Args::Req;
   static constexpr int N = (Args::MAX_REQ + 63) / 64;
-  typename Args::Req rec[N];
+  int32_t len[N], tensor[N], unit_prefix[N], wave_first[N], n_part[N], part0[N];
   __device__ __forceinline__ Records(const Args& a, int lane) {
-#pragma unroll
-    for (int k = 0; k < N; k++) rec[k] = a.req[min(64 * k + lane, Args::MAX_REQ - 1)];
+    static_for<0, N>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      const Req& r = a.req[min(64 * k + lane, Args::MAX_REQ - 1)];
+      len[k] = r.len; tensor[k] = r.tensor; unit_prefix[k] = r.unit_prefix;
+      wave_first[k] = r.wave_first; n_part[k] = r.n_part; part0[k] = r.part0;
+    });
   }
   // request whose units include unit number pos of a kv head's sequence: the last b with unit_prefix[b] <= pos
   __device__ __forceinline__ int32_t find(int32_t n_req, int32_t pos, int lane) const {
     int32_t cnt = 0;
-#pragma unroll
-    for (int k = 0; k < N; k++) cnt += __popcll(__builtin_amdgcn_ballot_w64(64 * k + lane < n_req && rec[k].unit_prefix <= pos));
+    static_for<0, N>([&](auto kc) {
+      constexpr int k = decltype(kc)::value;
+      cnt += __popcll(__builtin_amdgcn_ballot_w64(64 * k + lane < n_req && unit_prefix[k] <= pos));
+    });
     return cnt - 1;
   }
-  __device__ __forceinline__ typename Args::Req of(int32_t b) const {      // b: the same in all lanes
-    auto get = [&](auto field) __attribute__((always_inline)) {
-      int32_t v = rec[0].*field;
-#pragma unroll
-      for (int k = 1; k < N; k++) v = b >= 64 * k ? rec[k].*field : v;
-      return __builtin_amdgcn_readlane(v, b & 63);
-    };
-    using R = typename Args::Req;
-    return {get(&R::len), get(&R::tensor), get(&R::unit_prefix), get(&R::wave_first), get(&R::n_part), get(&R::part0)};
+  __device__ __forceinline__ Req of(int32_t b) const {      // b: the same in all lanes
+    return {get(len, b), get(tensor, b), get(unit_prefix, b), get(wave_first, b), get(n_part, b), get(part0, b)};
+  }
+
+ private:
+  static __device__ __forceinline__ int32_t get(const int32_t (&field)[N], int32_t b) {
+    int32_t v = field[0];
+    // (values, not places, to choose from: a choice of places makes the compiler put the records into LDS and scratch memory)
+    static_for<1, N>([&](auto kc) {
+      const int32_t w = field[decltype(kc)::value];
+      v = b >= 64 * decltype(kc)::value ? w : v;
+    });
+    return __builtin_amdgcn_readlane(v, b & 63);
   }
 };
 
@@ -609,11 +620,11 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws_, uint1
 // V of the tile is in flight while its scores are computed, K of the next tile while V is multiplied.
 // Scores are kept in log2 units (scale_log2 = scale * log2 e).
 // ---------------------------------------------------------------------------------------------
-template <int D, int G, bool APPEND, bool DIRECT>
+template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                                     const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
                                                     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
-                                                    int32_t g_first, const BatchArgs& a) {
+                                                    int32_t g_first, const Args& a) {
   constexpr int NW = SHARE_WAVES;
   constexpr int LPR = D / 8;             // lanes per row = 16-byte pieces per row
   constexpr int RPW = 64 / LPR;          // rows per wave-wide load
@@ -638,7 +649,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const Records<BatchArgs> records(a, lane);
+  const Records<Args> records(a, lane);
   wanted(a.n_req, a.waves_per_head, a.units_each, a.units_extra, a.by_waves.mul, a.by_waves.shift, a.q_row0, g_first);
   wanted(pv.chunk_bytes, pv.tokens_per_chunk, pv.tiles_per_chunk, pv.max_slots, pv.n_q_heads, pv.n_kv_heads, pv.group, q);
   wanted(pv.base, pv.table, pv.vbase, k_new, pv.by_chunk.mul, pv.by_chunk.shift, pv.by_tiles.mul, pv.by_tiles.shift);
@@ -676,7 +687,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
 #define ELLM_NEXT_TILE()                                                                            \
   if (left == 1) {                                                                                  \
     cb += 1;                                                                                        \
-    const BatchArgs::Req nx_ = a.req[cb];                                                           \
+    const typename Args::Req nx_ = a.req[cb];                                                           \
     len = nx_.len;                                                                                  \
     left = units_of(len, pv, pv.tiles_per_chunk, TILE_TOKENS);                                                   \
     c_np = nx_.n_part;                                                                              \
@@ -846,13 +857,13 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
   results.clear(wave, lane);             // (behind the first loads it is slower: LDS writes wait for loads to LDS)
   const int32_t index = blockIdx.x * NW + wave;
   if (index < a.waves_per_head * pv.n_kv_heads) {
-    const Share<BatchArgs> sh = locate_share(a, records, index, lane);
+    const Share<Args> sh = locate_share(a, records, index, lane);
     const int32_t g = sh.g, n_tiles = sh.n_units;
     const int hq0 = g * pv.group + g_first;            // first q head handled here
     // cursor: the tile whose K is in LDS or on its way there. cb: its request; len, walk: that
     // request's length and its table row or base address (read-only for the kernel's lifetime: uniform loads)
     int32_t cb = sh.b;
-    const BatchArgs::Req& first = sh.first;
+    const typename Args::Req& first = sh.first;
     int32_t len = first.len;
     TensorWalk walk = tensor_walk<DIRECT>(pv, first.tensor);
     const int32_t tile0 = sh.u_lo - first.unit_prefix;
@@ -1023,16 +1034,16 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
 // that cap (it is what their schedule was tuned under); the 4- and 8-head instances, which keep the
 // whole query rows and the matrix-core accumulators in registers, are compiled without it and do
 // not spill.
-template <int D, int G, bool APPEND, bool DIRECT>
+template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void decode_tile_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
-    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, Args a) {
   decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
 }
-template <int D, int G, bool APPEND, bool DIRECT>
+template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_tile_kernel_wide(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
-    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, BatchArgs a) {
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, Args a) {
   decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
 }
 
@@ -1501,10 +1512,10 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
 
 // Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
 // the accumulation registers, which ordinary instructions cannot read.
-template <int D, int U, int SW, bool APPEND, bool DIRECT>
+template <int D, int U, int SW, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
-    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, BatchArgs a) {
+    float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, Args a) {
   decode_unit_body<D, U, APPEND, DIRECT, 0, SW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
 }
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
@@ -1529,9 +1540,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // ---------------------------------------------------------------------------------------------
 constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
 
-template <int D, int W, bool IN_ORDER = false>
+template <int D, int W, class Args, bool IN_ORDER = false>
 __global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
-                                                                int32_t n_q_heads, int32_t group, BatchArgs a) {
+                                                                int32_t n_q_heads, int32_t group, Args a) {
   constexpr int F = D / 4, RP = W * 64 / F, AHEAD = COMBINE_AHEAD;
   __shared__ __attribute__((aligned(16))) float4 sums[RP][F];
   const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
@@ -1622,17 +1633,17 @@ __global__ __launch_bounds__(256) void read_kernel(const uint4* __restrict__ src
 // the K/V rows a decode over this batch reads, with the same work partition and load shape (one
 // wave per share of the same cut, up to 64 rows at a time, 128-bit loads), but no arithmetic
 template <int D, bool DIRECT>
-__global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __restrict__ sink, BatchArgs a) {
+__global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __restrict__ sink, GroupArgs a) {
   constexpr int LPR = D / 8, RPW = 64 / LPR, NL = 64 / RPW, ROWB = D * 2;
   const int lane = threadIdx.x;
   const int sub = lane % LPR, rg = lane / LPR;
   const int32_t Tc = pv.tokens_per_chunk;
   uint32_t x = 0;
   {
-    const Share<BatchArgs> sh = locate_share(a, Records<BatchArgs>(a, lane), blockIdx.x, lane);
+    const Share<GroupArgs> sh = locate_share(a, Records<GroupArgs>(a, lane), blockIdx.x, lane);
     const int32_t g = sh.g;
     int32_t cb = sh.b;
-    BatchArgs::Req rec = sh.first;
+    GroupArgs::Req rec = sh.first;
     const int32_t ut = a.unit_tokens, upc = (Tc + ut - 1) / ut;
     const int32_t u0 = (sh.u_lo - rec.unit_prefix) * a.step_units;
     int32_t left = units_of(rec.len, pv, upc, ut) - u0, todo = sh.n_units;
@@ -1748,12 +1759,12 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
 
 template <int D>
 static const void* partial_kernel_ptr(int group, bool tiles) {
-  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, true, false>;
+  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, true, false, GroupArgs>;
   if constexpr (D == 128) {
-    if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false>;
-    if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false>;
+    if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false, GroupArgs>;
+    if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false, GroupArgs>;
   }
-  return group == 2 ? (const void*)decode_tile_kernel<D, 2, true, false> : (const void*)decode_tile_kernel<D, 1, true, false>;
+  return group == 2 ? (const void*)decode_tile_kernel<D, 2, true, false, GroupArgs> : (const void*)decode_tile_kernel<D, 1, true, false, GroupArgs>;
 }
 
 int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
@@ -1773,16 +1784,17 @@ static void launch_timed(Kernel kernel, unsigned grid, unsigned threads, hipStre
   else hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, args...);
 }
 
-// the same launch, described for the kernels that take few requests (the combine pass, which reads split_req, is not one)
-static FewArgs few_of(const BatchArgs& a) {
-  FewArgs f;
-  f.n_req = a.n_req; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens; f.step_units = a.step_units;
-  f.units_per_head = a.units_per_head; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
-  f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots; f.by_waves = a.by_waves;
-  f.wg_waves = a.wg_waves; f.merge_parts = a.merge_parts; f.in_order_parts = a.in_order_parts; f.n_split_req = a.n_split_req;
-  std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
-  for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};
+// the same launch, described for kernels that take fewer requests
+template <class Args>
+static Args args_of(const BatchArgs& a) {
+  Args f;
+  f.n_req = a.n_req; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
+  f.by_waves = a.by_waves; f.step_units = a.step_units; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens;
+  f.units_per_head = a.units_per_head; f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots;
+  f.merge_parts = a.merge_parts; f.n_split_req = a.n_split_req; f.wg_waves = a.wg_waves; f.in_order_parts = a.in_order_parts;
+  std::copy_n(a.split_req, Args::MAX_REQ / 4, f.split_req);
   for (int i = 0; i < a.n_req; i++) f.req[i] = {a.req[i].len, a.req[i].tensor, a.req[i].unit_prefix, a.req[i].wave_first, a.req[i].n_part, a.req[i].part0};
+  for (int i = a.n_req; i < Args::MAX_REQ; i++) f.req[i] = {};
   return f;
 }
 
@@ -1792,16 +1804,21 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
                             hipEvent_t ev_stop) {
   const unsigned waves = (unsigned)(a.waves_per_head * pv.n_kv_heads), grid = (waves + SHARE_WAVES - 1) / SHARE_WAVES;
   if (a.unit_tokens == TILE_TOKENS) {
-    auto go = [&](auto kernel) {
-      launch_timed(kernel, grid, 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
-                   (uint16_t*)out, scale_log2, 0, a);
+    auto tiles = [&](const auto& args) {
+      using Args = std::decay_t<decltype(args)>;
+      auto go = [&](auto kernel) {
+        launch_timed(kernel, grid, 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
+                     (uint16_t*)out, scale_log2, 0, args);
+      };
+      if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT, Args>);
+      else if (pv.group == 2) go(decode_tile_kernel<D, 2, APPEND, DIRECT, Args>);
+      if constexpr (D == 128) {
+        if (pv.group == 4) go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT, Args>);
+        else if (pv.group == 8) go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT, Args>);
+      }
     };
-    if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT>);
-    else if (pv.group == 2) go(decode_tile_kernel<D, 2, APPEND, DIRECT>);
-    if constexpr (D == 128) {
-      if (pv.group == 4) go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT>);
-      else if (pv.group == 8) go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT>);
-    }
+    if (a.n_req <= GROUP_REQ) tiles(args_of<GroupArgs>(a));
+    else tiles(a);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }
@@ -1816,24 +1833,35 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
       if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
       else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
     };
-    if (a.n_req <= FewArgs::MAX_REQ) in_blocks(few_of(a));
+    if (a.n_req <= FewArgs::MAX_REQ) in_blocks(args_of<FewArgs>(a));
+    else if (a.n_req <= GROUP_REQ) in_blocks(args_of<GroupArgs>(a));
     else in_blocks(a);
     ELLM_HIP_CHECK_LAUNCH();
     return 0;
   }
   // a group of more than HEADS_PER_PASS q heads is covered by several launches over the same K/V: the
   // first of them takes the start time, the last one the end time
-  for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
-    const int n = std::min(HEADS_PER_PASS, pv.group - done);
-    auto go = [&](auto kernel, unsigned n_wg, unsigned threads) {
-      launch_timed(kernel, n_wg, threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q,
-                   (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, done, n, a);
-    };
-    if (a.wg_waves == 1) go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT>, waves, 64);
-    else go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT>, grid, 64 * SHARE_WAVES);
-    ELLM_HIP_CHECK_LAUNCH();
-  }
-  return 0;
+  auto shares = [&](const auto& args) {
+    using Args = std::decay_t<decltype(args)>;
+    for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
+      const int n = std::min(HEADS_PER_PASS, pv.group - done);
+      auto go = [&](auto kernel, unsigned n_wg, unsigned threads) {
+        launch_timed(kernel, n_wg, threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q,
+                     (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, done, n, args);
+      };
+      // (launches of more than GROUP_REQ requests have one pass, and workgroups of four waves)
+      if constexpr (Args::MAX_REQ <= GROUP_REQ)
+        if (a.wg_waves == 1) {
+          go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT, Args>, waves, 64);
+          ELLM_HIP_CHECK_LAUNCH();
+          continue;
+        }
+      go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT, Args>, grid, 64 * SHARE_WAVES);
+      ELLM_HIP_CHECK_LAUNCH();
+    }
+    return 0;
+  };
+  return a.n_req <= GROUP_REQ ? shares(args_of<GroupArgs>(a)) : shares(a);
 }
 
 template <int D>
@@ -1858,12 +1886,17 @@ int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const 
   // where every wave leaves partials there can be few of them each for many requests: as many waves as these fill
   const bool single = a.wg_waves == 1 && a.step_units <= STEP_UNITS;
   const int fill = single ? a.parts_per_head / a.n_split_req * pv.head_dim / (COMBINE_AHEAD * 256) : 4;    // by 1, by 4, more
-  auto go = [&](auto kernel, unsigned waves) {
-    hipLaunchKernelGGL(kernel, dim3(a.n_split_req, pv.n_q_heads), dim3(64 * waves), 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
+  auto pass = [&](const auto& args) {
+    using Args = std::decay_t<decltype(args)>;
+    auto go = [&](auto kernel, unsigned waves) {
+      hipLaunchKernelGGL(kernel, dim3(a.n_split_req, pv.n_q_heads), dim3(64 * waves), 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, args);
+    };
+    if (a.in_order_parts) pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, Args, true>, 8) : go(decode_combine_kernel<64, 4, Args, true>, 4);
+    else if (pv.head_dim == 128) fill < 1 ? go(decode_combine_kernel<128, 2, Args>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4, Args>, 4) : go(decode_combine_kernel<128, 8, Args>, 8);
+    else fill < 1 ? go(decode_combine_kernel<64, 1, Args>, 1) : go(decode_combine_kernel<64, 4, Args>, 4);
   };
-  if (a.in_order_parts) pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, true>, 8) : go(decode_combine_kernel<64, 4, true>, 4);
-  else if (pv.head_dim == 128) fill < 1 ? go(decode_combine_kernel<128, 2>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4>, 4) : go(decode_combine_kernel<128, 8>, 8);
-  else fill < 1 ? go(decode_combine_kernel<64, 1>, 1) : go(decode_combine_kernel<64, 4>, 4);
+  if (a.n_req <= GROUP_REQ) pass(args_of<GroupArgs>(a));
+  else pass(a);
   ELLM_HIP_CHECK_LAUNCH();
   return 0;
 }
@@ -1886,7 +1919,8 @@ int launch_read(const void* src, int64_t bytes, uint32_t* sink, hipStream_t stre
   return 0;
 }
 
-int launch_kv_stream(const PoolView& pv, uint32_t* sink, const BatchArgs& a, hipStream_t stream) {
+int launch_kv_stream(const PoolView& pv, uint32_t* sink, const BatchArgs& batch, hipStream_t stream) {
+  const GroupArgs a = args_of<GroupArgs>(batch);
   const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
   if (a.n_req <= 0 || grid == 0) return 0;
   if (pv.head_dim == 128 && pv.vbase) hipLaunchKernelGGL((kv_stream_kernel<128, true>), dim3(grid), dim3(64), 0, stream, pv, sink, a);

@@ -10,7 +10,8 @@
 
 namespace ellm {
 
-constexpr int MAX_LAUNCH_REQ = 128;   // requests described by one launch's kernel arguments (3.2 KB in all)
+constexpr int MAX_LAUNCH_REQ = 256;   // requests described by one decode launch's kernel arguments (6.5 KB in all)
+constexpr int GROUP_REQ = 128;        // larger batches go in launches of so many (decode: 3.2 KB of arguments), and appends do
 constexpr int MAX_PATCH = 448;        // table entries patched by one launch
 constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of one chunk a wave handles at a time
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
@@ -66,6 +67,7 @@ struct PoolView {
 template <int REQS>
 struct BatchArgsOf {
   static constexpr int MAX_REQ = REQS;
+  BatchArgsOf() {}            // (filled in field by field: not worth clearing first)
   // (first what a wave needs before anything else: one load of eight words)
   int32_t n_req;
   int32_t waves_per_head;     // <= units_per_head
@@ -98,15 +100,17 @@ struct BatchArgsOf {
   int32_t in_order_parts;     // requests of up to so many partials are added up in the attention kernel's order
 };
 using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ>;
+// what kernels take up to GROUP_REQ requests
+using GroupArgs = BatchArgsOf<GROUP_REQ>;
 // what a launch in blocks of few requests hands to its kernel instead: the host writes the arguments to device memory for
 // each launch; with 0.6 KB instead of 4 a call of 4 requests of up to 256 tokens took 7.37 us instead of 7.67 (0.5 and 3.2 KB now)
 using FewArgs = BatchArgsOf<16>;
 
 struct AppendArgs {
   int32_t n_req, total_new;
-  int32_t tensor[MAX_LAUNCH_REQ];
-  int32_t len_before[MAX_LAUNCH_REQ];
-  int32_t tok0[MAX_LAUNCH_REQ];    // first new-token row of request b, relative to this launch
+  int32_t tensor[GROUP_REQ];
+  int32_t len_before[GROUP_REQ];
+  int32_t tok0[GROUP_REQ];    // first new-token row of request b, relative to this launch
 };
 
 struct PatchArgs {
