@@ -1,4 +1,5 @@
-"""ctypes binding of libellm.so: the functions of include/ellm.h under the same names.
+"""Binding of libellm.so: the functions of include/ellm.h under the same names, through ctypes; the calls that a serving loop
+makes for every layer convert plain arguments in native code (_calls, csrc/python_calls.cpp).
 
 Argument marshalling only. Device buffers are passed as torch tensors (or raw integer addresses),
 host arrays as numpy arrays or sequences; a negative return code raises EllmError carrying the
@@ -14,10 +15,15 @@ import numpy as np
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libellm.so")
 
-if not os.path.exists(LIB_PATH):
-    raise ImportError(
-        f"{LIB_PATH} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
-        "or python paper_2506_15155_amd/build.py). There is no fallback implementation.")
+CALLS_PATH = os.path.join(HERE, "_calls.so")
+
+for _path in (LIB_PATH, CALLS_PATH):
+    if not os.path.exists(_path):
+        raise ImportError(
+            f"{_path} is missing: build it first (python -c 'import __graft_entry__ as g; g.build()' "
+            "or python paper_2506_15155_amd/build.py). There is no fallback implementation.")
+
+from . import _calls  # noqa: E402
 
 lib = C.CDLL(LIB_PATH)
 
@@ -123,6 +129,9 @@ lib.ellm_workspace_bytes.argtypes = [C.POINTER(_Desc), C.c_int32]
 lib.ellm_debug_decode_kernel.restype = C.c_char_p
 lib.ellm_debug_decode_kernel.argtypes = [_vp, _i32p, C.c_int32, C.c_int32]
 
+_calls.bind(np.ndarray, *(C.cast(getattr(lib, n), C.c_void_p).value for n in (
+    "ellm_decode_attention", "ellm_decode_attention_noalloc", "ellm_kv_append_decode", "ellm_kv_append", "ellm_kv_premap_next")))
+
 EXPORTED = sorted(list(_sigs) + ["ellm_last_error", "ellm_workspace_bytes", "ellm_debug_decode_kernel"])
 
 
@@ -167,6 +176,7 @@ def _stream(stream) -> int | None:
         import torch
         if torch.cuda.is_initialized():
             try:        # torch's own short cut to the handle: 0.2 us, against 2.7 for the stream object
+                _calls.bind_torch(vars(torch.cuda), vars(torch._C))
                 return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
             except AttributeError:
                 pass
@@ -252,6 +262,10 @@ def ellm_kv_premap_ahead(pool, ids, tokens_ahead, flags=0, check=True):
 
 def ellm_kv_premap_next(pool, ids, flags=0, check=True):
     """Returns the number of chunks mapped (check=True) or (rc, n)."""
+    if check:
+        rc = _calls.premap_next(pool, ids, flags)
+        if rc is not None:
+            return _ret(rc, True)
     keep, p, n = _i32(ids)
     out = C.c_int32(0)
     rc = lib.ellm_kv_premap_next(pool, p, n, int(flags), C.byref(out))
@@ -335,28 +349,39 @@ def ellm_pool_set_act_busy(pool, chunk_ids, busy, check=True):
 
 
 def ellm_kv_append(pool, ids, k_new, v_new, n_new=None, stream=None, check=True):
-    keep, p, n = _i32(ids)
-    keep_n, pn, _ = _i32(n_new)
-    s = _stream(stream)
-    return _ret(lib.ellm_kv_append(pool, p, n, pn, _ptr(k_new), _ptr(v_new), s), check)
+    rc = _calls.append(pool, ids, k_new, v_new, n_new, stream)
+    if rc is None:
+        keep, p, n = _i32(ids)
+        keep_n, pn, _ = _i32(n_new)
+        s = _stream(stream)
+        rc = lib.ellm_kv_append(pool, p, n, pn, _ptr(k_new), _ptr(v_new), s)
+    return rc if rc >= 0 else _ret(rc, check)
 
 
 def ellm_decode_attention(pool, ids, q, out, scale=0.0, stream=None, check=True):
-    keep, p, n = _i32(ids)
-    s = _stream(stream)
-    return _ret(lib.ellm_decode_attention(pool, p, n, _ptr(q), _ptr(out), float(scale), s), check)
+    rc = _calls.decode(False, pool, ids, q, out, scale, stream)
+    if rc is None:
+        keep, p, n = _i32(ids)
+        s = _stream(stream)
+        rc = lib.ellm_decode_attention(pool, p, n, _ptr(q), _ptr(out), float(scale), s)
+    return rc if rc >= 0 else _ret(rc, check)
 
 
 def ellm_decode_attention_noalloc(pool, ids, q, out, scale=0.0, stream=None, check=True):
-    keep, p, n = _i32(ids)
-    s = _stream(stream)
-    return _ret(lib.ellm_decode_attention_noalloc(pool, p, n, _ptr(q), _ptr(out), float(scale), s), check)
+    rc = _calls.decode(True, pool, ids, q, out, scale, stream)
+    if rc is None:
+        keep, p, n = _i32(ids)
+        s = _stream(stream)
+        rc = lib.ellm_decode_attention_noalloc(pool, p, n, _ptr(q), _ptr(out), float(scale), s)
+    return rc if rc >= 0 else _ret(rc, check)
 
 
 def ellm_kv_append_decode(pool, ids, k_new, v_new, q, out, scale=0.0, stream=None, check=True):
-    keep, p, n = _i32(ids)
-    return _ret(lib.ellm_kv_append_decode(pool, p, n, _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out), float(scale),
-                                          _stream(stream)), check)
+    rc = _calls.append_decode(pool, ids, k_new, v_new, q, out, scale, stream)
+    if rc is None:
+        keep, p, n = _i32(ids)
+        rc = lib.ellm_kv_append_decode(pool, p, n, _ptr(k_new), _ptr(v_new), _ptr(q), _ptr(out), float(scale), _stream(stream))
+    return rc if rc >= 0 else _ret(rc, check)
 
 
 def ellm_chunk_deflate_to_host(pool, tid, first_slot, n_slots, check=True):

@@ -1,0 +1,97 @@
+"""The binding's native argument conversion against its general one, on the CPU: every form of arguments that is accepted gives the
+same results and tables either way, and what is refused is refused by both."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2506_15155_amd as E
+from paper_2506_15155_amd import binding
+
+NATIVE = ("decode", "append_decode", "append", "premap_next")
+
+
+class Nothing:
+    """In the place of the native calls: handles no form."""
+
+    def __getattr__(self, name):
+        return (lambda *a: None) if name in NATIVE else getattr(binding._calls, name)
+
+
+class Address:
+    def __init__(self, at):
+        self.at = at
+
+    def data_ptr(self):
+        return self.at
+
+
+def forms(values):
+    a = np.asarray(values, np.int32)
+    wide = np.zeros(2 * len(a), np.int32)
+    wide[::2] = a
+    fixed = a.copy()
+    fixed.flags.writeable = False
+    return {"array": a, "list": list(values), "int64": a.astype(np.int64), "int16": a.astype(np.int16), "strided": wide[::2],
+            "read-only": fixed, "two dimensions": a.reshape(1, -1), "swapped": a.astype(a.dtype.newbyteorder()),
+            "unsigned": a.astype(np.uint32), "subclass": a.view(np.recarray), "tensor": torch.tensor(a), "tuple": tuple(values)}
+
+
+FORMS = list(forms([0]))
+POINTERS = {"int": 0x1000, "none": None, "object": Address(0x2000), "tensor": torch.zeros(4, dtype=torch.bfloat16), "numpy": np.zeros(4, np.uint16),
+            "numpy int": np.int64(0x1000), "bool": True, "text": "x", "huge": 1 << 70, "negative": -16, "method": Address("x")}
+
+
+def walk(ids_form, n_form, pointer, stream):
+    """What a sequence of calls returns or raises, and the tables afterwards."""
+    P = E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, flags=1, device_bytes=12 << 14)
+    for _ in range(3):
+        E.ellm_tensor_create(P, 48)
+    seen = []
+
+    def call(f, *a, **k):
+        try:
+            seen.append(f(P, *a, **k))
+        except Exception as e:
+            seen.append((type(e).__name__, getattr(e, "code", None)))
+
+    ids = lambda *v: forms(v)[ids_form]
+    p = POINTERS[pointer]
+    call(E.ellm_kv_premap_next, ids(0, 1, 2))
+    call(E.ellm_kv_premap_next, ids(0, 1, 2), flags=1, check=False)
+    call(E.ellm_kv_append, ids(0, 2), p, 0x3000, forms([3, 5])[n_form], stream=stream)
+    call(E.ellm_kv_append, ids(1), 0x3000, p, stream=stream)
+    call(E.ellm_kv_append, ids(1, 1), 0x3000, 0x3000, stream=stream, check=False)
+    call(E.ellm_kv_append, ids(9), 0x3000, 0x3000, stream=stream)
+    for f in (E.ellm_decode_attention, E.ellm_decode_attention_noalloc):
+        for scale in (0.0, 1, np.float32(0.5), float("inf"), "x"):
+            call(f, ids(0, 2), p, 0x3000, scale=scale, stream=stream)
+        call(f, ids(0, 2), 0x3000, p, stream=stream, check=False)
+    call(E.ellm_kv_append_decode, ids(0), p, 0x3000, 0x3000, 0x3000, stream=stream)
+    call(E.ellm_kv_append_decode, ids(0), 0x3000, 0x3000, 0x3000, p, 0.5, stream=stream, check=False)
+    call(E.ellm_kv_premap_next, ids(0, 7))
+    tables = [(list(t), n) for t, n in (E.ellm_tensor_get_table(P, i) for i in range(3))]
+    E.ellm_pool_destroy(P)
+    return seen, tables
+
+
+@pytest.mark.parametrize("ids_form,n_form,pointer,stream",
+                         [(f, "array", "int", 0) for f in FORMS] + [("array", f, "object", 0) for f in FORMS] +
+                         [("array", "array", p, 0) for p in POINTERS] + [("array", "array", "tensor", s) for s in (None, 7, Address(1), "x")])
+def test_the_same_either_way(monkeypatch, ids_form, n_form, pointer, stream):
+    native = walk(ids_form, n_form, pointer, stream)
+    monkeypatch.setattr(binding, "_calls", Nothing())
+    assert walk(ids_form, n_form, pointer, stream) == native
+
+
+def test_plain_arguments_are_handled_natively():
+    P = E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, flags=1, device_bytes=12 << 14)
+    E.ellm_tensor_create(P, 48)
+    ids, t = np.zeros(1, np.int32), torch.zeros(4, dtype=torch.bfloat16)
+    assert binding._calls.premap_next(P, ids, 0) == 1
+    assert binding._calls.append(P, ids, t, t, None, 0) == 0 and binding._calls.append(P, ids, t, t, ids + 2, 0) == 0
+    assert binding._calls.decode(False, P, ids, t, t, 0.0, 0) == E.ERR.NO_DEVICE == binding._calls.decode(True, P, ids, t, t, 0.0, 0)
+    assert binding._calls.append_decode(P, ids, t, t, t, t, 0.0, 0) == E.ERR.NO_DEVICE
+    assert E.ellm_tensor_get_table(P, 0)[1] == 3
+    with pytest.raises(TypeError):
+        binding._calls.decode(P, ids)
+    E.ellm_pool_destroy(P)
