@@ -157,6 +157,7 @@ struct ellm_pool {
   bool vmm_async = true;                     // false: every call waits for the jobs it asked for
   std::vector<uint64_t> vmm_slot_job;        // per (tensor, slot): the map job that makes it readable
   std::vector<uint64_t> vmm_tensor_job;      // per tensor: the newest of those
+  ellm::PoolView view = {};            // what of it does not change, from pool_create on
   int32_t split_override = 0;
   int32_t wave_slots = 0;              // waves of a decode launch: one per SIMD of the GPU (0 = not asked yet)
   int32_t compute_units = 0;           // of the GPU, known with wave_slots
@@ -198,20 +199,24 @@ int core_changed(ellm_pool* p, int rc) {
 // fixed_ws: for a launch whose partial results are in the library's fixed workspace. A captured call of the entry point
 // that uses it may be replayed while another entry point's launch runs on the same pool: they share nothing they write.
 ellm::PoolView view_of(const ellm_pool* p, bool fixed_ws = false) {
-  ellm::PoolView v;
+  ellm::PoolView v = p->view;
   v.base = p->device_base;
   v.table = p->d_table;
   v.vbase = (p->vmm && !p->vmm_table_kernels) ? p->d_vbase : nullptr;
   v.merged = p->d_merged + (fixed_ws ? p->merged_words : 0);
-  v.chunk_bytes = p->geom.chunk_bytes;
-  v.tokens_per_chunk = p->geom.tokens_per_chunk;
-  v.tiles_per_chunk = (p->geom.tokens_per_chunk + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
-  v.units_per_chunk = (p->geom.tokens_per_chunk + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
-  v.max_slots = p->geom.max_slots;
-  v.n_q_heads = p->geom.n_q_heads;
-  v.n_kv_heads = p->geom.n_kv_heads;
-  v.head_dim = p->geom.head_dim;
-  v.group = p->geom.group;
+  return v;
+}
+ellm::PoolView constant_view(const ellm::Geometry& g) {
+  ellm::PoolView v = {};
+  v.chunk_bytes = g.chunk_bytes;
+  v.tokens_per_chunk = g.tokens_per_chunk;
+  v.tiles_per_chunk = (g.tokens_per_chunk + ellm::TILE_TOKENS - 1) / ellm::TILE_TOKENS;
+  v.units_per_chunk = (g.tokens_per_chunk + ellm::UNIT_TOKENS - 1) / ellm::UNIT_TOKENS;
+  v.max_slots = g.max_slots;
+  v.n_q_heads = g.n_q_heads;
+  v.n_kv_heads = g.n_kv_heads;
+  v.head_dim = g.head_dim;
+  v.group = g.group;
   v.by_chunk = ellm::divisor(v.tokens_per_chunk);
   v.by_tiles = ellm::divisor(v.tiles_per_chunk);
   v.by_units = ellm::divisor(v.units_per_chunk);
@@ -1120,6 +1125,7 @@ int ellm_pool_create(const ellm_pool_desc* d, ellm_pool** out) {
   p->geom.group = d->n_q_heads / d->n_kv_heads;
   p->geom.max_tensors = (int32_t)d->max_tensors;
   p->geom.max_slots = (int32_t)d->max_slots_per_tensor;
+  p->view = constant_view(p->geom);
   p->core.reset(new PoolCore(p->geom, d->initial_owner));
   p->device_base = (char*)d->device_base;
   p->host_base = (char*)d->host_base;

@@ -1713,48 +1713,49 @@ int static_workspace(float** ptr, size_t* bytes) {
 // ---------------------------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------------------------
-#define ELLM_HIP_CHECK_LAUNCH()                      \
-  do {                                               \
-    hipError_t e_ = hipGetLastError();               \
-    if (e_ != hipSuccess) return (int)e_;            \
-  } while (0)
+// A launch by the kernel's address and the places of its arguments. The launch syntax copies every argument by value twice on
+// the way to the same call and takes the launch's shape through thread-local storage: a decode call of one request 2.77 -> 2.52 us
+// on the host, of four short ones 2.95 -> 2.70. ev0 / ev1 (either may be NULL): events that take the kernel's own start and end times (the runtime's extended
+// launch attaches them to the kernel's dispatch, so no marker of its own goes into the stream and the time between them is the
+// kernel's duration).
+template <typename... P, typename... A>
+static int launch(void (*kernel)(P...), dim3 grid, unsigned threads, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, const A&... a) {
+  static_assert((std::is_same_v<std::remove_cv_t<P>, A> && ...), "the arguments are read as the kernel's own types");
+  void* args[] = {const_cast<void*>(static_cast<const void*>(&a))...};
+  const hipError_t e = ev0 || ev1 ? hipExtLaunchKernel((const void*)kernel, grid, dim3(threads), args, 0, stream, ev0, ev1, 0)
+                                  : hipLaunchKernel((const void*)kernel, grid, dim3(threads), args, 0, stream);
+  if (e != hipSuccess) (void)hipGetLastError();      // reported here, and not by the next one who asks
+  return (int)e;
+}
+template <typename... P, typename... A>
+static int launch(void (*kernel)(P...), dim3 grid, unsigned threads, hipStream_t stream, const A&... a) {
+  return launch(kernel, grid, threads, stream, (hipEvent_t) nullptr, (hipEvent_t) nullptr, a...);
+}
 
 int launch_table_patch(int32_t* table, const PatchArgs& a, hipStream_t stream) {
   if (a.n <= 0) return 0;
-  hipLaunchKernelGGL(table_patch_kernel, dim3((a.n + 255) / 256), dim3(256), 0, stream, table, a);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return launch(table_patch_kernel, dim3((a.n + 255) / 256), 256, stream, table, a);
 }
 
 int launch_fill(uint32_t* words, uint32_t value, size_t n, hipStream_t stream) {
   if (n == 0) return 0;
-  hipLaunchKernelGGL(fill_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, words, value, n);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return launch(fill_kernel, dim3((unsigned)((n + 255) / 256)), 256, stream, words, value, n);
 }
 
 int launch_kv_append(const PoolView& pv, const void* k_new, const void* v_new, const AppendArgs& a,
                      hipStream_t stream) {
   if (a.total_new <= 0) return 0;
-  const dim3 grid((unsigned)a.total_new), block(256);
-  const uint4 *k = (const uint4*)k_new, *v = (const uint4*)v_new;
-  if (pv.head_dim == 128 && pv.vbase) hipLaunchKernelGGL((kv_append_kernel<128, true>), grid, block, 0, stream, pv, k, v, a);
-  else if (pv.head_dim == 128) hipLaunchKernelGGL((kv_append_kernel<128, false>), grid, block, 0, stream, pv, k, v, a);
-  else if (pv.vbase) hipLaunchKernelGGL((kv_append_kernel<64, true>), grid, block, 0, stream, pv, k, v, a);
-  else hipLaunchKernelGGL((kv_append_kernel<64, false>), grid, block, 0, stream, pv, k, v, a);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  auto go = [&](auto kernel) { return launch(kernel, dim3((unsigned)a.total_new), 256, stream, pv, (const uint4*)k_new, (const uint4*)v_new, a); };
+  if (pv.head_dim == 128) return pv.vbase ? go(kv_append_kernel<128, true>) : go(kv_append_kernel<128, false>);
+  return pv.vbase ? go(kv_append_kernel<64, true>) : go(kv_append_kernel<64, false>);
 }
 
 int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyArgs& a, bool to_host, int workgroups, hipStream_t stream) {
   if (a.n <= 0) return 0;
   // a workgroup should still have 16 KiB to move
-  int wpc = std::max(1, workgroups / a.n);
+  int32_t wpc = std::max(1, workgroups / a.n);
   wpc = std::max(1, std::min<int>(wpc, (int)(chunk_bytes / (16u << 10))));
-  hipLaunchKernelGGL(chunk_copy_kernel, dim3((unsigned)(a.n * wpc)), dim3(256), 0, stream, pool, host, chunk_bytes, wpc,
-                     to_host ? 1 : 0, a);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return launch(chunk_copy_kernel, dim3((unsigned)(a.n * wpc)), 256, stream, pool, host, chunk_bytes, wpc, (int32_t)(to_host ? 1 : 0), a);
 }
 
 template <int D>
@@ -1773,15 +1774,6 @@ int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, f, 64 * SHARE_WAVES, 0) != hipSuccess || n < 1) n = 1;
   return n * SHARE_WAVES;
-}
-
-// ev0 / ev1 (either may be NULL): events that take the kernel's own start and end times (the
-// runtime's extended launch attaches them to the kernel's dispatch, so no marker of its own goes
-// into the stream and the time between them is the kernel's duration)
-template <typename Kernel, typename... Args>
-static void launch_timed(Kernel kernel, unsigned grid, unsigned threads, hipStream_t stream, hipEvent_t ev0, hipEvent_t ev1, Args... args) {
-  if (ev0 || ev1) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, ev0, ev1, 0, args...);
-  else hipLaunchKernelGGL(kernel, dim3(grid), dim3(threads), 0, stream, args...);
 }
 
 // the same launch, described for kernels that take fewer requests
@@ -1807,37 +1799,30 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     auto tiles = [&](const auto& args) {
       using Args = std::decay_t<decltype(args)>;
       auto go = [&](auto kernel) {
-        launch_timed(kernel, grid, 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new, (const uint4*)v_new, ws,
-                     (uint16_t*)out, scale_log2, 0, args);
+        return launch(kernel, dim3(grid), 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new,
+                      (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)0, args);
       };
-      if (pv.group == 1) go(decode_tile_kernel<D, 1, APPEND, DIRECT, Args>);
-      else if (pv.group == 2) go(decode_tile_kernel<D, 2, APPEND, DIRECT, Args>);
       if constexpr (D == 128) {
-        if (pv.group == 4) go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT, Args>);
-        else if (pv.group == 8) go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT, Args>);
+        if (pv.group == 4) return go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT, Args>);
+        if (pv.group == 8) return go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT, Args>);
       }
+      return pv.group == 1 ? go(decode_tile_kernel<D, 1, APPEND, DIRECT, Args>) : go(decode_tile_kernel<D, 2, APPEND, DIRECT, Args>);
     };
-    if (a.n_req <= GROUP_REQ) tiles(args_of<GroupArgs>(a));
-    else tiles(a);
-    ELLM_HIP_CHECK_LAUNCH();
-    return 0;
+    return a.n_req <= GROUP_REQ ? tiles(args_of<GroupArgs>(a)) : tiles(a);
   }
   if (a.step_units > STEP_UNITS) {
     auto go = [&](auto kernel, unsigned n_waves, const auto& args) {
-      launch_timed(kernel, waves, 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
-                   (uint16_t*)out, scale_log2, 0, pv.group, args);
+      return launch(kernel, dim3(waves), 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
+                    (uint16_t*)out, scale_log2, (int32_t)0, pv.group, args);
     };
     auto in_blocks = [&](const auto& args) {
       using Args = std::decay_t<decltype(args)>;
       constexpr int U = tile_units<D>, NW = BLOCK_UNITS / U;
-      if (a.step_units <= BLOCK_UNITS) go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
-      else go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
+      if (a.step_units <= BLOCK_UNITS) return go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
+      return go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
     };
-    if (a.n_req <= FewArgs::MAX_REQ) in_blocks(args_of<FewArgs>(a));
-    else if (a.n_req <= GROUP_REQ) in_blocks(args_of<GroupArgs>(a));
-    else in_blocks(a);
-    ELLM_HIP_CHECK_LAUNCH();
-    return 0;
+    if (a.n_req <= FewArgs::MAX_REQ) return in_blocks(args_of<FewArgs>(a));
+    return a.n_req <= GROUP_REQ ? in_blocks(args_of<GroupArgs>(a)) : in_blocks(a);
   }
   // a group of more than HEADS_PER_PASS q heads is covered by several launches over the same K/V: the
   // first of them takes the start time, the last one the end time
@@ -1846,18 +1831,15 @@ static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new
     for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
       const int n = std::min(HEADS_PER_PASS, pv.group - done);
       auto go = [&](auto kernel, unsigned n_wg, unsigned threads) {
-        launch_timed(kernel, n_wg, threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv, (const uint16_t*)q,
-                     (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, done, n, args);
+        return launch(kernel, dim3(n_wg), threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv,
+                      (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)done, (int32_t)n, args);
       };
+      int e = -1;
       // (launches of more than GROUP_REQ requests have one pass, and workgroups of four waves)
       if constexpr (Args::MAX_REQ <= GROUP_REQ)
-        if (a.wg_waves == 1) {
-          go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT, Args>, waves, 64);
-          ELLM_HIP_CHECK_LAUNCH();
-          continue;
-        }
-      go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT, Args>, grid, 64 * SHARE_WAVES);
-      ELLM_HIP_CHECK_LAUNCH();
+        if (a.wg_waves == 1) e = go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT, Args>, waves, 64);
+      if (e < 0) e = go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT, Args>, grid, 64 * SHARE_WAVES);
+      if (e) return e;
     }
     return 0;
   };
@@ -1889,46 +1871,37 @@ int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const 
   auto pass = [&](const auto& args) {
     using Args = std::decay_t<decltype(args)>;
     auto go = [&](auto kernel, unsigned waves) {
-      hipLaunchKernelGGL(kernel, dim3(a.n_split_req, pv.n_q_heads), dim3(64 * waves), 0, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, args);
+      return launch(kernel, dim3(a.n_split_req, pv.n_q_heads), 64 * waves, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, args);
     };
-    if (a.in_order_parts) pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, Args, true>, 8) : go(decode_combine_kernel<64, 4, Args, true>, 4);
-    else if (pv.head_dim == 128) fill < 1 ? go(decode_combine_kernel<128, 2, Args>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4, Args>, 4) : go(decode_combine_kernel<128, 8, Args>, 8);
-    else fill < 1 ? go(decode_combine_kernel<64, 1, Args>, 1) : go(decode_combine_kernel<64, 4, Args>, 4);
+    if (a.in_order_parts) return pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, Args, true>, 8) : go(decode_combine_kernel<64, 4, Args, true>, 4);
+    if (pv.head_dim == 128)
+      return fill < 1 ? go(decode_combine_kernel<128, 2, Args>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4, Args>, 4) : go(decode_combine_kernel<128, 8, Args>, 8);
+    return fill < 1 ? go(decode_combine_kernel<64, 1, Args>, 1) : go(decode_combine_kernel<64, 4, Args>, 4);
   };
-  if (a.n_req <= GROUP_REQ) pass(args_of<GroupArgs>(a));
-  else pass(a);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return a.n_req <= GROUP_REQ ? pass(args_of<GroupArgs>(a)) : pass(a);
 }
 
 int launch_copy(void* dst, const void* src, int64_t bytes, hipStream_t stream) {
   const int64_t n = bytes / 16;
   if (n <= 0) return 0;
   const int64_t blocks = std::min<int64_t>((n + 1023) / 1024, 256 * 32);
-  hipLaunchKernelGGL(copy_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (uint4*)dst, (const uint4*)src, n);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return launch(copy_kernel, dim3((unsigned)blocks), 256, stream, (uint4*)dst, (const uint4*)src, n);
 }
 
 int launch_read(const void* src, int64_t bytes, uint32_t* sink, hipStream_t stream) {
   const int64_t n = bytes / 16;
   if (n <= 0) return 0;
   const int64_t blocks = std::min<int64_t>((n + 2047) / 2048, 256 * 32);
-  hipLaunchKernelGGL(read_kernel, dim3((unsigned)blocks), dim3(256), 0, stream, (const uint4*)src, n, sink);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  return launch(read_kernel, dim3((unsigned)blocks), 256, stream, (const uint4*)src, n, sink);
 }
 
 int launch_kv_stream(const PoolView& pv, uint32_t* sink, const BatchArgs& batch, hipStream_t stream) {
   const GroupArgs a = args_of<GroupArgs>(batch);
   const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
   if (a.n_req <= 0 || grid == 0) return 0;
-  if (pv.head_dim == 128 && pv.vbase) hipLaunchKernelGGL((kv_stream_kernel<128, true>), dim3(grid), dim3(64), 0, stream, pv, sink, a);
-  else if (pv.head_dim == 128) hipLaunchKernelGGL((kv_stream_kernel<128, false>), dim3(grid), dim3(64), 0, stream, pv, sink, a);
-  else if (pv.vbase) hipLaunchKernelGGL((kv_stream_kernel<64, true>), dim3(grid), dim3(64), 0, stream, pv, sink, a);
-  else hipLaunchKernelGGL((kv_stream_kernel<64, false>), dim3(grid), dim3(64), 0, stream, pv, sink, a);
-  ELLM_HIP_CHECK_LAUNCH();
-  return 0;
+  auto go = [&](auto kernel) { return launch(kernel, dim3(grid), 64, stream, pv, sink, a); };
+  if (pv.head_dim == 128) return pv.vbase ? go(kv_stream_kernel<128, true>) : go(kv_stream_kernel<128, false>);
+  return pv.vbase ? go(kv_stream_kernel<64, true>) : go(kv_stream_kernel<64, false>);
 }
 
 }  // namespace ellm
