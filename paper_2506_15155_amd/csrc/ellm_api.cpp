@@ -312,14 +312,13 @@ int ensure_device(ellm_pool* p) {
     p->host_out.assign(p->geom.n_host_slots, 0);
     p->copy_seen.assign(p->geom.max_tensors, ellm_pool::CopySeen());
     p->compute_covers.assign(ellm_pool::EV_RING, 0);
-    // The marks behind copies order them with kernels and copies of this GPU only (the host waits for a copy's data with
-    // ellm_pool_sync, for its end with these): no system-scope fence, whose write-back of the caches is 3 of the 11 us from a
-    // kernel to one on another stream behind it. Offload and fetch of one 2 MiB chunk each and a decode 136 -> 127 us a pass, 27
-    // chunks of 8 requests 1700 -> 1664, 24 of 16 requests 1610 -> 1540. The marks behind attention keep it: a copy engine may read next what kernels wrote.
+    // All marks carry the system-scope fence. Without it behind copies a hop from one stream to the next is 3 of 11 us shorter (27
+    // chunks out and in 1700 -> 1664 us a pass), but a copy engine may read next, in host memory or in a chunk, what the copy
+    // kernel wrote, and only the fence orders that.
     for (ellm_pool::Ring* r : {&p->r_compute, &p->r_in, &p->r_out})
       for (int i = 0; i < ellm_pool::EV_RING; i++) {
         hipEvent_t e;
-        HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming | (r == &p->r_compute ? 0 : hipEventDisableSystemFence)), "hipEventCreate");
+        HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming), "hipEventCreate");
         r->ev.push_back(e);
       }
   }
