@@ -432,10 +432,11 @@ struct Partials {
       for (int u = 0; u < N; u++)
 #pragma unroll
         for (int k = 0; k < KB; k++) {
-          // (the same row for every u: what differs between them is the same for all lanes)
-          const int32_t xk = x + k * step, row = xk / F, more = (j0 + u) * group;
-          ml[k][u] = __builtin_amdgcn_raw_buffer_load_b64(pairs, row * (WS_ML * 4), more * (WS_ML * 4), CPOL_DEVICE);
-          v[k][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, row * (D * 4) + xk % F * 16, more * (D * 4), CPOL_DEVICE);
+          // (all of the offset lies in the lanes: it is what the buffer's range is compared with, while a part of it in a
+          // scalar register is taken off the range first, of which rows past the last would leave less than nothing)
+          const int32_t xk = x + k * step, row = (j0 + u) * group + xk / F;
+          ml[k][u] = __builtin_amdgcn_raw_buffer_load_b64(pairs, row * (WS_ML * 4), 0, CPOL_DEVICE);
+          v[k][u] = __builtin_amdgcn_raw_buffer_load_b128(rows, row * (D * 4) + xk % F * 16, 0, CPOL_DEVICE);
         }
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
