@@ -58,3 +58,28 @@ def test_one_launch(pool_mode, kernel, n_kv, group, dim, tokens, n, lo, hi, one)
     assert rc == 0 and torch.equal(fused, again)
     B.close()
 
+
+
+@pytest.mark.parametrize("n,dim,group", [(200, 128, 4), (256, 64, 3)])
+def test_replays(n, dim, group):
+    """Captured, with the longest arguments that a launch has: every replay gives the eager call's bits, with other calls between."""
+    rng = np.random.default_rng(n)
+    lens = [int(x) for x in rng.integers(30, 700, size=n)]
+    B, ids, q = load(2, group, dim, 64, lens, 32)
+    assert launches(B, ids, q) == 1
+    rc, want = B.decode(ids, q)
+    assert rc == 0
+    dq, out = H.dev_bits(q), torch.empty_like(want)
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, stream=stream):
+        assert E.ellm_decode_attention(B.pool, ids, dq, out, check=False) == 0
+        assert E.ellm_decode_attention_noalloc(B.pool, ids, dq, out, check=False) == 0
+    for _ in range(4):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        rc, eager = B.decode(ids[: n // 2], q[: n // 2])
+        assert rc == 0
+    B.close()
