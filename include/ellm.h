@@ -27,7 +27,7 @@
  * thread drives it. Every call validates its whole argument set on the host before it changes any
  * state or launches anything; a call that returns an error from these checks has changed nothing.
  * The one error that can come later is ELLM_ERR_HIP from a kernel launch the runtime refuses: a
- * call that works in several launches (more than 128 requests, decode calls often only more than 256) has
+ * call that works in several launches (more than 128 requests; in a decode call two groups of 128 may share one) has
  * then done the work of the launches before it, completely, and nothing of the rest (see ellm_kv_append).
  *
  * Device memory of the library: the mirror of the chunk tables (behind it the counters of partial
@@ -158,11 +158,12 @@ int ellm_pool_destroy(ellm_pool* pool);
 
 /* Bytes of device workspace a pool of this geometry allocates for the partial results of split
  * decode attention (Sec. 5 "Efficient Kernels": the sequence is split and partial softmax results
- * are combined), for batches of up to max_batch requests: a decode launch of up to 128
- * requests runs one wave per SIMD of the GPU; every wave has room for one partial result per
+ * are combined), for batches of up to max_batch requests: a decode launch is planned for at most 128
+ * requests and runs one wave per SIMD of the GPU; every wave has room for one partial result per
  * request its share touches (most workgroups write one for all their waves), so a launch takes at most
  * SIMDs + n_kv_heads * (min(max_batch, 128) - 1) partial slots of G * (head_dim + 2) floats, and the launches of one call reuse the same slots.
- * A batch of up to 256 requests is one launch where its workgroups' partial results fit the same slots.
+ * The two groups of a batch of 129 to 256 requests share a launch where they run the same kernel and the partial results that their
+ * workgroups leave fit the same slots; each keeps the plan, and so the output bits, of a call of its own.
  * Uses the current HIP device's SIMD count (a nominal 1024 without a device). Only the head
  * counts and head_dim of desc are read. 0 for a bad argument. */
 uint64_t ellm_workspace_bytes(const ellm_pool_desc* desc, int32_t max_batch);
@@ -324,7 +325,7 @@ int ellm_decode_attention(ellm_pool* pool, const ellm_tensor_id* ids, int32_t ba
  * for it. Same arguments, checks, kernels, partition and output bits as ellm_decode_attention.
  * Additional errors: INVALID if the pool's device-side metadata has not been created yet (creating
  * it allocates; ellm_pool_prepare and every append / migration call do it, so a pool whose tensors
- * hold tokens has it); RANGE if a launch of the batch (in launches of 128 requests) needs more partial results than the fixed workspace
+ * hold tokens has it); RANGE if a launch of the batch (one for every 128 requests) needs more partial results than the fixed workspace
  * holds (a launch of n requests needs at most SIMDs + n_kv_heads * (n - 1) slots of G * (head_dim + 2) * 4
  * bytes: 3.2 MB for 64 requests of 32 q / 8 kv heads of 128 on 1024 SIMDs). Every GPU the library
  * runs on holds one such workspace from load to process end, shared by all pools and all calls of
@@ -349,7 +350,7 @@ int ellm_decode_attention_noalloc(ellm_pool* pool, const ellm_tensor_id* ids, in
  * with one token per request; NULL k_new / v_new with batch > 0 -> INVALID; then the checks of
  * ellm_decode_attention on the lengths after the append. A call that fails these checks has changed
  * nothing; a refused launch (HIP) leaves the groups of 128 requests before it appended and decoded
- * and the rest untouched, as in ellm_kv_append (a batch of 129 to 256 requests is one launch as a rule, and then one group). */
+ * and the rest untouched, as in ellm_kv_append (two groups that share a launch, see ellm_workspace_bytes, count as one). */
 int ellm_kv_append_decode(ellm_pool* pool, const ellm_tensor_id* ids, int32_t batch, const void* k_new,
                           const void* v_new, const void* q, void* out, float scale, void* stream);
 

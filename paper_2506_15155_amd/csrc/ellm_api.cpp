@@ -81,8 +81,8 @@ struct ellm_pool {
   // device-side metadata, created by the first call that needs the device
   bool dev_ready = false;
   int32_t* d_table = nullptr;
-  uint32_t* d_merged = nullptr;        // in the same allocation: two sets of counters (see PoolView::merged) of merged_words
-  size_t merged_words = 0;             // words each, one set for each workspace a launch's partial results can be in
+  uint32_t* d_merged = nullptr;        // in the same allocation: sets of counters (see PoolView::merged) of merged_words words
+  size_t merged_words = 0;             // each, two (see PairArgs) for each workspace a launch's partial results can be in
   float* d_ws = nullptr;               // partial results of one decode launch (see BatchArgs)
   int64_t ws_cap_slots = 0;            // partial slots it holds
   float* static_ws = nullptr;          // this device's copy of the library's fixed workspace
@@ -158,6 +158,7 @@ struct ellm_pool {
   std::vector<uint64_t> vmm_slot_job;        // per (tensor, slot): the map job that makes it readable
   std::vector<uint64_t> vmm_tensor_job;      // per tensor: the newest of those
   ellm::PoolView view = {};            // what of it does not change, from pool_create on
+  ellm::PairArgs pair;                 // see pair_up
   int32_t split_override = 0;
   int32_t wave_slots = 0;              // waves of a decode launch: one per SIMD of the GPU (0 = not asked yet)
   int32_t compute_units = 0;           // of the GPU, known with wave_slots
@@ -203,7 +204,7 @@ ellm::PoolView view_of(const ellm_pool* p, bool fixed_ws = false) {
   v.base = p->device_base;
   v.table = p->d_table;
   v.vbase = (p->vmm && !p->vmm_table_kernels) ? p->d_vbase : nullptr;
-  v.merged = p->d_merged + (fixed_ws ? p->merged_words : 0);
+  v.merged = p->d_merged + (fixed_ws ? 2 * p->merged_words : 0);
   return v;
 }
 ellm::PoolView constant_view(const ellm::Geometry& g) {
@@ -249,20 +250,20 @@ size_t slot_bytes(int32_t group, int32_t head_dim) { return (size_t)group * (hea
 
 int ensure_device(ellm_pool* p) {
   if (p->dev_ready) return ELLM_OK;
-  // the table mirror and, behind it, the two sets of counters of partial results, all 0
+  // the table mirror and, behind it, the sets of counters of partial results, all 0
   const std::vector<int32_t>& table = p->core->table();
   const size_t counters_at = (table.size() + 63) / 64 * 64;
   const size_t lines = std::max((size_t)p->geom.n_kv_heads * ellm::MAX_LAUNCH_REQ, (size_t)device_simds() / ellm::SIMDS_PER_CU);   // blocks: one per CU
   p->merged_words = lines * ellm::MERGE_STRIDE;
-  HIP_TRY(hipMalloc((void**)&p->d_table, (counters_at + 2 * p->merged_words) * sizeof(int32_t)), "hipMalloc(table mirror)");
+  HIP_TRY(hipMalloc((void**)&p->d_table, (counters_at + 4 * p->merged_words) * sizeof(int32_t)), "hipMalloc(table mirror)");
   p->d_merged = (uint32_t*)p->d_table + counters_at;
   // the counters by a kernel on the default stream, which the copy of the table comes after and the host waits for
-  const int e = ellm::launch_fill(p->d_merged, 0, 2 * p->merged_words, nullptr);
+  const int e = ellm::launch_fill(p->d_merged, 0, 4 * p->merged_words, nullptr);
   if (e) return hip_err((hipError_t)e, "counter fill launch");
   HIP_TRY(hipMemcpy(p->d_table, table.data(), table.size() * sizeof(int32_t), hipMemcpyHostToDevice), "hipMemcpy(table mirror)");
   (void)p->core->take_dirty();   // the full upload covers everything so far
   // the workspace is sized once, for the largest launch the automatic partition can produce
-  p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::GROUP_REQ));
+  p->ws_cap_slots = launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::MAX_LAUNCH_REQ));
   HIP_TRY(hipMalloc((void**)&p->d_ws, (size_t)p->ws_cap_slots * slot_bytes(p->geom.group, p->geom.head_dim)), "hipMalloc(workspace)");
   if (p->vmm) {
     const size_t vb = (size_t)p->geom.max_tensors * sizeof(uint64_t);
@@ -300,7 +301,7 @@ int ensure_device(ellm_pool* p) {
     const int e = ellm::static_workspace(&p->static_ws, &bytes);
     if (e) return hip_err((hipError_t)e, "hipGetSymbolAddress(fixed workspace)");
     p->static_ws_slots = (int64_t)(bytes / slot_bytes(p->geom.group, p->geom.head_dim));
-    p->launches.reserve(((size_t)p->geom.max_tensors + ellm::GROUP_REQ - 1) / ellm::GROUP_REQ + 1);
+    p->launches.reserve(((size_t)p->geom.max_tensors + ellm::MAX_LAUNCH_REQ - 1) / ellm::MAX_LAUNCH_REQ);
     p->units_tmp.reserve(ellm::MAX_LAUNCH_REQ);
     p->by64_tmp.reserve(ellm::MAX_LAUNCH_REQ);
   }
@@ -355,7 +356,7 @@ int set_counters(ellm_pool* p, uint32_t value, hipStream_t stream) {
   if (rc) return rc;
   p->last_stream = stream;
   p->have_last_stream = true;
-  const int e = ellm::launch_fill(p->d_merged, value, 2 * p->merged_words, stream);
+  const int e = ellm::launch_fill(p->d_merged, value, 4 * p->merged_words, stream);
   return e ? hip_err((hipError_t)e, "counter fill launch") : ELLM_OK;
 }
 
@@ -870,7 +871,7 @@ int32_t wave_slots(ellm_pool* p) {
   return slots;
 }
 
-// The partition of one launch (at most MAX_LAUNCH_REQ requests, see plan_next). For each kv head the units (up to
+// The partition of one launch (at most MAX_LAUNCH_REQ requests). For each kv head the units (up to
 // UNIT_TOKENS tokens of one chunk) of all requests form one sequence, dealt out evenly to as many waves
 // as the GPU has SIMDs (all kv heads together): every wave reads the same amount to within one unit,
 // all are resident from the start, and a wave whose share crosses from one request into the next
@@ -886,9 +887,8 @@ using ellm::TILE_TOKENS;
 
 // how many partial slots per kv head the cut of sequences of n[i] steps into `waves` shares needs; with
 // a != NULL the cut is written there. Either all shared requests go to the combine pass or, where all have up to merge_parts
-// parts, none does. by_workgroup: slots for the partial results that workgroups of SHARE_WAVES waves leave, and not one for each
-// wave, which is how the workspace's documented size counts
-int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0, bool by_workgroup = false) {
+// parts, none does.
+int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, ellm::BatchArgs* a, int32_t merge_parts = 0) {
   const int64_t each = total / waves, more = total - each * waves;
   // wave that holds step x: the first `more` waves hold each + 1 steps, the others each
   auto wave_of = [&](int64_t x) { return x < more * (each + 1) ? x / (each + 1) : more + (x - more * (each + 1)) / each; };
@@ -902,13 +902,7 @@ int64_t cut_shares(const std::vector<int32_t>& n, int64_t total, int64_t waves, 
       a->req[i].part0 = w1 > w0 ? (int32_t)std::min<int64_t>(parts, 0x7fffffff) : 0;
     }
     most = std::max(most, w1 - w0 + 1);
-    if (w1 > w0) {   // a request shared by several waves: partial results
-      constexpr int64_t S = ellm::SHARE_WAVES;
-      const int64_t n_part = w1 - w0 + 1;
-      if (!by_workgroup) parts += n_part;
-      else if (waves % S == 0) parts += w1 / S - w0 / S + 1;
-      else parts += std::min(n_part, (n_part + S - 2) / S + 1);    // the most workgroups that they can lie in
-    }
+    if (w1 > w0) parts += w1 - w0 + 1;   // a request shared by several waves: partial results
     at += n[i];
   }
   if (a) {
@@ -975,7 +969,6 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   };
   bool tiles = ellm::tile_kernel(p->geom.head_dim, p->geom.group, Tc);
   const int64_t slots = wave_slots(p), cus = p->compute_units;
-  const bool by_workgroup = n_req > ellm::GROUP_REQ;
   int64_t blocks = 0, longest = 0;     // what workgroups of several waves would take, in a launch small enough for that
   int32_t counted = 0;                 // not all of them once it is clear that there are too many
   for (; counted < n_req && (blocks + n_req - counted) * n_kv <= 2 * cus; counted++) {
@@ -1023,17 +1016,17 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
       // (for both entry points, which share the cut).
       const int64_t cap = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim)) / n_kv;
       const bool by_steps = steps <= room;
-      const int64_t need = by_steps ? step_parts : waves + n_req - 1 > cap ? cut_shares(units, total, waves, nullptr, 0, by_workgroup) : 0;
+      const int64_t need = by_steps ? step_parts : waves + n_req - 1 > cap ? cut_shares(units, total, waves, nullptr) : 0;
       bool coarser = false;
       if (need > cap) {
         std::vector<int32_t>& by64 = p->by64_tmp;
         by64.resize(n_req);
         int64_t n64 = 0;
         for (int32_t i = 0; i < n_req; i++) n64 += by64[i] = (int32_t)tiles_in(a.req[i].len);
-        coarser = cut_shares(by64, n64, std::min(room, n64), nullptr, 0, by_workgroup) <= cap;
+        coarser = cut_shares(by64, n64, std::min(room, n64), nullptr) <= cap;
       }
       if (coarser) {
-        while (waves > 1 && cut_shares(units, total, waves, nullptr, 0, by_workgroup) > cap) waves -= (waves + 15) / 16;
+        while (waves > 1 && cut_shares(units, total, waves, nullptr) > cap) waves -= (waves + 15) / 16;
       } else if (by_steps) {
         a.step_units = ellm::STEP_UNITS;
         for (int32_t i = 0; i < n_req; i++) units[i] = (units[i] + ellm::STEP_UNITS - 1) / ellm::STEP_UNITS;
@@ -1045,7 +1038,7 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   const bool single = ellm::single_waves(p->geom.group, block_units > 0, total * a.step_units, waves, n_req);
   const int32_t merge_parts = single ? 0 : ellm::merge_parts(p->geom.head_dim, p->geom.group, block_units > 0, tiles);
   a.wg_waves = block_units || single ? 1 : ellm::SHARE_WAVES;
-  const int64_t parts = cut_shares(units, total, waves, &a, merge_parts, by_workgroup && a.wg_waves > 1);
+  const int64_t parts = cut_shares(units, total, waves, &a, merge_parts);
   a.in_order_parts = block_units ? merge_parts : 0;
   a.n_req = n_req;
   a.q_row0 = q_row0;
@@ -1059,24 +1052,30 @@ void plan_launch(ellm_pool* p, const int32_t* ids, int32_t n_req, int32_t q_row0
   p->plan_slots = parts * n_kv;
 }
 
-// The next launch of a batch of which b0 requests have been planned: how many requests it takes. Launches are of up to
-// GROUP_REQ requests; a batch of up to twice as many is one launch if its partial results fit where those of the others
-// fit (the workspace, and the fixed one: both entry points share the cut). A second launch is a second time for the first
-// chunk to arrive and for the last waves to end. us a call, two launches / one: 200 requests of 64 to 8192 tokens, 4 q heads each, 8
-// kv heads of 128, 190.6 / 182.8, of 100 to 300, 1 q head 37.1 / 29.4; 150 of 1000 to 3000, 4 kv heads 105.1 / 97.1; 197 of 22 to 111, 16 kv
-// heads, 6 q heads each 35.8 / 27.2; 136 of 3 to 156, 1 kv head, in blocks 11.6 / 9.3. Groups of more than HEADS_PER_PASS q heads, whose
-// waves leave a partial result each, and cuts set by hand stay at GROUP_REQ.
-int32_t plan_next(ellm_pool* p, const int32_t* ids, int32_t batch, int32_t b0, ellm::BatchArgs& a, int32_t extra = 0) {
-  if (batch > ellm::GROUP_REQ && batch <= ellm::MAX_LAUNCH_REQ && p->geom.group <= ellm::HEADS_PER_PASS && p->split_override == 0 &&
-      p->waves_percent == 100 && b0 == 0) {
-    plan_launch(p, ids, batch, 0, a, extra);
-    const int64_t fixed = (int64_t)(ellm::STATIC_WS_BYTES / slot_bytes(p->geom.group, p->geom.head_dim));
-    if (p->plan_slots <= std::min(fixed, launch_slot_bound(device_simds(), p->geom.n_kv_heads, std::min<int32_t>(p->geom.max_tensors, ellm::GROUP_REQ))))
-      return batch;
+// Whether the two groups of a batch of up to 2 * MAX_LAUNCH_REQ requests go in one launch (then p->pair is it): where both run the
+// same kernel in one pass and the partial results of both, counted by workgroup, fit `cap` slots. Each keeps its plan, so what a
+// request is rounded to does not depend on it. A second launch is a second time for the first chunk to arrive, after a time in
+// which the first one's last waves end. us a call in a replayed graph, two launches / one: 8 kv heads of 128, 4 q heads each, 200
+// requests of 64 to 4000 tokens 254.9 / 252.3, 256 of 20 to 120 29.5 / 27.9; 1 q head, 200 of 100 to 300 36.9 / 30.8; 8, 200 of 100 to
+// 600 66.8 / 65.1; 4 kv heads, 150 of 1000 to 3000 105.9 / 101.8; 6 q heads, 256 of 200 to 900 107.5 / 99.8, 16 kv heads, 197 of 22 to 111
+// 37.8 / 29.1; 2 kv heads of 64, 16 q heads, 256 of 200 to 2000 39.0 / 31.7; blocks: 1 kv head, 4 q heads, 136 of 3 to 156 8.9 / 4.5, of
+// up to 32 units: 2 kv heads, 8 q heads, 200 of 300 to 500 22.2 / 19.9.
+bool pair_up(ellm_pool* p, int64_t cap) {
+  if (p->launches.size() != 2 || p->geom.group > ellm::HEADS_PER_PASS || p->split_override != 0 || p->waves_percent != 100) return false;
+  auto kernel = [](const ellm::BatchArgs& a) {
+    return a.unit_tokens == TILE_TOKENS ? 0 : a.step_units <= ellm::STEP_UNITS ? 1 : a.step_units <= ellm::BLOCK_UNITS ? 2 : 3;
+  };
+  if (kernel(p->launches[0]) != kernel(p->launches[1])) return false;
+  ellm::PairArgs& a = p->pair;
+  int64_t slots[2];
+  for (int i = 0; i < 2; i++) {
+    a.half[i] = p->launches[i];
+    slots[i] = ellm::slots_by_workgroup(a.half[i], p->geom.n_kv_heads) * p->geom.n_kv_heads;
   }
-  const int32_t n = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
-  plan_launch(p, ids + b0, n, b0, a, extra);
-  return n;
+  a.counters = (uint32_t)p->merged_words;
+  const int64_t each = (int64_t)(slot_bytes(p->geom.group, p->geom.head_dim) / sizeof(float));
+  a.floats = (uint64_t)(slots[0] * each + 63) / 64 * 64;       // (rows are read 16 bytes at a time)
+  return (int64_t)a.floats + slots[1] * each <= cap * each;
 }
 
 // a debug hook can make the n-th launch from now fail as if the runtime had refused it
@@ -1220,7 +1219,7 @@ int ellm_kv_append(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, const
   int32_t most_new = 0;
   for (int32_t b = 0; b < batch; b++) most_new = std::max(most_new, n_new ? n_new[b] : 1);
   if (!p->metadata_only && (rc = enter_compute(p, stream, ids, batch, most_new))) return rc;
-  // One launch per group of GROUP_REQ requests; a group's lengths advance as soon as its launch
+  // One launch per group of MAX_LAUNCH_REQ requests; a group's lengths advance as soon as its launch
   // has been accepted, so rows written and lengths agree at every point, also when the runtime
   // refuses a later launch.
   const size_t tok_bytes = (size_t)p->geom.n_kv_heads * p->geom.head_dim * 2;
@@ -1228,8 +1227,8 @@ int ellm_kv_append(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, const
   int64_t row0 = 0;
   int err = ELLM_OK;
   int32_t done = 0;
-  for (int32_t b0 = 0; b0 < batch && !err; b0 += ellm::GROUP_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
+  for (int32_t b0 = 0; b0 < batch && !err; b0 += ellm::MAX_LAUNCH_REQ) {
+    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
     a.n_req = nb;
     int32_t t = 0;
     for (int32_t i = 0; i < nb; i++) {
@@ -1320,8 +1319,9 @@ int ellm_decode_plan(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, int
   if (rc) return rc;
   ellm::BatchArgs a;
   int32_t per_wave = 0;
-  for (int32_t b0 = 0, nb; b0 < batch; b0 += nb) {
-    nb = plan_next(p, ids, batch, b0, a);
+  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
+    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
+    plan_launch(p, ids + b0, nb, b0, a);
     per_wave = std::max(per_wave, (a.units_each + (a.units_extra > 0 ? 1 : 0)) * a.step_units * a.unit_tokens);
     if (n_split)
       for (int32_t i = 0; i < nb; i++)
@@ -1340,7 +1340,7 @@ const char* ellm_debug_decode_kernel(ellm_pool* p, const ellm_tensor_id* ids, in
   }
   if (core_err(p, p->core->decode_check(ids, batch, extra_tokens))) return nullptr;
   ellm::BatchArgs a;
-  plan_next(p, ids, batch, 0, a, extra_tokens);
+  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
   if (a.unit_tokens == TILE_TOKENS) return "decode_tile_kernel";
   return a.step_units > ellm::STEP_UNITS ? "decode_block_kernel" : "decode_unit_kernel";
 }
@@ -1350,7 +1350,7 @@ int ellm_debug_combined_requests(ellm_pool* p, const ellm_tensor_id* ids, int32_
   int rc = core_err(p, p->core->decode_check(ids, batch, extra_tokens));
   if (rc) return rc;
   ellm::BatchArgs a;
-  plan_next(p, ids, batch, 0, a, extra_tokens);
+  plan_launch(p, ids, std::min<int32_t>(batch, ellm::MAX_LAUNCH_REQ), 0, a, extra_tokens);
   return a.n_split_req;
 }
 
@@ -1372,21 +1372,12 @@ static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, c
   std::vector<ellm::BatchArgs>& launches = p->launches;
   launches.clear();
   int64_t most_slots = 0;
-  for (int32_t b0 = 0, nb; b0 < batch; b0 += nb) {
+  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
     launches.emplace_back();
-    nb = plan_next(p, ids, batch, b0, launches.back(), extra);
+    plan_launch(p, ids + b0, std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0), b0, launches.back(), extra);
     if (p->plan_total_units > 0x7fffffffll || p->plan_waves * p->geom.n_kv_heads > 0x7fffffffll || p->plan_slots > 0x7fffffffll)
       return set_err(ELLM_ERR_RANGE, "decode_attention: too much work for one call");
     most_slots = std::max(most_slots, p->plan_slots);
-  }
-  // (what the fixed workspace takes is what it would take in launches of GROUP_REQ requests)
-  if (ws_fixed && launches[0].n_req > ellm::GROUP_REQ && launch_slot_bound(device_simds(), p->geom.n_kv_heads, ellm::GROUP_REQ) > ws_fixed_slots) {
-    ellm::BatchArgs& a = launches.emplace_back();
-    for (int32_t b0 = 0; b0 < batch; b0 += ellm::GROUP_REQ) {
-      plan_launch(p, ids + b0, std::min<int32_t>(ellm::GROUP_REQ, batch - b0), b0, a, extra);
-      most_slots = std::max(most_slots, p->plan_slots);
-    }
-    launches.pop_back();
   }
   if (ws_fixed && most_slots > ws_fixed_slots)
     return set_err(ELLM_ERR_RANGE, "decode_attention_noalloc: the batch needs more partial results than the fixed "
@@ -1399,22 +1390,26 @@ static int decode_impl(ellm_pool* p, const ellm_tensor_id* ids, int32_t batch, c
   const float scale_log2 = scale * 1.4426950408889634f;
 
   const ellm::PoolView pv = view_of(p, ws_fixed != nullptr);
+  const bool pair = pair_up(p, ws_fixed ? ws_fixed_slots : p->ws_cap_slots);
   int err = ELLM_OK;
-  for (const ellm::BatchArgs& a : launches) {
+  for (size_t i = 0; i < (pair ? 1 : launches.size()) && !err; i++) {
     bool prof = (size_t)(p->prof_used + 1) * 2 <= p->prof_ev.size();
     if (prof && p->prof_stride > 1) {
       prof = p->prof_phase == 0;
       p->prof_phase = (p->prof_phase + 1) % p->prof_stride;
     }
     if (launch_refused(p)) { err = set_err(ELLM_ERR_HIP, "decode partial launch: refused (debug hook)"); break; }
-    int e = ellm::launch_decode_partial(pv, q, k_new, v_new, ws, out, scale_log2, a, stream,
-                                        prof ? p->prof_ev[2 * p->prof_used] : nullptr,
-                                        prof ? p->prof_ev[2 * p->prof_used + 1] : nullptr);
+    const hipEvent_t ev_start = prof ? p->prof_ev[2 * p->prof_used] : nullptr, ev_stop = prof ? p->prof_ev[2 * p->prof_used + 1] : nullptr;
+    int e = pair ? ellm::launch_decode_pair(pv, q, k_new, v_new, ws, out, scale_log2, p->pair, stream, ev_start, ev_stop)
+                 : ellm::launch_decode_partial(pv, q, k_new, v_new, ws, out, scale_log2, launches[i], stream, ev_start, ev_stop);
     if (e) { err = hip_err((hipError_t)e, "decode partial launch"); break; }
-    *n_launched += a.n_req;
+    *n_launched += pair ? batch : launches[i].n_req;
     if (prof) p->prof_used++;
-    e = ellm::launch_decode_combine(pv, ws, out, a, stream);
-    if (e) { err = hip_err((hipError_t)e, "decode combine launch"); break; }
+    for (int h = 0; h < (pair ? 2 : 1) && !err; h++) {
+      e = pair ? ellm::launch_decode_combine(pv, ws + (h ? p->pair.floats : 0), out, p->pair.half[h], stream)
+               : ellm::launch_decode_combine(pv, ws, out, launches[i], stream);
+      if (e) err = hip_err((hipError_t)e, "decode combine launch");
+    }
   }
   // also after a refused launch: the chunks of the requests already launched are in use on the stream
   if (*n_launched > 0 && (rc = leave_compute(p, stream, ids, *n_launched)) && !err) err = rc;
@@ -1502,7 +1497,7 @@ uint64_t ellm_workspace_bytes(const ellm_pool_desc* d, int32_t max_batch) {
   if (!d || max_batch < 1 || !d->n_kv_heads || !d->n_q_heads || d->n_q_heads % d->n_kv_heads ||
       (d->head_dim != 64 && d->head_dim != 128))
     return 0;
-  const int32_t n_req = std::min<int32_t>(max_batch, ellm::GROUP_REQ);
+  const int32_t n_req = std::min<int32_t>(max_batch, ellm::MAX_LAUNCH_REQ);
   return (uint64_t)launch_slot_bound(device_simds(), d->n_kv_heads, n_req) *
          slot_bytes(d->n_q_heads / d->n_kv_heads, d->head_dim);
 }
@@ -1707,8 +1702,8 @@ int ellm_debug_kv_stream_read(ellm_pool* p, const ellm_tensor_id* ids, int32_t b
   if (rc) return rc;
   const ellm::PoolView pv = view_of(p);
   ellm::BatchArgs a;
-  for (int32_t b0 = 0; b0 < batch; b0 += ellm::GROUP_REQ) {
-    const int32_t nb = std::min<int32_t>(ellm::GROUP_REQ, batch - b0);
+  for (int32_t b0 = 0; b0 < batch; b0 += ellm::MAX_LAUNCH_REQ) {
+    const int32_t nb = std::min<int32_t>(ellm::MAX_LAUNCH_REQ, batch - b0);
     plan_launch(p, ids + b0, nb, b0, a);
     int e = ellm::launch_kv_stream(pv, (uint32_t*)sink, a, stream);
     if (e) return hip_err((hipError_t)e, "kv stream launch");

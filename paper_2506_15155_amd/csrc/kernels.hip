@@ -348,6 +348,19 @@ __device__ __forceinline__ Share<Args> locate_share(const Args& a, const Records
   return s;
 }
 
+// Calls body(pool, workspace, plan, number of this workgroup in the plan): of a pair, with what belongs to this workgroup's half.
+template <class Args, class Body>
+__device__ __forceinline__ void in_launch(const PoolView& pv, float* ws, const Args& a, Body body) {
+  if constexpr (std::is_same_v<Args, PairArgs>) {
+    const bool second = blockIdx.x >= a.workgroups;
+    PoolView mine = pv;
+    mine.merged += second ? a.counters : 0u;
+    body(mine, ws + (second ? a.floats : 0u), a.half[second ? 1 : 0], (int32_t)(blockIdx.x - (second ? a.workgroups : 0u)));
+  } else {
+    body(pv, ws, a, (int32_t)blockIdx.x);
+  }
+}
+
 // which four dims of a head piece f of a partial result's row holds: rows keep the dims in the order in which the
 // lanes of the kernel that wrote them store neighbouring pieces
 template <int D>
@@ -513,7 +526,7 @@ __device__ __forceinline__ void leave_partial(const PoolView& pv, float* ws, con
 // heads of 64 66.4 -> 65.7, chunks of 16 tokens 33.6 -> 33.3, the 8B-shaped step 1995 -> 1985.
 template <int D, int HEADS, class Args>
 __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws_, uint16_t* __restrict__ out, const Args& a, const Records<Args>& records,
-                                           const Results<D, HEADS>& res, int32_t g_first, int32_t n_heads, int32_t wave, int32_t lane) {
+                                           const Results<D, HEADS>& res, int32_t g_first, int32_t n_heads, int32_t workgroup, int32_t wave, int32_t lane) {
   constexpr int F = D / 4, SLOTS = Results<D, HEADS>::SLOTS, NONE = Results<D, HEADS>::NONE;
   float* const ws = held(ws_);
   const int32_t waves_per_head = held(a.waves_per_head), parts_per_head = held(a.parts_per_head), ws_slots = held(a.ws_slots),
@@ -547,7 +560,7 @@ __device__ __forceinline__ void end_shares(const PoolView& pv, float* ws_, uint1
     const bool whole = n == rq.n_part && rq.n_part <= merge_parts;
     const Parts parts = parts_of(rq.wave_first, rq.n_part, waves_per_head, g, SHARE_WAVES);
     const int64_t slot0 = (int64_t)g * parts_per_head + rq.part0;
-    const int64_t row0 = (slot0 + ((int32_t)blockIdx.x - parts.first)) * group + g_first;
+    const int64_t row0 = (slot0 + (workgroup - parts.first)) * group + g_first;
     // (stores past this wave's heads are dropped by the buffers' range)
     const auto rows = buffer_at(ws + row0 * D, h1 * (D * 4));
     const auto pairs = buffer_at(ws + (int64_t)ws_slots * group * D + row0 * WS_ML, h1 * (WS_ML * 4));
@@ -625,7 +638,7 @@ template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                                     const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
                                                     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
-                                                    int32_t g_first, const Args& a) {
+                                                    int32_t g_first, const Args& a, int32_t workgroup) {
   constexpr int NW = SHARE_WAVES;
   constexpr int LPR = D / 8;             // lanes per row = 16-byte pieces per row
   constexpr int RPW = 64 / LPR;          // rows per wave-wide load
@@ -856,7 +869,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
   }
 
   results.clear(wave, lane);             // (behind the first loads it is slower: LDS writes wait for loads to LDS)
-  const int32_t index = blockIdx.x * NW + wave;
+  const int32_t index = workgroup * NW + wave;
   if (index < a.waves_per_head * pv.n_kv_heads) {
     const Share<Args> sh = locate_share(a, records, index, lane);
     const int32_t g = sh.g, n_tiles = sh.n_units;
@@ -1019,7 +1032,7 @@ __device__ __forceinline__ void decode_tile_body(const PoolView& pv, const uint1
       }
     }
   }
-  end_shares<D, G>(pv, ws, out, a, records, results, g_first, G, wave, lane);
+  end_shares<D, G>(pv, ws, out, a, records, results, g_first, G, workgroup, wave, lane);
 #undef ELLM_LOAD_Q
 #undef ELLM_LOAD_NEW_ROW
 #undef ELLM_LOAD_TILE
@@ -1039,13 +1052,17 @@ template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(2))) void decode_tile_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, Args a) {
-  decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
+  in_launch(pv, ws, a, [&](const PoolView& pv, float* ws, const auto& a, int32_t workgroup) __attribute__((always_inline)) {
+    decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a, workgroup);
+  });
 }
 template <int D, int G, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SHARE_WAVES) __attribute__((amdgpu_waves_per_eu(1, 1))) void decode_tile_kernel_wide(
     PoolView pv, const uint16_t* __restrict__ q, const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, Args a) {
-  decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a);
+  in_launch(pv, ws, a, [&](const PoolView& pv, float* ws, const auto& a, int32_t workgroup) __attribute__((always_inline)) {
+    decode_tile_body<D, G, APPEND, DIRECT>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, a, workgroup);
+  });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1119,7 +1136,7 @@ template <int D, int U, bool APPEND, bool DIRECT, int NW, int SW, class Args>
 __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint16_t* __restrict__ q,
                                             const char* __restrict__ k_new, const char* __restrict__ v_new,
                                             float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2,
-                                            int32_t g_first, int32_t n_heads, const Args& a) {
+                                            int32_t g_first, int32_t n_heads, const Args& a, int32_t workgroup) {
   constexpr int P = D / 32;          // products along a row = 16-byte pieces of K, dwords of a V row, per lane
   constexpr int ROWB = D * 2, E = D / 16, VB = E * 2;
   static_assert(U % 2 == 0, "PV takes two units at a time");
@@ -1132,7 +1149,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   const int32_t Tc = pv.tokens_per_chunk;
   const uint64_t plane = (uint64_t)Tc * ROWB;        // V plane follows the K plane of the same head
 
-  const int32_t index = NW ? blockIdx.x : blockIdx.x * SW + wave;
+  const int32_t index = NW ? workgroup : workgroup * SW + wave;
   const Share<Args> sh = locate_share(a, records, NW ? index : min(index, a.waves_per_head * pv.n_kv_heads - 1), lane);
   const int32_t g = sh.g;
   const int32_t hq0 = g * pv.group + g_first;        // first q head handled here
@@ -1508,7 +1525,7 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
   } else if constexpr (SW > 1) {
     results.clear(wave, lane);
   }
-  if constexpr (SW > 1) end_shares<D, HEADS_PER_PASS>(pv, ws, out, a, records, results, g_first, n_heads, wave, lane);
+  if constexpr (SW > 1) end_shares<D, HEADS_PER_PASS>(pv, ws, out, a, records, results, g_first, n_heads, workgroup, wave, lane);
 }
 
 // Launched with one wave per SIMD. The register cap of two keeps the matrix instructions' results out of
@@ -1517,7 +1534,9 @@ template <int D, int U, int SW, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * SW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_unit_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, Args a) {
-  decode_unit_body<D, U, APPEND, DIRECT, 0, SW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  in_launch(pv, ws, a, [&](const PoolView& pv, float* ws, const auto& a, int32_t workgroup) __attribute__((always_inline)) {
+    decode_unit_body<D, U, APPEND, DIRECT, 0, SW>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a, workgroup);
+  });
 }
 // Small launches are bound by latency: 4 requests of up to 256 tokens, 8 heads of 64: 12.1 -> 8.5 us a call,
 // of which one launch instead of two is 3 us of host time. Launches of 50 MB of K and V, in wide blocks with four units
@@ -1526,7 +1545,9 @@ template <int D, int U, int NW, bool APPEND, bool DIRECT, class Args>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2))) void decode_block_kernel(
     PoolView pv, const uint16_t* __restrict__ q, const char* __restrict__ k_new, const char* __restrict__ v_new,
     float* __restrict__ ws, uint16_t* __restrict__ out, float scale_log2, int32_t g_first, int32_t n_heads, Args a) {
-  decode_unit_body<D, U, APPEND, DIRECT, NW, 1>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a);
+  in_launch(pv, ws, a, [&](const PoolView& pv, float* ws, const auto& a, int32_t workgroup) __attribute__((always_inline)) {
+    decode_unit_body<D, U, APPEND, DIRECT, NW, 1>(pv, q, k_new, v_new, ws, out, scale_log2, g_first, n_heads, a, workgroup);
+  });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1541,9 +1562,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2, 2)))
 // ---------------------------------------------------------------------------------------------
 constexpr int COMBINE_AHEAD = 4;     // rows a lane asks for before it waits
 
-template <int D, int W, class Args, bool IN_ORDER = false>
+template <int D, int W, bool IN_ORDER = false>
 __global__ __launch_bounds__(64 * W) void decode_combine_kernel(const float* __restrict__ ws, uint16_t* __restrict__ out,
-                                                                int32_t n_q_heads, int32_t group, Args a) {
+                                                                int32_t n_q_heads, int32_t group, BatchArgs a) {
   constexpr int F = D / 4, RP = W * 64 / F, AHEAD = COMBINE_AHEAD;
   __shared__ __attribute__((aligned(16))) float4 sums[RP][F];
   const int h = blockIdx.y, lane = threadIdx.x & 63, f = threadIdx.x % F, row = threadIdx.x / F;
@@ -1634,17 +1655,17 @@ __global__ __launch_bounds__(256) void read_kernel(const uint4* __restrict__ src
 // the K/V rows a decode over this batch reads, with the same work partition and load shape (one
 // wave per share of the same cut, up to 64 rows at a time, 128-bit loads), but no arithmetic
 template <int D, bool DIRECT>
-__global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __restrict__ sink, GroupArgs a) {
+__global__ __launch_bounds__(64) void kv_stream_kernel(PoolView pv, uint32_t* __restrict__ sink, BatchArgs a) {
   constexpr int LPR = D / 8, RPW = 64 / LPR, NL = 64 / RPW, ROWB = D * 2;
   const int lane = threadIdx.x;
   const int sub = lane % LPR, rg = lane / LPR;
   const int32_t Tc = pv.tokens_per_chunk;
   uint32_t x = 0;
   {
-    const Share<GroupArgs> sh = locate_share(a, Records<GroupArgs>(a, lane), blockIdx.x, lane);
+    const Share<BatchArgs> sh = locate_share(a, Records<BatchArgs>(a, lane), blockIdx.x, lane);
     const int32_t g = sh.g;
     int32_t cb = sh.b;
-    GroupArgs::Req rec = sh.first;
+    BatchArgs::Req rec = sh.first;
     const int32_t ut = a.unit_tokens, upc = (Tc + ut - 1) / ut;
     const int32_t u0 = (sh.u_lo - rec.unit_prefix) * a.step_units;
     int32_t left = units_of(rec.len, pv, upc, ut) - u0, todo = sh.n_units;
@@ -1761,12 +1782,12 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
 
 template <int D>
 static const void* partial_kernel_ptr(int group, bool tiles) {
-  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, true, false, GroupArgs>;
+  if (!tiles) return (const void*)decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, true, false, BatchArgs>;
   if constexpr (D == 128) {
-    if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false, GroupArgs>;
-    if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false, GroupArgs>;
+    if (group == 8) return (const void*)decode_tile_kernel_wide<D, 8, true, false, BatchArgs>;
+    if (group == 4) return (const void*)decode_tile_kernel_wide<D, 4, true, false, BatchArgs>;
   }
-  return group == 2 ? (const void*)decode_tile_kernel<D, 2, true, false, GroupArgs> : (const void*)decode_tile_kernel<D, 1, true, false, GroupArgs>;
+  return group == 2 ? (const void*)decode_tile_kernel<D, 2, true, false, BatchArgs> : (const void*)decode_tile_kernel<D, 1, true, false, BatchArgs>;
 }
 
 int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
@@ -1777,91 +1798,94 @@ int partial_waves_per_cu(int head_dim, int group, int tokens_per_chunk) {
   return n * SHARE_WAVES;
 }
 
-// the same launch, described for kernels that take fewer requests
-template <class Args>
-static Args args_of(const BatchArgs& a) {
-  Args f;
+// the same launch, described for kernels that take fewer requests (the combine pass, which reads split_req, is not one)
+static FewArgs few_of(const BatchArgs& a) {
+  FewArgs f;
   f.n_req = a.n_req; f.waves_per_head = a.waves_per_head; f.units_each = a.units_each; f.units_extra = a.units_extra;
   f.by_waves = a.by_waves; f.step_units = a.step_units; f.q_row0 = a.q_row0; f.unit_tokens = a.unit_tokens;
   f.units_per_head = a.units_per_head; f.parts_per_head = a.parts_per_head; f.ws_slots = a.ws_slots;
   f.merge_parts = a.merge_parts; f.n_split_req = a.n_split_req; f.wg_waves = a.wg_waves; f.in_order_parts = a.in_order_parts;
-  std::copy_n(a.split_req, Args::MAX_REQ / 4, f.split_req);
+  std::fill_n(f.split_req, FewArgs::MAX_REQ / 4, 0u);
+  for (int i = 0; i < FewArgs::MAX_REQ; i++) f.req[i] = {};
   for (int i = 0; i < a.n_req; i++) f.req[i] = {a.req[i].len, a.req[i].tensor, a.req[i].unit_prefix, a.req[i].wave_first, a.req[i].n_part, a.req[i].part0};
-  for (int i = a.n_req; i < Args::MAX_REQ; i++) f.req[i] = {};
   return f;
 }
 
-template <int D, bool APPEND, bool DIRECT>
-static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
-                            void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
-                            hipEvent_t ev_stop) {
-  const unsigned waves = (unsigned)(a.waves_per_head * pv.n_kv_heads), grid = (waves + SHARE_WAVES - 1) / SHARE_WAVES;
+// a: the plan, or one of the two in `args`, which run the same kernel; workgroups: of all of it
+template <int D, bool APPEND, bool DIRECT, class Args>
+static int launch_partial_i(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws, void* out, float scale_log2,
+                            const BatchArgs& a, const Args& args, unsigned workgroups, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  constexpr bool PAIR = std::is_same_v<Args, PairArgs>;
   if (a.unit_tokens == TILE_TOKENS) {
-    auto tiles = [&](const auto& args) {
-      using Args = std::decay_t<decltype(args)>;
-      auto go = [&](auto kernel) {
-        return launch(kernel, dim3(grid), 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new,
-                      (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)0, args);
-      };
-      if constexpr (D == 128) {
-        if (pv.group == 4) return go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT, Args>);
-        if (pv.group == 8) return go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT, Args>);
-      }
-      return pv.group == 1 ? go(decode_tile_kernel<D, 1, APPEND, DIRECT, Args>) : go(decode_tile_kernel<D, 2, APPEND, DIRECT, Args>);
+    auto go = [&](auto kernel) {
+      return launch(kernel, dim3(workgroups), 64 * SHARE_WAVES, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const uint4*)k_new,
+                    (const uint4*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)0, args);
     };
-    return a.n_req <= GROUP_REQ ? tiles(args_of<GroupArgs>(a)) : tiles(a);
+    if constexpr (D == 128) {
+      if (pv.group == 4) return go(decode_tile_kernel_wide<D, 4, APPEND, DIRECT, Args>);
+      if (pv.group == 8) return go(decode_tile_kernel_wide<D, 8, APPEND, DIRECT, Args>);
+    }
+    return pv.group == 1 ? go(decode_tile_kernel<D, 1, APPEND, DIRECT, Args>) : go(decode_tile_kernel<D, 2, APPEND, DIRECT, Args>);
   }
   if (a.step_units > STEP_UNITS) {
-    auto go = [&](auto kernel, unsigned n_waves, const auto& args) {
-      return launch(kernel, dim3(waves), 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws,
-                    (uint16_t*)out, scale_log2, (int32_t)0, pv.group, args);
+    auto go = [&](auto kernel, unsigned n_waves, const auto& its) {
+      return launch(kernel, dim3(workgroups), 64 * n_waves, stream, ev_start, ev_stop, pv, (const uint16_t*)q, (const char*)k_new,
+                    (const char*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)0, pv.group, its);
     };
-    auto in_blocks = [&](const auto& args) {
-      using Args = std::decay_t<decltype(args)>;
+    auto in_blocks = [&](const auto& its) {
+      using Its = std::decay_t<decltype(its)>;
       constexpr int U = tile_units<D>, NW = BLOCK_UNITS / U;
-      if (a.step_units <= BLOCK_UNITS) return go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Args>, NW, args);
-      return go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Args>, WIDE_WAVES, args);
+      if (a.step_units <= BLOCK_UNITS) return go(decode_block_kernel<D, U, NW, APPEND, DIRECT, Its>, NW, its);
+      return go(decode_block_kernel<D, WIDE_UNITS / WIDE_WAVES, WIDE_WAVES, APPEND, DIRECT, Its>, WIDE_WAVES, its);
     };
-    if (a.n_req <= FewArgs::MAX_REQ) return in_blocks(args_of<FewArgs>(a));
-    return a.n_req <= GROUP_REQ ? in_blocks(args_of<GroupArgs>(a)) : in_blocks(a);
+    if constexpr (!PAIR)
+      if (a.n_req <= FewArgs::MAX_REQ) return in_blocks(few_of(a));
+    return in_blocks(args);
   }
   // a group of more than HEADS_PER_PASS q heads is covered by several launches over the same K/V: the
   // first of them takes the start time, the last one the end time
-  auto shares = [&](const auto& args) {
-    using Args = std::decay_t<decltype(args)>;
-    for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
-      const int n = std::min(HEADS_PER_PASS, pv.group - done);
-      auto go = [&](auto kernel, unsigned n_wg, unsigned threads) {
-        return launch(kernel, dim3(n_wg), threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv,
-                      (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)done, (int32_t)n, args);
-      };
-      int e = -1;
-      // (launches of more than GROUP_REQ requests have one pass, and workgroups of four waves)
-      if constexpr (Args::MAX_REQ <= GROUP_REQ)
-        if (a.wg_waves == 1) e = go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT, Args>, waves, 64);
-      if (e < 0) e = go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT, Args>, grid, 64 * SHARE_WAVES);
-      if (e) return e;
-    }
-    return 0;
-  };
-  return a.n_req <= GROUP_REQ ? shares(args_of<GroupArgs>(a)) : shares(a);
+  for (int done = 0; done < pv.group; done += HEADS_PER_PASS) {
+    const int n = std::min(HEADS_PER_PASS, pv.group - done);
+    auto go = [&](auto kernel, unsigned threads) {
+      return launch(kernel, dim3(workgroups), threads, stream, done == 0 ? ev_start : nullptr, done + n >= pv.group ? ev_stop : nullptr, pv,
+                    (const uint16_t*)q, (const char*)k_new, (const char*)v_new, ws, (uint16_t*)out, scale_log2, (int32_t)done, (int32_t)n, args);
+    };
+    int e = -1;
+    if constexpr (!PAIR)               // (single_waves() is for several passes)
+      if (a.wg_waves == 1) e = go(decode_unit_kernel<D, tile_units<D>, 1, APPEND, DIRECT, Args>, 64);
+    if (e < 0) e = go(decode_unit_kernel<D, tile_units<D>, SHARE_WAVES, APPEND, DIRECT, Args>, 64 * SHARE_WAVES);
+    if (e) return e;
+  }
+  return 0;
 }
 
-template <int D>
-static int launch_partial_d(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
-                            void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
-                            hipEvent_t ev_stop) {
-  auto go = [&](auto launch) { return launch(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop); };
-  if (k_new) return pv.vbase ? go(launch_partial_i<D, true, true>) : go(launch_partial_i<D, true, false>);
-  return pv.vbase ? go(launch_partial_i<D, false, true>) : go(launch_partial_i<D, false, false>);
+template <class Args>
+static int launch_partial(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws, void* out, float scale_log2,
+                          const BatchArgs& a, const Args& args, unsigned workgroups, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  auto go = [&](auto launch) { return launch(pv, q, k_new, v_new, ws, out, scale_log2, a, args, workgroups, stream, ev_start, ev_stop); };
+  auto of_size = [&](auto dim) {
+    constexpr int D = decltype(dim)::value;
+    if (k_new) return pv.vbase ? go(launch_partial_i<D, true, true, Args>) : go(launch_partial_i<D, true, false, Args>);
+    return pv.vbase ? go(launch_partial_i<D, false, true, Args>) : go(launch_partial_i<D, false, false, Args>);
+  };
+  return pv.head_dim == 128 ? of_size(std::integral_constant<int, 128>{}) : of_size(std::integral_constant<int, 64>{});
+}
+
+static unsigned workgroups_of(const PoolView& pv, const BatchArgs& a) {
+  return ((unsigned)(a.waves_per_head * pv.n_kv_heads) + a.wg_waves - 1) / a.wg_waves;
 }
 
 int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
                           void* out, float scale_log2, const BatchArgs& a, hipStream_t stream, hipEvent_t ev_start,
                           hipEvent_t ev_stop) {
   if (a.n_req <= 0 || a.waves_per_head <= 0) return 0;
-  return pv.head_dim == 128 ? launch_partial_d<128>(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop)
-                            : launch_partial_d<64>(pv, q, k_new, v_new, ws, out, scale_log2, a, stream, ev_start, ev_stop);
+  return launch_partial(pv, q, k_new, v_new, ws, out, scale_log2, a, a, workgroups_of(pv, a), stream, ev_start, ev_stop);
+}
+
+int launch_decode_pair(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws, void* out, float scale_log2,
+                       PairArgs& a, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  a.workgroups = workgroups_of(pv, a.half[0]);
+  return launch_partial(pv, q, k_new, v_new, ws, out, scale_log2, a.half[0], a, a.workgroups + workgroups_of(pv, a.half[1]), stream, ev_start, ev_stop);
 }
 
 int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream) {
@@ -1869,17 +1893,13 @@ int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const 
   // where every wave leaves partials there can be few of them each for many requests: as many waves as these fill
   const bool single = a.wg_waves == 1 && a.step_units <= STEP_UNITS;
   const int fill = single ? a.parts_per_head / a.n_split_req * pv.head_dim / (COMBINE_AHEAD * 256) : 4;    // by 1, by 4, more
-  auto pass = [&](const auto& args) {
-    using Args = std::decay_t<decltype(args)>;
-    auto go = [&](auto kernel, unsigned waves) {
-      return launch(kernel, dim3(a.n_split_req, pv.n_q_heads), 64 * waves, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, args);
-    };
-    if (a.in_order_parts) return pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, Args, true>, 8) : go(decode_combine_kernel<64, 4, Args, true>, 4);
-    if (pv.head_dim == 128)
-      return fill < 1 ? go(decode_combine_kernel<128, 2, Args>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4, Args>, 4) : go(decode_combine_kernel<128, 8, Args>, 8);
-    return fill < 1 ? go(decode_combine_kernel<64, 1, Args>, 1) : go(decode_combine_kernel<64, 4, Args>, 4);
+  auto go = [&](auto kernel, unsigned waves) {
+    return launch(kernel, dim3(a.n_split_req, pv.n_q_heads), 64 * waves, stream, ws, (uint16_t*)out, pv.n_q_heads, pv.group, a);
   };
-  return a.n_req <= GROUP_REQ ? pass(args_of<GroupArgs>(a)) : pass(a);
+  if (a.in_order_parts) return pv.head_dim == 128 ? go(decode_combine_kernel<128, 8, true>, 8) : go(decode_combine_kernel<64, 4, true>, 4);
+  if (pv.head_dim == 128)
+    return fill < 1 ? go(decode_combine_kernel<128, 2>, 2) : fill < 4 ? go(decode_combine_kernel<128, 4>, 4) : go(decode_combine_kernel<128, 8>, 8);
+  return fill < 1 ? go(decode_combine_kernel<64, 1>, 1) : go(decode_combine_kernel<64, 4>, 4);
 }
 
 int launch_copy(void* dst, const void* src, int64_t bytes, hipStream_t stream) {
@@ -1896,8 +1916,7 @@ int launch_read(const void* src, int64_t bytes, uint32_t* sink, hipStream_t stre
   return launch(read_kernel, dim3((unsigned)blocks), 256, stream, (const uint4*)src, n, sink);
 }
 
-int launch_kv_stream(const PoolView& pv, uint32_t* sink, const BatchArgs& batch, hipStream_t stream) {
-  const GroupArgs a = args_of<GroupArgs>(batch);
+int launch_kv_stream(const PoolView& pv, uint32_t* sink, const BatchArgs& a, hipStream_t stream) {
   const unsigned grid = (unsigned)(a.waves_per_head * pv.n_kv_heads);
   if (a.n_req <= 0 || grid == 0) return 0;
   auto go = [&](auto kernel) { return launch(kernel, dim3(grid), 64, stream, pv, sink, a); };

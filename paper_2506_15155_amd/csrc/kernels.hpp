@@ -10,8 +10,7 @@
 
 namespace ellm {
 
-constexpr int MAX_LAUNCH_REQ = 256;   // requests described by one decode launch's kernel arguments (6.5 KB in all)
-constexpr int GROUP_REQ = 128;        // larger batches go in launches of so many (decode: 3.2 KB of arguments), and appends do
+constexpr int MAX_LAUNCH_REQ = 128;   // requests that a launch is planned for (3.2 KB of arguments); larger batches go in groups of so many
 constexpr int MAX_PATCH = 448;        // table entries patched by one launch
 constexpr int TILE_TOKENS = 64;       // the kernel that walks tiles: rows of one chunk a wave handles at a time
 constexpr int UNIT_TOKENS = 16;       // the kernel that walks units: rows of one chunk the work is dealt out by
@@ -79,8 +78,8 @@ struct BatchArgsOf {
   int32_t q_row0;             // row of the first request in q / out
   int32_t unit_tokens;        // TILE_TOKENS or UNIT_TOKENS: what the work is dealt out by, and which kernel walks it
   int32_t units_per_head;     // units of all requests of the launch, for one kv head
-  int32_t parts_per_head;     // partial slots per kv head = sum of n_part over the split requests (where workgroups are
-                              // waves of several shares, a request uses no more than it spans workgroups)
+  int32_t parts_per_head;     // partial slots per kv head: the sum of n_part over the split requests (where workgroups are
+                              // waves of several shares, a request uses no more than it spans workgroups), or slots_by_workgroup()
   int32_t ws_slots;           // n_kv_heads * parts_per_head
   int32_t merge_parts;        // requests with 2 <= n_part <= merge_parts are added up by the workgroup that ends last;
                               // 0 where any request has more than merge_parts()
@@ -100,17 +99,46 @@ struct BatchArgsOf {
   int32_t in_order_parts;     // requests of up to so many partials are added up in the attention kernel's order
 };
 using BatchArgs = BatchArgsOf<MAX_LAUNCH_REQ>;
-// what kernels take up to GROUP_REQ requests
-using GroupArgs = BatchArgsOf<GROUP_REQ>;
 // what a launch in blocks of few requests hands to its kernel instead: the host writes the arguments to device memory for
 // each launch; with 0.6 KB instead of 4 a call of 4 requests of up to 256 tokens took 7.37 us instead of 7.67 (0.5 and 3.2 KB now)
 using FewArgs = BatchArgsOf<16>;
 
+// The two groups of a batch of up to 2 * MAX_LAUNCH_REQ requests in one launch: the workgroups of the second behind those of the
+// first, each with its own plan, slots and counters, so that every output is bit for bit that of two launches.
+struct PairArgs {
+  BatchArgs half[2];
+  uint32_t workgroups;        // of the first
+  uint32_t counters;          // words from the first one's counters to the second's
+  uint64_t floats;            // from the first one's workspace to the second's
+};
+
+// Slots for the partial results that the attention kernel of a planned launch leaves, counted by workgroup: returned are those of a
+// kv head, and part0 and the slots of `a` are set to them. A request that one workgroup has all of needs none, unless the combine
+// pass takes it; where a head's waves are no multiple of SHARE_WAVES its workgroups differ from head to head, and what is counted
+// is the most that n_part waves can lie in. (The plan itself reserves a slot for each wave, which is the documented bound.)
+inline int64_t slots_by_workgroup(BatchArgs& a, int32_t n_kv_heads) {
+  const int32_t S = a.wg_waves;
+  int64_t parts = 0;
+  for (int32_t i = 0; i < a.n_req; i++) {
+    auto& r = a.req[i];
+    int32_t n = 0;
+    if (r.n_part > 1) {
+      n = a.waves_per_head % S == 0 ? (r.wave_first + r.n_part - 1) / S - r.wave_first / S + 1 : std::min(r.n_part, (r.n_part + S - 2) / S + 1);
+      if (n == 1 && a.merge_parts > 0) n = 0;
+    }
+    r.part0 = n ? (int32_t)parts : 0;
+    parts += n;
+  }
+  a.parts_per_head = (int32_t)parts;
+  a.ws_slots = (int32_t)parts * n_kv_heads;
+  return parts;
+}
+
 struct AppendArgs {
   int32_t n_req, total_new;
-  int32_t tensor[GROUP_REQ];
-  int32_t len_before[GROUP_REQ];
-  int32_t tok0[GROUP_REQ];    // first new-token row of request b, relative to this launch
+  int32_t tensor[MAX_LAUNCH_REQ];
+  int32_t len_before[MAX_LAUNCH_REQ];
+  int32_t tok0[MAX_LAUNCH_REQ];    // first new-token row of request b, relative to this launch
 };
 
 struct PatchArgs {
@@ -249,6 +277,9 @@ int launch_chunk_copy(char* pool, char* host, uint32_t chunk_bytes, const CopyAr
 int launch_decode_partial(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws,
                           void* out, float scale_log2, const BatchArgs& a, hipStream_t stream,
                           hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
+// the two plans of `a`, which run the same kernel, in one launch
+int launch_decode_pair(const PoolView& pv, const void* q, const void* k_new, const void* v_new, float* ws, void* out, float scale_log2,
+                       PairArgs& a, hipStream_t stream, hipEvent_t ev_start = nullptr, hipEvent_t ev_stop = nullptr);
 int launch_decode_combine(const PoolView& pv, const float* ws, void* out, const BatchArgs& a, hipStream_t stream);
 
 // Device address and size of the library's fixed workspace on the current device (resolved once per
