@@ -170,6 +170,12 @@ def _i32(a):
         return arr, _i32_one.from_address(arr.ctypes.data), arr.size
 
 
+def _holds(array, count, what):
+    """The library reads `count` entries: an array of fewer is refused here, where its size is known (None: none is given)."""
+    if array is not None and array.size < count:
+        raise ValueError(f"{what}: {array.size} entries where {count} are read")
+
+
 def _stream(stream) -> int | None:
     """hipStream_t of a torch stream (or a raw handle). None selects torch's current stream."""
     if stream is None:
@@ -205,6 +211,7 @@ def ellm_pool_create(device_buf, host_buf, chunk_bytes, n_q_heads, n_kv_heads, h
     own = None
     if initial_owner is not None:
         own = np.ascontiguousarray(initial_owner, dtype=np.uint8)
+        _holds(own, d.device_bytes // d.chunk_bytes if d.chunk_bytes else 0, "initial_owner")
         d.initial_owner = own.ctypes.data
     out = _vp()
     rc = lib.ellm_pool_create(C.byref(d), C.byref(out))
@@ -331,6 +338,7 @@ def ellm_debug_vmm_latency(chunk_bytes, n_chunks, check=True):
 
 def ellm_tensor_map_chunks(pool, tid, first_slot, n_slots, chunk_ids=None, flags=0, check=True):
     keep, p, _ = _i32(chunk_ids)
+    _holds(keep, n_slots, "chunk_ids")
     return _ret(lib.ellm_tensor_map_chunks(pool, tid, first_slot, n_slots, p, flags), check)
 
 
@@ -353,6 +361,7 @@ def ellm_kv_append(pool, ids, k_new, v_new, n_new=None, stream=None, check=True)
     if rc is None:
         keep, p, n = _i32(ids)
         keep_n, pn, _ = _i32(n_new)
+        _holds(keep_n, n, "n_new")
         s = _stream(stream)
         rc = lib.ellm_kv_append(pool, p, n, pn, _ptr(k_new), _ptr(v_new), s)
     return rc if rc >= 0 else _ret(rc, check)
@@ -390,6 +399,7 @@ def ellm_chunk_deflate_to_host(pool, tid, first_slot, n_slots, check=True):
 
 def ellm_chunk_inflate_from_host(pool, tid, first_slot, n_slots, chunk_ids=None, check=True):
     keep, p, _ = _i32(chunk_ids)
+    _holds(keep, n_slots, "chunk_ids")
     return _ret(lib.ellm_chunk_inflate_from_host(pool, tid, first_slot, n_slots, p), check)
 
 

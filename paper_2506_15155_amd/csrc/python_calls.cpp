@@ -162,7 +162,10 @@ PyObject* append(PyObject*, PyObject* const* a, Py_ssize_t n_args) {
   const int32_t *ids, *n_new = nullptr;
   int32_t n, n_n;
   TAKE(pool_and_ids(a, &pool, &ids, &n));
-  if (a[4] != Py_None) TAKE(numbers(a[4], &n_new, &n_n));
+  if (a[4] != Py_None) {
+    TAKE(numbers(a[4], &n_new, &n_n));
+    if (n_n < n) Py_RETURN_NONE;               // refused by binding.py
+  }
   TAKE(stream_of(a[5], &stream));
   TAKE(pointer(a[2], &k));
   TAKE(pointer(a[3], &v));

@@ -95,3 +95,34 @@ def test_plain_arguments_are_handled_natively():
     with pytest.raises(TypeError):
         binding._calls.decode(P, ids)
     E.ellm_pool_destroy(P)
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("form", ["array", "list", "int64"])
+def test_arrays_shorter_than_their_count_are_refused(monkeypatch, native, form):
+    """Token counts for fewer requests than are named, chunks for fewer slots, owners for fewer chunks: nothing behind the array
+    is read, and nothing changes. What is left over is ignored, as ever."""
+    if not native:
+        monkeypatch.setattr(binding, "_calls", Nothing())
+    P = E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, flags=1, device_bytes=12 << 14)
+    ids = np.arange(3, dtype=np.int32)
+    for _ in ids:
+        E.ellm_tensor_create(P, 48)
+    E.ellm_kv_premap_next(P, ids)
+    tables = lambda: [(list(t), n) for t, n in (E.ellm_tensor_get_table(P, i) for i in range(3))]
+    before = tables()
+    some = np.array([1, 2, 3, 1], np.int32)                 # (the numbers behind the array would be taken for counts)
+    for n in (0, 1, 2):
+        for check in (True, False):
+            with pytest.raises(ValueError):
+                E.ellm_kv_append(P, ids, 0x3000, 0x3000, forms(some)["array"][:n] if form == "array" else forms(some[:n])[form], stream=0, check=check)
+    with pytest.raises(ValueError):
+        E.ellm_tensor_map_chunks(P, 0, 1, 2, forms([7])[form])
+    with pytest.raises(ValueError):
+        E.ellm_chunk_inflate_from_host(P, 0, 0, 2, forms([7])[form])
+    with pytest.raises(ValueError):
+        E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, initial_owner=[0] * 11, flags=1, device_bytes=12 << 14)
+    assert tables() == before and E.ellm_pool_self_check(P) == 0
+    assert E.ellm_kv_append(P, ids, 0x3000, 0x3000, forms(some)[form], stream=0) == 0
+    assert [n for _, n in tables()] == [1, 2, 3]
+    E.ellm_pool_destroy(P)
