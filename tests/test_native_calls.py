@@ -8,13 +8,14 @@ import paper_2506_15155_amd as E
 from paper_2506_15155_amd import binding
 
 NATIVE = ("decode", "append_decode", "append", "premap_next")
+REAL = binding._calls
 
 
 class Nothing:
     """In the place of the native calls: handles no form."""
 
     def __getattr__(self, name):
-        return (lambda *a: None) if name in NATIVE else getattr(binding._calls, name)
+        return (lambda *a: None) if name in NATIVE else getattr(REAL, name)
 
 
 class Address:
@@ -83,6 +84,15 @@ def test_the_same_either_way(monkeypatch, ids_form, n_form, pointer, stream):
     assert walk(ids_form, n_form, pointer, stream) == native
 
 
+def test_the_stand_in_passes_on_what_it_does_not_replace(monkeypatch):
+    """With torch up, the general way hands torch's names to the native module: as it is, and not to the stand-in for ever."""
+    monkeypatch.setattr(binding, "_calls", Nothing())
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1230, raising=False)
+    assert binding._stream(None) == 0x1230
+
+
 def test_plain_arguments_are_handled_natively():
     P = E.ellm_pool_create(None, None, 1 << 14, 8, 2, 128, 4, 4, flags=1, device_bytes=12 << 14)
     E.ellm_tensor_create(P, 48)
@@ -126,3 +136,39 @@ def test_arrays_shorter_than_their_count_are_refused(monkeypatch, native, form):
     assert E.ellm_kv_append(P, ids, 0x3000, 0x3000, forms(some)[form], stream=0) == 0
     assert [n for _, n in tables()] == [1, 2, 3]
     E.ellm_pool_destroy(P)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("native", [True, False])
+def test_no_stream_is_torchs_current_one(monkeypatch, native):
+    """While a stream is captured: what is called without a stream is recorded there, and runs when the graph does."""
+    tokens, kv, dim, n = 64, 2, 64, 3
+    cb = tokens * 4 * kv * dim
+    dev = torch.empty(4 * n * cb, dtype=torch.uint8, device="cuda")
+    pool = E.ellm_pool_create(dev, None, cb, kv, kv, dim, n, 4)
+    ids = np.array([E.ellm_tensor_create(pool, 4 * tokens) for _ in range(n)], np.int32)
+    for i in ids:
+        E.ellm_tensor_map_chunks(pool, int(i), 0, 4)
+    rows = torch.randn(100 * n, kv, dim, device="cuda").to(torch.bfloat16)
+    E.ellm_kv_append(pool, ids, rows, rows, np.full(n, 100, np.int32))
+    q = torch.randn(n, kv, dim, device="cuda").to(torch.bfloat16)
+    want = torch.empty_like(q)
+    E.ellm_decode_attention(pool, ids, q, want)
+    torch.cuda.synchronize()
+    if not native:
+        monkeypatch.setattr(binding, "_calls", Nothing())
+    outs = torch.zeros(2, *q.shape, dtype=q.dtype, device="cuda")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=torch.cuda.Stream()):
+        if native:
+            assert binding._calls.decode(False, pool, ids, q, outs[0], 0.0, None) == 0
+        E.ellm_decode_attention(pool, ids, q, outs[0])
+        E.ellm_decode_attention_noalloc(pool, ids, q, outs[1])
+    torch.cuda.synchronize()
+    assert not outs.any()
+    for _ in range(3):
+        outs.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(outs[0], want) and torch.equal(outs[1], want)
+    E.ellm_pool_destroy(pool)
