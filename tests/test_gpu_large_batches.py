@@ -85,17 +85,17 @@ def test_replays(n, dim, group):
     assert launches(B, ids, q) == 1
     rc, want = B.decode(ids, q)
     assert rc == 0
-    dq, out = H.dev_bits(q), torch.empty_like(want)
+    dq, outs = H.dev_bits(q), torch.empty(2, *want.shape, dtype=want.dtype, device="cuda")
     graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
     torch.cuda.synchronize()
     with torch.cuda.graph(graph, stream=stream):
-        assert E.ellm_decode_attention(B.pool, ids, dq, out, check=False) == 0
-        assert E.ellm_decode_attention_noalloc(B.pool, ids, dq, out, check=False) == 0
+        assert E.ellm_decode_attention(B.pool, ids, dq, outs[0], check=False) == 0
+        assert E.ellm_decode_attention_noalloc(B.pool, ids, dq, outs[1], check=False) == 0
     for _ in range(4):
-        out.zero_()
+        outs.zero_()
         graph.replay()
         torch.cuda.synchronize()
-        assert torch.equal(out, want)
+        assert torch.equal(outs[0], want) and torch.equal(outs[1], want)
         rc, eager = B.decode(ids[: n // 2], q[: n // 2])
         assert rc == 0
     B.close()
