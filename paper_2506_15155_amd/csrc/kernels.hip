@@ -1180,22 +1180,23 @@ __device__ __forceinline__ void decode_unit_body(const PoolView& pv, const uint1
     t.part = part;
     t.flags = first;
     t.base = DIRECT ? walk.tbase : pv.base;
-    // (which table entries are wanted is known before any of them is asked for: their loads are on the way together)
-    int32_t in_slot[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
-      const bool there = u == 0 || u < t.n;
-      in_slot[u] = there ? slot : in_slot[u ? u - 1 : 0];
-      t.r[u] = there ? r : t.r[u ? u - 1 : 0];
-      t.nv[u] = there ? min(UNIT_TOKENS, min(Tc - r, len - (slot * Tc + r))) : 0;
-      t.tail = there ? t.nv[u] : t.tail;
-      if (u < t.n - 1 || (u < t.n && rem_req > t.n)) {     // there is a next unit of this request
-        r += UNIT_TOKENS;
-        if (r >= Tc) { r = 0; slot += 1; }
+      if (u == 0 || u < t.n) {
+        t.at[u] = DIRECT ? (uint32_t)slot : (uint32_t)walk.trow[slot];
+        t.r[u] = r;
+        t.nv[u] = min(UNIT_TOKENS, min(Tc - r, len - (slot * Tc + r)));
+        t.tail = t.nv[u];
+        if (u < t.n - 1 || (t.n > 0 && rem_req > t.n)) {   // there is a next unit of this request
+          r += UNIT_TOKENS;
+          if (r >= Tc) { r = 0; slot += 1; }
+        }
+      } else {
+        t.at[u] = t.at[u - 1];
+        t.r[u] = t.r[u - 1];
+        t.nv[u] = 0;
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; u++) t.at[u] = DIRECT ? (uint32_t)in_slot[u] : (uint32_t)walk.trow[in_slot[u]];
     if (t.n == 0) t.nv[0] = 0;                       // past the end of the share
     rem_req -= t.n;
     rem_share -= t.n;
