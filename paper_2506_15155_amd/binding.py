@@ -9,13 +9,14 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from importlib.machinery import EXTENSION_SUFFIXES
 
 import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(HERE, "libellm.so")
 
-CALLS_PATH = os.path.join(HERE, "_calls.so")
+CALLS_PATH = os.path.join(HERE, "_calls" + EXTENSION_SUFFIXES[0])
 
 for _path in (LIB_PATH, CALLS_PATH):
     if not os.path.exists(_path):

@@ -1,4 +1,4 @@
-"""Build libellm.so (HIP, gfx950) in-tree with hipcc, and _calls.so, the native part of the Python binding, with g++."""
+"""Build libellm.so (HIP, gfx950) in-tree with hipcc, and _calls, the native part of the Python binding, with g++."""
 from __future__ import annotations
 
 import os
@@ -9,7 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libellm.so")
-CALLS = os.path.join(HERE, "_calls.so")
+# (named for the interpreter it is built for: another one does not load it)
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 CALLS_SOURCE = os.path.join(CSRC, "python_calls.cpp")
 SOURCES = ["pool_core.cpp", "ellm_api.cpp", "kernels.hip"]
 HEADERS = ["pool_core.hpp", "kernels.hpp", "divide.hpp", "map_queue.hpp", os.path.join(ROOT, "include", "ellm.h")]

@@ -1,5 +1,7 @@
 """The binding's native argument conversion against its general one, on the CPU: every form of arguments that is accepted gives the
 same results and tables either way, and what is refused is refused by both."""
+import sysconfig
+
 import numpy as np
 import pytest
 import torch
@@ -91,6 +93,11 @@ def test_the_stand_in_passes_on_what_it_does_not_replace(monkeypatch):
     monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 0, raising=False)
     monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: 0x1230, raising=False)
     assert binding._stream(None) == 0x1230
+
+
+def test_the_native_module_is_this_interpreters():
+    """Built for another one, it is missing and not loaded as it is."""
+    assert binding._calls.__file__ == binding.CALLS_PATH and binding.CALLS_PATH.endswith("_calls" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 
 def test_plain_arguments_are_handled_natively():
