@@ -114,16 +114,19 @@ struct PairArgs {
 
 // Slots for the partial results that the attention kernel of a planned launch leaves, counted by workgroup: returned are those of a
 // kv head, and part0 and the slots of `a` are set to them. A request that one workgroup has all of needs none, unless the combine
-// pass takes it; where a head's waves are no multiple of SHARE_WAVES its workgroups differ from head to head, and what is counted
-// is the most that n_part waves can lie in. (The plan itself reserves a slot for each wave, which is the documented bound.)
+// pass takes it; where a head's waves are no multiple of SHARE_WAVES its workgroups begin elsewhere from head to head (and as in the
+// first ones from the SHARE_WAVES-th head on), and the most count. (The plan itself reserves a slot for each wave, which is the documented bound.)
 inline int64_t slots_by_workgroup(BatchArgs& a, int32_t n_kv_heads) {
-  const int32_t S = a.wg_waves;
+  const int32_t ways = a.waves_per_head % SHARE_WAVES ? std::min<int32_t>(n_kv_heads, SHARE_WAVES) : 1;
   int64_t parts = 0;
   for (int32_t i = 0; i < a.n_req; i++) {
     auto& r = a.req[i];
     int32_t n = 0;
     if (r.n_part > 1) {
-      n = a.waves_per_head % S == 0 ? (r.wave_first + r.n_part - 1) / S - r.wave_first / S + 1 : std::min(r.n_part, (r.n_part + S - 2) / S + 1);
+      if (a.wg_waves == 1) n = r.n_part;
+      else
+        for (uint32_t g = 0, w0 = r.wave_first; g < (uint32_t)ways; g++, w0 += a.waves_per_head)
+          n = std::max(n, (int32_t)((w0 % SHARE_WAVES + r.n_part - 1) / SHARE_WAVES) + 1);
       if (n == 1 && a.merge_parts > 0) n = 0;
     }
     r.part0 = n ? (int32_t)parts : 0;

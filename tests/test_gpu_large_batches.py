@@ -32,7 +32,7 @@ def in_groups(B, ids, q):
 # the kernels of the two groups, whether they share a launch, the lengths, and longer requests (at, tokens)
 @pytest.mark.parametrize("kernels,n_kv,group,dim,tokens,n,lo,hi,long,one", [
     ("tile tile", 3, 4, 128, 64, 200, 300, 900, [], True), ("tile tile", 2, 8, 128, 64, 256, 200, 600, [(127, 3000), (128, 2100)], True),
-    ("tile tile", 1, 1, 128, 64, 250, 600, 1500, [], True), ("tile tile", 5, 2, 64, 64, 193, 300, 900, [], True),
+    ("tile tile", 1, 1, 128, 64, 250, 600, 1500, [], True), ("tile tile", 7, 4, 128, 64, 147, 1000, 1300, [], True), ("tile tile", 5, 2, 64, 64, 193, 300, 900, [], True),
     ("tile tile", 8, 1, 64, 64, 200, 300, 700, [], True), ("tile tile", 8, 2, 128, 64, 192, 200, 600, [], True),
     ("unit unit", 2, 12, 64, 64, 256, 300, 900, [(40, 3000)], True), ("unit unit", 8, 3, 64, 16, 220, 1, 300, [], True),
     ("unit unit", 1, 8, 128, 64, 256, 200, 300, [], True), ("unit unit", 8, 3, 64, 64, 200, 5, 40, [], True),
@@ -42,11 +42,11 @@ def in_groups(B, ids, q):
     ("tile tile", 2, 8, 128, 64, 200, 100, 300, [(3, 9000), (140, 20000)], True),                       # by combine passes
     ("unit unit", 2, 12, 64, 64, 256, 300, 900, [(140, 30000)], True),                                  # the second only
     ("tile unit", 3, 4, 128, 64, 129, 30, 900, [(43, 3000), (128, 2100)], False), ("unit block", 3, 6, 128, 24, 190, 100, 500, [], False),
-    ("tile block", 4, 4, 128, 64, 160, 480, 520, [], False), ("tile tile", 7, 4, 128, 64, 147, 1000, 1300, [], False),
+    ("tile block", 4, 4, 128, 64, 160, 480, 520, [], False), ("tile tile", 3, 4, 128, 64, 256, 300, 900, [], False),
     ("block block", 2, 4, 128, 64, 257, 30, 500, [], False), ("unit unit", 2, 34, 64, 64, 140, 30, 300, [], False)])
 def test_one_launch(pool_mode, kernels, n_kv, group, dim, tokens, n, lo, hi, long, one):
-    """One launch where both groups run the same kernel and their partial results fit (7 kv heads: 146 waves a head, which
-    straddle workgroups), and the same bits either way."""
+    """One launch where both groups run the same kernel and their partial results fit (3 and 7 kv heads: 341 and 146 waves a
+    head, which straddle workgroups), and the same bits either way."""
     rng = np.random.default_rng(n)
     lens = [int(x) for x in rng.integers(lo, hi + 1, size=n)]
     for at, length in long:
