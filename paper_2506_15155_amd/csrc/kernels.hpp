@@ -137,7 +137,9 @@ inline int64_t slots_by_workgroup(BatchArgs& a, int32_t n_kv_heads) {
   return parts;
 }
 
-struct AppendArgs {
+// (aligned: every workgroup reads one or a few neighbours of each array, which 24 more bytes of PoolView had put across two cache
+// lines; prompts of four requests 123.8 us a call, aligned 123.5, ahead of that 123.3)
+struct alignas(64) AppendArgs {
   int32_t n_req, total_new;
   int32_t tensor[MAX_LAUNCH_REQ];
   int32_t len_before[MAX_LAUNCH_REQ];
