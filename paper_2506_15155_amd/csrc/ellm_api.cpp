@@ -503,8 +503,8 @@ int enter_compute(ellm_pool* p, hipStream_t stream, const int32_t* ids, int32_t 
   if (rc) return rc;
   if (p->vmm && (rc = vmm_wait_slots(p, ids, batch, extra))) return rc;
   if ((rc = follow_on(p, stream))) return rc;
-  // (the table is read on this stream alone: its patch runs while the copies are still on their way, 6 us of the chain from a
-  // fetch to the attention behind it)
+  // (the table is read on this stream alone: its patch runs while the copies are still on their way. One 2 MiB chunk out, one in and a
+  // decode 135.5 -> 131 us a pass, two of each 202.5 -> 199, four requests 790 -> 784)
   if ((rc = flush_table(p, stream))) return rc;
   p->last_stream = stream;
   p->have_last_stream = true;
